@@ -520,23 +520,24 @@ struct ProjJob {            // one scan's forward projection
 hipError_t launch_project_jobs(const ProjJob *jobs, int n, hipStream_t s);
 hipError_t launch_project(const float *vol, int64_t stride, const GridK &g, const ConeK &c,
                           const float *angles, int V, float *proj, hipStream_t s);
-struct BwdJob {             // one scan's back-projection (all jobs per view, or all summed)
+struct BwdJob {             // one scan's back-projection, one volume per view
     const float *g_proj;
     GridK g;
     ConeK c;
     const float *angles;
     int V;
     float *g_vol;
-    int64_t stride;         // 0: sum over views into one volume
-    void *ws;               // project_bwd_workspace(g, c, V) bytes
+    int64_t stride;         // elements between views' volumes
+    void *ws;               // project_bwd_views_workspace(g, c, V) bytes
     unsigned *vmax;         // optional [V], zeroed: largest |g_vol| per view (float bits)
 };
 hipError_t launch_project_bwd_jobs(const BwdJob *jobs, int n, hipStream_t s);
+size_t project_bwd_views_workspace(const GridK &g, const pmf_cone_t &c, int V);
+// stride 0: the sum over views into one volume; ws = project_bwd_workspace bytes
 size_t project_bwd_workspace(const GridK &g, const pmf_cone_t &c, int V);
-// vmax (optional, [V] zeroed uint): largest |g_vol| of each view, as float bits
 hipError_t launch_project_bwd(const float *g_proj, const GridK &g, const ConeK &c,
                               const float *angles, int V, float *g_vol, int64_t stride, void *ws,
-                              hipStream_t s, unsigned *vmax = nullptr);
+                              hipStream_t s);
 
 // loss
 size_t fdk_workspace(const pmf_cone_t &c, int V);

@@ -17,6 +17,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "pmf_internal.h"
 
@@ -503,8 +504,7 @@ struct BoundK {
 
 // One scan's share of a ragged back-projection launch: workgroups
 // [first[k], first[k+1]) belong to scan k, view-major (nbv items per view,
-// the brick count of the orientation with more bricks) or one per brick when
-// summing over views.
+// the column chunks of the orientation with more).
 struct BwdK {
     const float *g_proj;
     GridK g;
@@ -516,11 +516,11 @@ struct BwdK {
     int V;
     float *g_vol;
     int64_t stride;
-    float *pads;            // [V (or 1)][nbb][NPMAX]: one box per brick
+    float *pads;            // [V][nbb][NPMAX]: one box per brick
     int nbb;                // bricks per view (the orientation with more)
-    int zc;                 // bricks per chunk along axis 2 (per-view mode)
-    int nbv;                // work items per view (column chunks, or bricks when summing)
-    int items;              // nbv * V, or nbv when summing over views
+    int zc;                 // bricks per chunk along axis 2
+    int nbv;                // column chunks per view
+    int items;              // nbv * V
     BoundK kb;
     MarchK mk;
     unsigned *vmax;
@@ -842,7 +842,7 @@ __device__ __forceinline__ void bp_scatter(const BwdK &bj, const BrickGeo &q, in
     }
 }
 
-// Per-view mode: one workgroup walks a chunk of up to ZC bricks along
+// One workgroup walks a chunk of up to ZC bricks along
 // axis 2 of one (b0, b1) column for one view.  The high pad layer of each
 // brick (z = S2 in its box) is the low layer of the next one: it is carried
 // in LDS (integer sums: exact), so only the chunk's last brick stages it.
@@ -943,57 +943,6 @@ __device__ __forceinline__ void bp_column(const BwdK &bj, int view, int item, in
     }
 }
 
-// Summed over views: one brick per workgroup (chunks of one brick), every
-// view in order with its own scale, float sums per box entry; all pads are
-// staged.
-template <int S0, int S1, int S2, int NW, int NPMAX, bool MERGE>
-__device__ __forceinline__ void bp_summed(const BwdK &bj, int bid, int *__restrict__ acc,
-                                          RunP (*__restrict__ runs)[64],
-                                          int (*__restrict__ ends)[64]) {
-    constexpr int P1 = S1 + 1, P2 = S2 + 1;
-    constexpr int NP = (S0 + 1) * P1 * P2;
-    static_assert(NP <= NPMAX, "box larger than the LDS array");
-    constexpr int NT = 64 * NW;
-    constexpr int PER = (NP + NT - 1) / NT;
-    const GridK &g = bj.g;
-    const int nb0 = (g.n[0] + S0 - 1) / S0, nb1 = (g.n[1] + S1 - 1) / S1;
-    const int nb2 = (g.n[2] + S2 - 1) / S2;
-    if (bid >= nb0 * nb1 * nb2) return;
-    const int b2 = bid % nb2, b1 = (bid / nb2) % nb1, b0 = bid / (nb2 * nb1);
-    const BrickGeo q = brick_geo<S0, S1, S2>(g, b0, b1, b2);
-    float sum[PER];
-#pragma unroll
-    for (int k = 0; k < PER; ++k) sum[k] = 0.0f;
-    for (int v = 0; v < bj.V; ++v) {
-        const double th = (double)bj.angles[v];
-        const double ct = cos(th), st = sin(th);
-        const float scale = bp_scale(bj, v, ct, st);
-        if (!q.cells || !(scale > 0.0f)) continue;
-        for (int i = threadIdx.x; i < NP; i += NT) acc[i] = 0;
-        __syncthreads();
-        bp_scatter<S0, S1, S2, NW, MERGE>(bj, q, v, ct, st, scale, acc, runs, ends);
-        __syncthreads();
-        const float inv = 1.0f / scale;
-#pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const int i = threadIdx.x + NT * k;
-            if (i < NP) sum[k] += (float)acc[i] * inv;
-        }
-        __syncthreads();
-    }
-    float *pad = bj.pads + (int64_t)bid * NPMAX;
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const int i = threadIdx.x + NT * k;
-        if (i >= NP) continue;
-        const int z = i % P2, y = (i / P2) % P1, x = i / (P1 * P2);
-        const int gx = q.B[0] + x, gy = q.B[1] + y, gz = q.B[2] + z;
-        if (gx >= g.n[0] || gy >= g.n[1] || gz >= g.n[2]) continue;
-        if (x < S0 && y < S1 && z < S2) bj.g_vol[((int64_t)gx * g.n[1] + gy) * g.n[2] + gz] = sum[k];
-        else pad[i] = sum[k];
-    }
-}
-
 // Waves per SIMD that the LDS of one workgroup (box + run staging) allows
 // on a 160 KB CU, at most six: the register budget is set to match, so the
 // compiler does not trade occupancy the LDS cannot use for registers.
@@ -1006,7 +955,7 @@ constexpr int bwd_waves_per_simd(int L, int W, int H, int NW) {
 
 // L x W x H cells per brick (L along the axis the view's rays mostly
 // follow), NW waves per workgroup.
-template <int L, int W, int H, int NW, bool SUM, bool MERGE, int ZC>
+template <int L, int W, int H, int NW, bool MERGE, int ZC>
 __global__ __launch_bounds__(64 * NW)
 __attribute__((amdgpu_waves_per_eu(bwd_waves_per_simd(L, W, H, NW))))
 void k_project_bwd(BwdTab t) {
@@ -1020,19 +969,11 @@ void k_project_bwd(BwdTab t) {
     const BwdK &bj = t.s[job];
     const int local = job_item(t, job, (int)blockIdx.x);
     if (local >= bj.items) return;
-    if constexpr (SUM) {
-        // summed over views: one orientation for all views (the first's)
-        if (bj.orient[0])
-            bp_summed<W, L, H, NW, NPMAX, MERGE>(bj, local, acc, runs, ends);
-        else
-            bp_summed<L, W, H, NW, NPMAX, MERGE>(bj, local, acc, runs, ends);
-    } else {
-        const int view = local / bj.nbv, item = local - view * bj.nbv;
-        if (bj.orient[view])
-            bp_column<W, L, H, NW, NPMAX, MERGE, ZC>(bj, view, item, acc, runs, ends);
-        else
-            bp_column<L, W, H, NW, NPMAX, MERGE, ZC>(bj, view, item, acc, runs, ends);
-    }
+    const int view = local / bj.nbv, item = local - view * bj.nbv;
+    if (bj.orient[view])
+        bp_column<W, L, H, NW, NPMAX, MERGE, ZC>(bj, view, item, acc, runs, ends);
+    else
+        bp_column<L, W, H, NW, NPMAX, MERGE, ZC>(bj, view, item, acc, runs, ends);
 }
 
 // Fix-up of the brick faces: a voxel on the low face of its brick, where the
@@ -1046,12 +987,12 @@ void k_project_bwd(BwdTab t) {
 // each face voxel is completed once.  Blocks stride over one view's rows
 // (one atomic for vmax per block).
 template <int S0, int S1, int S2, int NPMAX>
-__device__ __forceinline__ void bp_fixup(const BwdK &bj, int view, int sum_views, float *red) {
+__device__ __forceinline__ void bp_fixup(const BwdK &bj, int view, float *red) {
     constexpr int S[3] = {S0, S1, S2};
     constexpr int P1 = S1 + 1, P2 = S2 + 1;
     const GridK &g = bj.g;
     const int nb[3] = {(g.n[0] + S0 - 1) / S0, (g.n[1] + S1 - 1) / S1, (g.n[2] + S2 - 1) / S2};
-    const int zc = sum_views ? 1 : bj.zc;
+    const int zc = bj.zc;
     const int nz = (nb[2] - 1) / zc;        // axis-2 planes at chunk boundaries
     // work rows: family 0 (axis-0 planes) and family 1 (axis-1 planes) are
     // lines along axis 2, rows_per lines to a row of work; family 2: per
@@ -1066,7 +1007,7 @@ __device__ __forceinline__ void bp_fixup(const BwdK &bj, int view, int sum_views
     const int l0 = (nb[0] - 1) * g.n[1], l1 = (nb[1] - 1) * g.n[0];  // lines of families 0, 1
     const int r0 = (l0 + lpr - 1) / lpr, r1 = (l1 + lpr - 1) / lpr;
     const int r2 = nz > 0 ? (g.n[0] * g.n[1] + lines2 - 1) / lines2 : 0;
-    float *out = bj.g_vol + (sum_views ? 0 : (int64_t)view * bj.stride);
+    float *out = bj.g_vol + (int64_t)view * bj.stride;
     const float *pads = bj.pads + (int64_t)view * bj.nbb * NPMAX;
     float mx = 0.0f;
     for (int row = blockIdx.x; row < r0 + r1 + r2; row += gridDim.x) {
@@ -1120,7 +1061,7 @@ __device__ __forceinline__ void bp_fixup(const BwdK &bj, int view, int sum_views
         mx = fmaxf(mx, fabsf(val));
       }
     }
-    if (bj.vmax && !sum_views) {
+    if (bj.vmax) {
         mx = wave_max(mx);
         if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
         __syncthreads();
@@ -1132,14 +1073,14 @@ __device__ __forceinline__ void bp_fixup(const BwdK &bj, int view, int sum_views
 }
 
 template <int L, int W, int H>
-__global__ __launch_bounds__(256) void k_project_bwd_fixup(BwdK bj, int sum_views) {
+__global__ __launch_bounds__(256) void k_project_bwd_fixup(BwdK bj) {
     constexpr int NPMAX = (L + 1) * (W + 1) * (H + 1);
     __shared__ float red[4];
     const int view = blockIdx.y;
     if (bj.orient[view])
-        bp_fixup<W, L, H, NPMAX>(bj, view, sum_views, red);
+        bp_fixup<W, L, H, NPMAX>(bj, view, red);
     else
-        bp_fixup<L, W, H, NPMAX>(bj, view, sum_views, red);
+        bp_fixup<L, W, H, NPMAX>(bj, view, red);
 }
 
 // Geometry constants of the per-view bound on contributions per voxel
@@ -1237,7 +1178,7 @@ static int bricks_per_view(const GridK &g, int L, int W, int H) {
     return std::max(cnt(L, W), cnt(W, L));
 }
 
-// Work items per view in per-view mode: (b0, b1) columns x chunks, for the
+// Work items per view: (b0, b1) columns x chunks, for the
 // orientation with more.
 static int column_items_per_view(const GridK &g, int L, int W, int H, int zc) {
     const int nz = ((g.n[2] + H - 1) / H + zc - 1) / zc;
@@ -1256,22 +1197,74 @@ static size_t pad_floats(const GridK &g) {
     return m;
 }
 
-size_t project_bwd_workspace(const GridK &g, const pmf_cone_t &c, int V) {
+size_t project_bwd_views_workspace(const GridK &g, const pmf_cone_t &c, int V) {
     return align256(sizeof(RayK) * (size_t)c.nu * (size_t)c.nv * (size_t)V) +
            align256(sizeof(unsigned) * 2 * (size_t)V) + align256(sizeof(int) * (size_t)V) +
            align256(sizeof(float) * pad_floats(g) * (size_t)V);
 }
 
+// Summed over views (one g_vol for all): the views are back-projected as in
+// the per-view form, a round of them at a time, into volumes of the
+// workspace, which k_sum_views adds up in view order.  The per-view form
+// fills the chip (view x column chunk workgroups, each view in its own
+// orientation, axis-2 pads carried in LDS); bricks that own every view in
+// turn leave it idle (64 workgroups for a 64^3 grid, 1,248 long ones for
+// 256x256x128) and stage every pad.  Measured, back-projection only: 10 views
+// of 128x96 onto 64^3 SUMMED_SMALL; 8 views of 512x384 onto
+// 256x256x128 SUMMED_LARGE.  A round holds at least 16 views (156
+// column chunks each at 256x256x128: above the 1,536 workgroups a full chunk
+// length asks for), more while its volumes stay below 512 MB.
+static int sum_round(const GridK &g, int V) {
+    const int64_t fit = ((int64_t)512 << 20) / (4 * grid_size(g));
+    return (int)std::min<int64_t>(V, std::max<int64_t>(16, fit));
+}
+
+// Workspace of pmf_project_bwd: the per-view part for V views, then one
+// round's volumes.
+size_t project_bwd_workspace(const GridK &g, const pmf_cone_t &c, int V) {
+    return project_bwd_views_workspace(g, c, V) +
+           (V > 1 ? align256(sizeof(float) * (size_t)grid_size(g) * (size_t)sum_round(g, V)) : 0);
+}
+
+// out[i] = (ADD: out[i] +) vols[0][i] + vols[1][i] + ..., in view order.
+// Bound by the reads; VEC moves 16 bytes per lane (N % 4 == 0 and both
+// arrays 16-byte aligned).
+template <bool ADD, bool VEC>
+__global__ __launch_bounds__(256) void k_sum_views(const float *__restrict__ vols, int64_t N,
+                                                   int R, float *__restrict__ out) {
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    using T = std::conditional_t<VEC, f4, float>;
+    const int64_t n = VEC ? N / 4 : N;
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const T *in = (const T *)vols + i;
+    T sum = ADD ? ((const T *)out)[i] : *in;
+    int r = ADD ? 0 : 1;
+#pragma unroll 8
+    for (; r < R; ++r) sum += in[(int64_t)r * n];
+    ((T *)out)[i] = sum;
+}
+
+static hipError_t launch_sum_views(const float *vols, int64_t N, int R, bool add, float *out,
+                                   hipStream_t s) {
+    const bool vec = (N & 3) == 0 && (((uintptr_t)vols | (uintptr_t)out) & 15) == 0;
+    const unsigned nb = (unsigned)(((vec ? N / 4 : N) + 255) / 256);
+    ProfScope prof_("sum_views", s);
+    if (add && vec) k_sum_views<true, true><<<nb, 256, 0, s>>>(vols, N, R, out);
+    else if (add) k_sum_views<true, false><<<nb, 256, 0, s>>>(vols, N, R, out);
+    else if (vec) k_sum_views<false, true><<<nb, 256, 0, s>>>(vols, N, R, out);
+    else k_sum_views<false, false><<<nb, 256, 0, s>>>(vols, N, R, out);
+    return hipGetLastError();
+}
+
 template <int L, int W, int H, int NW, bool MERGE, int ZC>
 static hipError_t project_bwd_bricks(const BwdJob *jobs, int n, hipStream_t s) {
     constexpr int NPMAX = (L + 1) * (W + 1) * (H + 1);
-    const bool sum_views = jobs[0].stride == 0;
     BwdTab t{};
     t.n = n;
     t.first[0] = 0;
     for (int k = 0; k < n; ++k) {
         const BwdJob &j = jobs[k];
-        if ((j.stride == 0) != sum_views) return hipErrorInvalidValue;
         char *w = (char *)j.ws;
         RayK *rays = (RayK *)w;
         w += align256(sizeof(RayK) * (size_t)j.c.nu * (size_t)j.c.nv * (size_t)j.V);
@@ -1303,9 +1296,9 @@ static hipError_t project_bwd_bricks(const BwdJob *jobs, int n, hipStream_t s) {
         b.stride = j.stride;
         b.pads = pads;
         b.nbb = bricks_per_view(j.g, L, W, H);
-        b.zc = sum_views ? 1 : ZC;
-        b.nbv = sum_views ? b.nbb : column_items_per_view(j.g, L, W, H, b.zc);
-        b.items = b.nbv * (sum_views ? 1 : j.V);
+        b.zc = ZC;
+        b.nbv = column_items_per_view(j.g, L, W, H, b.zc);
+        b.items = b.nbv * j.V;
         b.kb = make_bound(j.g, j.c);
         b.mk = make_march(j.g);
         b.vmax = j.vmax;
@@ -1314,10 +1307,7 @@ static hipError_t project_bwd_bricks(const BwdJob *jobs, int n, hipStream_t s) {
     for (int k = n + 1; k <= MAXS; ++k) t.first[k] = t.first[n];
     {
         ProfScope prof_("project_bwd", s);
-        if (sum_views)
-            k_project_bwd<L, W, H, NW, true, MERGE, 1><<<(unsigned)t.first[n], 64 * NW, 0, s>>>(t);
-        else
-            k_project_bwd<L, W, H, NW, false, MERGE, ZC><<<(unsigned)t.first[n], 64 * NW, 0, s>>>(t);
+        k_project_bwd<L, W, H, NW, MERGE, ZC><<<(unsigned)t.first[n], 64 * NW, 0, s>>>(t);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -1326,11 +1316,11 @@ static hipError_t project_bwd_bricks(const BwdJob *jobs, int n, hipStream_t s) {
         ProfScope prof_("project_bwd_fixup", s);
         // blocks per view: about 16k over the views (measured: 2k, 4k, 8k
         // and 16k blocks took 0.235, 0.202, 0.185 and 0.178 ms at 32 views)
-        const int V = sum_views ? 1 : t.s[k].V;
+        const int V = t.s[k].V;
         const int per_view = std::max(1, std::min(2048, 16384 / V));
         (void)N;
         k_project_bwd_fixup<L, W, H><<<dim3((unsigned)per_view, (unsigned)V), 256, 0, s>>>(
-            t.s[k], sum_views ? 1 : 0);
+            t.s[k]);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     (void)NPMAX;
@@ -1345,7 +1335,7 @@ static hipError_t project_bwd_chunked(const BwdJob *jobs, int n, hipStream_t s) 
     if constexpr (ZC > 1) {
         int64_t items = 0;
         for (int k = 0; k < n; ++k) items += (int64_t)jobs[k].V * column_items_per_view(jobs[k].g, L, W, H, ZC);
-        if (jobs[0].stride != 0 && items < 1536)
+        if (items < 1536)
             return project_bwd_chunked<L, W, H, NW, MERGE, ZC / 2>(jobs, n, s);
     }
     return project_bwd_bricks<L, W, H, NW, MERGE, ZC>(jobs, n, s);
@@ -1369,9 +1359,26 @@ hipError_t launch_project_bwd_jobs(const BwdJob *jobs, int n, hipStream_t s) {
 
 hipError_t launch_project_bwd(const float *g_proj, const GridK &g, const ConeK &c,
                               const float *angles, int V, float *g_vol, int64_t stride, void *ws,
-                              hipStream_t s, unsigned *vmax) {
-    const BwdJob j{g_proj, g, c, angles, V, g_vol, stride, ws, vmax};
-    return launch_project_bwd_jobs(&j, 1, s);
+                              hipStream_t s) {
+    const int64_t N = grid_size(g);
+    if (stride != 0 || V == 1) {
+        const BwdJob j{g_proj, g, c, angles, V, g_vol, stride != 0 ? stride : N, ws, nullptr};
+        return launch_project_bwd_jobs(&j, 1, s);
+    }
+    pmf_cone_t pc{};
+    pc.nu = c.nu;
+    pc.nv = c.nv;
+    float *vols = (float *)((char *)ws + project_bwd_views_workspace(g, pc, V));
+    const int round = sum_round(g, V);
+    for (int v0 = 0; v0 < V; v0 += round) {
+        const int R = std::min(round, V - v0);
+        const BwdJob j{g_proj + (int64_t)v0 * c.nu * c.nv, g, c, angles + v0, R, vols, N, ws,
+                       nullptr};
+        hipError_t e = launch_project_bwd_jobs(&j, 1, s);
+        if (e != hipSuccess) return e;
+        if ((e = launch_sum_views(vols, N, R, v0 > 0, g_vol, s)) != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace pmf
