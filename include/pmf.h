@@ -181,6 +181,17 @@ int pmf_warp_bwd(const float *ref, const pmf_grid_t *grid, const float *dvf, int
  * in every view.  angles: device [V] (rad).  proj: [V][nv][nu]. */
 int pmf_project(const float *vol, int64_t vol_stride, const pmf_grid_t *grid,
                 const pmf_cone_t *cone, const float *angles, int V, float *proj, void *stream);
+/* pmf_project with scratch space (same arguments, results bit for bit and
+ * errors): the volumes are first copied to a layout in which a sample takes
+ * half the loads.  ws: pmf_project_workspace() bytes (8 per voxel; one volume
+ * for vol_stride = 0, up to 8 at a time otherwise); where that is 0 (few rays
+ * for the volume, or a volume too large for the layout) ws may be NULL.
+ * PMF_EWORKSPACE if it is missing or short. */
+size_t pmf_project_workspace(const pmf_grid_t *grid, const pmf_cone_t *cone, int V,
+                             int64_t vol_stride);
+int pmf_project_ws(const float *vol, int64_t vol_stride, const pmf_grid_t *grid,
+                   const pmf_cone_t *cone, const float *angles, int V, float *proj, void *ws,
+                   size_t ws_bytes, void *stream);
 
 /* Exact adjoint (back-projection) of pmf_project given g_proj [V][nv][nu]:
  * g_vol_v = P_v^T g_proj[v].  vol_stride = N writes one volume per view

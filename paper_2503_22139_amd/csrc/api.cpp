@@ -308,19 +308,47 @@ int pmf_warp_bwd(const float *ref, const pmf_grid_t *grid, const float *dvf, int
 }
 
 // -------------------------------------------------------------- projection
-int pmf_project(const float *vol, int64_t vol_stride, const pmf_grid_t *grid,
-                const pmf_cone_t *cone, const float *angles, int V, float *proj, void *stream) {
+static int project_args(const float *vol, int64_t vol_stride, const pmf_grid_t *grid,
+                        const pmf_cone_t *cone, const float *angles, int V, const float *proj) {
     PMF_CHECK(check_grid(grid, "grid"));
     PMF_CHECK(check_cone(cone, grid));
     if (V < 1) return fail(PMF_EINVAL, "project: V must be >= 1");
     if (!vol || !angles || !proj) return fail(PMF_EINVAL, "project: null pointer");
     if (vol_stride < 0) return fail(PMF_EINVAL, "project: vol_stride < 0");
-    GridK g = make_grid(*grid);
-    if (vol_stride != 0 && vol_stride < grid_size(g))
+    if (vol_stride != 0 && vol_stride < grid_size(make_grid(*grid)))
         return fail(PMF_EINVAL, "project: vol_stride must be 0 or >= N");
-    ConeK c = make_cone(*cone, g);
-    return hip_status(launch_project(vol, vol_stride, g, c, angles, V, proj, as_stream(stream)),
+    return PMF_OK;
+}
+
+int pmf_project(const float *vol, int64_t vol_stride, const pmf_grid_t *grid,
+                const pmf_cone_t *cone, const float *angles, int V, float *proj, void *stream) {
+    PMF_CHECK(project_args(vol, vol_stride, grid, cone, angles, V, proj));
+    const GridK g = make_grid(*grid);
+    return hip_status(launch_project(vol, vol_stride, g, make_cone(*cone, g), angles, V, proj,
+                                     as_stream(stream)),
                       "project");
+}
+
+size_t pmf_project_workspace(const pmf_grid_t *grid, const pmf_cone_t *cone, int V,
+                             int64_t vol_stride) {
+    if (!grid || !cone || V < 1 || cone->nu < 1 || cone->nv < 1) return 0;
+    for (int a = 0; a < 3; ++a)
+        if (grid->n[a] < 1) return 0;
+    const GridK g = make_grid(*grid);
+    return project_workspace(g, make_cone(*cone, g), V, vol_stride);
+}
+
+int pmf_project_ws(const float *vol, int64_t vol_stride, const pmf_grid_t *grid,
+                   const pmf_cone_t *cone, const float *angles, int V, float *proj, void *ws,
+                   size_t ws_bytes, void *stream) {
+    PMF_CHECK(project_args(vol, vol_stride, grid, cone, angles, V, proj));
+    const GridK g = make_grid(*grid);
+    const ConeK c = make_cone(*cone, g);
+    const size_t need = project_workspace(g, c, V, vol_stride);
+    if (need > 0) PMF_CHECK(check_ws(ws, ws_bytes, need));
+    return hip_status(
+        launch_project_ws(vol, vol_stride, g, c, angles, V, proj, ws, as_stream(stream)),
+        "project_ws");
 }
 
 size_t pmf_project_bwd_workspace(const pmf_grid_t *grid, const pmf_cone_t *cone, int V) {

@@ -63,17 +63,6 @@ __device__ __forceinline__ float sample_disp_paired(const float *__restrict__ vp
     return lerp1(lerp1(c00, c01, f1), lerp1(c10, c11, f1), f0);
 }
 
-// y-paired copy of a volume: out[2j] = V[j], out[2j+1] = V[j + n2] (0 on the
-// last row, which no trilinear read takes).
-__global__ __launch_bounds__(256) void k_pair_volume(const float *__restrict__ in, GridK g,
-                                                     float2 *__restrict__ out) {
-    const int64_t N = grid_size(g);
-    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= N) return;
-    const int iy = (int)((j / g.n[2]) % g.n[1]);
-    out[j] = make_float2(in[j], iy + 1 < g.n[1] ? in[j + g.n[2]] : 0.0f);
-}
-
 // Body of one voxel; the restrict-qualified parameters (kept through
 // inlining) let the per-view coefficients come through scalar loads.  With
 // PAIRED the warped volumes are written in the y-paired layout the
@@ -164,7 +153,7 @@ struct GOut {
 // slots are summed over the waves in a fixed order into the brick's partials
 // (reduced over bricks by k_reduce_coeff_parts / _final), so it is deterministic.
 struct WCK {
-    const float *ref;       // y-paired when paired (see k_pair_volume)
+    const float *ref;       // y-paired when paired (see launch_pair_volume)
     int paired;
     GridK g;
     LevelsK lv;
@@ -452,14 +441,6 @@ __global__ __launch_bounds__(256) void k_reduce_coeff_final(const float *__restr
     if (threadIdx.x == 0) g_coeff[o] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// The warped volumes go to the workspace in the y-paired layout when the
-// projection's 32-bit byte offsets and 24-bit strides still hold for it
-// (2 N floats < 2^32 bytes, 2 n1 n2 < 2^24).
-static bool use_paired(const GridK &g) {
-    return grid_size(g) * 8 < ((int64_t)1 << 32) &&
-           2 * (int64_t)g.n[1] * g.n[2] < ((int64_t)1 << 24);
-}
-
 // Workspace: the warped volumes (y-paired when possible), then the y-paired
 // copy of the reference volume.
 size_t warp_project_workspace(const LevelsK &lv, int V, const GridK &g, const pmf_cone_t &c) {
@@ -488,14 +469,10 @@ hipError_t launch_warp_project_jobs(const WPJob *jobs, int n, hipStream_t s) {
         c.ref = j.ref;
         if (paired) {
             // y-paired copy of the reference volume after the warped volumes
-            float2 *rp = (float2 *)((char *)j.ws + align256(sizeof(float) * (size_t)N * j.V * 2));
-            {
-                ProfScope prof_("pair_volume", s);
-                k_pair_volume<<<(unsigned)((N + 255) / 256), 256, 0, s>>>(j.ref, j.g, rp);
-            }
-            hipError_t e = hipGetLastError();
+            float *rp = (float *)((char *)j.ws + align256(sizeof(float) * (size_t)N * j.V * 2));
+            hipError_t e = launch_pair_volume(j.ref, j.g, rp, s);
             if (e != hipSuccess) return e;
-            c.ref = (const float *)rp;
+            c.ref = rp;
         }
         c.g = j.g;
         c.lv = j.lv;
@@ -585,7 +562,7 @@ namespace {
 struct BwdScan {
     BwdLayout lay;
     float *gI, *gbuf, *partial, *stage;
-    float2 *pref;           // y-paired reference volume, or null
+    float *pref;            // y-paired reference volume, or null
     void *rays, *adjws;
     unsigned *vmax;         // [V + 1]: per view, then the largest
     long long *fix;         // [N]
@@ -611,7 +588,7 @@ BwdScan bwd_scan(const WPBJob &j) {
     w += b.lay.vmax;
     b.fix = (long long *)w;
     w += b.lay.fix;
-    b.pref = b.lay.pref ? (float2 *)w : nullptr;
+    b.pref = b.lay.pref ? (float *)w : nullptr;
     w += b.lay.pref;
     b.adjws = w;
     const int64_t N = grid_size(j.g);
@@ -660,14 +637,7 @@ hipError_t launch_warp_project_bwd_jobs(const WPBJob *jobs, int n, hipStream_t s
         if ((e = launch_max_u32(sc[k].vmax, j.V, sc[k].vmax + j.V, s)) != hipSuccess) return e;
         if ((e = launch_fill_i32((int32_t *)sc[k].fix, 2 * grid_size(j.g), 0, s)) != hipSuccess)
             return e;
-        if (sc[k].pref) {
-            const int64_t N = grid_size(j.g);
-            {
-                ProfScope prof_("pair_volume", s);
-                k_pair_volume<<<(unsigned)((N + 255) / 256), 256, 0, s>>>(j.ref, j.g, sc[k].pref);
-            }
-            if ((e = hipGetLastError()) != hipSuccess) return e;
-        }
+        if (sc[k].pref && (e = launch_pair_volume(j.ref, j.g, sc[k].pref, s)) != hipSuccess) return e;
     }
     for (int v0 = 0; v0 < vmax_views; v0 += VCH) {
         WCTab t{};
@@ -679,7 +649,7 @@ hipError_t launch_warp_project_bwd_jobs(const WPBJob *jobs, int n, hipStream_t s
             const int vc = j.V - v0 < VCH ? j.V - v0 : VCH;
             const int64_t N = grid_size(j.g);
             WCK &w = t.s[t.n];
-            w.ref = sc[k].pref ? (const float *)sc[k].pref : j.ref;
+            w.ref = sc[k].pref ? sc[k].pref : j.ref;
             w.paired = sc[k].pref != nullptr;
             w.g = j.g;
             w.lv = j.lv;

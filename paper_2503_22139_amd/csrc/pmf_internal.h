@@ -516,10 +516,19 @@ struct ProjJob {            // one scan's forward projection
     int V;
     float *proj;
     bool paired;            // vol in the y-paired layout (2 floats per voxel; all jobs alike)
+    int call_views = 0;     // views of the whole call where this is a round of it
 };
 hipError_t launch_project_jobs(const ProjJob *jobs, int n, hipStream_t s);
 hipError_t launch_project(const float *vol, int64_t stride, const GridK &g, const ConeK &c,
                           const float *angles, int V, float *proj, hipStream_t s);
+// The paired layout is used when the projection's 32-bit byte offsets and
+// 24-bit strides hold for it (2 N floats < 2^32 bytes, 2 n1 n2 < 2^24).
+bool use_paired(const GridK &g);
+hipError_t launch_pair_volume(const float *in, const GridK &g, float *out, hipStream_t s);
+// projection with scratch for paired copies: project_workspace bytes (0: none used)
+size_t project_workspace(const GridK &g, const ConeK &c, int V, int64_t stride);
+hipError_t launch_project_ws(const float *vol, int64_t stride, const GridK &g, const ConeK &c,
+                             const float *angles, int V, float *proj, void *ws, hipStream_t s);
 struct BwdJob {             // one scan's back-projection, one volume per view
     const float *g_proj;
     GridK g;
@@ -530,6 +539,8 @@ struct BwdJob {             // one scan's back-projection, one volume per view
     int64_t stride;         // elements between views' volumes
     void *ws;               // project_bwd_views_workspace(g, c, V) bytes
     unsigned *vmax;         // optional [V], zeroed: largest |g_vol| per view (float bits)
+    float *sum = nullptr;   // one job alone: the sum over its views (g_vol is then scratch),
+    int sum_add = 0;        // added to what is there
 };
 hipError_t launch_project_bwd_jobs(const BwdJob *jobs, int n, hipStream_t s);
 size_t project_bwd_views_workspace(const GridK &g, const pmf_cone_t &c, int V);

@@ -17,7 +17,6 @@
 #include <math.h>
 
 #include <algorithm>
-#include <type_traits>
 
 #include "pmf_internal.h"
 
@@ -268,10 +267,13 @@ struct ProjTab {
     int n;
 };
 
-template <int WU, int WV, int AU, bool PAIRED>
+// SPLIT: a wave tile is marched by SPLIT waves of the workgroup, each taking a
+// contiguous share of every ray's samples; the shares are added in order.
+template <int WU, int WV, int AU, bool PAIRED, int SPLIT>
 __global__ __launch_bounds__(256) void k_project(ProjTab t) {
     static_assert(WU * WV == 64 && AU >= 1 && 4 % AU == 0, "wave tile must hold 64 pixels");
-    constexpr int BU = WU * AU, BV = WV * (4 / AU);
+    static_assert(SPLIT == 1 || SPLIT == 4, "one share per wave of the workgroup");
+    constexpr int BU = SPLIT == 1 ? WU * AU : WU, BV = SPLIT == 1 ? WV * (4 / AU) : WV;
     // within each scan, each XCD takes one contiguous range of its (view,
     // tile) items: whole views and neighbouring tiles share an L2 (measured
     // faster than sharing each view across all XCDs), and every XCD gets an
@@ -286,39 +288,44 @@ __global__ __launch_bounds__(256) void k_project(ProjTab t) {
     const int v = local / pj.ntiles, tile = local - v * pj.ntiles;
     const int tu = tile % pj.tiles_u, tv = tile / pj.tiles_u;
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-    const int iu = tu * BU + (w % AU) * WU + l % WU;
-    const int iv = tv * BV + (w / AU) * WV + l / WU;
-    if (iu >= c.nu || iv >= c.nv) return;
+    const int iu = tu * BU + (SPLIT == 1 ? (w % AU) * WU : 0) + l % WU;
+    const int iv = tv * BV + (SPLIT == 1 ? (w / AU) * WV : 0) + l / WU;
+    const bool on = iu < c.nu && iv < c.nv;
+    if (SPLIT == 1 && !on) return;
     const double th = (double)pj.angles[v];
     const RayK r = ray_setup(g, c, cos(th), sin(th), iu, iv);
     const char *__restrict__ vb = (const char *)(pj.vol + (int64_t)v * pj.stride);
+    // this wave's samples [first, end)
+    const int per = SPLIT == 1 ? r.n : (r.n + SPLIT - 1) / SPLIT;
+    const int first = SPLIT == 1 ? 0 : min(w * per, r.n), end = min(first + per, r.n);
     float acc0 = 0.0f, acc1 = 0.0f;
     auto sample = [&](float sf) {
         const float u0 = fmaf(sf, r.su[0], r.bu[0]), u1 = fmaf(sf, r.su[1], r.bu[1]),
                     u2 = fmaf(sf, r.su[2], r.bu[2]);
         return PAIRED ? march_sample_paired(vb, mk, u0, u1, u2) : march_sample(vb, mk, u0, u1, u2);
     };
-    auto body = [&](float sf) {
-        const float u0 = fmaf(sf, r.su[0], r.bu[0]), u1 = fmaf(sf, r.su[1], r.bu[1]),
-                    u2 = fmaf(sf, r.su[2], r.bu[2]);
-        return PAIRED ? march_body_paired(vb, mk, u0, u1, u2) : march_body(vb, mk, u0, u1, u2);
-    };
-    // clamped head, unclamped body in pairs, clamped tail (a fixed order per
-    // ray whatever the launch shape)
+    // clamped head, unclamped body, clamped tail (a fixed order per ray
+    // whatever the tile)
     int sb, se;
     body_range(r, mk, sb, se);
-    sb = min(sb, r.n);
-    se = min(se, r.n);
-    int s = 0;
+    sb = min(max(sb, first), end);
+    se = min(max(se, sb), end);
+    int s = first;
     for (; s < sb; ++s) acc0 += sample((float)s);
-    if constexpr (PAIRED) {
+    float sf = (float)s;
+    auto body = [&](float x) {
+        const float u0 = fmaf(x, r.su[0], r.bu[0]), u1 = fmaf(x, r.su[1], r.bu[1]),
+                    u2 = fmaf(x, r.su[2], r.bu[2]);
+        return PAIRED ? march_body_paired(vb, mk, u0, u1, u2) : march_body(vb, mk, u0, u1, u2);
+    };
+    if constexpr (PAIRED && SPLIT == 1) {
         // Consecutive samples of a ray often share a cell: a lane reloads its
         // eight corners only when the cell changes, which takes that lane out
-        // of the gather (the loads are the limit here, not the arithmetic).
+        // of the gather (the loads are the limit here, not the arithmetic:
+        // two VALU instructions fewer per sample measured no change).
         uint32_t last = 0xffffffffu;
         float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f, a3 = 0.0f, d0 = 0.0f, d1 = 0.0f, d2 = 0.0f,
               d3 = 0.0f;
-        float sf = (float)s;
         for (; s < se; ++s, sf += 1.0f) {
             const float u0 = fmaf(sf, r.su[0], r.bu[0]), u1 = fmaf(sf, r.su[1], r.bu[1]),
                         u2 = fmaf(sf, r.su[2], r.bu[2]);
@@ -337,14 +344,24 @@ __global__ __launch_bounds__(256) void k_project(ProjTab t) {
             acc1 += lerp1(lerp1(x00, x01, f1), lerp1(x10, x11, f1), f0);
         }
     } else {
-        float sf = (float)s;
-        for (; s + 1 < se; s += 2, sf += 2.0f) {
-            acc0 += body(sf);
-            acc1 += body(sf + 1.0f);
+        // four samples' loads in flight (few waves: the march is latency-bound)
+        for (; s + 3 < se; s += 4, sf += 4.0f) {
+            const float x0 = body(sf), x1 = body(sf + 1.0f), x2 = body(sf + 2.0f),
+                        x3 = body(sf + 3.0f);
+            acc1 = (((acc1 + x0) + x1) + x2) + x3;
         }
+        for (; s < se; ++s, sf += 1.0f) acc1 += body(sf);
     }
-    for (; s < r.n; ++s) acc0 += sample((float)s);
-    pj.proj[((int64_t)v * c.nv + iv) * c.nu + iu] = (acc0 + acc1) * r.delta;
+    for (; s < end; ++s) acc0 += sample((float)s);
+    float sum = acc0 + acc1;
+    if constexpr (SPLIT > 1) {
+        __shared__ float part[SPLIT][64];
+        part[w][l] = sum;
+        __syncthreads();
+        if (w > 0 || !on) return;
+        sum = (part[0][l] + part[1][l]) + (part[2][l] + part[3][l]);
+    }
+    pj.proj[((int64_t)v * c.nv + iv) * c.nu + iu] = sum * r.delta;
 }
 
 // Per-ray constants of every view, per view the brick orientation of the
@@ -976,6 +993,42 @@ void k_project_bwd(BwdTab t) {
         bp_column<L, W, H, NW, NPMAX, MERGE, ZC>(bj, view, item, acc, runs, ends);
 }
 
+// The pads that the bricks below a face voxel staged for it, added in a fixed
+// order (neighbour mask 1..7): voxel l of brick b, mask the axes on whose low
+// face it lies.
+template <int S0, int S1, int S2, int NPMAX>
+__device__ __forceinline__ float bp_pad_sum(const float *__restrict__ pads, const int nb[3],
+                                            const int b[3], const int l[3], int mask) {
+    constexpr int P1 = S1 + 1, P2 = S2 + 1;
+    float sum = 0.0f;
+#pragma unroll
+    for (int d = 1; d < 8; ++d) {
+        if ((d & mask) != d) continue;
+        const int q0 = b[0] - (d & 1), q1 = b[1] - ((d >> 1) & 1), q2 = b[2] - ((d >> 2) & 1);
+        const int lq0 = (d & 1) ? S0 : l[0], lq1 = (d & 2) ? S1 : l[1], lq2 = (d & 4) ? S2 : l[2];
+        const int nbid = (q0 * nb[1] + q1) * nb[2] + q2;
+        sum += pads[(int64_t)nbid * NPMAX + (lq0 * P1 + lq1) * P2 + lq2];
+    }
+    return sum;
+}
+
+// The axes (bits) on which voxel p sits on the low face of a brick whose lower
+// neighbour staged a pad for it; its brick b and place l in it.
+template <int S0, int S1, int S2>
+__device__ __forceinline__ int bp_face(const int p[3], int zc, int b[3], int l[3]) {
+    constexpr int S[3] = {S0, S1, S2};
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        b[a] = p[a] / S[a];                 // constant divisors
+        l[a] = p[a] - b[a] * S[a];
+    }
+    int mask = 0;
+    if (l[0] == 0 && b[0] > 0) mask |= 1;
+    if (l[1] == 0 && b[1] > 0) mask |= 2;
+    if (l[2] == 0 && b[2] > 0 && b[2] % zc == 0) mask |= 4;
+    return mask;
+}
+
 // Fix-up of the brick faces: a voxel on the low face of its brick, where the
 // brick below it on that axis staged its pad, gets the pads of the bricks
 // below it, added in a fixed order (neighbour mask 1..7), and its share of
@@ -988,8 +1041,6 @@ void k_project_bwd(BwdTab t) {
 // (one atomic for vmax per block).
 template <int S0, int S1, int S2, int NPMAX>
 __device__ __forceinline__ void bp_fixup(const BwdK &bj, int view, float *red) {
-    constexpr int S[3] = {S0, S1, S2};
-    constexpr int P1 = S1 + 1, P2 = S2 + 1;
     const GridK &g = bj.g;
     const int nb[3] = {(g.n[0] + S0 - 1) / S0, (g.n[1] + S1 - 1) / S1, (g.n[2] + S2 - 1) / S2};
     const int zc = bj.zc;
@@ -1035,26 +1086,9 @@ __device__ __forceinline__ void bp_fixup(const BwdK &bj, int view, float *red) {
         }
         if (p[0] >= g.n[0] || p[1] >= g.n[1] || p[2] >= g.n[2]) continue;
         int b[3], l[3];
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            b[a] = p[a] / S[a];                 // constant divisors
-            l[a] = p[a] - b[a] * S[a];
-        }
-        int mask = 0;
-        if (l[0] == 0 && b[0] > 0) mask |= 1;
-        if (l[1] == 0 && b[1] > 0) mask |= 2;
-        if (l[2] == 0 && b[2] > 0 && b[2] % zc == 0) mask |= 4;
+        const int mask = bp_face<S0, S1, S2>(p, zc, b, l);
         if (!(mask >> fam & 1) || (mask & ((1 << fam) - 1))) continue;
-        float sum = 0.0f;
-#pragma unroll
-        for (int d = 1; d < 8; ++d) {
-            if ((d & mask) != d) continue;
-            const int q0 = b[0] - (d & 1), q1 = b[1] - ((d >> 1) & 1), q2 = b[2] - ((d >> 2) & 1);
-            const int lq0 = (d & 1) ? S0 : l[0], lq1 = (d & 2) ? S1 : l[1],
-                      lq2 = (d & 4) ? S2 : l[2];
-            const int nbid = (q0 * nb[1] + q1) * nb[2] + q2;
-            sum += pads[(int64_t)nbid * NPMAX + (lq0 * P1 + lq1) * P2 + lq2];
-        }
+        const float sum = bp_pad_sum<S0, S1, S2, NPMAX>(pads, nb, b, l, mask);
         float *o = out + ((int64_t)p[0] * g.n[1] + p[1]) * g.n[2] + p[2];
         const float val = *o + sum;
         *o = val;
@@ -1107,9 +1141,9 @@ static BoundK make_bound(const GridK &g, const ConeK &c) {
     return b;
 }
 
-template <int WU, int WV, int AU>
+template <int WU, int WV, int AU, int SPLIT>
 static void project_tiled(const ProjJob *jobs, int n, hipStream_t s) {
-    constexpr int BU = WU * AU, BV = WV * (4 / AU);
+    constexpr int BU = SPLIT == 1 ? WU * AU : WU, BV = SPLIT == 1 ? WV * (4 / AU) : WV;
     ProjTab t{};
     t.n = n;
     t.first[0] = 0;
@@ -1131,9 +1165,27 @@ static void project_tiled(const ProjJob *jobs, int n, hipStream_t s) {
     for (int k = n + 1; k <= MAXS; ++k) t.first[k] = t.first[n];
     if (t.first[n] == 0) return;
     if (jobs[0].paired)
-        k_project<WU, WV, AU, true><<<(unsigned)t.first[n], 256, 0, s>>>(t);
+        k_project<WU, WV, AU, true, SPLIT><<<(unsigned)t.first[n], 256, 0, s>>>(t);
     else
-        k_project<WU, WV, AU, false><<<(unsigned)t.first[n], 256, 0, s>>>(t);
+        k_project<WU, WV, AU, false, SPLIT><<<(unsigned)t.first[n], 256, 0, s>>>(t);
+}
+
+// Up to 800,000 rays (four views of 512x384) four waves share every ray:
+// whole rays leave one to three waves on a SIMD, each a serial chain of loads.
+// The shares also keep four samples' loads in flight instead of reusing a
+// cell's corners (which pays once the loads are the bound).  Whole call,
+// whole rays against shares: 256x256x128 paired one view 212 / 139 us, two
+// 252 / 237, four 454 / 419, eight 765 / 784; 128x128x64 paired one view
+// 89 / 64, four 151 / 159; 64^3 plain ten views of 128x96 (122,880 rays) 50 / 15.
+constexpr int64_t SPLIT_RAYS = 800000;
+
+template <int WU, int WV, int AU>
+static void project_tile(const ProjJob *jobs, int n, hipStream_t s) {
+    int64_t rays = 0;
+    for (int k = 0; k < n; ++k)
+        rays += (int64_t)std::max(jobs[k].V, jobs[k].call_views) * jobs[k].c.nu * jobs[k].c.nv;
+    if (rays <= SPLIT_RAYS) project_tiled<WU, WV, AU, 4>(jobs, n, s);
+    else project_tiled<WU, WV, AU, 1>(jobs, n, s);
 }
 
 hipError_t launch_project_jobs(const ProjJob *jobs, int n, hipStream_t s) {
@@ -1142,15 +1194,15 @@ hipError_t launch_project_jobs(const ProjJob *jobs, int n, hipStream_t s) {
         if (jobs[k].paired != jobs[0].paired) return hipErrorInvalidValue;
     ProfScope prof_("project", s);
     switch (tune_get(KNOB_PROJECT_TILE)) {
-        case 0: project_tiled<16, 4, 1>(jobs, n, s); break;
-        case 1: project_tiled<8, 8, 2>(jobs, n, s); break;
-        case 2: project_tiled<4, 16, 4>(jobs, n, s); break;
-        case 3: project_tiled<2, 32, 4>(jobs, n, s); break;
-        case 4: project_tiled<32, 2, 1>(jobs, n, s); break;
-        case 5: project_tiled<1, 64, 4>(jobs, n, s); break;
-        case 6: project_tiled<2, 32, 2>(jobs, n, s); break;
-        case 7: project_tiled<1, 64, 2>(jobs, n, s); break;
-        default: project_tiled<2, 32, 1>(jobs, n, s); break;
+        case 0: project_tile<16, 4, 1>(jobs, n, s); break;
+        case 1: project_tile<8, 8, 2>(jobs, n, s); break;
+        case 2: project_tile<4, 16, 4>(jobs, n, s); break;
+        case 3: project_tile<2, 32, 4>(jobs, n, s); break;
+        case 4: project_tile<32, 2, 1>(jobs, n, s); break;
+        case 5: project_tile<1, 64, 4>(jobs, n, s); break;
+        case 6: project_tile<2, 32, 2>(jobs, n, s); break;
+        case 7: project_tile<1, 64, 2>(jobs, n, s); break;
+        default: project_tile<2, 32, 1>(jobs, n, s); break;
     }
     return hipGetLastError();
 }
@@ -1159,6 +1211,66 @@ hipError_t launch_project(const float *vol, int64_t stride, const GridK &g, cons
                           const float *angles, int V, float *proj, hipStream_t s) {
     const ProjJob j{vol, stride, g, c, angles, V, proj, false};
     return launch_project_jobs(&j, 1, s);
+}
+
+// y-paired copy of a volume: out[2j] = V[j], out[2j+1] = V[j + n2] (0 on the
+// last row, which no trilinear read takes).
+__global__ __launch_bounds__(256) void k_pair_volume(const float *__restrict__ in, GridK g,
+                                                     float2 *__restrict__ out) {
+    const int64_t N = grid_size(g);
+    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (j >= N) return;
+    const int iy = (int)((j / g.n[2]) % g.n[1]);
+    out[j] = make_float2(in[j], iy + 1 < g.n[1] ? in[j + g.n[2]] : 0.0f);
+}
+
+hipError_t launch_pair_volume(const float *in, const GridK &g, float *out, hipStream_t s) {
+    ProfScope prof_("pair_volume", s);
+    k_pair_volume<<<(unsigned)((grid_size(g) + 255) / 256), 256, 0, s>>>(in, g, (float2 *)out);
+    return hipGetLastError();
+}
+
+bool use_paired(const GridK &g) {
+    return grid_size(g) * 8 < ((int64_t)1 << 32) &&
+           2 * (int64_t)g.n[1] * g.n[2] < ((int64_t)1 << 24);
+}
+
+// pmf_project over y-paired copies of the volumes.  The march is bound by its
+// load instructions (four 8-byte ones per sample in the plain layout, two of
+// 16 bytes in the paired one, about 16 CU cycles each), the copy by its 12
+// bytes per voxel.  Measured, whole call, plain against paired:
+// 256x256x128 and 512x384, one view 198 / 139 us, eight views 1512 / 765;
+// 128x128x64 one view 92 / 64; 64^3 and 16 views of 128x96 24 / 27;
+// 256x256x128 and 96x64, one view 21 / 43, 16 views 106 / 110.  So copies are
+// made from 150,000 rays per volume on, and from one ray per 128 voxels on.
+constexpr int PAIR_VIEWS = 8;           // per-view volumes copied at a time
+
+size_t project_workspace(const GridK &g, const ConeK &c, int V, int64_t stride) {
+    const int64_t N = grid_size(g);
+    const int64_t rays = (int64_t)c.nu * c.nv * (stride == 0 ? V : 1);
+    if (!use_paired(g) || rays < 150000 || rays * 128 < N) return 0;
+    return sizeof(float) * 2 * (size_t)N * (size_t)(stride == 0 ? 1 : std::min(V, PAIR_VIEWS));
+}
+
+hipError_t launch_project_ws(const float *vol, int64_t stride, const GridK &g, const ConeK &c,
+                             const float *angles, int V, float *proj, void *ws, hipStream_t s) {
+    if (project_workspace(g, c, V, stride) == 0)
+        return launch_project(vol, stride, g, c, angles, V, proj, s);
+    const int64_t N = grid_size(g);
+    float *pair = (float *)ws;
+    const int step = stride == 0 ? V : PAIR_VIEWS;
+    for (int v0 = 0; v0 < V; v0 += step) {
+        const int R = std::min(step, V - v0);
+        hipError_t e;
+        for (int r = 0; r < (stride == 0 ? 1 : R); ++r)
+            if ((e = launch_pair_volume(vol + (v0 + r) * stride, g, pair + 2 * N * r, s)) !=
+                hipSuccess)
+                return e;
+        const ProjJob j{pair, stride == 0 ? 0 : 2 * N, g, c, angles + v0, R,
+                        proj + (int64_t)v0 * c.nu * c.nv, true, V};
+        if ((e = launch_project_jobs(&j, 1, s)) != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 // Brick shapes of PMF_TUNE_BACKPROJECT_BRICK: L x W x H cells, waves.
@@ -1210,8 +1322,8 @@ size_t project_bwd_views_workspace(const GridK &g, const pmf_cone_t &c, int V) {
 // orientation, axis-2 pads carried in LDS); bricks that own every view in
 // turn leave it idle (64 workgroups for a 64^3 grid, 1,248 long ones for
 // 256x256x128) and stage every pad.  Measured, back-projection only: 10 views
-// of 128x96 onto 64^3 SUMMED_SMALL; 8 views of 512x384 onto
-// 256x256x128 SUMMED_LARGE.  A round holds at least 16 views (156
+// of 128x96 onto 64^3 266 -> 30 us; 8 views of 512x384 onto
+// 256x256x128 3.04 -> 2.07 ms.  A round holds at least 16 views (156
 // column chunks each at 256x256x128: above the 1,536 workgroups a full chunk
 // length asks for), more while its volumes stay below 512 MB.
 static int sum_round(const GridK &g, int V) {
@@ -1226,34 +1338,105 @@ size_t project_bwd_workspace(const GridK &g, const pmf_cone_t &c, int V) {
            (V > 1 ? align256(sizeof(float) * (size_t)grid_size(g) * (size_t)sum_round(g, V)) : 0);
 }
 
-// out[i] = (ADD: out[i] +) vols[0][i] + vols[1][i] + ..., in view order.
-// Bound by the reads; VEC moves 16 bytes per lane (N % 4 == 0 and both
-// arrays 16-byte aligned).
-template <bool ADD, bool VEC>
-__global__ __launch_bounds__(256) void k_sum_views(const float *__restrict__ vols, int64_t N,
-                                                   int R, float *__restrict__ out) {
-    typedef float f4 __attribute__((ext_vector_type(4)));
-    using T = std::conditional_t<VEC, f4, float>;
-    const int64_t n = VEC ? N / 4 : N;
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const T *in = (const T *)vols + i;
-    T sum = ADD ? ((const T *)out)[i] : *in;
-    int r = ADD ? 0 : 1;
-#pragma unroll 8
-    for (; r < R; ++r) sum += in[(int64_t)r * n];
-    ((T *)out)[i] = sum;
+// The pads of the H voxels that brick b holds of one line along axis 2 (place
+// l0, l1 in the brick; f: bp_face of its first voxel), in bp_pad_sum's order,
+// with whole rows of a neighbour's box loaded at once.
+template <int S0, int S1, int S2>
+__device__ __forceinline__ void bp_pad_row(const float *__restrict__ pads, const int nb[3],
+                                           const int b[3], const int l[3], int f, float s[S2]) {
+    constexpr int P1 = S1 + 1, P2 = S2 + 1;
+    constexpr int64_t NP = (int64_t)(S0 + 1) * P1 * P2;
+    float top[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int i = 0; i < S2; ++i) s[i] = 0.0f;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        if ((d & f) != d) continue;
+        const int box = ((b[0] - (d & 1)) * nb[1] + (b[1] - (d >> 1))) * nb[2] + b[2];
+        const int row = (((d & 1) ? S0 : l[0]) * P1 + ((d & 2) ? S1 : l[1])) * P2;
+        if (d > 0) {
+            const float *pr = pads + (int64_t)box * NP + row;
+#pragma unroll
+            for (int i = 0; i < S2; ++i) s[i] += pr[i];
+        }
+        if (f & 4) top[d] = pads[(int64_t)(box - 1) * NP + row + S2];
+    }
+    s[0] = (((s[0] + top[0]) + top[1]) + top[2]) + top[3];
 }
 
-static hipError_t launch_sum_views(const float *vols, int64_t N, int R, bool add, float *out,
-                                   hipStream_t s) {
-    const bool vec = (N & 3) == 0 && (((uintptr_t)vols | (uintptr_t)out) & 15) == 0;
-    const unsigned nb = (unsigned)(((vec ? N / 4 : N) + 255) / 256);
+// out = (add: out +) the views' volumes in view order, each with the pads of
+// its face voxels (what k_project_bwd_fixup adds, in the same order): one pass
+// instead of a read-modify-write of every view's faces (a cache line in four
+// holds one when every brick stages its axis-2 pad) and then the sum.  A
+// thread owns the H voxels that one brick holds of an (x, y) line, so its
+// loads of a view are independent.  Bound by reading the volumes.  VEC:
+// 16-byte loads (n2 a multiple of 4, the volumes and out 16-byte aligned).
+template <int L, int W, int H, bool VEC>
+__global__ __launch_bounds__(256) void k_sum_views(BwdK bj, int add, float *__restrict__ out) {
+    static_assert(H % 4 == 0, "rows of whole float4");
+    constexpr int NPMAX = (L + 1) * (W + 1) * (H + 1);
+    const GridK &g = bj.g;
+    const int nz = (g.n[2] + H - 1) / H;
+    const unsigned t = blockIdx.x * blockDim.x + threadIdx.x;
+    const unsigned line = t / (unsigned)nz;
+    if (line >= (unsigned)g.n[0] * (unsigned)g.n[1]) return;
+    const int k = (int)(t - line * (unsigned)nz);
+    const int p[3] = {(int)(line / (unsigned)g.n[1]), (int)(line % (unsigned)g.n[1]), k * H};
+    const int m = min(H, g.n[2] - p[2]);    // voxels of the row (the staged rows hold H)
+    int b0[3], l0[3], b1[3], l1[3];         // brick and place in each orientation
+    const int f0 = bp_face<L, W, H>(p, bj.zc, b0, l0), f1 = bp_face<W, L, H>(p, bj.zc, b1, l1);
+    const int nb0[3] = {(g.n[0] + L - 1) / L, (g.n[1] + W - 1) / W, nz};
+    const int nb1[3] = {(g.n[0] + W - 1) / W, (g.n[1] + L - 1) / L, nz};
+    const int64_t j = (int64_t)line * g.n[2] + p[2];
+    float sum[H];
+#pragma unroll
+    for (int i = 0; i < H; ++i) sum[i] = add && i < m ? out[j + i] : 0.0f;
+#pragma unroll 2
+    for (int v = 0; v < bj.V; ++v) {
+        const float *in = bj.g_vol + (int64_t)v * bj.stride + j;
+        const float *pads = bj.pads + (int64_t)v * bj.nbb * NPMAX;
+        float x[H], s[H];
+        if constexpr (VEC) {
+#pragma unroll
+            for (int q = 0; q < H; q += 4) {
+                const float4 a = q < m ? *(const float4 *)(in + q) : make_float4(0, 0, 0, 0);
+                x[q] = a.x;
+                x[q + 1] = a.y;
+                x[q + 2] = a.z;
+                x[q + 3] = a.w;
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < H; ++i) x[i] = i < m ? in[i] : 0.0f;
+        }
+        if (bj.orient[v]) bp_pad_row<W, L, H>(pads, nb1, b1, l1, f1, s);
+        else bp_pad_row<L, W, H>(pads, nb0, b0, l0, f0, s);
+#pragma unroll
+        for (int i = 0; i < H; ++i) sum[i] += x[i] + s[i];
+    }
+    if constexpr (VEC) {
+#pragma unroll
+        for (int q = 0; q < H; q += 4)
+            if (q < m)
+                *(float4 *)(out + j + q) =
+                    make_float4(sum[q], sum[q + 1], sum[q + 2], sum[q + 3]);
+    } else {
+#pragma unroll
+        for (int i = 0; i < H; ++i)
+            if (i < m) out[j + i] = sum[i];
+    }
+}
+
+template <int L, int W, int H>
+static hipError_t launch_sum_views(const BwdK &b, const BwdJob &j, hipStream_t s) {
     ProfScope prof_("sum_views", s);
-    if (add && vec) k_sum_views<true, true><<<nb, 256, 0, s>>>(vols, N, R, out);
-    else if (add) k_sum_views<true, false><<<nb, 256, 0, s>>>(vols, N, R, out);
-    else if (vec) k_sum_views<false, true><<<nb, 256, 0, s>>>(vols, N, R, out);
-    else k_sum_views<false, false><<<nb, 256, 0, s>>>(vols, N, R, out);
+    const int64_t rows = (int64_t)j.g.n[0] * j.g.n[1] * ((j.g.n[2] + H - 1) / H);
+    const unsigned nb = (unsigned)((rows + 255) / 256);
+    if ((j.g.n[2] & 3) == 0 && (j.stride & 3) == 0 &&
+        (((uintptr_t)j.g_vol | (uintptr_t)j.sum) & 15) == 0)
+        k_sum_views<L, W, H, true><<<nb, 256, 0, s>>>(b, j.sum_add, j.sum);
+    else
+        k_sum_views<L, W, H, false><<<nb, 256, 0, s>>>(b, j.sum_add, j.sum);
     return hipGetLastError();
 }
 
@@ -1311,14 +1494,13 @@ static hipError_t project_bwd_bricks(const BwdJob *jobs, int n, hipStream_t s) {
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    if (jobs[0].sum) return launch_sum_views<L, W, H>(t.s[0], jobs[0], s);   // adds the pads too
     for (int k = 0; k < n; ++k) {
-        const int64_t N = grid_size(t.s[k].g);
         ProfScope prof_("project_bwd_fixup", s);
         // blocks per view: about 16k over the views (measured: 2k, 4k, 8k
         // and 16k blocks took 0.235, 0.202, 0.185 and 0.178 ms at 32 views)
         const int V = t.s[k].V;
         const int per_view = std::max(1, std::min(2048, 16384 / V));
-        (void)N;
         k_project_bwd_fixup<L, W, H><<<dim3((unsigned)per_view, (unsigned)V), 256, 0, s>>>(
             t.s[k]);
         if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -1327,18 +1509,32 @@ static hipError_t project_bwd_bricks(const BwdJob *jobs, int n, hipStream_t s) {
     return hipSuccess;
 }
 
-// A chunked walk needs enough workgroups to fill the chip (a few per CU):
-// a launch with few views (the plain schedule's one) takes shorter chunks,
-// halving them until the column-chunk items reach 1536.
-template <int L, int W, int H, int NW, bool MERGE, int ZC>
+// Chunks of ZC bricks along axis 2 carry the axis-2 pads in LDS; single
+// bricks balance better over the chip.  Measured, whole call at 256x256x128
+// and 512x384 (78 x 2 chunks of 8 per view), chunks of 8 against single
+// bricks: 12 views 2.59 / 2.49 ms, 16 views 3.72 / 3.45, 24 views 4.83 / 4.93,
+// 32 views 6.31 / 6.56 (and 8 views in chunks of 4, as many workgroups as 4
+// views in chunks of 2: 2.25 / 1.69): chunks from 3,072 of them on.
+template <int L, int W, int H, int NW, int ZC>
 static hipError_t project_bwd_chunked(const BwdJob *jobs, int n, hipStream_t s) {
-    if constexpr (ZC > 1) {
-        int64_t items = 0;
-        for (int k = 0; k < n; ++k) items += (int64_t)jobs[k].V * column_items_per_view(jobs[k].g, L, W, H, ZC);
-        if (items < 1536)
-            return project_bwd_chunked<L, W, H, NW, MERGE, ZC / 2>(jobs, n, s);
-    }
-    return project_bwd_bricks<L, W, H, NW, MERGE, ZC>(jobs, n, s);
+    int64_t items = 0;
+    for (int k = 0; k < n; ++k)
+        items += (int64_t)jobs[k].V * column_items_per_view(jobs[k].g, L, W, H, ZC);
+    if (items < 3072) return project_bwd_bricks<L, W, H, NW, true, 1>(jobs, n, s);
+    return project_bwd_bricks<L, W, H, NW, true, ZC>(jobs, n, s);
+}
+
+// The default brick, or a smaller one where the launch has fewer than 1,536
+// of the default (two per slot of the chip: the last round would be nearly
+// empty).  Whole call, 44x20x8 against 32x16x8: 256x256x128 one view (1,248
+// bricks) 374 / 293 us, two views 628 / 586, four 946 / 962; 128x128x64 one view (168)
+// 169 / 120, four views 301 / 266, eight (1,344) 420 / 416, twelve 591 / 578.
+static hipError_t project_bwd_default(const BwdJob *jobs, int n, hipStream_t s) {
+    int64_t items = 0;
+    for (int k = 0; k < n; ++k)
+        items += (int64_t)jobs[k].V * column_items_per_view(jobs[k].g, 44, 20, 8, 1);
+    if (items < 1536) return project_bwd_bricks<32, 16, 8, 8, true, 1>(jobs, n, s);
+    return project_bwd_chunked<44, 20, 8, 8, 8>(jobs, n, s);
 }
 
 hipError_t launch_project_bwd_jobs(const BwdJob *jobs, int n, hipStream_t s) {
@@ -1346,13 +1542,13 @@ hipError_t launch_project_bwd_jobs(const BwdJob *jobs, int n, hipStream_t s) {
     static_assert(NBRICKS == 9, "tune candidates");
     switch (tune_get(KNOB_BACKPROJECT_BRICK)) {
         case 1: return project_bwd_bricks<48, 16, 8, 8, false, 1>(jobs, n, s);
-        case 2: return project_bwd_chunked<32, 16, 8, 8, true, 8>(jobs, n, s);
-        case 3: return project_bwd_chunked<44, 16, 8, 8, true, 8>(jobs, n, s);
-        case 4: return project_bwd_chunked<44, 20, 8, 8, true, 8>(jobs, n, s);
-        case 5: return project_bwd_chunked<40, 20, 8, 8, true, 8>(jobs, n, s);
-        case 6: return project_bwd_chunked<48, 16, 8, 8, true, 8>(jobs, n, s);
-        case 7: return project_bwd_chunked<64, 16, 8, 12, true, 8>(jobs, n, s);
-        case 8: return project_bwd_chunked<52, 16, 8, 8, true, 8>(jobs, n, s);
+        case 2: return project_bwd_chunked<32, 16, 8, 8, 8>(jobs, n, s);
+        case 3: return project_bwd_chunked<44, 16, 8, 8, 8>(jobs, n, s);
+        case 4: return project_bwd_default(jobs, n, s);
+        case 5: return project_bwd_chunked<40, 20, 8, 8, 8>(jobs, n, s);
+        case 6: return project_bwd_chunked<48, 16, 8, 8, 8>(jobs, n, s);
+        case 7: return project_bwd_chunked<64, 16, 8, 12, 8>(jobs, n, s);
+        case 8: return project_bwd_chunked<52, 16, 8, 8, 8>(jobs, n, s);
         default: return project_bwd_bricks<48, 16, 8, 8, true, 1>(jobs, n, s);
     }
 }
@@ -1372,11 +1568,11 @@ hipError_t launch_project_bwd(const float *g_proj, const GridK &g, const ConeK &
     const int round = sum_round(g, V);
     for (int v0 = 0; v0 < V; v0 += round) {
         const int R = std::min(round, V - v0);
-        const BwdJob j{g_proj + (int64_t)v0 * c.nu * c.nv, g, c, angles + v0, R, vols, N, ws,
-                       nullptr};
+        BwdJob j{g_proj + (int64_t)v0 * c.nu * c.nv, g, c, angles + v0, R, vols, N, ws, nullptr};
+        j.sum = g_vol;
+        j.sum_add = v0 > 0;
         hipError_t e = launch_project_bwd_jobs(&j, 1, s);
         if (e != hipSuccess) return e;
-        if ((e = launch_sum_views(vols, N, R, v0 > 0, g_vol, s)) != hipSuccess) return e;
     }
     return hipSuccess;
 }

@@ -85,6 +85,9 @@ _SIGS = {
     "pmf_warp_bwd": ([_P, C.POINTER(PmfGrid), _P, C.c_int, _P, _P, _P, _P, _SZ, _P], C.c_int),
     "pmf_project": ([_P, C.c_int64, C.POINTER(PmfGrid), C.POINTER(PmfCone), _P, C.c_int, _P, _P],
                     C.c_int),
+    "pmf_project_workspace": ([C.POINTER(PmfGrid), C.POINTER(PmfCone), C.c_int, C.c_int64], _SZ),
+    "pmf_project_ws": ([_P, C.c_int64, C.POINTER(PmfGrid), C.POINTER(PmfCone), _P, C.c_int, _P, _P,
+                        _SZ, _P], C.c_int),
     "pmf_project_bwd_workspace": ([C.POINTER(PmfGrid), C.POINTER(PmfCone), C.c_int], _SZ),
     "pmf_project_bwd": ([_P, C.POINTER(PmfGrid), C.POINTER(PmfCone), _P, C.c_int, _P, C.c_int64,
                          _P, _SZ, _P], C.c_int),
@@ -278,6 +281,16 @@ def workspace(nbytes: int, device) -> torch.Tensor:
     return buf
 
 
+def _ws_at_hand(nbytes: int, device) -> Optional[torch.Tensor]:
+    """workspace(), or None where it would have to be allocated while the
+    current stream is captured (for calls that can do without one)."""
+    key = (str(device), torch.cuda.current_stream(device).cuda_stream)
+    buf = _ws_cache.get(key)
+    if (buf is None or buf.numel() < nbytes) and torch.cuda.is_current_stream_capturing():
+        return None
+    return workspace(nbytes, device)
+
+
 def _gauss(mean, scale, quat, value) -> PmfGauss:
     m = mean.shape[0]
     return PmfGauss(_ptr(mean), _ptr(scale), _ptr(quat), _ptr(value), m, value.shape[1])
@@ -378,8 +391,13 @@ def pmf_project(vol, grid: Grid, cone: Cone, angles, shared: Optional[bool] = No
         out = _empty((V, cone.nv, cone.nu), vol.device)
     g = make_grid(grid)
     cn = make_cone(cone)
-    _check(lib().pmf_project(_ptr(vol), stride, C.byref(g), C.byref(cn), _ptr(angles), V, _ptr(out),
-                             _stream()))
+    args = (_ptr(vol), stride, C.byref(g), C.byref(cn), _ptr(angles), V, _ptr(out))
+    nbytes = lib().pmf_project_workspace(C.byref(g), C.byref(cn), V, stride)
+    ws = _ws_at_hand(nbytes, vol.device) if nbytes else None
+    if ws is None:
+        _check(lib().pmf_project(*args, _stream()))
+    else:
+        _check(lib().pmf_project_ws(*args, C.c_void_p(ws.data_ptr()), ws.numel(), _stream()))
     return out
 
 
