@@ -465,9 +465,6 @@ hipError_t launch_accumulate(float *dst, const float *src, int64_t n, hipStream_
 hipError_t launch_absmax(const float *x, int64_t n, uint32_t *out, hipStream_t s);
 // out[0] = max of n unsigned words (float bits of non-negative floats)
 hipError_t launch_max_u32(const uint32_t *in, int n, uint32_t *out, hipStream_t s);
-// dst = fix / fix_scale(*mx) (add: dst += ...)
-hipError_t launch_fix_to_float(const long long *fix, int64_t n, const uint32_t *mx, bool add,
-                               float *dst, hipStream_t s);
 
 // voxelize
 struct VoxPlan {
