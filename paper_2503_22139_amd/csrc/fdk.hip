@@ -14,136 +14,459 @@
 // "quick FDK reconstruction".
 //
 // Layout of the filtered projections (workspace): per view a zero-bordered
-// plane of (nv + 2) x (nu + 2) float4 "quads"; quad (j, c) holds the four
-// bilinear taps qp(j, c), qp(j, c + 1), qp(j + 1, c), qp(j + 1, c + 1) of the
-// padded image qp(j, c) = q[j - 1][c - 1] (0 on the border and beyond).  A
-// back-projection sample clamps its padded pixel coordinates into
+// plane of (nv + 2) x (nu + 3) pairs; pair (j, c) holds qp(j, c), qp(j + 1, c)
+// of the padded image qp(j, c) = q[j - 1][c - 1] (0 on the border and beyond),
+// so the 2 x 2 taps at (j, c) are the 16 contiguous bytes of pairs c and c + 1.
+// A back-projection sample clamps its padded pixel coordinates into
 // [0, nu + 1] x [0, nv + 1] -- any sample that leaves the detector then reads
 // zero taps, exactly as the definition asks -- and fetches its whole 2 x 2
-// neighbourhood with one 16-byte load, with no bounds test.
+// neighbourhood with one 16-byte load, with no bounds test.  (Quads of all
+// four taps, 16 bytes per pixel, took the same load but twice the memory: a
+// workgroup's patch of a view, 45 KB, then missed the 32 KB L1.)
 #include <math.h>
+
+#include <algorithm>
 
 #include "pmf_internal.h"
 
 namespace pmf {
 
-constexpr int FDK_R = 8;               // outputs per lane per chunk: n = b0 + lane + 64 j
-constexpr int FDK_CH = 64 * FDK_R;     // outputs per chunk
-constexpr int FDK_PAD = 64;            // zeros on each side of the row in LDS
 constexpr int BP_ZC = 16;              // voxels along axis 2 per back-projection thread
 
-// First (odd) lag of the tap table and its number of rows.
-static inline int fdk_t0(int nu) { return 1 - 2 * ((nu + 1) / 2); }
-static inline int fdk_taps(int nu) {
-    const int bmax = ((nu - 1) / FDK_CH) * FDK_CH;
-    return (bmax + 63 - fdk_t0(nu)) / 2 + 1;
+// ---------------------------------------------------------------- filter
+// The ramp filter of a row, q[n] = sum_m h[n - m] p~[m] (h[0] = 1 / (4 tau),
+// h[d odd] = -1 / (pi^2 tau d^2)), as a circular convolution of length M =
+// 2^P >= 2 nu - 1 by FFT.  h is even, so its transform is real, and two rows
+// are filtered at once as the real and imaginary parts of one sequence.  All
+// of it is double: for smooth rows on fine pixels q is a small difference of
+// large terms.  The direct sum over odd lags (~nu / 2 double FMAs per output,
+// issue-bound) took 1.6 ms for 660 views of 512x384; the transforms' ~90 per
+// output leave 1.0 ms.
+//
+// Transform: 16 points per thread; in-place decimation-in-frequency passes of
+// radix 16 and a last one of radix 2^(P mod 4) (16 when that is 1), whose
+// digit-reversed output is what the inverse's passes, the same in reverse,
+// take as input -- no reordering, and the last forward pass, the product and
+// the first inverse pass stay in registers.  LDS holds the sequence between
+// passes; its index is XORed so that 16 neighbouring lanes hit distinct 16-byte
+// banks in every pass (measured on the 1024-point passes, strides 64, 4 and 1).
+typedef double2 cplx;
+
+__device__ __forceinline__ cplx cmul(cplx a, cplx b) {
+    return {fma(a.x, b.x, -(a.y * b.y)), fma(a.x, b.y, a.y * b.x)};
+}
+__device__ __forceinline__ cplx cadd(cplx a, cplx b) { return {a.x + b.x, a.y + b.y}; }
+__device__ __forceinline__ cplx csub(cplx a, cplx b) { return {a.x - b.x, a.y - b.y}; }
+
+// In-place DFTs (INV: the conjugate transform, unscaled).  X[k] lands at
+// dft_slot<R>(k).
+template <bool INV>
+__device__ __forceinline__ void dft2(cplx &a, cplx &b) {
+    const cplx s = cadd(a, b);
+    b = csub(a, b);
+    a = s;
+}
+template <bool INV>
+__device__ __forceinline__ void dft4(cplx &a, cplx &b, cplx &c, cplx &d) {
+    const cplx t0 = cadd(a, c), t1 = csub(a, c), t2 = cadd(b, d), u = csub(b, d);
+    const cplx t3 = INV ? cplx{-u.y, u.x} : cplx{u.y, -u.x};      // -+i (b - d)
+    a = cadd(t0, t2);
+    b = cadd(t1, t3);
+    c = csub(t0, t2);
+    d = csub(t1, t3);
+}
+// a * exp(-+2 pi i k / 16)
+template <bool INV, int K>
+__device__ __forceinline__ cplx rot16(cplx a) {
+    constexpr double C[16] = {1.0, 0.92387953251128675613, 0.70710678118654752440,
+                              0.38268343236508977173, 0.0, -0.38268343236508977173,
+                              -0.70710678118654752440, -0.92387953251128675613, -1.0,
+                              -0.92387953251128675613, -0.70710678118654752440,
+                              -0.38268343236508977173, 0.0, 0.38268343236508977173,
+                              0.70710678118654752440, 0.92387953251128675613};
+    if constexpr (K == 0) return a;
+    else return cmul(a, cplx{C[K], INV ? C[(K + 12) % 16] : -C[(K + 12) % 16]});
+}
+template <int R>
+__device__ constexpr int dft_slot(int k) {
+    return R == 16 ? 4 * (k % 4) + k / 4 : R == 8 ? 2 * (k % 4) + k / 4 : k;
+}
+// The 16-point DFT, in two levels of dft4.  HALF: its upper eight inputs are 0
+// (forward) or its upper eight outputs are not wanted (inverse), as in the
+// pass that holds the row: the row fills at most half of the transform.
+template <bool INV, bool HALF>
+__device__ __forceinline__ void dft16(cplx *x) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        if constexpr (HALF && !INV) {
+            const cplx a = x[j], b = x[j + 4], ib = {b.y, -b.x};        // -i b
+            x[j] = cadd(a, b);
+            x[j + 4] = cadd(a, ib);
+            x[j + 8] = csub(a, b);
+            x[j + 12] = csub(a, ib);
+        } else {
+            dft4<INV>(x[j], x[j + 4], x[j + 8], x[j + 12]);
+        }
+    }
+    x[5] = rot16<INV, 1>(x[5]);
+    x[9] = rot16<INV, 2>(x[9]);
+    x[13] = rot16<INV, 3>(x[13]);
+    x[6] = rot16<INV, 2>(x[6]);
+    x[10] = rot16<INV, 4>(x[10]);
+    x[14] = rot16<INV, 6>(x[14]);
+    x[7] = rot16<INV, 3>(x[7]);
+    x[11] = rot16<INV, 6>(x[11]);
+    x[15] = rot16<INV, 9>(x[15]);
+#pragma unroll
+    for (int k = 0; k < 16; k += 4) {
+        if constexpr (HALF && INV) {            // outputs k / 4 and k / 4 + 4 only
+            const cplx a = x[k], b = x[k + 1], c = x[k + 2], d = x[k + 3];
+            const cplx u = csub(b, d);
+            x[k] = cadd(cadd(a, c), cadd(b, d));
+            x[k + 1] = cadd(csub(a, c), cplx{-u.y, u.x});
+        } else {
+            dft4<INV>(x[k], x[k + 1], x[k + 2], x[k + 3]);
+        }
+    }
 }
 
-// Tap table of the odd lags: wt[k][j] = -1 / (pi^2 tau d^2), d = t0 + 2k +
-// 64j -- the weight of input m for output n when n - m = d.  Uniform per
-// loop step of the filter, so the filter reads eight of them with one
-// scalar load.
-__global__ void k_fdk_taps(double tau, int t0, int K, double *__restrict__ wt) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= K * FDK_R) return;
-    const double d = (double)t0 + 2.0 * (i / FDK_R) + 64.0 * (i % FDK_R);
-    wt[i] = -1.0 / (M_PI * M_PI * tau * d * d);
+template <bool INV, int R>
+__device__ __forceinline__ void dft(cplx *x) {
+    if constexpr (R == 2) {
+        dft2<INV>(x[0], x[1]);
+    } else if constexpr (R == 4) {
+        dft4<INV>(x[0], x[1], x[2], x[3]);
+    } else if constexpr (R == 8) {
+        dft4<INV>(x[0], x[2], x[4], x[6]);
+        dft4<INV>(x[1], x[3], x[5], x[7]);
+        x[3] = rot16<INV, 2>(x[3]);
+        x[5] = rot16<INV, 4>(x[5]);
+        x[7] = rot16<INV, 6>(x[7]);
+#pragma unroll
+        for (int k = 0; k < 8; k += 2) dft2<INV>(x[k], x[k + 1]);
+    } else {
+        dft16<INV, false>(x);
+    }
 }
 
-// One wave per (detector row i, view v): cosine-weighted row into LDS (zero
-// borders), the filtered row q[n] = p~[n] / (4 tau) + sum_{n - m odd}
-// wt(n - m) p~[m] with each lane owning the outputs b0 + lane + 64 j (the
-// lag n - m = t + 64 j then depends on the loop counter t and j only), then
-// the row's taps written into the quads of padded rows i + 1 (top pair) and
-// i (bottom pair).  Block row nv writes the plane's zero border rows.  The
-// row and the sums are double: for smooth rows on fine pixels q is a small
-// difference of the centre tap and the long odd-lag sum (they cancel exactly
-// on a constant row), and float sums of ~nu/2 terms lose its low digits.
-// On gfx950 a double FMA issues at the rate of an unpacked float one.
-__global__ __launch_bounds__(64) void k_fdk_filter(const float *__restrict__ proj, pmf_cone_t c,
-                                                   const double *__restrict__ wt, int t0,
-                                                   float4 *__restrict__ qq) {
-    extern __shared__ double lds[];
-    const int nu = c.nu, nv = c.nv, lane = threadIdx.x;
-    const int i = blockIdx.x, v = blockIdx.y;
-    const int P = nu + 2;
-    float4 *const plane = qq + (int64_t)v * (nv + 2) * P;
-    float2 *const half = (float2 *)plane;           // quad e: half[2e] = top, half[2e + 1] = bottom
-    if (i == nv) {
-        for (int col = lane; col < P; col += 64) {
-            half[2 * (int64_t)col] = make_float2(0.0f, 0.0f);
-            half[2 * ((int64_t)nv * P + col) + 1] = make_float2(0.0f, 0.0f);
-            plane[(int64_t)(nv + 1) * P + col] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        }
-        return;
-    }
-    double *const row = lds;                         // row[m + FDK_PAD], m in [-64, nu + 64)
-    // out[n + 1] = q[n]; out[0] = out[nu + 1] = out[nu + 2] = 0 (the last
-    // quad column pairs the border tap nu + 1 with the one beyond it)
-    float *const out = (float *)(lds + nu + 2 * FDK_PAD);
-    const int64_t base = ((int64_t)v * nv + i) * nu;
-    const double b = ((double)i - 0.5 * (nv - 1) + c.off_v) * c.dv;
-    const double sdd = c.sdd, sb = sdd * sdd + b * b;
-    for (int m = lane - FDK_PAD; m < nu + FDK_PAD; m += 64) {
-        double x = 0.0;
-        if (m >= 0 && m < nu) {
-            const double a = ((double)m - 0.5 * (nu - 1) + c.off_u) * c.du;
-            x = (double)proj[base + m] * sdd / sqrt(sb + a * a);
-        }
-        row[m + FDK_PAD] = x;
-    }
-    if (lane == 0) {
-        out[0] = 0.0f;
-        out[nu + 1] = 0.0f;
-        out[nu + 2] = 0.0f;
-    }
-    __syncthreads();
-    const double c0 = (double)c.sdd / (4.0 * (double)c.du * c.sad);
-    for (int b0 = 0; b0 < nu; b0 += FDK_CH) {
-        double acc[FDK_R];
-#pragma unroll
-        for (int j = 0; j < FDK_R; ++j) acc[j] = 0.0;
-        const int ts = (b0 - nu + 1) | 1;            // first odd lag with an input on the row
-        const double *wk = wt + ((ts - t0) >> 1) * FDK_R;
-        const double *xr = row + FDK_PAD + b0 + lane - ts;
-#pragma unroll 4
-        for (int t = ts; t <= b0 + 63; t += 2, wk += FDK_R, xr -= 2) {
-            const double x = *xr;
-#pragma unroll
-            for (int j = 0; j < FDK_R; ++j) acc[j] = fma(wk[j], x, acc[j]);
-        }
-#pragma unroll
-        for (int j = 0; j < FDK_R; ++j) {
-            const int n = b0 + lane + 64 * j;
-            if (n < nu) out[n + 1] = (float)fma(c0, row[FDK_PAD + n], acc[j]);
-        }
-    }
-    __syncthreads();
-    for (int col = lane; col < P; col += 64) {
-        const float2 p = make_float2(out[col], out[col + 1]);
-        half[2 * ((int64_t)(i + 1) * P + col)] = p;
-        half[2 * ((int64_t)i * P + col) + 1] = p;
-    }
+// A copy of u that the compiler cannot connect with it: addresses derived from
+// it are computed where they are used.  (Kept across the passes and the loop
+// over rows they took 150 registers, and with them two waves in three.)
+__device__ __forceinline__ int fresh(int u) {
+    asm volatile("" : "+v"(u));
+    return u;
 }
+
+__device__ __forceinline__ int fft_at(int i) { return i ^ ((i >> 4) & 3) ^ (((i >> 6) & 3) << 2); }
+
+template <int P>
+struct Fft {
+    static constexpr int M = 1 << P;
+    static constexpr int TPP = M / 16;                          // threads per transform
+    static constexpr int NP = P % 4 == 0 ? P / 4 - 1 : P / 4;   // radix-16 passes
+    static constexpr int LR = P % 4 == 0 ? 16 : 1 << (P % 4);   // radix of the last pass
+    static constexpr int G = 16 / LR;                           // its groups per thread
+    static constexpr int THREADS = TPP < 64 ? 64 : TPP;
+    static constexpr int PER = THREADS / TPP;                   // transforms per workgroup
+    static constexpr int WAVES = 2;                             // per SIMD: LDS (16 bytes a point) leaves 2.5
+
+    // first point and spacing of thread u's 16 points in pass p
+    static __device__ __forceinline__ int first(int p, int u) {
+        const int S = (M >> (4 * p)) / 16;
+        return (u / S) * 16 * S + u % S;
+    }
+    static __device__ __forceinline__ constexpr int step(int p) { return (M >> (4 * p)) / 16; }
+
+    // x[k] *= exp(-+2 pi i t k / L), L = M >> 4p the pass's block, t the
+    // thread's place in its sixteenth
+    template <bool INV>
+    static __device__ __forceinline__ void twiddle(cplx *x, const cplx *__restrict__ tw, int p,
+                                                   int u, const int *slot) {
+        const int t = u % step(p);
+        auto root = [&](int k) {
+            const cplx w = tw[(t * k) << (4 * p)];
+            return cplx{w.x, INV ? -w.y : w.y};
+        };
+        auto mul = [&](int k, cplx w) { x[slot[k]] = cmul(x[slot[k]], w); };
+        // four roots read, the others as products (at most two deep)
+        const cplx w1 = root(1), w2 = root(2), w3 = cmul(w1, w2);
+        mul(1, w1);
+        mul(2, w2);
+        mul(3, w3);
+#pragma unroll
+        for (int h = 4; h < 16; h += 4) {
+            const cplx w = h < 12 ? root(h) : cmul(root(4), root(8));
+            mul(h, w);
+            mul(h + 1, cmul(w, w1));
+            mul(h + 2, cmul(w, w2));
+            mul(h + 3, cmul(w, w3));
+        }
+    }
+
+    // x: the thread's points of pass 0 on entry (HALF: x[8..] are 0 and not
+    // read), of the last pass on return (in slot order)
+    template <bool HALF>
+    static __device__ __forceinline__ void forward(cplx *x, cplx *sh, const cplx *__restrict__ tw,
+                                                   int id) {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            const int u = fresh(id);
+            constexpr int slot[16] = {0, 4, 8, 12, 1, 5, 9, 13, 2, 6, 10, 14, 3, 7, 11, 15};
+            const int b = first(p, u), S = step(p);
+            if (p > 0) {
+#pragma unroll
+                for (int j = 0; j < 16; ++j) x[j] = sh[fft_at(b + j * S)];
+            }
+            if (p == 0) dft16<false, HALF>(x);
+            else dft16<false, false>(x);
+            twiddle<false>(x, tw, p, u, slot);
+#pragma unroll
+            for (int k = 0; k < 16; ++k) sh[fft_at(b + k * S)] = x[slot[k]];
+            __syncthreads();
+        }
+        const int u = fresh(id);
+#pragma unroll
+        for (int q = 0; q < G; ++q) {
+            const int b = (u + q * TPP) * LR;
+#pragma unroll
+            for (int j = 0; j < LR; ++j) x[q * LR + j] = sh[fft_at(b + j)];
+            dft<false, LR>(x + q * LR);
+        }
+    }
+
+    // the inverse, from the last pass's points (slot order) to the lower eight
+    // of pass 0's (point j at dft_slot<16>(j))
+    static __device__ __forceinline__ void inverse(cplx *x, cplx *sh, const cplx *__restrict__ tw,
+                                                   int id) {
+        constexpr int same[16] = {0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15};
+        const int ul = fresh(id);
+#pragma unroll
+        for (int q = 0; q < G; ++q) {
+            const int b = (ul + q * TPP) * LR;
+            cplx y[LR];
+#pragma unroll
+            for (int k = 0; k < LR; ++k) y[k] = x[q * LR + dft_slot<LR>(k)];
+            dft<true, LR>(y);
+#pragma unroll
+            for (int j = 0; j < LR; ++j) sh[fft_at(b + j)] = y[dft_slot<LR>(j)];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int p = NP - 1; p >= 0; --p) {
+            const int u = fresh(id);
+            const int b = first(p, u), S = step(p);
+#pragma unroll
+            for (int k = 0; k < 16; ++k) x[k] = sh[fft_at(b + k * S)];
+            twiddle<true>(x, tw, p, u, same);
+            if (p == 0) {
+                dft16<true, true>(x);
+            } else {
+                dft16<true, false>(x);
+#pragma unroll
+                for (int j = 0; j < 16; ++j) sh[fft_at(b + j * S)] = x[dft_slot<16>(j)];
+                __syncthreads();
+            }
+        }
+    }
+};
 
 struct FdkView {
     float ct, st, sx, sy;    // cos, sin, source position SAD (cos, sin)
 };
 
-__global__ void k_fdk_views(const float *__restrict__ angles, int V, float sad,
-                            FdkView *__restrict__ out) {
-    const int v = blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= V) return;
-    const double th = angles[v], ct = cos(th), st = sin(th);
-    out[v] = {(float)ct, (float)st, (float)(sad * ct), (float)(sad * st)};
+// Views' sources, and the FFT's twiddles exp(-2 pi i m / M), m < M.
+__global__ void k_fdk_tables(const float *__restrict__ angles, int V, float sad,
+                             FdkView *__restrict__ out, int M, cplx *__restrict__ tw) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < V) {
+        const double th = angles[i], ct = cos(th), st = sin(th);
+        out[i] = {(float)ct, (float)st, (float)(sad * ct), (float)(sad * st)};
+    }
+    if (i < M) {
+        double s, c;
+        sincospi(2.0 * i / M, &s, &c);
+        tw[i] = {c, -s};
+    }
+}
+
+// 1 / sqrt(s) for a positive s: the hardware's estimate and two Newton steps
+// (each squares its relative error), a few ulp.
+__device__ __forceinline__ double rsqrt_nr(double s) {
+    double y = __builtin_amdgcn_rsq(s);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) y = fma(0.5 * y, fma(-(s * y), y, 1.0), y);
+    return y;
+}
+
+// Transform of the filter's taps over M (real), in the order of the last
+// pass's points.  One workgroup.
+template <int P>
+__global__ __launch_bounds__(Fft<P>::THREADS) void k_fdk_ramp(double tau, int nu,
+                                                              const cplx *__restrict__ tw,
+                                                              double *__restrict__ H) {
+    using F = Fft<P>;
+    __shared__ cplx sh[F::PER * F::M];
+    const int u = threadIdx.x % F::TPP;
+    cplx x[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+        const int m = F::first(0, u) + j * F::step(0);
+        const int d = m < nu ? m : F::M - m;            // lag; |lag| < nu or no tap
+        const double dd = (double)d;
+        x[j] = {d >= nu ? 0.0 : d == 0 ? 0.25 / tau : (d & 1) ? -1.0 / (M_PI * M_PI * tau * dd * dd) : 0.0,
+                0.0};
+    }
+    F::template forward<false>(x, sh + (threadIdx.x / F::TPP) * F::M, tw, u);
+    if ((int)threadIdx.x >= F::TPP) return;
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+        H[(u + (i / F::LR) * F::TPP) * F::LR + i % F::LR] = x[i].x / (double)F::M;
+}
+
+// Filters FDK_ROWS rows of one view per transform slot, two at a time, and
+// writes them into the padded plane's pairs: padded row i + 1 holds rows i and
+// i + 1, so a row is kept until the next one is there, and only the slot's
+// first and last padded rows are written by halves (the neighbours write the
+// others).  The plane's border columns and rows are written too.
+constexpr int FDK_ROWS = 8;
+
+template <int P>
+__global__ __launch_bounds__(Fft<P>::THREADS)
+__attribute__((amdgpu_waves_per_eu(Fft<P>::WAVES))) void k_fdk_filter(const float *__restrict__ proj,
+                                                                pmf_cone_t c, double tau,
+                                                                const cplx *__restrict__ tw,
+                                                                const double *__restrict__ H,
+                                                                float2 *__restrict__ qq) {
+    using F = Fft<P>;
+    __shared__ cplx smem[F::PER * F::M];
+    const int nu = c.nu, nv = c.nv, pitch = nu + 3;
+    const int u = threadIdx.x % F::TPP, v = blockIdx.y;
+    cplx *const sh = smem + (threadIdx.x / F::TPP) * F::M;
+    const int r0 = ((int)blockIdx.x * F::PER + (int)threadIdx.x / F::TPP) * FDK_ROWS;
+    const int r1 = min(r0 + FDK_ROWS, nv);          // r0 >= nv: the slot only keeps the barriers
+    float2 *const plane = qq + (int64_t)v * (nv + 2) * pitch;
+    const double sdd = c.sdd;
+    constexpr int S = F::step(0);
+    // padded row j, columns 1 .. nu at this thread's points, and the border
+    // columns; HALF: 0 both of a pair, 1 the first, 2 the second
+    auto store = [&](int j, int half, const float *top, const float *bot) {
+        float2 *const row = plane + (int64_t)j * pitch;
+        const int b0 = F::first(0, fresh(u));
+        auto put = [&](int col, float a, float b) {
+            if (half == 0) row[col] = make_float2(a, b);
+            else if (half == 1) row[col].x = a;
+            else row[col].y = b;
+        };
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int n = b0 + k * S;
+            if (n < nu) put(n + 1, top[k], bot[k]);
+        }
+        if (u < 3) put(u == 0 ? 0 : nu + u, 0.0f, 0.0f);
+    };
+    float prev[8], zero[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) prev[k] = zero[k] = 0.0f;
+#pragma unroll 1
+    for (int q = 0; q < FDK_ROWS; q += 2) {
+        const int i = r0 + q;
+        const double ba = ((double)i - 0.5 * (nv - 1) + c.off_v) * c.dv;
+        const double bb = ((double)(i + 1) - 0.5 * (nv - 1) + c.off_v) * c.dv;
+        const double sa = sdd * sdd + ba * ba, sb = sdd * sdd + bb * bb;
+        const float *row = proj + ((int64_t)v * nv + i) * nu;
+        auto pixel = [&](int n) {                   // cosine-weighted rows i, i + 1
+            const double a = ((double)n - 0.5 * (nu - 1) + c.off_u) * c.du, aa = a * a;
+            return cplx{i < r1 ? (double)row[n] * (sdd * rsqrt_nr(sa + aa)) : 0.0,
+                        i + 1 < r1 ? (double)row[nu + n] * (sdd * rsqrt_nr(sb + aa)) : 0.0};
+        };
+        cplx x[16];
+        bool odd = false;
+        const int b0 = F::first(0, fresh(u));
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {           // n < M / 2 covers the row
+            const int n = b0 + k * S;
+            x[k] = n < nu ? pixel(n) : cplx{0.0, 0.0};
+            odd = odd || !isfinite(x[k].x) || !isfinite(x[k].y);
+        }
+        float qa[8], qb[8];
+        if (__syncthreads_or(odd)) {
+            // a value that is not finite would spread over both rows of the
+            // transform: the sum over odd lags itself
+            for (int k = 0; k < 8; ++k) {
+                const int n = b0 + k * S;
+                if (n >= nu) continue;
+                const cplx p = pixel(n);
+                cplx t = {0.25 / tau * p.x, 0.25 / tau * p.y};
+                for (int m = (n + 1) & 1; m < nu; m += 2) {
+                    const double w = -1.0 / (M_PI * M_PI * tau * (double)(n - m) * (double)(n - m));
+                    const cplx y = pixel(m);
+                    t.x = fma(w, y.x, t.x);
+                    t.y = fma(w, y.y, t.y);
+                }
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    qa[j] = j == k ? (float)t.x : qa[j];
+                    qb[j] = j == k ? (float)t.y : qb[j];
+                }
+            }
+        } else {
+            F::template forward<true>(x, sh, tw, u);
+            const int uh = fresh(u);
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                const double h = H[(uh + (k / F::LR) * F::TPP) * F::LR + k % F::LR];
+                x[k].x *= h;
+                x[k].y *= h;
+            }
+            F::inverse(x, sh, tw, u);
+            __syncthreads();                        // sh is free for the next two rows
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                qa[k] = (float)x[dft_slot<16>(k)].x;
+                qb[k] = (float)x[dft_slot<16>(k)].y;
+            }
+        }
+        if (i < r1) {
+            store(i, q > 0 || i == 0 ? 0 : 2, prev, qa);
+            if (i + 1 < r1) store(i + 1, 0, qa, qb);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) prev[k] = i + 1 < r1 ? qb[k] : qa[k];
+        }
+    }
+    if (r0 >= nv) return;
+    store(r1, r1 == nv ? 0 : 1, prev, zero);
+    if (r1 == nv) store(nv + 1, 0, zero, zero);
+}
+
+// Smallest transform that holds a row's linear convolution.
+static int fdk_log2(int nu) {
+    int P = 6;
+    while ((1 << P) < 2 * nu - 1) ++P;
+    return P;
+}
+
+template <int P>
+static hipError_t fdk_filter(const float *proj, const pmf_cone_t &c, int V, double tau,
+                             const cplx *tw, double *H, float2 *qq, hipStream_t s) {
+    using F = Fft<P>;
+    k_fdk_ramp<P><<<1, F::THREADS, 0, s>>>(tau, c.nu, tw, H);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const int slots = (c.nv + FDK_ROWS - 1) / FDK_ROWS;
+    ProfScope prof_("fdk_filter", s);
+    k_fdk_filter<P><<<dim3((unsigned)((slots + F::PER - 1) / F::PER), (unsigned)V), F::THREADS, 0, s>>>(
+        proj, c, tau, tw, H, qq);
+    return hipGetLastError();
 }
 
 struct FdkBp {
     float sad, inv_tu, inv_tv, cu, cv, umax, vmax, wsc, hz;
-    unsigned row_bytes;      // (nu + 2) * 16
+    unsigned row_bytes;      // (nu + 3) * 8
     int64_t plane_bytes;     // (nv + 2) * row_bytes
     int tx, ty;              // 16 x 16 column tiles along axes 0, 1
 };
+
+typedef float taps __attribute__((ext_vector_type(4), aligned(8)));
 
 // Workgroup = 16 x 16 voxel columns (each wave an 8 x 8 patch, so one wave's
 // samples of a view fall on a few neighbouring detector cache lines) x
@@ -153,7 +476,13 @@ struct FdkBp {
 // numbered so that each XCD gets a contiguous slab along axis 2 (one band of
 // detector rows in every view).  Threads past the grid edge compute on
 // clamped positions and store nothing.
-__global__ __launch_bounds__(256, 8) void k_fdk_bp(const float4 *__restrict__ qq, FdkBp p,
+// Bound by the L1: a load of 64 lanes takes a tag lookup per cache line that
+// each four lanes touch and two cycles more per miss (22.3 lookups and 2.6
+// misses: 4.31 ms for 660 views onto 256x256x128; with lanes row by row
+// instead of in Morton order 24.6 lookups, 4.37 ms; with 16-byte quads per
+// pixel 4.71 ms).  Lanes along the rays (views in two groups) measured no
+// fewer lookups.
+__global__ __launch_bounds__(256, 8) void k_fdk_bp(const float2 *__restrict__ qq, FdkBp p,
                                                 const FdkView *__restrict__ views, int V, GridK g,
                                                 float *__restrict__ vol) {
     const int b = xcd_block(blockIdx.x, gridDim.x);
@@ -161,8 +490,10 @@ __global__ __launch_bounds__(256, 8) void k_fdk_bp(const float4 *__restrict__ qq
     const int zc = b / tiles, tile = b - zc * tiles;
     const int tyi = tile / p.tx, txi = tile - tyi * p.tx;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int ix = txi * 16 + (w & 1) * 8 + (lane & 7);
-    const int iy = tyi * 16 + (w >> 1) * 8 + (lane >> 3);
+    // the lane's column of the wave's 8 x 8, in Morton order
+    const int mx = (lane & 1) | ((lane >> 1) & 2) | ((lane >> 2) & 4);
+    const int my = ((lane >> 1) & 1) | ((lane >> 2) & 2) | ((lane >> 3) & 4);
+    const int ix = txi * 16 + (w & 1) * 8 + mx, iy = tyi * 16 + (w >> 1) * 8 + my;
     const int iz0 = zc * BP_ZC;
     const float x = g.c0[0] + min(ix, g.n[0] - 1) * g.h[0];
     const float y = g.c0[1] + min(iy, g.n[1] - 1) * g.h[1];
@@ -179,7 +510,7 @@ __global__ __launch_bounds__(256, 8) void k_fdk_bp(const float4 *__restrict__ qq
         const float r = p.sad / U;
         const float fu = __builtin_amdgcn_fmed3f(fmaf(r * tu, p.inv_tu, p.cu), 0.0f, p.umax);
         const float wu = __builtin_amdgcn_fractf(fu);
-        const unsigned colb = (unsigned)(int)fu * 16u;
+        const unsigned colb = (unsigned)(int)fu * 8u;
         const float wr2 = p.wsc * r * r;
         const float rv = r * p.inv_tv;
         const float fv0 = fmaf(rv, z0, p.cv), dfv = rv * p.hz;
@@ -188,8 +519,9 @@ __global__ __launch_bounds__(256, 8) void k_fdk_bp(const float4 *__restrict__ qq
             const float fv = __builtin_amdgcn_fmed3f(fmaf((float)k, dfv, fv0), 0.0f, p.vmax);
             const float wv = __builtin_amdgcn_fractf(fv);
             const unsigned off = __umul24((unsigned)(int)fv, p.row_bytes) + colb;
-            const float4 e = *(const float4 *)(pl + off);
-            const float top = fmaf(wu, e.y - e.x, e.x), bot = fmaf(wu, e.w - e.z, e.z);
+            // qp(j, c), (j + 1, c), (j, c + 1), (j + 1, c + 1)
+            const taps e = *(const taps *)(pl + off);
+            const float top = fmaf(wu, e.z - e.x, e.x), bot = fmaf(wu, e.w - e.y, e.y);
             acc[k] = fmaf(wr2, fmaf(wv, bot - top, top), acc[k]);
         }
     }
@@ -201,39 +533,43 @@ __global__ __launch_bounds__(256, 8) void k_fdk_bp(const float4 *__restrict__ qq
 }
 
 static size_t fdk_plane_bytes(const pmf_cone_t &c) {
-    return sizeof(float4) * (size_t)(c.nu + 2) * (c.nv + 2);
+    return sizeof(float2) * (size_t)(c.nu + 3) * (c.nv + 2);
 }
 
+// Workspace: the views' planes, the views, the FFT's twiddles and the ramp's
+// transform.
 size_t fdk_workspace(const pmf_cone_t &c, int V) {
+    const size_t M = (size_t)1 << fdk_log2(c.nu);
     return align256(fdk_plane_bytes(c) * V) + align256(sizeof(FdkView) * (size_t)V) +
-           align256(sizeof(double) * FDK_R * (size_t)fdk_taps(c.nu));
-}
-
-size_t fdk_filter_lds(const pmf_cone_t &c) {
-    return sizeof(double) * (size_t)(c.nu + 2 * FDK_PAD) + sizeof(float) * (size_t)(c.nu + 3);
+           align256(sizeof(cplx) * M) + align256(sizeof(double) * M);
 }
 
 hipError_t launch_fdk(const float *proj, const pmf_cone_t &c, const float *angles, int V,
                       const GridK &g, float *vol, void *ws, hipStream_t s) {
     char *w = (char *)ws;
-    float4 *qq = (float4 *)w;
+    float2 *qq = (float2 *)w;
     w += align256(fdk_plane_bytes(c) * V);
     FdkView *views = (FdkView *)w;
     w += align256(sizeof(FdkView) * (size_t)V);
-    double *wt = (double *)w;
+    const int P = fdk_log2(c.nu), M = 1 << P;
+    cplx *tw = (cplx *)w;
+    w += align256(sizeof(cplx) * (size_t)M);
+    double *H = (double *)w;
     const double tau = (double)c.du * c.sad / c.sdd;
-    const int t0 = fdk_t0(c.nu), K = fdk_taps(c.nu);
     hipError_t e;
-    k_fdk_taps<<<(unsigned)((K * FDK_R + 255) / 256), 256, 0, s>>>(tau, t0, K, wt);
+    k_fdk_tables<<<(unsigned)((std::max(V, M) + 255) / 256), 256, 0, s>>>(angles, V, c.sad, views, M, tw);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    k_fdk_views<<<(unsigned)((V + 255) / 256), 256, 0, s>>>(angles, V, c.sad, views);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    {
-        ProfScope prof_("fdk_filter", s);
-        k_fdk_filter<<<dim3((unsigned)c.nv + 1, (unsigned)V), 64, fdk_filter_lds(c), s>>>(proj, c, wt,
-                                                                                         t0, qq);
+    switch (P) {
+        case 6: e = fdk_filter<6>(proj, c, V, tau, tw, H, qq, s); break;
+        case 7: e = fdk_filter<7>(proj, c, V, tau, tw, H, qq, s); break;
+        case 8: e = fdk_filter<8>(proj, c, V, tau, tw, H, qq, s); break;
+        case 9: e = fdk_filter<9>(proj, c, V, tau, tw, H, qq, s); break;
+        case 10: e = fdk_filter<10>(proj, c, V, tau, tw, H, qq, s); break;
+        case 11: e = fdk_filter<11>(proj, c, V, tau, tw, H, qq, s); break;
+        case 12: e = fdk_filter<12>(proj, c, V, tau, tw, H, qq, s); break;
+        default: e = fdk_filter<13>(proj, c, V, tau, tw, H, qq, s); break;   // rows of at most 4096
     }
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if (e != hipSuccess) return e;
     FdkBp p;
     p.sad = c.sad;
     p.inv_tu = (float)((double)c.sdd / ((double)c.du * c.sad));
@@ -244,7 +580,7 @@ hipError_t launch_fdk(const float *proj, const pmf_cone_t &c, const float *angle
     p.vmax = (float)(c.nv + 1);
     p.wsc = (float)(M_PI / V);
     p.hz = g.h[2];
-    p.row_bytes = 16u * (unsigned)(c.nu + 2);
+    p.row_bytes = 8u * (unsigned)(c.nu + 3);
     p.plane_bytes = (int64_t)fdk_plane_bytes(c);
     p.tx = (g.n[0] + 15) / 16;
     p.ty = (g.n[1] + 15) / 16;
