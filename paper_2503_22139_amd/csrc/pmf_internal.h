@@ -473,6 +473,7 @@ struct VoxPlan {
     int64_t ntiles;
     int64_t cap;       // capacity of the (tile, gaussian) list
     int maxtiles;      // Gaussians overlapping more tiles go to the large list
+    int nch;           // chunks of the binning
 };
 VoxPlan vox_plan(int64_t m, int c, const GridK &g);
 size_t vox_workspace(const VoxPlan &p, int64_t m);

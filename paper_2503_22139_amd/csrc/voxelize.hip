@@ -2,7 +2,7 @@
 //
 // Forward: tile-binned.  Each Gaussian's truncation ellipsoid is bounded by
 // a box of voxels; Gaussians are binned into the tiles their box overlaps
-// (count, scan, fill).  One workgroup owns a tile.  One-channel sets (the
+// (a counting sort).  One workgroup owns a tile.  One-channel sets (the
 // reference, ~150 Gaussians per tile) are splatted: the waves lay the
 // (Gaussian, column) pairs of batches of the tile's Gaussians over their
 // lanes and add into an LDS copy of the tile in fixed point.  Three- and
@@ -20,6 +20,8 @@
 // reduces them across the wave; one lane per Gaussian applies the chain rule
 // through Sigma = R diag(s^2) R^T and the quaternion normalisation.
 #include <math.h>
+
+#include <algorithm>
 
 #include "pmf_internal.h"
 
@@ -121,187 +123,222 @@ __device__ __forceinline__ bool far_from_grid(const float *__restrict__ mean,
 }
 
 // ---------------------------------------------------------------- binning
-// Tile counters sit one per 128-byte line: the count pass's atomics are
-// device-scope and contend per line, and a packed array puts every tile's
-// atomics on a few dozen lines.  Each atomic's old value is the pair's place
-// in its tile's list, so the fill pass writes the lists without atomics.
-constexpr int CNT_STRIDE = 32;
+// A counting sort of the (Gaussian, tile) pairs by tile.  The set is cut into
+// chunks, one workgroup each: k_vox_bin builds the chunk's Gaussians and counts
+// its pairs per tile in LDS (an atomic's old value is the pair's place among
+// the chunk's), k_vox_chunks turns the chunks' counts of a tile into places
+// and totals, and k_vox_fill scans the totals and writes each pair to its
+// place.  (Counting in global memory took a device-scope atomic per pair, which
+// contend per cache line: 100 + 19 us of 150 for the 200k set, and eight
+// launches; now FIG_BIN.)  Counts are held for BIN_W tiles at a time; a grid of
+// more walks its Gaussians again for each further window.
+struct VoxTiles {                      // a set's tiles and chunks
+    int T0, T1, T2, nt1, nt2, ntiles;
+    int maxtiles;                      // more tiles than this: a large Gaussian
+    int64_t chunk;                     // Gaussians per chunk
+};
 
-__global__ __launch_bounds__(256) void k_vox_prep(pmf_gauss_t gs, GridK g, float k, int T0,
-                                                  int T1, int T2, int nt1, int nt2, int maxtiles,
-                                                  GaussK *__restrict__ rec,
-                                                  int32_t *__restrict__ tile_count,
-                                                  int32_t *__restrict__ slot,
-                                                  int32_t *__restrict__ is_large) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= gs.m) return;
-    is_large[i] = 0;
-    if (far_from_grid(gs.mean, gs.scale, i, k, g)) {
-        GaussK r = {};
-        r.lo0 = r.lo1 = r.lo2 = 1;            // empty box: no tile, no voxel
-        rec[i] = r;
-        return;
-    }
-    GaussFull G;
-    gauss_full(gs.mean, gs.scale, gs.quat, i, k, g, G);
-    GaussK r;
-    for (int a = 0; a < 3; ++a) r.mu[a] = G.mu[a];
-    r.a00 = G.A[0][0];
-    r.a01 = G.A[0][1];
-    r.a02 = G.A[0][2];
-    r.a11 = G.A[1][1];
-    r.a12 = G.A[1][2];
-    r.a22 = G.A[2][2];
-    r.lo0 = G.lo[0];
-    r.lo1 = G.lo[1];
-    r.lo2 = G.lo[2];
-    r.hi0 = G.hi[0];
-    r.hi1 = G.hi[1];
-    r.hi2 = G.hi[2];
-    r.pad0 = r.pad1 = 0;
-    rec[i] = r;
-    if (G.lo[0] > G.hi[0] || G.lo[1] > G.hi[1] || G.lo[2] > G.hi[2]) return;
-    const int t0a = G.lo[0] / T0, t0b = G.hi[0] / T0;
-    const int t1a = G.lo[1] / T1, t1b = G.hi[1] / T1;
-    const int t2a = G.lo[2] / T2, t2b = G.hi[2] / T2;
-    const int64_t cnt = (int64_t)(t0b - t0a + 1) * (t1b - t1a + 1) * (t2b - t2a + 1);
-    if (cnt > maxtiles) {
-        is_large[i] = 1;
-        return;
-    }
-    // the count's old value is this pair's place in the tile's list: kept
-    // (pair q of Gaussian i at slot[q m + i]) so the fill needs no atomics
-    int q = 0;
-    for (int a = t0a; a <= t0b; ++a)
-        for (int b = t1a; b <= t1b; ++b)
-            for (int c = t2a; c <= t2b; ++c, ++q)
-                slot[(int64_t)q * gs.m + i] =
-                    atomicAdd(&tile_count[((a * nt1 + b) * nt2 + c) * CNT_STRIDE], 1);
+constexpr int BIN_W = 12288;           // tiles per window (48 KB of LDS)
+constexpr int BIN_T = 512;             // threads per chunk
+
+// A Gaussian's tile box [t*a, t*b] in record order; the pairs are numbered
+// q = 0.. with axis 2 fastest.
+struct TileBox {
+    int a0, b0, a1, b1, a2, b2;
+    int64_t count;                     // 0: no voxel
+};
+__device__ __forceinline__ TileBox tile_box(const GaussK &r, int T0, int T1, int T2) {
+    TileBox t{};
+    if (r.lo0 > r.hi0 || r.lo1 > r.hi1 || r.lo2 > r.hi2) return t;
+    t.a0 = r.lo0 / T0;
+    t.b0 = r.hi0 / T0;
+    t.a1 = r.lo1 / T1;
+    t.b1 = r.hi1 / T1;
+    t.a2 = r.lo2 / T2;
+    t.b2 = r.hi2 / T2;
+    t.count = (int64_t)(t.b0 - t.a0 + 1) * (t.b1 - t.a1 + 1) * (t.b2 - t.a2 + 1);
+    return t;
 }
 
-// Exclusive scan of n counts (CNT_STRIDE apart) by one workgroup of 1024
-// threads: off[0..n] (dense).  Each thread takes a run of up to SCAN_U counts (loaded
-// together and kept in registers for the second pass); the block's scan is
-// a DPP scan per wave plus the wave totals.
-constexpr int SCAN_U = 8;
-__global__ __launch_bounds__(1024) void k_scan(const int32_t *__restrict__ cnt, int64_t n,
-                                               int32_t *__restrict__ off) {
-    __shared__ int32_t wsum[16];
-    const int64_t per = (n + 1023) / 1024;
-    const int64_t b = threadIdx.x * per;
-    const int64_t e = b + per < n ? b + per : n;
-    const bool few = per <= SCAN_U;       // uniform
-    int32_t v[SCAN_U];
-    int32_t s = 0;
-    if (few) {
-#pragma unroll
-        for (int k = 0; k < SCAN_U; ++k) v[k] = b + k < e ? cnt[(b + k) * CNT_STRIDE] : 0;
-#pragma unroll
-        for (int k = 0; k < SCAN_U; ++k) s += v[k];
-    } else {
-        for (int64_t i = b; i < e; ++i) s += cnt[i * CNT_STRIDE];
-    }
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int32_t incl = wave_incl_sum(s);
-    if (lane == 63) wsum[wave] = incl;
-    __syncthreads();
-    int32_t base = 0;
-    for (int w = 0; w < wave; ++w) base += wsum[w];
-    int32_t run = base + incl - s;
-    if (few) {
-#pragma unroll
-        for (int k = 0; k < SCAN_U; ++k) {
-            if (b + k < e) {
-                off[b + k] = run;
-                run += v[k];
+// Calls f(tile - w0, q) for the box's pairs with a tile in [w0, w0 + BIN_W).
+template <class F>
+__device__ __forceinline__ void each_pair(const TileBox &t, const VoxTiles &p, int w0, F &&f) {
+    int q = 0;
+    for (int a = t.a0; a <= t.b0; ++a)
+        for (int b = t.a1; b <= t.b1; ++b)
+            for (int c = t.a2; c <= t.b2; ++c, ++q) {
+                const int w = (a * p.nt1 + b) * p.nt2 + c - w0;
+                if (w >= 0 && w < BIN_W) f(w, q);
+            }
+}
+
+__global__ __launch_bounds__(BIN_T) void k_vox_bin(pmf_gauss_t gs, GridK g, float k, VoxTiles p,
+                                                   GaussK *__restrict__ rec,
+                                                   int32_t *__restrict__ part,
+                                                   int32_t *__restrict__ slot,
+                                                   int32_t *__restrict__ nlarge) {
+    extern __shared__ int32_t hist[];
+    __shared__ int32_t nl;
+    const int64_t i0 = (int64_t)blockIdx.x * p.chunk, i1 = min(i0 + p.chunk, gs.m);
+    int32_t *const row = part + (int64_t)blockIdx.x * p.ntiles;
+    if (threadIdx.x == 0) nl = 0;
+    for (int w0 = 0; w0 < p.ntiles; w0 += BIN_W) {
+        const int nw = min(BIN_W, p.ntiles - w0);
+        for (int t = threadIdx.x; t < nw; t += BIN_T) hist[t] = 0;
+        __syncthreads();
+        for (int64_t i = i0 + threadIdx.x; i < i1; i += BIN_T) {
+            GaussK r = {};
+            if (w0 > 0) {
+                r = rec[i];
+            } else {
+                if (far_from_grid(gs.mean, gs.scale, i, k, g)) {
+                    r.lo0 = r.lo1 = r.lo2 = 1;        // empty box: no tile, no voxel
+                } else {
+                    GaussFull G;
+                    gauss_full(gs.mean, gs.scale, gs.quat, i, k, g, G);
+                    for (int a = 0; a < 3; ++a) r.mu[a] = G.mu[a];
+                    r.a00 = G.A[0][0];
+                    r.a01 = G.A[0][1];
+                    r.a02 = G.A[0][2];
+                    r.a11 = G.A[1][1];
+                    r.a12 = G.A[1][2];
+                    r.a22 = G.A[2][2];
+                    r.lo0 = G.lo[0];
+                    r.lo1 = G.lo[1];
+                    r.lo2 = G.lo[2];
+                    r.hi0 = G.hi[0];
+                    r.hi1 = G.hi[1];
+                    r.hi2 = G.hi[2];
+                }
+                rec[i] = r;
+            }
+            const TileBox t = tile_box(r, p.T0, p.T1, p.T2);
+            if (t.count > p.maxtiles) {
+                if (w0 == 0) atomicAdd(&nl, 1);
+            } else if (t.count > 0) {
+                each_pair(t, p, w0, [&](int w, int q) {
+                    slot[(int64_t)q * gs.m + i] = atomicAdd(&hist[w], 1);
+                });
             }
         }
-    } else {
-        for (int64_t i = b; i < e; ++i) {
-            off[i] = run;
-            run += cnt[i * CNT_STRIDE];
-        }
+        __syncthreads();
+        for (int t = threadIdx.x; t < nw; t += BIN_T) row[w0 + t] = hist[t];
+        __syncthreads();
     }
-    if (threadIdx.x == 1023) off[n] = base + incl;
+    if (threadIdx.x == 0) nlarge[1 + blockIdx.x] = nl;
 }
 
-// The large Gaussians in ascending index order (so that every tile adds
-// them in one fixed order), by a three-step compaction: per block of 256
-// Gaussians the count of large ones, an exclusive scan of the counts (one
-// workgroup), and per block the positions of its large ones (ballots).
-__global__ __launch_bounds__(256) void k_large_count(const int32_t *__restrict__ is_large,
-                                                     int64_t m, int32_t *__restrict__ blk) {
-    __shared__ int32_t part[4];
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const bool f = i < m && is_large[i];
-    const unsigned long long b = __ballot(f);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = __popcll(b);
-    __syncthreads();
-    if (threadIdx.x == 0) blk[blockIdx.x] = part[0] + part[1] + part[2] + part[3];
-}
-
-// In place: blk[0..n) counts -> exclusive offsets; *total = their sum.
-__global__ __launch_bounds__(1024) void k_scan_counts(int32_t *__restrict__ blk, int n,
-                                                      int32_t *__restrict__ total) {
-    __shared__ int32_t part[1024];
-    const int per = (n + 1023) / 1024;
-    const int b = threadIdx.x * per;
-    const int e = min(b + per, n);
+// Per tile: the chunks' counts -> the places of their first pairs in the tile's
+// list, in place, and the tile's total.  A workgroup takes 64 tiles (a lane
+// each), its four waves a quarter of the chunks each.
+__global__ __launch_bounds__(256) void k_vox_chunks(int32_t *__restrict__ part, int ntiles, int nch,
+                                                    int32_t *__restrict__ total) {
+    __shared__ int32_t sums[4][64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int t = blockIdx.x * 64 + lane;
+    const int per = (nch + 3) / 4, c0 = min(w * per, nch), c1 = min(c0 + per, nch);
     int32_t s = 0;
-    for (int i = b; i < e; ++i) s += blk[i];
-    part[threadIdx.x] = s;
+    if (t < ntiles) {
+#pragma unroll 16
+        for (int c = c0; c < c1; ++c) s += part[(int64_t)c * ntiles + t];
+    }
+    sums[w][lane] = s;
     __syncthreads();
-    for (int o = 1; o < 1024; o <<= 1) {
-        const int32_t t = threadIdx.x >= (unsigned)o ? part[threadIdx.x - o] : 0;
-        __syncthreads();
-        part[threadIdx.x] += t;
-        __syncthreads();
+    if (t >= ntiles) return;
+    int32_t run = 0;
+    for (int k = 0; k < w; ++k) run += sums[k][lane];
+#pragma unroll 16
+    for (int c = c0; c < c1; ++c) {
+        const int32_t x = part[(int64_t)c * ntiles + t];
+        part[(int64_t)c * ntiles + t] = run;
+        run += x;
     }
-    int32_t run = part[threadIdx.x] - s;
-    for (int i = b; i < e; ++i) {
-        const int32_t c = blk[i];
-        blk[i] = run;
-        run += c;
-    }
-    if (threadIdx.x == 1023) *total = part[1023];
+    if (w == 3) total[t] = run;
 }
 
-__global__ __launch_bounds__(256) void k_large_fill(const int32_t *__restrict__ is_large,
-                                                    int64_t m, const int32_t *__restrict__ blk,
+// Exclusive scan of v over the workgroup (BIN_T threads), the sum added to carry.
+__device__ __forceinline__ int32_t block_excl_sum(int32_t v, int32_t *wsum, int32_t &carry) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int32_t incl = wave_incl_sum(v);
+    if (lane == 63) wsum[w] = incl;
+    __syncthreads();
+    int32_t base = carry, sum = 0;
+#pragma unroll
+    for (int k = 0; k < BIN_T / 64; ++k) {
+        if (k < w) base += wsum[k];
+        sum += wsum[k];
+    }
+    carry += sum;
+    __syncthreads();
+    return base + incl - v;
+}
+
+// Each chunk scans the tiles' totals (the first one stores them as the lists'
+// offsets) and writes its pairs to their places, and its large Gaussians, in
+// ascending order, to the large list.
+__global__ __launch_bounds__(BIN_T) void k_vox_fill(int64_t m, const GaussK *__restrict__ rec,
+                                                    VoxTiles p, const int32_t *__restrict__ part,
+                                                    const int32_t *__restrict__ total,
+                                                    const int32_t *__restrict__ slot,
+                                                    int32_t *__restrict__ nlarge,
+                                                    int32_t *__restrict__ off,
+                                                    int32_t *__restrict__ list,
                                                     int32_t *__restrict__ large) {
-    __shared__ int32_t part[4];
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const bool f = i < m && is_large[i];
-    const unsigned long long b = __ballot(f);
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    if (lane == 0) part[w] = __popcll(b);
+    extern __shared__ int32_t base[];
+    __shared__ int32_t wsum[BIN_T / 64];
+    const int64_t i0 = (int64_t)blockIdx.x * p.chunk, i1 = min(i0 + p.chunk, m);
+    const int32_t *const row = part + (int64_t)blockIdx.x * p.ntiles;
+    const bool first = blockIdx.x == 0;
+    int32_t carry = 0;
+    for (int w0 = 0; w0 < p.ntiles; w0 += BIN_W) {
+        const int nw = min(BIN_W, p.ntiles - w0);
+        for (int t0 = 0; t0 < nw; t0 += 4 * BIN_T) {
+            // four neighbouring tiles per thread
+            const int t = t0 + 4 * (int)threadIdx.x;
+            int32_t v[4], s = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                v[k] = t + k < nw ? total[w0 + t + k] : 0;
+                s += v[k];
+            }
+            int32_t o = block_excl_sum(s, wsum, carry);
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (t + k < nw) {
+                    if (first) off[w0 + t + k] = o;
+                    base[t + k] = o + row[w0 + t + k];
+                    o += v[k];
+                }
+        }
+        __syncthreads();
+        for (int64_t i = i0 + threadIdx.x; i < i1; i += BIN_T) {
+            const TileBox t = tile_box(rec[i], p.T0, p.T1, p.T2);
+            if (t.count == 0 || t.count > p.maxtiles) continue;
+            each_pair(t, p, w0, [&](int w, int q) {
+                list[base[w] + slot[(int64_t)q * m + i]] = (int32_t)i;
+            });
+        }
+        __syncthreads();
+    }
+    if (first && threadIdx.x == 0) off[p.ntiles] = carry;
+    // the large list: this chunk's place in it, then its entries by ballots
+    int32_t before = 0, all = 0;
+    for (int c0 = 0; c0 < (int)gridDim.x; c0 += BIN_T) {
+        const int c = c0 + (int)threadIdx.x;
+        const int32_t x = c < (int)gridDim.x ? nlarge[1 + c] : 0;
+        const int32_t e = block_excl_sum(x, wsum, all);
+        if (c == (int)blockIdx.x) base[0] = e;      // the pairs are written: base is free
+    }
     __syncthreads();
-    int base = blk[blockIdx.x];
-    for (int k = 0; k < w; ++k) base += part[k];
-    const int below = __popcll(b & ((1ull << lane) - 1ull));
-    if (f) large[base + below] = (int32_t)i;
-}
-
-__global__ __launch_bounds__(256) void k_vox_fill(int64_t m, const GaussK *__restrict__ rec,
-                                                  int T0, int T1, int T2, int nt1, int nt2,
-                                                  int maxtiles, const int32_t *__restrict__ off,
-                                                  const int32_t *__restrict__ slot,
-                                                  int32_t *__restrict__ list) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= m) return;
-    const GaussK r = rec[i];
-    if (r.lo0 > r.hi0 || r.lo1 > r.hi1 || r.lo2 > r.hi2) return;
-    const int t0a = r.lo0 / T0, t0b = r.hi0 / T0;
-    const int t1a = r.lo1 / T1, t1b = r.hi1 / T1;
-    const int t2a = r.lo2 / T2, t2b = r.hi2 / T2;
-    const int64_t cnt = (int64_t)(t0b - t0a + 1) * (t1b - t1a + 1) * (t2b - t2a + 1);
-    if (cnt > maxtiles) return;
-    // the pairs in the count pass's order, each to the place that pass drew
-    int q = 0;
-    for (int a = t0a; a <= t0b; ++a)
-        for (int b = t1a; b <= t1b; ++b)
-            for (int c = t2a; c <= t2b; ++c, ++q)
-                list[off[(a * nt1 + b) * nt2 + c] + slot[(int64_t)q * m + i]] = (int32_t)i;
+    before = base[0];
+    if (first && threadIdx.x == 0) nlarge[0] = all;
+    if (nlarge[1 + blockIdx.x] == 0) return;
+    for (int64_t j0 = i0; j0 < i1; j0 += BIN_T) {
+        const int64_t i = j0 + threadIdx.x;
+        const bool f = i < i1 && tile_box(rec[i], p.T0, p.T1, p.T2).count > p.maxtiles;
+        const int32_t e = block_excl_sum(f ? 1 : 0, wsum, before);
+        if (f) large[e] = (int32_t)i;
+    }
 }
 
 // ------------------------------------------------------------ tile splat
@@ -357,8 +394,9 @@ __device__ __forceinline__ bool col_range(float a22, float b2, float cq, float z
 // it visits is inside the ellipsoid) and adds value x e^(-m/2) of each
 // in-mask voxel.  The lanes are spread over the columns of many Gaussians,
 // not one Gaussian's few.
-constexpr int VB = 16;
-
+//
+// NW waves per workgroup: 4, or 16 (in smaller batches) where the grid has so
+// few tiles that each tile's list is a long serial walk (VOX_FEW).
 struct VoxB {                 // one Gaussian of a wave's batch, box clipped to the tile
     float mu[3];
     float a00, a01, a02, a11, a12, a22;
@@ -366,8 +404,8 @@ struct VoxB {                 // one Gaussian of a wave's batch, box clipped to 
     int ncols;
 };
 
-template <int T0, int T1, int T2, int CT>
-__global__ __launch_bounds__(256) void k_vox_tile(const GaussK *__restrict__ rec,
+template <int T0, int T1, int T2, int CT, int NW, int VB>
+__global__ __launch_bounds__(64 * NW) void k_vox_tile(const GaussK *__restrict__ rec,
                                                   const float *__restrict__ value, int Crt, GridK g,
                                                   float k2, int nt1, int nt2,
                                                   const int32_t *__restrict__ off,
@@ -376,7 +414,7 @@ __global__ __launch_bounds__(256) void k_vox_tile(const GaussK *__restrict__ rec
                                                   const int32_t *__restrict__ nlarge,
                                                   float *__restrict__ vol) {
     constexpr int TV = T0 * T1 * T2;
-    constexpr int NW = 4;
+    constexpr int NT = 64 * NW;
     constexpr int CM = CT > 0 ? CT : MAXC_VOX;
     const int C = CT > 0 ? CT : Crt;
     extern __shared__ int acc[];          // C tile planes
@@ -384,7 +422,7 @@ __global__ __launch_bounds__(256) void k_vox_tile(const GaussK *__restrict__ rec
     __shared__ float scale[CM];
     __shared__ VoxB bt[NW][VB];
     __shared__ float bv[NW][VB][CM];      // value x scale per batch entry
-    for (int i = threadIdx.x; i < C * TV; i += 256) acc[i] = 0;
+    for (int i = threadIdx.x; i < C * TV; i += NT) acc[i] = 0;
     const int t = blockIdx.x;
     const int tz = t % nt2, ty = (t / nt2) % nt1, tx = t / (nt2 * nt1);
     const int b0 = tx * T0, b1 = ty * T1, b2 = tz * T2;
@@ -400,15 +438,16 @@ __global__ __launch_bounds__(256) void k_vox_tile(const GaussK *__restrict__ rec
     // the list, so neither does the scale (results repeat bit for bit)
     for (int c = 0; c < C; ++c) {
         float mx = 0.0f;
-        for (int e = beg + (int)threadIdx.x; e < end; e += 256)
+        for (int e = beg + (int)threadIdx.x; e < end; e += NT)
             mx = fmaxf(mx, fabsf(value[(int64_t)list[e] * C + c]));
         mx = wave_max(mx);
         if (lane == 0) cs[wave][c] = mx;
     }
     __syncthreads();
     if (threadIdx.x < (unsigned)C) {
-        const float mx = fmaxf(fmaxf(cs[0][threadIdx.x], cs[1][threadIdx.x]),
-                               fmaxf(cs[2][threadIdx.x], cs[3][threadIdx.x]));
+        float mx = 0.0f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) mx = fmaxf(mx, cs[w][threadIdx.x]);
         const float S = (float)(end - beg) * mx;
         scale[threadIdx.x] = S > 0.0f ? 1073741824.0f / (S * 1.0001f) : 0.0f;
     }
@@ -493,7 +532,7 @@ __global__ __launch_bounds__(256) void k_vox_tile(const GaussK *__restrict__ rec
     __syncthreads();
     // fixed point -> float, in place
     float *const accf = (float *)acc;
-    for (int i = threadIdx.x; i < C * TV; i += 256) {
+    for (int i = threadIdx.x; i < C * TV; i += NT) {
         const float sc = scale[i / TV];
         accf[i] = sc > 0.0f ? (float)acc[i] / sc : 0.0f;
     }
@@ -502,7 +541,7 @@ __global__ __launch_bounds__(256) void k_vox_tile(const GaussK *__restrict__ rec
     // order (a fixed order: the results repeat bit for bit)
     if (nl > 0) {
         __syncthreads();
-        for (int li = threadIdx.x; li < TV; li += 256) {
+        for (int li = threadIdx.x; li < TV; li += NT) {
             const int ix = b0 + li / (T1 * T2), iy = b1 + (li / T2) % T1, iz = b2 + li % T2;
             if (ix > e0 || iy > e1 || iz > e2) continue;
             const float d0g = fmaf((float)ix, g.h[0], g.c0[0]);
@@ -526,7 +565,7 @@ __global__ __launch_bounds__(256) void k_vox_tile(const GaussK *__restrict__ rec
     }
     __syncthreads();
     const int64_t N = grid_size(g);
-    for (int i = threadIdx.x; i < C * TV; i += 256) {
+    for (int i = threadIdx.x; i < C * TV; i += NT) {
         const int c = i / TV, li = i % TV;
         const int z = li % T2, y = (li / T2) % T1, x = li / (T2 * T1);
         const int gx = b0 + x, gy = b1 + y, gz = b2 + z;
@@ -683,6 +722,8 @@ __global__ __launch_bounds__(256) void k_vox_gather(const GaussK *__restrict__ r
             if (z0 + s <= e2) vb[(int64_t)c * N + z0 + s] = out[s][c];
 }
 
+constexpr int64_t VOX_FEW = 512;
+
 VoxPlan vox_plan(int64_t m, int c, const GridK &g) {
     VoxPlan p;
     int T[3];
@@ -721,90 +762,102 @@ VoxPlan vox_plan(int64_t m, int c, const GridK &g) {
     }
     p.maxtiles = 32;
     p.cap = m * p.maxtiles;
+    // chunks of at least 128 Gaussians, at most 256 of them (one per CU), and
+    // no more than 2^24 (chunk, tile) counts unless that leaves fewer than 8
+    p.nch = (int)std::max<int64_t>(1, std::min<int64_t>({256, (m + 127) / 128,
+                                                         std::max<int64_t>(8, (1 << 24) / p.ntiles)}));
     return p;
 }
 
-size_t vox_workspace(const VoxPlan &p, int64_t m) {
-    size_t s = 0;
-    s += align256(sizeof(GaussK) * (size_t)(m > 0 ? m : 1));  // records
-    s += align256(sizeof(int32_t) * CNT_STRIDE * (size_t)p.ntiles);   // counts
-    s += align256(sizeof(int32_t) * (size_t)(p.ntiles + 1));          // offsets
-    s += align256(sizeof(int32_t) * (size_t)(p.cap > 0 ? p.cap : 1));  // list
-    s += align256(sizeof(int32_t) * (size_t)(m > 0 ? m : 1));  // large list
-    s += align256(sizeof(int32_t));                            // large count
-    s += align256(sizeof(int32_t) * (size_t)(m > 0 ? m : 1));  // large flags
-    s += align256(sizeof(int32_t) * (size_t)((m + 255) / 256 + 1));   // per-block counts
-    s += align256(sizeof(int32_t) * (size_t)(p.cap > 0 ? p.cap : 1));  // list places
-    return s;
+namespace {
+struct VoxWs {
+    GaussK *rec;
+    int32_t *part, *total, *off, *list, *large, *nlarge, *slot;
+    size_t bytes;
+};
+VoxWs vox_ws(void *base, const VoxPlan &p, int64_t m) {
+    VoxWs w;
+    char *const b = (char *)base;
+    size_t o = 0;
+    auto take = [&](size_t bytes) {
+        char *r = b ? b + o : nullptr;
+        o += align256(bytes);
+        return r;
+    };
+    const size_t n = (size_t)std::max<int64_t>(m, 1), cap = (size_t)std::max<int64_t>(p.cap, 1);
+    w.rec = (GaussK *)take(sizeof(GaussK) * n);                                  // records
+    w.part = (int32_t *)take(sizeof(int32_t) * (size_t)p.nch * (size_t)p.ntiles);   // chunks' counts
+    w.total = (int32_t *)take(sizeof(int32_t) * (size_t)p.ntiles);               // tiles' totals
+    w.off = (int32_t *)take(sizeof(int32_t) * (size_t)(p.ntiles + 1));           // lists' offsets
+    w.list = (int32_t *)take(sizeof(int32_t) * cap);
+    w.large = (int32_t *)take(sizeof(int32_t) * n);                              // large list
+    w.nlarge = (int32_t *)take(sizeof(int32_t) * (size_t)(p.nch + 1));           // its length, per chunk
+    w.slot = (int32_t *)take(sizeof(int32_t) * cap);                             // pairs' places
+    w.bytes = o;
+    return w;
 }
+}  // namespace
+
+size_t vox_workspace(const VoxPlan &p, int64_t m) { return vox_ws(nullptr, p, m).bytes; }
 
 hipError_t launch_voxelize(const pmf_gauss_t &gs, const GridK &g, float k, float *vol,
                            const VoxPlan &p, void *ws, hipStream_t s) {
-    char *w = (char *)ws;
     const int64_t m = gs.m;
-    GaussK *rec = (GaussK *)w;
-    w += align256(sizeof(GaussK) * (size_t)(m > 0 ? m : 1));
-    int32_t *cnt = (int32_t *)w;
-    w += align256(sizeof(int32_t) * CNT_STRIDE * (size_t)p.ntiles);
-    int32_t *off = (int32_t *)w;
-    w += align256(sizeof(int32_t) * (size_t)(p.ntiles + 1));
-    int32_t *list = (int32_t *)w;
-    w += align256(sizeof(int32_t) * (size_t)(p.cap > 0 ? p.cap : 1));
-    int32_t *large = (int32_t *)w;
-    w += align256(sizeof(int32_t) * (size_t)(m > 0 ? m : 1));
-    int32_t *nlarge = (int32_t *)w;
-    w += align256(sizeof(int32_t));
-    int32_t *is_large = (int32_t *)w;
-    w += align256(sizeof(int32_t) * (size_t)(m > 0 ? m : 1));
-    int32_t *blk = (int32_t *)w;
-    w += align256(sizeof(int32_t) * (size_t)((m + 255) / 256 + 1));
-    int32_t *slot = (int32_t *)w;
-
+    const VoxWs w = vox_ws(ws, p, m);
+    GaussK *const rec = w.rec;
+    int32_t *const off = w.off, *const list = w.list, *const large = w.large,
+                  *const nlarge = w.nlarge;
     const float k2 = isinf(k) ? INFINITY : k * k;
-    hipError_t e = launch_fill_i32(cnt, CNT_STRIDE * p.ntiles, 0, s);
-    if (e != hipSuccess) return e;
-    // with Gaussians, k_scan_counts writes the large-list length
-    if (m == 0 && (e = launch_fill_i32(nlarge, 1, 0, s)) != hipSuccess) return e;
-    if (m > 0) {
+    hipError_t e;
+    if (m == 0) {
+        if ((e = launch_fill_i32(off, p.ntiles + 1, 0, s)) != hipSuccess) return e;
+        if ((e = launch_fill_i32(nlarge, 1, 0, s)) != hipSuccess) return e;
+    } else {
+        VoxTiles t;
+        t.T0 = p.T[0];
+        t.T1 = p.T[1];
+        t.T2 = p.T[2];
+        t.nt1 = p.nt[1];
+        t.nt2 = p.nt[2];
+        t.ntiles = (int)p.ntiles;
+        t.maxtiles = p.maxtiles;
+        t.chunk = (m + p.nch - 1) / p.nch;
+        const size_t hist = sizeof(int32_t) * (size_t)std::min<int64_t>(p.ntiles, BIN_W);
         {
-            ProfScope prof_("voxelize_prep", s);
-            k_vox_prep<<<(unsigned)((m + 255) / 256), 256, 0, s>>>(
-                gs, g, k, p.T[0], p.T[1], p.T[2], p.nt[1], p.nt[2], p.maxtiles, rec, cnt, slot,
-                is_large);
+            ProfScope prof_("voxelize_bin", s);
+            k_vox_bin<<<(unsigned)p.nch, BIN_T, hist, s>>>(gs, g, k, t, rec, w.part, w.slot, nlarge);
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        const int nblk = (int)((m + 255) / 256);
-        k_large_count<<<(unsigned)nblk, 256, 0, s>>>(is_large, m, blk);
+        {
+            ProfScope prof_("voxelize_chunks", s);
+            k_vox_chunks<<<(unsigned)((p.ntiles + 63) / 64), 256, 0, s>>>(w.part, t.ntiles, p.nch,
+                                                                          w.total);
+        }
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        k_scan_counts<<<1, 1024, 0, s>>>(blk, nblk, nlarge);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        k_large_fill<<<(unsigned)nblk, 256, 0, s>>>(is_large, m, blk, large);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    {
-        ProfScope prof_("voxelize_scan", s);
-        k_scan<<<1, 1024, 0, s>>>(cnt, p.ntiles, off);
-    }
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    if (m > 0) {
         {
             ProfScope prof_("voxelize_fill", s);
-            k_vox_fill<<<(unsigned)((m + 255) / 256), 256, 0, s>>>(m, rec, p.T[0], p.T[1], p.T[2],
-                                                                  p.nt[1], p.nt[2], p.maxtiles, off,
-                                                                  slot, list);
+            k_vox_fill<<<(unsigned)p.nch, BIN_T, hist, s>>>(m, rec, t, w.part, w.total, w.slot,
+                                                           nlarge, off, list, large);
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     const size_t lds = sizeof(float) * (size_t)gs.c * (p.T[0] * p.T[1] * p.T[2]);
     {
         ProfScope prof_("voxelize_tile", s);
+        const bool few = p.ntiles <= VOX_FEW;
         const int sel = (p.T[1] == 16 ? 2 : 0) + (p.T[2] == 16 ? 1 : 0);
         const int cs = gs.c;
         // one channel: the LDS splat (many Gaussians per tile); 3 or 9
         // channels: voxel owners; other channel counts: the LDS splat
 #define VOX_TILE(T1_, T2_, CT_)                                                                   \
-    k_vox_tile<8, T1_, T2_, CT_><<<(unsigned)p.ntiles, 256, lds, s>>>(                           \
-        rec, gs.value, gs.c, g, k2, p.nt[1], p.nt[2], off, list, large, nlarge, vol)
+    do {                                                                                          \
+        if (few)                                                                                  \
+            k_vox_tile<8, T1_, T2_, CT_, 16, 8><<<(unsigned)p.ntiles, 1024, lds, s>>>(            \
+                rec, gs.value, gs.c, g, k2, p.nt[1], p.nt[2], off, list, large, nlarge, vol);     \
+        else                                                                                      \
+            k_vox_tile<8, T1_, T2_, CT_, 4, 16><<<(unsigned)p.ntiles, 256, lds, s>>>(             \
+                rec, gs.value, gs.c, g, k2, p.nt[1], p.nt[2], off, list, large, nlarge, vol);     \
+    } while (0)
 #define VOX_GATHER(T1_, T2_, CT_)                                                                 \
     k_vox_gather<8, T1_, T2_, CT_><<<(unsigned)p.ntiles, 256, 0, s>>>(                           \
         rec, gs.value, g, k2, p.nt[1], p.nt[2], off, list, large, nlarge, vol)
