@@ -46,8 +46,20 @@ struct GaussFull {
     int lo[3], hi[3];
 };
 
-// Sigma^-1 = R diag(s^-2) R^T and the voxel box that holds the ellipsoid
-// m <= k^2 (half-extent k sqrt(Sigma_aa) per axis, widened by one voxel).
+// Rounding allowance of a grid position along axis a, in voxels.
+__device__ __forceinline__ float voxel_margin(const GridK &g, int a, float c) {
+    return fmaf(1e-6f, fmaf(2.0f * fabsf(g.c0[a]), g.inv_h[a], fabsf(c) + (float)g.n[a]), 0.01f);
+}
+
+// Sigma^-1 = R diag(s^-2) R^T and the voxel box of the ellipsoid m <= k^2
+// (half-extent k sqrt(Sigma_aa) per axis).  The box holds every voxel whose
+// computed m passes m <= k^2: the rounding errors of m and of Sigma_aa are a
+// few 2^-24 (s_max / s_min)^2 of k^2, the half-extent is widened by 1e-5
+// (s_max / s_min)^2 (an ill-conditioned Gaussian takes its outermost voxels
+// plus one).  Exact boxes and column ranges matter: with one voxel more on
+// each side, 200k Gaussians of about 7 x 7 x 5 voxels walked twice the columns
+// and three times the voxels (256x256x128: k_vox_tile 243 -> 97 us, k_vox_bwd
+// 228 -> 147 us).
 __device__ __forceinline__ void gauss_full(const float *__restrict__ mean,
                                            const float *__restrict__ scale,
                                            const float *__restrict__ quat, int64_t i, float k,
@@ -80,6 +92,9 @@ __device__ __forceinline__ void gauss_full(const float *__restrict__ mean,
         for (int b = 0; b < 3; ++b)
             G.A[a][b] = G.R[a][0] * G.R[b][0] * is2[0] + G.R[a][1] * G.R[b][1] * is2[1] +
                         G.R[a][2] * G.R[b][2] * is2[2];
+    const float smax = fmaxf(fmaxf(fabsf(G.s[0]), fabsf(G.s[1])), fabsf(G.s[2]));
+    const float smin = fminf(fminf(fabsf(G.s[0]), fabsf(G.s[1])), fabsf(G.s[2]));
+    const float widen = fmaf(1e-5f, (smax / smin) * (smax / smin), 1.0f);
     for (int a = 0; a < 3; ++a) {
         if (isinf(k)) {
             G.lo[a] = 0;
@@ -89,8 +104,11 @@ __device__ __forceinline__ void gauss_full(const float *__restrict__ mean,
         const float var = G.R[a][0] * G.R[a][0] * s2[0] + G.R[a][1] * G.R[a][1] * s2[1] +
                           G.R[a][2] * G.R[a][2] * s2[2];
         const float ext = k * sqrtf(var);
-        float l = floorf((G.mu[a] - ext - g.c0[a]) * g.inv_h[a]) - 1.0f;
-        float u = ceilf((G.mu[a] + ext - g.c0[a]) * g.inv_h[a]) + 1.0f;
+        const float c = (G.mu[a] - g.c0[a]) * g.inv_h[a];
+        const float we = ext * widen * g.inv_h[a] + voxel_margin(g, a, c);
+        // (fmaxf and fminf drop a NaN: then the wide bound holds)
+        float l = fmaxf(ceilf(c - we), floorf((G.mu[a] - ext - g.c0[a]) * g.inv_h[a]) - 1.0f);
+        float u = fminf(floorf(c + we), ceilf((G.mu[a] + ext - g.c0[a]) * g.inv_h[a]) + 1.0f);
         l = fmaxf(l, 0.0f);
         u = fminf(u, (float)(g.n[a] - 1));
         if (!(l <= u)) {  // outside the grid (or NaN): empty box
@@ -130,7 +148,7 @@ __device__ __forceinline__ bool far_from_grid(const float *__restrict__ mean,
 // and totals, and k_vox_fill scans the totals and writes each pair to its
 // place.  (Counting in global memory took a device-scope atomic per pair, which
 // contend per cache line: 100 + 19 us of 150 for the 200k set, and eight
-// launches; now FIG_BIN.)  Counts are held for BIN_W tiles at a time; a grid of
+// launches; now three and 48 us.)  Counts are held for BIN_W tiles at a time; a grid of
 // more walks its Gaussians again for each further window.
 struct VoxTiles {                      // a set's tiles and chunks
     int T0, T1, T2, nt1, nt2, ntiles;
@@ -356,27 +374,28 @@ __device__ __forceinline__ float col_quad(float a22, float b2, float cq, float d
 }
 
 // z range [za, zb] of a column that the truncation ellipsoid m <= k2 can
-// reach: the roots of m(d2) = k2, widened by one voxel on each side and
-// clipped to [lo2, hi2]; false when the column's quadratic stays clearly
-// above k2.  Untruncated sets take the whole range.
-__device__ __forceinline__ bool col_range(float a22, float b2, float cq, float zc, float inv_h2,
-                                          float k2, bool untrunc, int lo2, int hi2, int &za,
-                                          int &zb) {
+// reach, clipped to [lo2, hi2]; false when the column's quadratic stays above
+// k2.  The range holds every voxel whose computed col_quad passes m <= k2: with
+// u = -b2 / (2 a22) the roots are u +- sqrt(disc), the rounding errors of
+// col_quad and of disc are below 1e-6 of u^2 + (|cq| + k2) / a22, and disc is
+// raised by 1e-4 of that.  zc: the Gaussian's centre in voxels; zm: the margin
+// of a voxel's position.  Untruncated sets take the whole range.
+__device__ __forceinline__ bool col_range(float a22, float b2, float cq, float zc, float zm,
+                                          float inv_h2, float k2, bool untrunc, int lo2, int hi2,
+                                          int &za, int &zb) {
     za = lo2;
     zb = hi2;
     if (untrunc) return true;
-    const float bh = 0.5f * b2;
-    float disc = fmaf(bh, bh, -a22 * (cq - k2));
-    const float tol = 1e-4f * (fmaf(bh, bh, a22 * (fabsf(cq) + k2)));
-    if (disc < -tol) return false;
-    disc = fmaxf(disc, 0.0f);
-    const float r = sqrtf(disc), inv_a = 1.0f / a22;
-    // d2 range -> voxel index range: iz = zc + d2 / h2, zc = (mu2 - c0_2) / h2
-    const float t_lo = zc + (-bh - r) * inv_a * inv_h2;
-    const float t_hi = zc + (-bh + r) * inv_a * inv_h2;
-    za = max(za, (int)floorf(t_lo) - 1);
-    zb = min(zb, (int)ceilf(t_hi) + 1);
-    return true;
+    const float ra = __builtin_amdgcn_rcpf(a22);
+    const float u = -0.5f * b2 * ra;
+    const float bound = fmaf(u, u, (fabsf(cq) + k2) * ra);
+    const float disc = fmaf(1e-4f, bound, fmaf(u, u, (k2 - cq) * ra));
+    if (disc < 0.0f) return false;
+    const float r = __builtin_amdgcn_sqrtf(disc);
+    // (fmaxf and fminf drop a NaN: then the box's bound holds)
+    za = (int)fmaxf(ceilf(fmaf(u - r, inv_h2, zc - zm)), (float)lo2);
+    zb = (int)fminf(floorf(fmaf(u + r, inv_h2, zc + zm)), (float)hi2);
+    return za <= zb;
 }
 
 // One workgroup per tile.  Accumulation is in 32-bit fixed point with
@@ -404,6 +423,16 @@ struct VoxB {                 // one Gaussian of a wave's batch, box clipped to 
     int ncols;
 };
 
+// Workgroup b runs on XCD b % 8, and with a power of two of tiles along axis 2
+// that would give each XCD the tiles of one axis-2 slab (and the middle slabs
+// of a body hold most of the Gaussians: CUs were busy 59% of the time, 73%
+// now), so the axis-2 tile index is rotated from column to column.
+__device__ __forceinline__ int rotated_tile(int b, int nt1, int nt2) {
+    const int c = b / nt2, z = b - c * nt2;
+    const int tx = c / nt1, ty = c - tx * nt1;
+    return c * nt2 + (z + tx + ty / 2) % nt2;
+}
+
 template <int T0, int T1, int T2, int CT, int NW, int VB>
 __global__ __launch_bounds__(64 * NW) void k_vox_tile(const GaussK *__restrict__ rec,
                                                   const float *__restrict__ value, int Crt, GridK g,
@@ -423,7 +452,7 @@ __global__ __launch_bounds__(64 * NW) void k_vox_tile(const GaussK *__restrict__
     __shared__ VoxB bt[NW][VB];
     __shared__ float bv[NW][VB][CM];      // value x scale per batch entry
     for (int i = threadIdx.x; i < C * TV; i += NT) acc[i] = 0;
-    const int t = blockIdx.x;
+    const int t = rotated_tile((int)blockIdx.x, nt1, nt2);
     const int tz = t % nt2, ty = (t / nt2) % nt1, tx = t / (nt2 * nt1);
     const int b0 = tx * T0, b1 = ty * T1, b2 = tz * T2;
     const int e0 = min(b0 + T0, g.n[0]) - 1, e1 = min(b1 + T1, g.n[1]) - 1,
@@ -509,8 +538,9 @@ __global__ __launch_bounds__(64 * NW) void k_vox_tile(const GaussK *__restrict__
             float cb2, cq;
             col_coeffs(q.a00, q.a01, q.a02, q.a11, q.a12, d0, d1, cb2, cq);
             int za, zb;
-            if (!col_range(q.a22, cb2, cq, (q.mu[2] - g.c0[2]) * inv_h2, inv_h2, k2, untrunc,
-                           q.lo2, q.hi2, za, zb))
+            const float zc = (q.mu[2] - g.c0[2]) * inv_h2;
+            if (!col_range(q.a22, cb2, cq, zc, voxel_margin(g, 2, zc), inv_h2, k2, untrunc, q.lo2,
+                           q.hi2, za, zb))
                 continue;
             const float a22 = q.a22, mu2 = q.mu[2];
             float vs[CM];
@@ -722,16 +752,21 @@ __global__ __launch_bounds__(256) void k_vox_gather(const GaussK *__restrict__ r
             if (z0 + s <= e2) vb[(int64_t)c * N + z0 + s] = out[s][c];
 }
 
+// Up to this many tiles (two per CU) k_vox_tile has 16 waves per tile, not
+// four: with fewer tiles than CUs can hold the longest list's walk is what the
+// launch takes (4,096 Gaussians in 64^3, 256 tiles: 59 us with 4 waves, 22 with
+// 16; a 32^3 block of 200k Gaussians, 64 tiles: 43 and 21).  With more the CUs
+// are full either way, and the smaller batches cost.
 constexpr int64_t VOX_FEW = 512;
 
 VoxPlan vox_plan(int64_t m, int c, const GridK &g) {
     VoxPlan p;
     int T[3];
     if (c <= 1) {
-        // 200k Gaussians into 256x256x128, binning + tiles: 8x16x16 0.50 ms
-        // (tiles 0.307), 8x8x32 0.49 ms (tiles 0.275: fewer columns cut at
-        // z faces, a little more binning), 8x16x32 0.66 ms and 8x8x64
-        // 0.63 ms (fewer, longer lists: the per-tile atomics contend)
+        // fewest columns cut at z faces; 8x16x32 and 8x8x64 leave fewer,
+        // longer lists, and their LDS atomics contend (200k Gaussians into
+        // 256x256x128, binning + tiles: 8x8x32 0.49 ms, 8x16x16 0.50, 8x16x32
+        // 0.66, 8x8x64 0.63; 0.15 ms now with the binning and boxes of today)
         T[0] = 8; T[1] = 8; T[2] = 32;
     } else if (c <= 4) {
         T[0] = 8; T[1] = 16; T[2] = 16;
@@ -969,7 +1004,7 @@ __global__ __launch_bounds__(64) void k_vox_bwd(pmf_gauss_t gs, GridK g, float k
             const int ny = q.hi1 - q.lo1 + 1;
             const int ncol = (q.hi0 - q.lo0 + 1) * ny;
             const float rny = __builtin_amdgcn_rcpf((float)ny);
-            const float zc = (q.mu[2] - g.c0[2]) * inv_h2;
+            const float zc = (q.mu[2] - g.c0[2]) * inv_h2, zm = voxel_margin(g, 2, zc);
             if constexpr (ZL) {
                 const int nz = q.hi2 - q.lo2 + 1;
                 const int zl = nz <= 4 ? 4 : nz <= 8 ? 8 : nz <= 16 ? 16 : nz <= 32 ? 32 : 64;
@@ -993,7 +1028,7 @@ __global__ __launch_bounds__(64) void k_vox_bwd(pmf_gauss_t gs, GridK g, float k
                     float cb2, cq;
                     col_coeffs(q.a00, q.a01, q.a02, q.a11, q.a12, d0, d1, cb2, cq);
                     int za, zb;
-                    if (!col_range(q.a22, cb2, cq, zc, inv_h2, k2, untrunc, q.lo2, q.hi2, za, zb))
+                    if (!col_range(q.a22, cb2, cq, zc, zm, inv_h2, k2, untrunc, q.lo2, q.hi2, za, zb))
                         continue;
                     const float *gcol = g_vol + ((int64_t)ix * g.n[1] + iy) * g.n[2];
                     for (int iz = za + zr; iz <= zb; iz += zl) {
@@ -1045,7 +1080,7 @@ __global__ __launch_bounds__(64) void k_vox_bwd(pmf_gauss_t gs, GridK g, float k
                 float cb2, cq;
                 col_coeffs(q.a00, q.a01, q.a02, q.a11, q.a12, d0, d1, cb2, cq);
                 int za, zb;
-                if (!col_range(q.a22, cb2, cq, zc, inv_h2, k2, untrunc, q.lo2, q.hi2, za, zb))
+                if (!col_range(q.a22, cb2, cq, zc, zm, inv_h2, k2, untrunc, q.lo2, q.hi2, za, zb))
                     continue;
                 const float *gcol = g_vol + ((int64_t)ix * g.n[1] + iy) * g.n[2];
                 float St = 0.0f, Sz = 0.0f, Szz = 0.0f;
