@@ -164,6 +164,15 @@ __device__ __forceinline__ float warp_sum(float v) {
     return v;
 }
 
+// A wave-uniform value in a vector register: VALU instructions with a scalar
+// operand issue at half the rate of those without.
+__device__ __forceinline__ float in_vgpr(float x) {
+    float r;
+    asm("v_mov_b32 %0, %1" : "=v"(r) : "s"(x));
+    return r;
+}
+__device__ __forceinline__ int in_vgpr(int x) { return __float_as_int(in_vgpr(__int_as_float(x))); }
+
 // Sum over the 64 lanes of a wave with DPP moves (VALU only, no LDS).
 // The total is valid in lane 63 (other lanes hold partial sums).
 template <int CTRL, int ROW_MASK = 0xf, int BANK_MASK = 0xf>
@@ -233,6 +242,23 @@ __device__ __forceinline__ void swap16(float &a, float &b) {
     a = __uint_as_float(r[0]);
     b = __uint_as_float(r[1]);
 }
+
+// Sums of four values over the wave: the lanes of row r (16 r to 16 r + 15) end
+// with the sum of value {0, 2, 1, 3}[r] (sum4_index).
+__device__ __forceinline__ float wave_sum4(float a, float b, float c, float d) {
+    swap32(a, b);
+    swap32(c, d);
+    a += b;
+    c += d;
+    swap16(a, c);
+    a += c;
+    a += dpp_mov<0xB1>(a);
+    a += dpp_mov<0x4E>(a);
+    a += dpp_mov<0x141>(a);
+    a += dpp_mov<0x140>(a);
+    return a;
+}
+__device__ __forceinline__ int sum4_index(int lane) { return (lane >> 5 & 1) | (lane >> 3 & 2); }
 
 // Reduce-scatter of 32 per-lane values over the 64 lanes of a wave: returns
 // the total over all lanes of value 16*b3 + 8*b2 + 4*b1 + 2*b0 + b4 (b_k =
