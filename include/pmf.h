@@ -401,7 +401,7 @@ size_t pmf_profile_names(char *buf, size_t len);
  *                              wavefronts, 8 = 52x16x8 (a launch of few
  *                              views takes shorter chunks, so that it still
  *                              fills the chip);
- *   PMF_TUNE_VOXELIZE_BWD      Gaussians per wavefront in pmf_voxelize_bwd:
+ *   PMF_TUNE_VOXELIZE_BWD      Gaussians per workgroup in pmf_voxelize_bwd:
  *                              0 = chosen from the set's size (default),
  *                              k = 1..7: 2^(k-1).
  * pmf_tune_candidates returns the number of choices of a knob (0 for an

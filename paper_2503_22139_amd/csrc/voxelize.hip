@@ -36,14 +36,16 @@ struct alignas(16) GaussK {
     float a22;
     int lo0, lo1, lo2;
     int hi0, hi1, hi2;
-    int pad0, pad1;
+    uint32_t rim;               // the binning's box: 4 bits per side beyond lo0, hi0, lo1, ...
+    int pad;
 };
 
 struct GaussFull {
     float mu[3], s[3], qh[4], qn;
     float R[3][3];
     float A[3][3];
-    int lo[3], hi[3];
+    int lo[3], hi[3];           // voxels that may lie inside (none: lo > hi on some axis)
+    uint32_t rim;               // GaussK
 };
 
 // Rounding allowance of a grid position along axis a, in voxels.
@@ -56,10 +58,12 @@ __device__ __forceinline__ float voxel_margin(const GridK &g, int a, float c) {
 // computed m passes m <= k^2: the rounding errors of m and of Sigma_aa are a
 // few 2^-24 (s_max / s_min)^2 of k^2, the half-extent is widened by 1e-5
 // (s_max / s_min)^2 (an ill-conditioned Gaussian takes its outermost voxels
-// plus one).  Exact boxes and column ranges matter: with one voxel more on
+// plus one).  The tiles' lists, whose lengths and largest values set the scales
+// of their fixed-point sums, go by a box of one voxel more on each side
+// (`rim`).  Exact boxes and column ranges matter: with one voxel more on
 // each side, 200k Gaussians of about 7 x 7 x 5 voxels walked twice the columns
-// and three times the voxels (256x256x128: k_vox_tile 243 -> 97 us, k_vox_bwd
-// 228 -> 147 us).
+// and three times the voxels (256x256x128: k_vox_tile 243 -> 111 us, k_vox_bwd
+// 228 -> 147 us, and 109 with its walks of today).
 __device__ __forceinline__ void gauss_full(const float *__restrict__ mean,
                                            const float *__restrict__ scale,
                                            const float *__restrict__ quat, int64_t i, float k,
@@ -95,6 +99,8 @@ __device__ __forceinline__ void gauss_full(const float *__restrict__ mean,
     const float smax = fmaxf(fmaxf(fabsf(G.s[0]), fabsf(G.s[1])), fabsf(G.s[2]));
     const float smin = fminf(fminf(fabsf(G.s[0]), fabsf(G.s[1])), fabsf(G.s[2]));
     const float widen = fmaf(1e-5f, (smax / smin) * (smax / smin), 1.0f);
+    G.rim = 0;
+    bool outside = false;
     for (int a = 0; a < 3; ++a) {
         if (isinf(k)) {
             G.lo[a] = 0;
@@ -106,17 +112,22 @@ __device__ __forceinline__ void gauss_full(const float *__restrict__ mean,
         const float ext = k * sqrtf(var);
         const float c = (G.mu[a] - g.c0[a]) * g.inv_h[a];
         const float we = ext * widen * g.inv_h[a] + voxel_margin(g, a, c);
-        // (fmaxf and fminf drop a NaN: then the wide bound holds)
-        float l = fmaxf(ceilf(c - we), floorf((G.mu[a] - ext - g.c0[a]) * g.inv_h[a]) - 1.0f);
-        float u = fminf(floorf(c + we), ceilf((G.mu[a] + ext - g.c0[a]) * g.inv_h[a]) + 1.0f);
-        l = fmaxf(l, 0.0f);
-        u = fminf(u, (float)(g.n[a] - 1));
-        if (!(l <= u)) {  // outside the grid (or NaN): empty box
+        const float wl = fmaxf(floorf((G.mu[a] - ext - g.c0[a]) * g.inv_h[a]) - 1.0f, 0.0f);
+        const float wu = fminf(ceilf((G.mu[a] + ext - g.c0[a]) * g.inv_h[a]) + 1.0f,
+                               (float)(g.n[a] - 1));
+        outside = outside || !(wl <= wu);
+        // (fmaxf and fminf drop a NaN: then the wide box holds)
+        const float l = fminf(fmaxf(ceilf(c - we), wl), wl + 15.0f);
+        const float u = fmaxf(fminf(floorf(c + we), wu), wu - 15.0f);
+        G.lo[a] = (int)l;
+        G.hi[a] = (int)u;
+        G.rim |= (uint32_t)(l - wl) << (8 * a) | (uint32_t)(wu - u) << (8 * a + 4);
+    }
+    if (outside) {
+        G.rim = 0;
+        for (int a = 0; a < 3; ++a) {
             G.lo[a] = 1;
             G.hi[a] = 0;
-        } else {
-            G.lo[a] = (int)l;
-            G.hi[a] = (int)u;
         }
     }
 }
@@ -159,7 +170,7 @@ struct VoxTiles {                      // a set's tiles and chunks
 constexpr int BIN_W = 12288;           // tiles per window (48 KB of LDS)
 constexpr int BIN_T = 512;             // threads per chunk
 
-// A Gaussian's tile box [t*a, t*b] in record order; the pairs are numbered
+// A Gaussian's tile box [t*a, t*b], of its voxel box and rim; the pairs are numbered
 // q = 0.. with axis 2 fastest.
 struct TileBox {
     int a0, b0, a1, b1, a2, b2;
@@ -167,13 +178,16 @@ struct TileBox {
 };
 __device__ __forceinline__ TileBox tile_box(const GaussK &r, int T0, int T1, int T2) {
     TileBox t{};
-    if (r.lo0 > r.hi0 || r.lo1 > r.hi1 || r.lo2 > r.hi2) return t;
-    t.a0 = r.lo0 / T0;
-    t.b0 = r.hi0 / T0;
-    t.a1 = r.lo1 / T1;
-    t.b1 = r.hi1 / T1;
-    t.a2 = r.lo2 / T2;
-    t.b2 = r.hi2 / T2;
+    const int lo0 = r.lo0 - (int)(r.rim & 15), hi0 = r.hi0 + (int)(r.rim >> 4 & 15);
+    const int lo1 = r.lo1 - (int)(r.rim >> 8 & 15), hi1 = r.hi1 + (int)(r.rim >> 12 & 15);
+    const int lo2 = r.lo2 - (int)(r.rim >> 16 & 15), hi2 = r.hi2 + (int)(r.rim >> 20 & 15);
+    if (lo0 > hi0 || lo1 > hi1 || lo2 > hi2) return t;
+    t.a0 = lo0 / T0;
+    t.b0 = hi0 / T0;
+    t.a1 = lo1 / T1;
+    t.b1 = hi1 / T1;
+    t.a2 = lo2 / T2;
+    t.b2 = hi2 / T2;
     t.count = (int64_t)(t.b0 - t.a0 + 1) * (t.b1 - t.a1 + 1) * (t.b2 - t.a2 + 1);
     return t;
 }
@@ -227,6 +241,7 @@ __global__ __launch_bounds__(BIN_T) void k_vox_bin(pmf_gauss_t gs, GridK g, floa
                     r.hi0 = G.hi[0];
                     r.hi1 = G.hi[1];
                     r.hi2 = G.hi[2];
+                    r.rim = G.rim;
                 }
                 rec[i] = r;
             }
@@ -367,6 +382,12 @@ __device__ __forceinline__ void col_coeffs(float a00, float a01, float a02, floa
                                            float d0, float d1, float &b2, float &cq) {
     b2 = 2.0f * fmaf(a02, d0, a12 * d1);
     cq = fmaf(a00 * d0, d0, fmaf(2.0f * a01 * d0, d1, a11 * d1 * d1));
+}
+
+// e^(-m/2).  (-log2(e) / 2 rounds to half of log2(e)'s float: the product is
+// that of e^x's own.)
+__device__ __forceinline__ float half_exp(float m) {
+    return __builtin_amdgcn_exp2f(-0.72134752044f * m);
 }
 
 __device__ __forceinline__ float col_quad(float a22, float b2, float cq, float d2) {
@@ -551,7 +572,7 @@ __global__ __launch_bounds__(64 * NW) void k_vox_tile(const GaussK *__restrict__
                 const float d2 = fmaf((float)iz, g.h[2], g.c0[2]) - mu2;
                 const float mm = col_quad(a22, cb2, cq, d2);
                 if (!(mm <= k2)) continue;
-                const float ev = __expf(-0.5f * mm);
+                const float ev = half_exp(mm);
 #pragma unroll
                 for (int c = 0; c < CM; ++c)
                     if (c < C) atomicAdd(&acc[c * TV + li], __float2int_rn(vs[c] * ev));
@@ -587,7 +608,7 @@ __global__ __launch_bounds__(64 * NW) void k_vox_tile(const GaussK *__restrict__
                 col_coeffs(p.a00, p.a01, p.a02, p.a11, p.a12, d0g - p.mu[0], d1g - p.mu[1], cb2, cq);
                 const float mm = col_quad(p.a22, cb2, cq, d2g - p.mu[2]);
                 if (!(mm <= k2)) continue;
-                const float ev = __expf(-0.5f * mm);
+                const float ev = half_exp(mm);
                 const float *vv = value + (int64_t)gi * C;
                 for (int c = 0; c < C; ++c) accf[c * TV + li] += vv[c] * ev;
             }
@@ -629,6 +650,7 @@ __global__ __launch_bounds__(256) void k_vox_gather(const GaussK *__restrict__ r
     static_assert(SEG >= 1 && T2 % SEG == 0 && TV % 256 == 0, "tile shape");
     __shared__ GaussK gsh[VG_CHUNK];
     __shared__ float gvs[VG_CHUNK][CT];
+    __shared__ int nsh;
     __shared__ float cs[4][CT];
     __shared__ float scale[CT];
     const int t = blockIdx.x;
@@ -677,18 +699,26 @@ __global__ __launch_bounds__(256) void k_vox_gather(const GaussK *__restrict__ r
 #pragma unroll
         for (int c = 0; c < CT; ++c) acc[s][c] = 0;
     for (int cb = beg; cb < end; cb += VG_CHUNK) {
-        const int n = min(VG_CHUNK, end - cb);
         __syncthreads();                  // scale ready / previous chunk consumed
-        if ((int)threadIdx.x < n) {
-            const int gi = list[cb + threadIdx.x];
-            gsh[threadIdx.x] = rec[gi];
-            for (int c = 0; c < CT; ++c) gvs[threadIdx.x][c] = value[(int64_t)gi * CT + c] * scale[c];
+        if (wave == 0) {                  // stages the Gaussians with voxels in the tile
+            const bool on = cb + lane < end;
+            const int gi = list[on ? cb + lane : cb];
+            const GaussK p = rec[gi];
+            const bool hit = on && max(p.lo0, b0) <= min(p.hi0, e0) &&
+                             max(p.lo1, b1) <= min(p.hi1, e1) && max(p.lo2, b2) <= min(p.hi2, e2);
+            const uint64_t hits = __ballot(hit);
+            if (hit) {
+                const int j = __popcll(hits & ((1ull << lane) - 1));
+                gsh[j] = p;
+                for (int c = 0; c < CT; ++c) gvs[j][c] = value[(int64_t)gi * CT + c] * scale[c];
+            }
+            if (lane == 0) nsh = __popcll(hits);
         }
         __syncthreads();
+        const int n = nsh;
         for (int e = 0; e < n; ++e) {
             const GaussK p = gsh[e];
-            if (p.hi0 < wx0 || p.lo0 > wx1 || p.hi1 < b1 || p.lo1 > e1 || p.hi2 < b2 || p.lo2 > e2)
-                continue;                                     // uniform
+            if (p.hi0 < wx0 || p.lo0 > wx1) continue;         // uniform
             if (ix < p.lo0 || ix > p.hi0 || iy < p.lo1 || iy > p.hi1 || z0 > p.hi2 ||
                 z0 + SEG - 1 < p.lo2)
                 continue;
@@ -698,7 +728,7 @@ __global__ __launch_bounds__(256) void k_vox_gather(const GaussK *__restrict__ r
             for (int s = 0; s < SEG; ++s) {
                 const float mm = col_quad(p.a22, cb2, cq, d2g[s] - p.mu[2]);
                 if (z0 + s >= p.lo2 && z0 + s <= p.hi2 && mm <= k2) {
-                    const float ev = __expf(-0.5f * mm);
+                    const float ev = half_exp(mm);
 #pragma unroll
                     for (int c = 0; c < CT; ++c) acc[s][c] += __float2int_rn(gvs[e][c] * ev);
                 }
@@ -726,7 +756,7 @@ __global__ __launch_bounds__(256) void k_vox_gather(const GaussK *__restrict__ r
             if (z0 + s < p.lo2 || z0 + s > p.hi2) continue;
             const float mm = col_quad(p.a22, cb2, cq, d2g[s] - p.mu[2]);
             if (!(mm <= k2)) continue;
-            const float ev = __expf(-0.5f * mm);
+            const float ev = half_exp(mm);
 #pragma unroll
             for (int c = 0; c < CT; ++c) out[s][c] += value[(int64_t)gi * CT + c] * ev;
         }
@@ -919,57 +949,231 @@ hipError_t launch_voxelize(const pmf_gauss_t &gs, const GridK &g, float k, float
 
 // ------------------------------------------------------------- backward
 
-// Adjoint, Gaussian owner.  A wave takes `per` consecutive Gaussians; lane
-// j < per builds Gaussian j's geometry and stages what the walk needs in
-// LDS.  The wave then walks each Gaussian's voxel box in turn with the
-// forward's columns (64 columns at a time over the lanes, z along each
-// lane's col_range) and accumulates per lane, with t = e sum_c v_c g_c:
+// Adjoint, Gaussian owner.  A workgroup takes `per` consecutive Gaussians: its
+// lanes j < per build their geometry and stage what the walks need in LDS, its
+// waves walk the voxel boxes of those that reach the grid, one Gaussian of a
+// wave at a time, and the lanes j < per apply the chain rule to the sums.  (With
+// set-up and chain by each wave for its own eight Gaussians, or its one, most of
+// its lanes were idle for half of the instructions: 200k Gaussians of which few
+// reach a 32^3 block 48 us, now 12.)  Fetches bound the walks of sets in no
+// order: 640 MB in 109 us for 200k Gaussians in 256x256x128 (147 before), and
+// for 16k of nine channels (117 us, 129 before), whose volume is 302 MB.  A walk sums, over the
+// voxels inside the ellipsoid, with t = e sum_c v_c g_c:
 //   sum e g_c (value gradients),
 //   sum t d    (mean gradient A sum t d),
 //   sum t d d^T (the gradient of the quadratic form),
-// where on a column (d0, d1 fixed) only sum t, sum t d2 and sum t d2^2 are
-// kept per voxel and folded into the others when the lane leaves the
-// column.  The sums are reduced across the wave, and at the end lane j
-// applies the chain rule through Sigma^-1 = R diag(s^-2) R^T and the
-// quaternion normalisation to Gaussian j.
+// in an order that only the Gaussian itself sets, and reduces them over the
+// wave; the chain rule goes on through Sigma^-1 = R diag(s^-2) R^T and the
+// quaternion normalisation.
 constexpr int BW_NS = 9;       // sums besides the channels: P0..P2, M00 M01 M02 M11 M12 M22
+constexpr int BW_WAVES = 4;    // waves per workgroup
+constexpr int BW_SLOTS = 512;  // voxels per window of a walk over several channels
 
-struct VoxG {                  // one Gaussian of the wave's batch
+struct VoxG {                  // one Gaussian of the workgroup's batch
     float mu[3];
     float a00, a01, a02, a11, a12, a22;
     int lo0, lo1, lo2, hi0, hi1, hi2;
 };
 
-//
-// ZL: the multi-channel layout.  Each voxel then loads C values, and lanes on
-// different columns would touch a cache line per lane per channel; instead
-// the lanes of a wave sit along z (zl lanes per column, 64 / zl columns per
-// step) so each load covers a few lines, and every voxel accumulates its
-// terms directly.
-template <int CT, bool ZL>
-__global__ __launch_bounds__(64) void k_vox_bwd(pmf_gauss_t gs, GridK g, float k, int per,
-                                                const float *__restrict__ g_vol,
-                                                pmf_gauss_grad_t gr) {
+// Column `col` of the box of q (axis 1 fastest): its offsets, its quadratic's
+// coefficients and its z range [za, zb] (za > zb: empty).
+struct VoxCol {
+    float d0, d1, b2, cq;
+    int ix, iy, za, zb;
+};
+__device__ __forceinline__ VoxCol vox_col(const VoxG &q, const GridK &g, int col, int ny, float rny,
+                                          float zc, float zm, float k2, bool untrunc) {
+    VoxCol c;
+    // col = cx * ny + cy (the float quotient is corrected to exact)
+    int cx = (int)(((float)col + 0.5f) * rny);
+    int cy = col - cx * ny;
+    if (cy < 0) {
+        --cx;
+        cy += ny;
+    } else if (cy >= ny) {
+        ++cx;
+        cy -= ny;
+    }
+    c.ix = q.lo0 + cx;
+    c.iy = q.lo1 + cy;
+    c.d0 = fmaf((float)c.ix, g.h[0], g.c0[0]) - q.mu[0];
+    c.d1 = fmaf((float)c.iy, g.h[1], g.c0[1]) - q.mu[1];
+    col_coeffs(q.a00, q.a01, q.a02, q.a11, q.a12, c.d0, c.d1, c.b2, c.cq);
+    if (!col_range(q.a22, c.b2, c.cq, zc, zm, g.inv_h[2], k2, untrunc, q.lo2, q.hi2, c.za, c.zb)) {
+        c.za = 0;
+        c.zb = -1;
+    }
+    return c;
+}
+
+// Sums of x[0..N) over the wave -> out[0..n), in LDS.
+template <int N>
+__device__ __forceinline__ void wave_sums(const float (&x)[N], int n, int lane, float *out) {
+    const int q = sum4_index(lane);
+#pragma unroll
+    for (int k = 0; k < N; k += 4) {
+        const float z = 0.0f;
+        const float t = wave_sum4(x[k], k + 1 < N ? x[k + 1 < N ? k + 1 : 0] : z,
+                                  k + 2 < N ? x[k + 2 < N ? k + 2 : 0] : z,
+                                  k + 3 < N ? x[k + 3 < N ? k + 3 : 0] : z);
+        if ((lane & 15) == 0 && k + q < n) out[k + q] = t;
+    }
+}
+
+// One channel: a lane per column, 64 columns at a time; a lane walks its
+// column's z range two voxels at a time and keeps only sum e g, sum e g d2 and
+// sum e g d2^2 of it, folded into the others when it leaves the column (the
+// factor v_0 of t waits for the chain rule).
+__device__ __forceinline__ void walk_columns(const VoxG &q, const GridK &g, float k2, bool untrunc,
+                                             const float *__restrict__ g_vol, int lane,
+                                             float *out) {
+    float x[1 + BW_NS];
+#pragma unroll
+    for (int k = 0; k < 1 + BW_NS; ++k) x[k] = 0.0f;
+    const int ny = q.hi1 - q.lo1 + 1;
+    const int ncol = (q.hi0 - q.lo0 + 1) * ny;
+    const float rny = __builtin_amdgcn_rcpf((float)ny);
+    const float zc = (q.mu[2] - g.c0[2]) * g.inv_h[2], zm = voxel_margin(g, 2, zc);
+    const float h2 = in_vgpr(g.h[2]), o2 = in_vgpr(g.c0[2]), kk = in_vgpr(k2);
+    for (int c0 = 0; c0 < ncol; c0 += 64) {
+        const int col = c0 + lane;
+        if (col >= ncol) continue;
+        const VoxCol c = vox_col(q, g, col, ny, rny, zc, zm, k2, untrunc);
+        const float *gz = g_vol + ((int64_t)c.ix * g.n[1] + c.iy) * g.n[2] + c.za;
+        float St = 0.0f, Sz = 0.0f, Szz = 0.0f, fz = (float)c.za;
+        auto voxel = [&](float z, float gl, bool in) {
+            const float d2 = fmaf(z, h2, o2) - q.mu[2];
+            const float mm = col_quad(q.a22, c.b2, c.cq, d2);
+            const float t = gl * (in && mm <= kk ? half_exp(mm) : 0.0f);
+            St += t;
+            const float td = t * d2;
+            Sz += td;
+            Szz = fmaf(td, d2, Szz);
+        };
+        for (int n = c.zb - c.za + 1; n > 0; n -= 2, gz += 2, fz += 2.0f) {
+            const float g0 = gz[0], g1 = gz[n > 1 ? 1 : 0];
+            voxel(fz, g0, true);
+            voxel(fz + 1.0f, g1, n > 1);
+        }
+        x[0] += St;
+        x[1] = fmaf(c.d0, St, x[1]);
+        x[2] = fmaf(c.d1, St, x[2]);
+        x[3] += Sz;
+        x[4] = fmaf(c.d0 * St, c.d0, x[4]);
+        x[5] = fmaf(c.d0 * St, c.d1, x[5]);
+        x[6] = fmaf(c.d0, Sz, x[6]);
+        x[7] = fmaf(c.d1 * St, c.d1, x[7]);
+        x[8] = fmaf(c.d1, Sz, x[8]);
+        x[9] += Szz;
+    }
+    wave_sums(x, 1 + BW_NS, lane, out);
+}
+
+// Several channels: a voxel loads C values, and lanes on different columns
+// would touch a cache line per lane and channel, so the voxels of 64 columns
+// are laid over the lanes in order (z fastest): each column's lane writes its
+// number to the places of its voxels, BW_SLOTS at a time, and a voxel's lane
+// reads its column from there.
+struct VoxSlots {
+    float4 q[64];                       // d0, d1, b2, cq of a column
+    int2 at[64];                        // volume offset and z index of place 0, if the column began there
+    uint8_t col[BW_SLOTS];
+};
+template <int CT>
+__device__ __forceinline__ void walk_voxels(const VoxG &q, const GridK &g, float k2, bool untrunc,
+                                            const float *__restrict__ g_vol, int C,
+                                            const float *val, VoxSlots &sl, int lane, float *out) {
+    constexpr int CM = CT > 0 ? CT : MAXC_VOX;
+    float x[CM + BW_NS], v[CM];
+#pragma unroll
+    for (int k = 0; k < CM + BW_NS; ++k) x[k] = 0.0f;
+#pragma unroll
+    for (int c = 0; c < CM; ++c) v[c] = c < C ? val[c] : 0.0f;
+    float *const m = x + CM;
+    const int64_t N = grid_size(g);
+    const int ny = q.hi1 - q.lo1 + 1;
+    const int ncol = (q.hi0 - q.lo0 + 1) * ny;
+    const float rny = __builtin_amdgcn_rcpf((float)ny);
+    const float zc = (q.mu[2] - g.c0[2]) * g.inv_h[2], zm = voxel_margin(g, 2, zc);
+    const float h2 = in_vgpr(g.h[2]), o2 = in_vgpr(g.c0[2]), kk = in_vgpr(k2);
+    for (int c0 = 0; c0 < ncol; c0 += 64) {                     // uniform
+        VoxCol c;
+        c.za = 0;
+        c.zb = -1;
+        if (c0 + lane < ncol) c = vox_col(q, g, c0 + lane, ny, rny, zc, zm, k2, untrunc);
+        const int len = c.zb - c.za + 1;
+        const int end = wave_incl_sum(len), beg = end - len;
+        const int total = __builtin_amdgcn_readlane(end, 63);
+        // the box's corner column begins at g_vol + box: offsets from it are int
+        if (len > 0) {
+            sl.q[lane] = make_float4(c.d0, c.d1, c.b2, c.cq);
+            sl.at[lane] = make_int2((c.ix - q.lo0) * g.n[1] + (c.iy - q.lo1), c.za - beg);
+        }
+        for (int w0 = 0; w0 < total; w0 += BW_SLOTS) {          // uniform
+            const int e = min(end - w0, BW_SLOTS);
+            for (int k = max(beg - w0, 0); k < e; ++k) sl.col[k] = (uint8_t)lane;
+            wave_lds_sync();
+            const int nw = min(total - w0, BW_SLOTS);
+            for (int p = lane; p < nw; p += 64) {
+                const int j = sl.col[p];
+                const float4 cf = sl.q[j];
+                const int2 at = sl.at[j];
+                const int iz = at.y + w0 + p;
+                const float *gp = g_vol + (((int64_t)q.lo0 * g.n[1] + q.lo1 + at.x) * g.n[2] + iz);
+                float gl[CM];
+#pragma unroll
+                for (int ch = 0; ch < CM; ++ch) gl[ch] = ch < C ? gp[ch * N] : 0.0f;
+                const float d2 = fmaf((float)iz, h2, o2) - q.mu[2];
+                const float mm = col_quad(q.a22, cf.z, cf.w, d2);
+                const float ev = mm <= kk ? half_exp(mm) : 0.0f;
+                float G = 0.0f;
+#pragma unroll
+                for (int ch = 0; ch < CM; ++ch) {
+                    if (ch < C) {
+                        x[ch] = fmaf(gl[ch], ev, x[ch]);
+                        G = fmaf(v[ch], gl[ch], G);
+                    }
+                }
+                const float t = G * ev;
+                const float t0 = t * cf.x, t1 = t * cf.y, t2 = t * d2;
+                m[0] += t0;
+                m[1] += t1;
+                m[2] += t2;
+                m[3] = fmaf(t0, cf.x, m[3]);
+                m[4] = fmaf(t0, cf.y, m[4]);
+                m[5] = fmaf(t0, d2, m[5]);
+                m[6] = fmaf(t1, cf.y, m[6]);
+                m[7] = fmaf(t1, d2, m[7]);
+                m[8] = fmaf(t2, d2, m[8]);
+            }
+            wave_lds_sync();
+        }
+    }
+    wave_sums(x, CM + BW_NS, lane, out);
+}
+
+template <int CT>
+__global__ __launch_bounds__(64 * BW_WAVES) void k_vox_bwd(pmf_gauss_t gs, GridK g, float k, int per,
+                                                           const float *__restrict__ g_vol,
+                                                           pmf_gauss_grad_t gr) {
     constexpr int CM = CT > 0 ? CT : MAXC_VOX;
     const int C = CT > 0 ? CT : gs.c;
-    // LDS for the wave's `per` Gaussians only (a one-Gaussian batch leaves
-    // room for many waves per CU): records, values, reduced sums
     extern __shared__ float4 bwd_smem[];
-    VoxG *const gb = (VoxG *)bwd_smem;
-    float(*const gval)[CM] = (float(*)[CM])(gb + per);
-    float(*const sums)[CM + BW_NS] = (float(*)[CM + BW_NS])(gval + per);
-    const int lane = threadIdx.x;
+    float(*const sums)[CM + BW_NS] = (float(*)[CM + BW_NS])bwd_smem;
+    VoxG *const gb = (VoxG *)(sums + per);
+    __shared__ int near[64], nnear;
+    const int t = (int)threadIdx.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6), nwaves = (int)blockDim.x / 64;
     const int64_t g0 = (int64_t)blockIdx.x * per;
     const float k2 = isinf(k) ? INFINITY : k * k;
     const bool untrunc = isinf(k2);
-    // set-up: lane j < per builds Gaussian g0 + j
-    if (lane < per) {
+    bool hit = false;
+    if (wave == 0) {
         const int64_t gi = g0 + lane;
-        VoxG q = {};
-        q.lo0 = q.lo1 = q.lo2 = 1;                  // empty box
-        if (gi < gs.m && !far_from_grid(gs.mean, gs.scale, gi, k, g)) {
+        if (lane < per && gi < gs.m && !far_from_grid(gs.mean, gs.scale, gi, k, g)) {
             GaussFull G;
             gauss_full(gs.mean, gs.scale, gs.quat, gi, k, g, G);
+            VoxG q;
             for (int a = 0; a < 3; ++a) q.mu[a] = G.mu[a];
             q.a00 = G.A[0][0];
             q.a01 = G.A[0][1];
@@ -983,179 +1187,31 @@ __global__ __launch_bounds__(64) void k_vox_bwd(pmf_gauss_t gs, GridK g, float k
             q.hi0 = G.hi[0];
             q.hi1 = G.hi[1];
             q.hi2 = G.hi[2];
-            for (int c = 0; c < C; ++c) gval[lane][c] = gs.value[gi * C + c];
+            hit = q.lo0 <= q.hi0 && q.lo1 <= q.hi1 && q.lo2 <= q.hi2;
+            gb[lane] = q;
         }
-        gb[lane] = q;
+        const uint64_t hits = __ballot(hit);
+        if (hit) near[__popcll(hits & ((1ull << lane) - 1))] = lane;
+        if (lane == 0) nnear = __popcll(hits);
     }
     __syncthreads();
-    const int64_t N = grid_size(g);
-    const float inv_h2 = g.inv_h[2];
-    const int nj = (int)min((int64_t)per, gs.m - g0);
-    for (int j = 0; j < nj; ++j) {                  // uniform
+    for (int i = wave; i < nnear; i += nwaves) {               // uniform
+        const int j = near[i];
         const VoxG q = gb[j];
-        float gv[CM];
-#pragma unroll
-        for (int c = 0; c < CM; ++c) gv[c] = 0.0f;
-        float P0 = 0, P1 = 0, P2 = 0, M00 = 0, M01 = 0, M02 = 0, M11 = 0, M12 = 0, M22 = 0;
-        if (q.lo0 <= q.hi0 && q.lo1 <= q.hi1 && q.lo2 <= q.hi2) {
-            float val[CM];
-#pragma unroll
-            for (int c = 0; c < CM; ++c) val[c] = c < C ? gval[j][c] : 0.0f;
-            const int ny = q.hi1 - q.lo1 + 1;
-            const int ncol = (q.hi0 - q.lo0 + 1) * ny;
-            const float rny = __builtin_amdgcn_rcpf((float)ny);
-            const float zc = (q.mu[2] - g.c0[2]) * inv_h2, zm = voxel_margin(g, 2, zc);
-            if constexpr (ZL) {
-                const int nz = q.hi2 - q.lo2 + 1;
-                const int zl = nz <= 4 ? 4 : nz <= 8 ? 8 : nz <= 16 ? 16 : nz <= 32 ? 32 : 64;
-                const int cpr = 64 / zl;
-                const int zr = lane & (zl - 1), cl = lane / zl;
-                for (int c0 = 0; c0 < ncol; c0 += cpr) {
-                    const int col = c0 + cl;
-                    if (col >= ncol) continue;
-                    int cx = (int)(((float)col + 0.5f) * rny);
-                    int cy = col - cx * ny;
-                    if (cy < 0) {
-                        --cx;
-                        cy += ny;
-                    } else if (cy >= ny) {
-                        ++cx;
-                        cy -= ny;
-                    }
-                    const int ix = q.lo0 + cx, iy = q.lo1 + cy;
-                    const float d0 = fmaf((float)ix, g.h[0], g.c0[0]) - q.mu[0];
-                    const float d1 = fmaf((float)iy, g.h[1], g.c0[1]) - q.mu[1];
-                    float cb2, cq;
-                    col_coeffs(q.a00, q.a01, q.a02, q.a11, q.a12, d0, d1, cb2, cq);
-                    int za, zb;
-                    if (!col_range(q.a22, cb2, cq, zc, zm, inv_h2, k2, untrunc, q.lo2, q.hi2, za, zb))
-                        continue;
-                    const float *gcol = g_vol + ((int64_t)ix * g.n[1] + iy) * g.n[2];
-                    for (int iz = za + zr; iz <= zb; iz += zl) {
-                        float gl[CM];
-#pragma unroll
-                        for (int c = 0; c < CM; ++c)
-                            if (c < C) gl[c] = gcol[c * N + iz];
-                        const float d2 = fmaf((float)iz, g.h[2], g.c0[2]) - q.mu[2];
-                        const float mm = col_quad(q.a22, cb2, cq, d2);
-                        const float ev = mm <= k2 ? __expf(-0.5f * mm) : 0.0f;
-                        float Gj = 0.0f;
-#pragma unroll
-                        for (int c = 0; c < CM; ++c) {
-                            if (c < C) {
-                                gv[c] = fmaf(gl[c], ev, gv[c]);
-                                Gj = fmaf(val[c], gl[c], Gj);
-                            }
-                        }
-                        const float t = Gj * ev;
-                        const float t0 = t * d0, t1 = t * d1, t2 = t * d2;
-                        P0 += t0;
-                        P1 += t1;
-                        P2 += t2;
-                        M00 = fmaf(t0, d0, M00);
-                        M01 = fmaf(t0, d1, M01);
-                        M02 = fmaf(t0, d2, M02);
-                        M11 = fmaf(t1, d1, M11);
-                        M12 = fmaf(t1, d2, M12);
-                        M22 = fmaf(t2, d2, M22);
-                    }
-                }
-            } else
-            for (int c0 = 0; c0 < ncol; c0 += 64) {
-                const int col = c0 + lane;
-                if (col >= ncol) continue;
-                // col = cx * ny + cy (the float quotient is corrected to exact)
-                int cx = (int)(((float)col + 0.5f) * rny);
-                int cy = col - cx * ny;
-                if (cy < 0) {
-                    --cx;
-                    cy += ny;
-                } else if (cy >= ny) {
-                    ++cx;
-                    cy -= ny;
-                }
-                const int ix = q.lo0 + cx, iy = q.lo1 + cy;
-                const float d0 = fmaf((float)ix, g.h[0], g.c0[0]) - q.mu[0];
-                const float d1 = fmaf((float)iy, g.h[1], g.c0[1]) - q.mu[1];
-                float cb2, cq;
-                col_coeffs(q.a00, q.a01, q.a02, q.a11, q.a12, d0, d1, cb2, cq);
-                int za, zb;
-                if (!col_range(q.a22, cb2, cq, zc, zm, inv_h2, k2, untrunc, q.lo2, q.hi2, za, zb))
-                    continue;
-                const float *gcol = g_vol + ((int64_t)ix * g.n[1] + iy) * g.n[2];
-                float St = 0.0f, Sz = 0.0f, Szz = 0.0f;
-                // every voxel of the range is loaded (the range lies in the
-                // grid); voxels outside the ellipsoid add exact zeros, so the
-                // loop has no branch and successive voxels' loads overlap
-                constexpr int UNR = CT == 1 ? 4 : 1;
-#pragma unroll UNR
-                for (int iz = za; iz <= zb; ++iz) {
-                    float gl[CM];
-#pragma unroll
-                    for (int c = 0; c < CM; ++c)
-                        if (c < C) gl[c] = gcol[c * N + iz];
-                    const float d2 = fmaf((float)iz, g.h[2], g.c0[2]) - q.mu[2];
-                    const float mm = col_quad(q.a22, cb2, cq, d2);
-                    const float ev = mm <= k2 ? __expf(-0.5f * mm) : 0.0f;
-                    float Gj = 0.0f;
-#pragma unroll
-                    for (int c = 0; c < CM; ++c) {
-                        if (c < C) {
-                            gv[c] = fmaf(gl[c], ev, gv[c]);
-                            Gj = fmaf(val[c], gl[c], Gj);
-                        }
-                    }
-                    const float t = Gj * ev;
-                    St += t;
-                    const float td = t * d2;
-                    Sz += td;
-                    Szz = fmaf(td, d2, Szz);
-                }
-                P0 = fmaf(d0, St, P0);
-                P1 = fmaf(d1, St, P1);
-                P2 += Sz;
-                M00 = fmaf(d0 * St, d0, M00);
-                M01 = fmaf(d0 * St, d1, M01);
-                M02 = fmaf(d0, Sz, M02);
-                M11 = fmaf(d1 * St, d1, M11);
-                M12 = fmaf(d1, Sz, M12);
-                M22 += Szz;
-            }
-        }
-#pragma unroll
-        for (int c = 0; c < CM; ++c)
-            if (c < C) gv[c] = wave_sum_lane63(gv[c]);
-        P0 = wave_sum_lane63(P0);
-        P1 = wave_sum_lane63(P1);
-        P2 = wave_sum_lane63(P2);
-        M00 = wave_sum_lane63(M00);
-        M01 = wave_sum_lane63(M01);
-        M02 = wave_sum_lane63(M02);
-        M11 = wave_sum_lane63(M11);
-        M12 = wave_sum_lane63(M12);
-        M22 = wave_sum_lane63(M22);
-        if (lane == 63) {
-            float *o = sums[j];
-#pragma unroll
-            for (int c = 0; c < CM; ++c)
-                if (c < C) o[c] = gv[c];
-            o[CM + 0] = P0;
-            o[CM + 1] = P1;
-            o[CM + 2] = P2;
-            o[CM + 3] = M00;
-            o[CM + 4] = M01;
-            o[CM + 5] = M02;
-            o[CM + 6] = M11;
-            o[CM + 7] = M12;
-            o[CM + 8] = M22;
+        if constexpr (CT == 1) {
+            walk_columns(q, g, k2, untrunc, g_vol, lane, sums[j]);
+        } else {
+            __shared__ VoxSlots slots[BW_WAVES];
+            walk_voxels<CT>(q, g, k2, untrunc, g_vol, C, gs.value + (g0 + j) * C, slots[wave], lane,
+                            sums[j]);
         }
     }
     __syncthreads();
     // chain rule: lane j for Gaussian g0 + j
-    const int64_t gi = g0 + lane;
-    if (lane >= nj) return;
-    const VoxG q = gb[lane];
-    if (!(q.lo0 <= q.hi0 && q.lo1 <= q.hi1 && q.lo2 <= q.hi2)) {   // no voxel: zero gradients
+    const int64_t gi = g0 + t;
+    if (t >= per || gi >= gs.m) return;
+    float *const o = sums[t];
+    if (!hit) {                           // no voxel: zero gradients (t < per: a lane of wave 0)
         for (int c = 0; c < C; ++c) gr.value[gi * C + c] = 0.0f;
         for (int a = 0; a < 3; ++a) {
             gr.mean[3 * gi + a] = 0.0f;
@@ -1166,8 +1222,11 @@ __global__ __launch_bounds__(64) void k_vox_bwd(pmf_gauss_t gs, GridK g, float k
     }
     GaussFull G;
     gauss_full(gs.mean, gs.scale, gs.quat, gi, k, g, G);
-    const float *o = sums[lane];
     for (int c = 0; c < C; ++c) gr.value[gi * C + c] = o[c];
+    if constexpr (CT == 1) {
+        const float v = gs.value[gi];
+        for (int c = 1; c <= BW_NS; ++c) o[c] *= v;
+    }
     const float P[3] = {o[CM + 0], o[CM + 1], o[CM + 2]};
     // mean: d/dmu of -m/2 is A d, so dL/dmu = A sum t d
     for (int a = 0; a < 3; ++a)
@@ -1206,28 +1265,25 @@ hipError_t launch_voxelize_bwd(const pmf_gauss_t &gs, const GridK &g, float k, c
     if (gs.m <= 0) return hipSuccess;
     {
         ProfScope prof_("voxelize_bwd", s);
-        // Gaussians per wave: at least ~12,500 waves (a dozen per SIMD) to
-        // hide the loads' latency, then as many Gaussians per wave as keeps
-        // that (the set-up and the chain rule run lane-parallel over a
-        // wave's Gaussians); measured on 200k one-channel and 1k-16k
-        // nine-channel sets
-        int per = 1;
+        // Gaussians per workgroup: as many as leave about 2,000 workgroups (64
+        // fill the lanes of the set-up and the chain rule), at least one per wave
+        int per = BW_WAVES;
         const int choice = tune_get(KNOB_VOXELIZE_BWD);
         if (choice > 0)
             per = 1 << (choice - 1);
         else
-            while (per < 64 && gs.m / (2 * per) > 12500) per *= 2;
-        const unsigned nb = (unsigned)((gs.m + per - 1) / per);
+            while (per < 64 && gs.m / (2 * per) >= 2000) per *= 2;
+        const unsigned nb = (unsigned)((gs.m + per - 1) / per), nt = 64u * std::min(per, BW_WAVES);
         const int cm = gs.c == 1 || gs.c == 3 || gs.c == 9 ? gs.c : MAXC_VOX;
-        const size_t lds = (size_t)per * (sizeof(VoxG) + sizeof(float) * (2 * cm + BW_NS));
+        const size_t lds = (size_t)per * (sizeof(VoxG) + sizeof(float) * (cm + BW_NS));
         if (gs.c == 1)
-            k_vox_bwd<1, false><<<nb, 64, lds, s>>>(gs, g, k, per, g_vol, gr);
+            k_vox_bwd<1><<<nb, nt, lds, s>>>(gs, g, k, per, g_vol, gr);
         else if (gs.c == 3)
-            k_vox_bwd<3, true><<<nb, 64, lds, s>>>(gs, g, k, per, g_vol, gr);
+            k_vox_bwd<3><<<nb, nt, lds, s>>>(gs, g, k, per, g_vol, gr);
         else if (gs.c == 9)
-            k_vox_bwd<9, true><<<nb, 64, lds, s>>>(gs, g, k, per, g_vol, gr);
+            k_vox_bwd<9><<<nb, nt, lds, s>>>(gs, g, k, per, g_vol, gr);
         else
-            k_vox_bwd<0, true><<<nb, 64, lds, s>>>(gs, g, k, per, g_vol, gr);
+            k_vox_bwd<0><<<nb, nt, lds, s>>>(gs, g, k, per, g_vol, gr);
     }
     return hipGetLastError();
 }

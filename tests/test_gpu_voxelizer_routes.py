@@ -96,3 +96,21 @@ def test_no_gaussians():
     z = np.zeros((0, 3), np.float32)
     out = ops.pmf_voxelize(T(z), T(z), T(np.zeros((0, 4))), T(np.zeros((0, 1))), grid, K)
     assert not out.any()
+
+
+# the adjoint's walks: boxes of fewer and more than 64 columns and columns of
+# more than a window of voxels, sets of one workgroup's size and around it
+@pytest.mark.parametrize("c", [1, 2, 3, 9])
+@pytest.mark.parametrize("m,s_vox,n", [(3, (6.0, 12.0), (40, 36, 90)), (4, (0.3, 0.6), (20, 21, 22)),
+                                       (65, (0.5, 2.0), (20, 21, 22)), (130, (0.05, 3.0), (9, 70, 11))])
+def test_adjoint_walks(m, s_vox, n, c):
+    print(m, s_vox, n, c, flush=True)
+    grid = Grid(n, (1.0, 1.2, 0.9), (1.0, 2.0, -3.0))
+    gs = synth.gaussians(np.random.default_rng(m), m, grid, c=c, s_vox=s_vox, value_sigma=1.0)
+    gv = synth.random_normal(m, (c,) + tuple(n))
+    want = oracle.voxelize_bwd(gs, grid, K, gv)
+    got = ops.pmf_voxelize_bwd(T(gs.mean), T(gs.scale), T(gs.quat), T(gs.value), grid, K, T(gv))
+    for name, g in zip(("mean", "scale", "quat", "value"), got):
+        w = want[name]
+        e = np.linalg.norm(g.cpu().numpy().astype(np.float64) - w)
+        assert e <= 1e-3 * np.linalg.norm(w), (name, e)
