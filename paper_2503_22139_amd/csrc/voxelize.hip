@@ -309,6 +309,11 @@ __device__ __forceinline__ int32_t block_excl_sum(int32_t v, int32_t *wsum, int3
 // Each chunk scans the tiles' totals (the first one stores them as the lists'
 // offsets) and writes its pairs to their places, and its large Gaussians, in
 // ascending order, to the large list.
+// With SHORT it also sums the chunks' counts itself: up to BIN_SHORT (chunk,
+// tile) counts that costs less than k_vox_chunks' launch.
+constexpr int BIN_SHORT = 1 << 14;
+
+template <bool SHORT>
 __global__ __launch_bounds__(BIN_T) void k_vox_fill(int64_t m, const GaussK *__restrict__ rec,
                                                     VoxTiles p, const int32_t *__restrict__ part,
                                                     const int32_t *__restrict__ total,
@@ -325,7 +330,24 @@ __global__ __launch_bounds__(BIN_T) void k_vox_fill(int64_t m, const GaussK *__r
     int32_t carry = 0;
     for (int w0 = 0; w0 < p.ntiles; w0 += BIN_W) {
         const int nw = min(BIN_W, p.ntiles - w0);
-        for (int t0 = 0; t0 < nw; t0 += 4 * BIN_T) {
+        for (int t0 = 0; SHORT && t0 < nw; t0 += BIN_T) {
+            const int t = t0 + (int)threadIdx.x;
+            int32_t all = 0, before = 0;
+            if (t < nw) {
+#pragma unroll 8
+                for (int c = 0; c < (int)gridDim.x; ++c) {
+                    const int32_t x = part[(int64_t)c * p.ntiles + w0 + t];
+                    all += x;
+                    before += c < (int)blockIdx.x ? x : 0;
+                }
+            }
+            const int32_t o = block_excl_sum(all, wsum, carry);
+            if (t < nw) {
+                if (first) off[w0 + t] = o;
+                base[t] = o + before;
+            }
+        }
+        for (int t0 = 0; !SHORT && t0 < nw; t0 += 4 * BIN_T) {
             // four neighbouring tiles per thread
             const int t = t0 + 4 * (int)threadIdx.x;
             int32_t v[4], s = 0;
@@ -635,25 +657,26 @@ __global__ __launch_bounds__(64 * NW) void k_vox_tile(const GaussK *__restrict__
 // atomics: the kernel holds little LDS and keeps many tiles in flight.
 constexpr int VG_CHUNK = 64;
 
-template <int T0, int T1, int T2, int CT>
-__global__ __launch_bounds__(256) void k_vox_gather(const GaussK *__restrict__ rec,
-                                                    const float *__restrict__ value, GridK g,
-                                                    float k2, int nt1, int nt2,
-                                                    const int32_t *__restrict__ off,
-                                                    const int32_t *__restrict__ list,
-                                                    const int32_t *__restrict__ large,
-                                                    const int32_t *__restrict__ nlarge,
-                                                    float *__restrict__ vol) {
+template <int T0, int T1, int T2, int CT, int NT>
+__global__ __launch_bounds__(NT) void k_vox_gather(const GaussK *__restrict__ rec,
+                                                   const float *__restrict__ value, GridK g,
+                                                   float k2, int nt1, int nt2,
+                                                   const int32_t *__restrict__ off,
+                                                   const int32_t *__restrict__ list,
+                                                   const int32_t *__restrict__ large,
+                                                   const int32_t *__restrict__ nlarge,
+                                                   float *__restrict__ vol) {
     constexpr int TV = T0 * T1 * T2;
-    constexpr int SEG = TV / 256;           // voxels per thread (along z)
+    constexpr int SEG = TV / NT;            // voxels per thread (along z)
     constexpr int NS = T2 / SEG;            // threads per column
-    static_assert(SEG >= 1 && T2 % SEG == 0 && TV % 256 == 0, "tile shape");
+    constexpr int NW = NT / 64;
+    static_assert(SEG >= 1 && T2 % SEG == 0 && TV % NT == 0, "tile shape");
     __shared__ GaussK gsh[VG_CHUNK];
     __shared__ float gvs[VG_CHUNK][CT];
     __shared__ int nsh;
-    __shared__ float cs[4][CT];
+    __shared__ float cs[NW][CT];
     __shared__ float scale[CT];
-    const int t = blockIdx.x;
+    const int t = rotated_tile((int)blockIdx.x, nt1, nt2);
     const int tz = t % nt2, ty = (t / nt2) % nt1, tx = t / (nt2 * nt1);
     const int b0 = tx * T0, b1 = ty * T1, b2 = tz * T2;
     const int e0 = min(b0 + T0, g.n[0]) - 1, e1 = min(b1 + T1, g.n[1]) - 1,
@@ -665,12 +688,53 @@ __global__ __launch_bounds__(256) void k_vox_gather(const GaussK *__restrict__ r
     const int ix = b0 + col / T1, iy = b1 + col % T1, z0 = b2 + seg * SEG;
     // x range of the wave's columns (a wave-uniform cull of each Gaussian)
     const int wx0 = b0 + (wave * 64 / NS) / T1, wx1 = b0 + ((wave * 64 + 63) / NS) / T1;
-    {
+    // lane's entry of a chunk, staged in LDS if it has voxels in the tile (one wave)
+    auto stage = [&](bool on, const GaussK &p, const float (&v)[CT]) {
+        const bool hit = on && max(p.lo0, b0) <= min(p.hi0, e0) &&
+                         max(p.lo1, b1) <= min(p.hi1, e1) && max(p.lo2, b2) <= min(p.hi2, e2);
+        const uint64_t hits = __ballot(hit);
+        if (hit) {
+            const int j = __popcll(hits & ((1ull << lane) - 1));
+            gsh[j] = p;
+#pragma unroll
+            for (int c = 0; c < CT; ++c) gvs[j][c] = v[c];
+        }
+        if (lane == 0) nsh = __popcll(hits);
+    };
+    auto scale_of = [&](float mx) {
+        const float S = (float)(end - beg) * mx;
+        return S > 0.0f ? 1073741824.0f / (S * 1.0001f) : 0.0f;
+    };
+    // A list of one chunk (the usual case) is read once, by one wave: its
+    // largest values and its staging need no second chain of loads.
+    const bool one = end - beg <= VG_CHUNK;                       // uniform
+    if (one) {
+        if (wave == 0) {
+            const bool on = beg + lane < end;
+            GaussK p = {};
+            float v[CT];
+#pragma unroll
+            for (int c = 0; c < CT; ++c) v[c] = 0.0f;
+            if (on) {
+                const int gi = list[beg + lane];
+#pragma unroll
+                for (int c = 0; c < CT; ++c) v[c] = value[(int64_t)gi * CT + c];
+                p = rec[gi];
+            }
+#pragma unroll
+            for (int c = 0; c < CT; ++c) {
+                const float sc = scale_of(wave_max(fabsf(v[c])));
+                v[c] *= sc;
+                if (lane == 0) scale[c] = sc;
+            }
+            stage(on, p, v);
+        }
+    } else {
         // one pass over the list: each entry's channels load together
         float mx[CT];
 #pragma unroll
         for (int c = 0; c < CT; ++c) mx[c] = 0.0f;
-        for (int e = beg + (int)threadIdx.x; e < end; e += 256) {
+        for (int e = beg + (int)threadIdx.x; e < end; e += NT) {
             const float *vv = value + (int64_t)list[e] * CT;
 #pragma unroll
             for (int c = 0; c < CT; ++c) mx[c] = fmaxf(mx[c], fabsf(vv[c]));
@@ -680,13 +744,13 @@ __global__ __launch_bounds__(256) void k_vox_gather(const GaussK *__restrict__ r
             const float m = wave_max(mx[c]);
             if (lane == 0) cs[wave][c] = m;
         }
-    }
-    __syncthreads();
-    if (threadIdx.x < (unsigned)CT) {
-        const float mx = fmaxf(fmaxf(cs[0][threadIdx.x], cs[1][threadIdx.x]),
-                               fmaxf(cs[2][threadIdx.x], cs[3][threadIdx.x]));
-        const float S = (float)(end - beg) * mx;
-        scale[threadIdx.x] = S > 0.0f ? 1073741824.0f / (S * 1.0001f) : 0.0f;
+        __syncthreads();
+        if (threadIdx.x < (unsigned)CT) {
+            float m = 0.0f;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) m = fmaxf(m, cs[w][threadIdx.x]);
+            scale[threadIdx.x] = scale_of(m);
+        }
     }
     const float d0g = fmaf((float)ix, g.h[0], g.c0[0]);
     const float d1g = fmaf((float)iy, g.h[1], g.c0[1]);
@@ -700,21 +764,18 @@ __global__ __launch_bounds__(256) void k_vox_gather(const GaussK *__restrict__ r
         for (int c = 0; c < CT; ++c) acc[s][c] = 0;
     for (int cb = beg; cb < end; cb += VG_CHUNK) {
         __syncthreads();                  // scale ready / previous chunk consumed
-        if (wave == 0) {                  // stages the Gaussians with voxels in the tile
-            const bool on = cb + lane < end;
-            const int gi = list[on ? cb + lane : cb];
-            const GaussK p = rec[gi];
-            const bool hit = on && max(p.lo0, b0) <= min(p.hi0, e0) &&
-                             max(p.lo1, b1) <= min(p.hi1, e1) && max(p.lo2, b2) <= min(p.hi2, e2);
-            const uint64_t hits = __ballot(hit);
-            if (hit) {
-                const int j = __popcll(hits & ((1ull << lane) - 1));
-                gsh[j] = p;
-                for (int c = 0; c < CT; ++c) gvs[j][c] = value[(int64_t)gi * CT + c] * scale[c];
+        if (!one) {
+            if (wave == 0) {
+                const bool on = cb + lane < end;
+                const int gi = list[on ? cb + lane : cb];
+                float v[CT];
+#pragma unroll
+                for (int c = 0; c < CT; ++c) v[c] = value[(int64_t)gi * CT + c] * scale[c];
+                const GaussK p = rec[gi];
+                stage(on, p, v);
             }
-            if (lane == 0) nsh = __popcll(hits);
+            __syncthreads();
         }
-        __syncthreads();
         const int n = nsh;
         for (int e = 0; e < n; ++e) {
             const GaussK p = gsh[e];
@@ -893,7 +954,8 @@ hipError_t launch_voxelize(const pmf_gauss_t &gs, const GridK &g, float k, float
             k_vox_bin<<<(unsigned)p.nch, BIN_T, hist, s>>>(gs, g, k, t, rec, w.part, w.slot, nlarge);
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        {
+        const bool brief = (int64_t)p.nch * p.ntiles <= BIN_SHORT;
+        if (!brief) {
             ProfScope prof_("voxelize_chunks", s);
             k_vox_chunks<<<(unsigned)((p.ntiles + 63) / 64), 256, 0, s>>>(w.part, t.ntiles, p.nch,
                                                                           w.total);
@@ -901,8 +963,12 @@ hipError_t launch_voxelize(const pmf_gauss_t &gs, const GridK &g, float k, float
         if ((e = hipGetLastError()) != hipSuccess) return e;
         {
             ProfScope prof_("voxelize_fill", s);
-            k_vox_fill<<<(unsigned)p.nch, BIN_T, hist, s>>>(m, rec, t, w.part, w.total, w.slot,
-                                                           nlarge, off, list, large);
+            if (brief)
+                k_vox_fill<true><<<(unsigned)p.nch, BIN_T, hist, s>>>(
+                    m, rec, t, w.part, w.total, w.slot, nlarge, off, list, large);
+            else
+                k_vox_fill<false><<<(unsigned)p.nch, BIN_T, hist, s>>>(
+                    m, rec, t, w.part, w.total, w.slot, nlarge, off, list, large);
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
@@ -924,8 +990,15 @@ hipError_t launch_voxelize(const pmf_gauss_t &gs, const GridK &g, float k, float
                 rec, gs.value, gs.c, g, k2, p.nt[1], p.nt[2], off, list, large, nlarge, vol);     \
     } while (0)
 #define VOX_GATHER(T1_, T2_, CT_)                                                                 \
-    k_vox_gather<8, T1_, T2_, CT_><<<(unsigned)p.ntiles, 256, 0, s>>>(                           \
-        rec, gs.value, g, k2, p.nt[1], p.nt[2], off, list, large, nlarge, vol)
+    do {                                                                                          \
+        constexpr int NT_ = 8 * T1_ * T2_ / 2;                                                    \
+        if (few)                                                                                  \
+            k_vox_gather<8, T1_, T2_, CT_, NT_><<<(unsigned)p.ntiles, NT_, 0, s>>>(               \
+                rec, gs.value, g, k2, p.nt[1], p.nt[2], off, list, large, nlarge, vol);           \
+        else                                                                                      \
+            k_vox_gather<8, T1_, T2_, CT_, 256><<<(unsigned)p.ntiles, 256, 0, s>>>(               \
+                rec, gs.value, g, k2, p.nt[1], p.nt[2], off, list, large, nlarge, vol);           \
+    } while (0)
 #define VOX_TILE_C(T1_, T2_)                                                                      \
     do {                                                                                          \
         if (cs == 1) VOX_TILE(T1_, T2_, 1);                                                       \
