@@ -657,8 +657,8 @@ __global__ __launch_bounds__(64 * NW) void k_vox_tile(const GaussK *__restrict__
 // atomics: the kernel holds little LDS and keeps many tiles in flight.
 constexpr int VG_CHUNK = 64;
 
-template <int T0, int T1, int T2, int CT, int NT>
-__global__ __launch_bounds__(NT) void k_vox_gather(const GaussK *__restrict__ rec,
+template <int T0, int T1, int T2, int CT>
+__global__ __launch_bounds__(256) void k_vox_gather(const GaussK *__restrict__ rec,
                                                    const float *__restrict__ value, GridK g,
                                                    float k2, int nt1, int nt2,
                                                    const int32_t *__restrict__ off,
@@ -667,6 +667,7 @@ __global__ __launch_bounds__(NT) void k_vox_gather(const GaussK *__restrict__ re
                                                    const int32_t *__restrict__ nlarge,
                                                    float *__restrict__ vol) {
     constexpr int TV = T0 * T1 * T2;
+    constexpr int NT = 256;
     constexpr int SEG = TV / NT;            // voxels per thread (along z)
     constexpr int NS = T2 / SEG;            // threads per column
     constexpr int NW = NT / 64;
@@ -979,7 +980,11 @@ hipError_t launch_voxelize(const pmf_gauss_t &gs, const GridK &g, float k, float
         const int sel = (p.T[1] == 16 ? 2 : 0) + (p.T[2] == 16 ? 1 : 0);
         const int cs = gs.c;
         // one channel: the LDS splat (many Gaussians per tile); 3 or 9
-        // channels: voxel owners; other channel counts: the LDS splat
+        // channels: voxel owners, but sixteen waves of the LDS splat on few
+        // tiles (1,000 to 16,000 Gaussians of three channels on 32x32x32 to
+        // 128x128x64, 64 to 512 tiles: 21, 21 and 66 us with voxel owners, 8,
+        // 10 and 21 with the splat; on 8,192 tiles of nine channels 110 us
+        // against 152); other channel counts: the LDS splat
 #define VOX_TILE(T1_, T2_, CT_)                                                                   \
     do {                                                                                          \
         if (few)                                                                                  \
@@ -991,12 +996,11 @@ hipError_t launch_voxelize(const pmf_gauss_t &gs, const GridK &g, float k, float
     } while (0)
 #define VOX_GATHER(T1_, T2_, CT_)                                                                 \
     do {                                                                                          \
-        constexpr int NT_ = 8 * T1_ * T2_ / 2;                                                    \
         if (few)                                                                                  \
-            k_vox_gather<8, T1_, T2_, CT_, NT_><<<(unsigned)p.ntiles, NT_, 0, s>>>(               \
-                rec, gs.value, g, k2, p.nt[1], p.nt[2], off, list, large, nlarge, vol);           \
+            k_vox_tile<8, T1_, T2_, CT_, 16, 8><<<(unsigned)p.ntiles, 1024, lds, s>>>(            \
+                rec, gs.value, gs.c, g, k2, p.nt[1], p.nt[2], off, list, large, nlarge, vol);     \
         else                                                                                      \
-            k_vox_gather<8, T1_, T2_, CT_, 256><<<(unsigned)p.ntiles, 256, 0, s>>>(               \
+            k_vox_gather<8, T1_, T2_, CT_><<<(unsigned)p.ntiles, 256, 0, s>>>(                    \
                 rec, gs.value, g, k2, p.nt[1], p.nt[2], off, list, large, nlarge, vol);           \
     } while (0)
 #define VOX_TILE_C(T1_, T2_)                                                                      \
