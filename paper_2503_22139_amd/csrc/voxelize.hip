@@ -263,16 +263,16 @@ __global__ __launch_bounds__(BIN_T) void k_vox_bin(pmf_gauss_t gs, GridK g, floa
 
 // Per tile: the chunks' counts -> the places of their first pairs in the tile's
 // list, in place, and the tile's total.  A workgroup takes 64 tiles (a lane
-// each), its four waves a quarter of the chunks each.
-__global__ __launch_bounds__(256) void k_vox_chunks(int32_t *__restrict__ part, int ntiles, int nch,
+// each), its sixteen waves a sixteenth of the chunks each.
+__global__ __launch_bounds__(1024) void k_vox_chunks(int32_t *__restrict__ part, int ntiles, int nch,
                                                     int32_t *__restrict__ total) {
-    __shared__ int32_t sums[4][64];
+    __shared__ int32_t sums[16][64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int t = blockIdx.x * 64 + lane;
-    const int per = (nch + 3) / 4, c0 = min(w * per, nch), c1 = min(c0 + per, nch);
+    const int per = (nch + 15) / 16, c0 = min(w * per, nch), c1 = min(c0 + per, nch);
     int32_t s = 0;
     if (t < ntiles) {
-#pragma unroll 16
+#pragma unroll 8
         for (int c = c0; c < c1; ++c) s += part[(int64_t)c * ntiles + t];
     }
     sums[w][lane] = s;
@@ -280,13 +280,13 @@ __global__ __launch_bounds__(256) void k_vox_chunks(int32_t *__restrict__ part, 
     if (t >= ntiles) return;
     int32_t run = 0;
     for (int k = 0; k < w; ++k) run += sums[k][lane];
-#pragma unroll 16
+#pragma unroll 8
     for (int c = c0; c < c1; ++c) {
         const int32_t x = part[(int64_t)c * ntiles + t];
         part[(int64_t)c * ntiles + t] = run;
         run += x;
     }
-    if (w == 3) total[t] = run;
+    if (w == 15) total[t] = run;
 }
 
 // Exclusive scan of v over the workgroup (BIN_T threads), the sum added to carry.
@@ -526,6 +526,7 @@ __global__ __launch_bounds__(64 * NW) void k_vox_tile(const GaussK *__restrict__
     __syncthreads();
     const bool untrunc = isinf(k2);
     const float inv_h2 = g.inv_h[2];
+    const float h2 = in_vgpr(g.h[2]), o2 = in_vgpr(g.c0[2]), kk = in_vgpr(k2);
     VoxB *const B = bt[wave];
     for (int eb = beg + wave * VB; eb < end; eb += NW * VB) {     // uniform per wave
         const int nb = min(VB, end - eb);
@@ -590,10 +591,11 @@ __global__ __launch_bounds__(64 * NW) void k_vox_tile(const GaussK *__restrict__
 #pragma unroll
             for (int c = 0; c < CM; ++c) vs[c] = c < C ? bv[wave][j][c] : 0.0f;
             int li = ((ix - b0) * T1 + (iy - b1)) * T2 + (za - b2);
-            for (int iz = za; iz <= zb; ++iz, ++li) {
-                const float d2 = fmaf((float)iz, g.h[2], g.c0[2]) - mu2;
+            float fz = (float)za;
+            for (int n = zb - za; n >= 0; --n, ++li, fz += 1.0f) {
+                const float d2 = fmaf(fz, h2, o2) - mu2;
                 const float mm = col_quad(a22, cb2, cq, d2);
-                if (!(mm <= k2)) continue;
+                if (!(mm <= kk)) continue;
                 const float ev = half_exp(mm);
 #pragma unroll
                 for (int c = 0; c < CM; ++c)
@@ -889,9 +891,11 @@ VoxPlan vox_plan(int64_t m, int c, const GridK &g) {
     }
     p.maxtiles = 32;
     p.cap = m * p.maxtiles;
-    // chunks of at least 128 Gaussians, at most 256 of them (one per CU), and
-    // no more than 2^24 (chunk, tile) counts unless that leaves fewer than 8
-    p.nch = (int)std::max<int64_t>(1, std::min<int64_t>({256, (m + 127) / 128,
+    // chunks of at least 128 Gaussians, at most 256 of them (one per CU) or,
+    // if that is more, of 512 Gaussians (a pass of their threads), and no
+    // more than 2^24 (chunk, tile) counts unless that leaves fewer than 8
+    const int64_t most = std::max<int64_t>(256, std::min<int64_t>(512, (m + BIN_T - 1) / BIN_T));
+    p.nch = (int)std::max<int64_t>(1, std::min<int64_t>({most, (m + 127) / 128,
                                                          std::max<int64_t>(8, (1 << 24) / p.ntiles)}));
     return p;
 }
@@ -958,7 +962,7 @@ hipError_t launch_voxelize(const pmf_gauss_t &gs, const GridK &g, float k, float
         const bool brief = (int64_t)p.nch * p.ntiles <= BIN_SHORT;
         if (!brief) {
             ProfScope prof_("voxelize_chunks", s);
-            k_vox_chunks<<<(unsigned)((p.ntiles + 63) / 64), 256, 0, s>>>(w.part, t.ntiles, p.nch,
+            k_vox_chunks<<<(unsigned)((p.ntiles + 63) / 64), 1024, 0, s>>>(w.part, t.ntiles, p.nch,
                                                                           w.total);
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
