@@ -153,6 +153,13 @@ __device__ __forceinline__ float sample_disp(const float *__restrict__ vol, cons
     return lerp1(lerp1(c00, c01, f1), lerp1(c10, c11, f1), f0);
 }
 
+// *p = max(*p, x).  Atomics on one cache line take about 12 ns each, one after
+// the other, so a value that cannot raise *p is not sent (a stale reading is
+// never above *p).  For launches in which most cannot: where all workgroups
+// end at once the readings only wait behind the atomics.
+__device__ __forceinline__ void raise_max(unsigned *p, unsigned x) {
+    if (x > __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(p, x);
+}
 // Largest value over the 64 lanes (every lane receives it).
 __device__ __forceinline__ float wave_max(float v) {
     for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));

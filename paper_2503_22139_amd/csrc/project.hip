@@ -371,13 +371,14 @@ __global__ __launch_bounds__(256) void k_project(ProjTab t) {
 // with one sample gives any voxel at most one contribution).  The grid is
 // (workgroups per view, V): a workgroup strides over the rays of one view and
 // adds its two figures with one atomic each.
-__global__ __launch_bounds__(256) void k_ray_table(GridK g, ConeK c,
+constexpr int RAY_T = 1024;
+__global__ __launch_bounds__(RAY_T) void k_ray_table(GridK g, ConeK c,
                                                    const float *__restrict__ angles,
                                                    const float *__restrict__ g_proj,
                                                    RayK *__restrict__ out,
                                                    unsigned *__restrict__ stats,
                                                    int *__restrict__ orient) {
-    __shared__ float red[8];
+    __shared__ float red[2][RAY_T / 64];
     const int npix = c.nu * c.nv;
     const int v = blockIdx.y;
     const double th = (double)angles[v];
@@ -399,13 +400,16 @@ __global__ __launch_bounds__(256) void k_ray_table(GridK g, ConeK c,
     }
     const int wave = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0) {
-        red[wave] = m;
-        red[4 + wave] = d;
+        red[0][wave] = m;
+        red[1][wave] = d;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-        d = fminf(fminf(red[4], red[5]), fminf(red[6], red[7]));
+#pragma unroll
+        for (int w = 1; w < RAY_T / 64; ++w) {
+            m = fmaxf(m, red[0][w]);
+            d = fminf(d, red[1][w]);
+        }
         // non-negative floats order like their bit patterns
         if (m > 0.0f) atomicMax(&stats[2 * v], __float_as_uint(m));
         if (d < INFINITY) atomicMin(&stats[2 * v + 1], __float_as_uint(d));
@@ -859,6 +863,15 @@ __device__ __forceinline__ void bp_scatter(const BwdK &bj, const BrickGeo &q, in
     }
 }
 
+// Place of entry z of row r (x * (S1 + 1) + y) in a brick's staged box: the
+// rows' z < S2, then the high layer z = S2 by itself, so that its neighbours
+// along axis 1 are neighbours in memory (a launch whose every brick stages it,
+// the sum of eight views at 256x256x128: 130 us with whole rows, 90 so).
+template <int S0, int S1, int S2>
+__device__ __forceinline__ int pad_at(int r, int z) {
+    return z < S2 ? r * S2 + z : (S0 + 1) * (S1 + 1) * S2 + r;
+}
+
 // One workgroup walks a chunk of up to ZC bricks along
 // axis 2 of one (b0, b1) column for one view.  The high pad layer of each
 // brick (z = S2 in its box) is the low layer of the next one: it is carried
@@ -939,11 +952,12 @@ __device__ __forceinline__ void bp_column(const BwdK &bj, int view, int item, in
                         for (int z = 0; z < S2; ++z)
                             if (q.B[2] + z < g.n[2] && !(z == 0 && zfix)) mx = fmaxf(mx, fabsf(val[z]));
                     }
-                    if (lastb && q.B[2] + S2 < g.n[2]) pad[r * P2 + S2] = val[S2];
+                    if (lastb && q.B[2] + S2 < g.n[2]) pad[pad_at<S0, S1, S2>(r, S2)] = val[S2];
                 } else {
 #pragma unroll
                     for (int z = 0; z < P2; ++z)
-                        if (q.B[2] + z < g.n[2] && (z < S2 || lastb)) pad[r * P2 + z] = val[z];
+                        if (q.B[2] + z < g.n[2] && (z < S2 || lastb))
+                            pad[pad_at<S0, S1, S2>(r, z)] = val[z];
                 }
             }
             if (!lastb) {
@@ -955,8 +969,21 @@ __device__ __forceinline__ void bp_column(const BwdK &bj, int view, int item, in
         __syncthreads();
     }
     if (bj.vmax) {
-        for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-        if (lane == 0 && mx > 0.0f) atomicMax(&bj.vmax[v], __float_as_uint(mx));
+        mx = wave_max(mx);
+        if constexpr (ZC == 1) {
+            // one brick per workgroup: many, of which few raise the maximum
+            if (lane == 0) raise_max(&bj.vmax[v], __float_as_uint(mx));
+        } else {
+            // one atomic per workgroup (the box is read: its words are free)
+            float *const red = (float *)acc;
+            if (lane == 0) red[threadIdx.x >> 6] = mx;
+            __syncthreads();
+            if (threadIdx.x == 0) {
+#pragma unroll
+                for (int w = 1; w < NW; ++w) mx = fmaxf(mx, red[w]);
+                if (mx > 0.0f) atomicMax(&bj.vmax[v], __float_as_uint(mx));
+            }
+        }
     }
 }
 
@@ -1007,7 +1034,7 @@ __device__ __forceinline__ float bp_pad_sum(const float *__restrict__ pads, cons
         const int q0 = b[0] - (d & 1), q1 = b[1] - ((d >> 1) & 1), q2 = b[2] - ((d >> 2) & 1);
         const int lq0 = (d & 1) ? S0 : l[0], lq1 = (d & 2) ? S1 : l[1], lq2 = (d & 4) ? S2 : l[2];
         const int nbid = (q0 * nb[1] + q1) * nb[2] + q2;
-        sum += pads[(int64_t)nbid * NPMAX + (lq0 * P1 + lq1) * P2 + lq2];
+        sum += pads[(int64_t)nbid * NPMAX + pad_at<S0, S1, S2>(lq0 * P1 + lq1, lq2)];
     }
     return sum;
 }
@@ -1101,7 +1128,7 @@ __device__ __forceinline__ void bp_fixup(const BwdK &bj, int view, float *red) {
         __syncthreads();
         if (threadIdx.x == 0) {
             mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-            if (mx > 0.0f) atomicMax(&bj.vmax[view], __float_as_uint(mx));
+            raise_max(&bj.vmax[view], __float_as_uint(mx));
         }
     }
 }
@@ -1353,13 +1380,13 @@ __device__ __forceinline__ void bp_pad_row(const float *__restrict__ pads, const
     for (int d = 0; d < 4; ++d) {
         if ((d & f) != d) continue;
         const int box = ((b[0] - (d & 1)) * nb[1] + (b[1] - (d >> 1))) * nb[2] + b[2];
-        const int row = (((d & 1) ? S0 : l[0]) * P1 + ((d & 2) ? S1 : l[1])) * P2;
+        const int row = ((d & 1) ? S0 : l[0]) * P1 + ((d & 2) ? S1 : l[1]);
         if (d > 0) {
-            const float *pr = pads + (int64_t)box * NP + row;
+            const float *pr = pads + (int64_t)box * NP + pad_at<S0, S1, S2>(row, 0);
 #pragma unroll
             for (int i = 0; i < S2; ++i) s[i] += pr[i];
         }
-        if (f & 4) top[d] = pads[(int64_t)(box - 1) * NP + row + S2];
+        if (f & 4) top[d] = pads[(int64_t)(box - 1) * NP + pad_at<S0, S1, S2>(row, S2)];
     }
     s[0] = (((s[0] + top[0]) + top[1]) + top[2]) + top[3];
 }
@@ -1461,9 +1488,12 @@ static hipError_t project_bwd_bricks(const BwdJob *jobs, int n, hipStream_t s) {
         if (e != hipSuccess) return e;
         {
             ProfScope prof_("ray_table", s);
-            const int per_view = (j.c.nu * j.c.nv + 255) / 256;
-            dim3 grid((unsigned)(per_view < 64 ? per_view : 64), (unsigned)j.V);
-            k_ray_table<<<grid, 256, 0, s>>>(j.g, j.c, j.angles, j.g_proj, rays, stats, orient);
+            // large workgroups, as each ends with two atomics on one cache
+            // line, and as many as give a view by itself a ray per thread (one
+            // view of 512x384 with 64 workgroups of 256: 22 us, now 13)
+            const int64_t blocks = ((int64_t)j.c.nu * j.c.nv + RAY_T - 1) / RAY_T;
+            dim3 grid((unsigned)std::min<int64_t>(blocks, std::max(16, 512 / j.V)), (unsigned)j.V);
+            k_ray_table<<<grid, RAY_T, 0, s>>>(j.g, j.c, j.angles, j.g_proj, rays, stats, orient);
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
         BwdK &b = t.s[k];
@@ -1498,7 +1528,9 @@ static hipError_t project_bwd_bricks(const BwdJob *jobs, int n, hipStream_t s) {
     for (int k = 0; k < n; ++k) {
         ProfScope prof_("project_bwd_fixup", s);
         // blocks per view: about 16k over the views (measured: 2k, 4k, 8k
-        // and 16k blocks took 0.235, 0.202, 0.185 and 0.178 ms at 32 views)
+        // and 16k blocks took 0.235, 0.202, 0.185 and 0.178 ms at 32 views).
+        // An atomic per block on the views' maxima was what bound it with
+        // little to complete (eight views of 128x128x64: 82 us, now 31)
         const int V = t.s[k].V;
         const int per_view = std::max(1, std::min(2048, 16384 / V));
         k_project_bwd_fixup<L, W, H><<<dim3((unsigned)per_view, (unsigned)V), 256, 0, s>>>(
