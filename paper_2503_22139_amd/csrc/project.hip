@@ -1365,28 +1365,56 @@ size_t project_bwd_workspace(const GridK &g, const pmf_cone_t &c, int V) {
            (V > 1 ? align256(sizeof(float) * (size_t)grid_size(g) * (size_t)sum_round(g, V)) : 0);
 }
 
-// The pads of the H voxels that brick b holds of one line along axis 2 (place
-// l0, l1 in the brick; f: bp_face of its first voxel), in bp_pad_sum's order,
-// with whole rows of a neighbour's box loaded at once.
-template <int S0, int S1, int S2>
+// The pads of Q of the voxels that brick b holds of one line along axis 2 (from
+// z0 on; place l0, l1 in the brick; f: bp_face of the line's first voxel in it),
+// in bp_pad_sum's order, with whole rows of a neighbour's box loaded at once.
+template <int S0, int S1, int S2, int Q>
 __device__ __forceinline__ void bp_pad_row(const float *__restrict__ pads, const int nb[3],
-                                           const int b[3], const int l[3], int f, float s[S2]) {
+                                           const int b[3], const int l[3], int f, int z0,
+                                           float s[Q]) {
     constexpr int P1 = S1 + 1, P2 = S2 + 1;
     constexpr int64_t NP = (int64_t)(S0 + 1) * P1 * P2;
     float top[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-    for (int i = 0; i < S2; ++i) s[i] = 0.0f;
+    for (int i = 0; i < Q; ++i) s[i] = 0.0f;
+    if constexpr (Q < S2) {
+        // without branches, so that several views' loads are in flight: a
+        // part that is not there is read from the brick's own box and dropped
+        const bool high = (f & 4) && z0 == 0;
+        const int own = (b[0] * nb[1] + b[1]) * nb[2] + b[2];
+        float w[4][Q];
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            const bool on = (d & f) == d;
+            const int box = on ? own - ((d & 1) * nb[1] + (d >> 1)) * nb[2] : own;
+            const int row = ((d & 1) ? S0 : l[0]) * P1 + ((d & 2) ? S1 : l[1]);
+            if (d > 0) {
+                const float *pr = pads + (int64_t)box * NP + pad_at<S0, S1, S2>(row, 0) + z0;
+#pragma unroll
+                for (int i = 0; i < Q; ++i) {
+                    w[d][i] = pr[i];
+                    w[d][i] = on ? w[d][i] : 0.0f;
+                }
+            }
+            top[d] = pads[(int64_t)(box - (high ? 1 : 0)) * NP + pad_at<S0, S1, S2>(row, S2)];
+            top[d] = on && high ? top[d] : 0.0f;
+        }
+#pragma unroll
+        for (int i = 0; i < Q; ++i) s[i] = (w[1][i] + w[2][i]) + w[3][i];
+        s[0] = (((s[0] + top[0]) + top[1]) + top[2]) + top[3];
+        return;
+    }
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
         if ((d & f) != d) continue;
         const int box = ((b[0] - (d & 1)) * nb[1] + (b[1] - (d >> 1))) * nb[2] + b[2];
         const int row = ((d & 1) ? S0 : l[0]) * P1 + ((d & 2) ? S1 : l[1]);
         if (d > 0) {
-            const float *pr = pads + (int64_t)box * NP + pad_at<S0, S1, S2>(row, 0);
+            const float *pr = pads + (int64_t)box * NP + pad_at<S0, S1, S2>(row, 0) + z0;
 #pragma unroll
-            for (int i = 0; i < S2; ++i) s[i] += pr[i];
+            for (int i = 0; i < Q; ++i) s[i] += pr[i];
         }
-        if (f & 4) top[d] = pads[(int64_t)(box - 1) * NP + pad_at<S0, S1, S2>(row, S2)];
+        if ((f & 4) && z0 == 0) top[d] = pads[(int64_t)(box - 1) * NP + pad_at<S0, S1, S2>(row, S2)];
     }
     s[0] = (((s[0] + top[0]) + top[1]) + top[2]) + top[3];
 }
@@ -1395,61 +1423,70 @@ __device__ __forceinline__ void bp_pad_row(const float *__restrict__ pads, const
 // its face voxels (what k_project_bwd_fixup adds, in the same order): one pass
 // instead of a read-modify-write of every view's faces (a cache line in four
 // holds one when every brick stages its axis-2 pad) and then the sum.  A
-// thread owns the H voxels that one brick holds of an (x, y) line, so its
-// loads of a view are independent.  Bound by reading the volumes.  VEC:
-// 16-byte loads (n2 a multiple of 4, the volumes and out 16-byte aligned).
-template <int L, int W, int H, bool VEC>
+// thread owns Q of the H voxels that one brick holds of an (x, y) line, so its
+// loads of a view are independent: all H where that fills the chip (bound by
+// reading the volumes then), else two (a chain of views per thread: 64^3, ten
+// views 17 us with all eight, 13 with two).  VEC: wide loads (n2 a multiple
+// of 4, the volumes and out 16-byte aligned).
+template <int L, int W, int H, int Q, bool VEC>
 __global__ __launch_bounds__(256) void k_sum_views(BwdK bj, int add, float *__restrict__ out) {
-    static_assert(H % 4 == 0, "rows of whole float4");
+    static_assert(H % Q == 0 && (Q % 4 == 0 || Q == 2), "whole pieces of a row");
     constexpr int NPMAX = (L + 1) * (W + 1) * (H + 1);
+    typedef float vec __attribute__((ext_vector_type(Q >= 4 ? 4 : 2)));
+    constexpr int VW = Q >= 4 ? 4 : 2;
     const GridK &g = bj.g;
     const int nz = (g.n[2] + H - 1) / H;
     const unsigned t = blockIdx.x * blockDim.x + threadIdx.x;
-    const unsigned line = t / (unsigned)nz;
+    const unsigned nq = (unsigned)nz * (H / Q);
+    const unsigned line = t / nq;
     if (line >= (unsigned)g.n[0] * (unsigned)g.n[1]) return;
-    const int k = (int)(t - line * (unsigned)nz);
+    const int kq = (int)(t - line * nq), k = kq / (H / Q), z0 = (kq - k * (H / Q)) * Q;
     const int p[3] = {(int)(line / (unsigned)g.n[1]), (int)(line % (unsigned)g.n[1]), k * H};
-    const int m = min(H, g.n[2] - p[2]);    // voxels of the row (the staged rows hold H)
+    const int m = min(Q, g.n[2] - p[2] - z0);    // voxels (the staged rows hold H)
+    if (m <= 0) return;
     int b0[3], l0[3], b1[3], l1[3];         // brick and place in each orientation
     const int f0 = bp_face<L, W, H>(p, bj.zc, b0, l0), f1 = bp_face<W, L, H>(p, bj.zc, b1, l1);
     const int nb0[3] = {(g.n[0] + L - 1) / L, (g.n[1] + W - 1) / W, nz};
     const int nb1[3] = {(g.n[0] + W - 1) / W, (g.n[1] + L - 1) / L, nz};
-    const int64_t j = (int64_t)line * g.n[2] + p[2];
-    float sum[H];
+    const int64_t j = (int64_t)line * g.n[2] + p[2] + z0;
+    float sum[Q];
 #pragma unroll
-    for (int i = 0; i < H; ++i) sum[i] = add && i < m ? out[j + i] : 0.0f;
-#pragma unroll 2
+    for (int i = 0; i < Q; ++i) sum[i] = add && i < m ? out[j + i] : 0.0f;
+    constexpr int VIEWS = Q < H ? 4 : 2;    // in flight
+#pragma unroll VIEWS
     for (int v = 0; v < bj.V; ++v) {
         const float *in = bj.g_vol + (int64_t)v * bj.stride + j;
         const float *pads = bj.pads + (int64_t)v * bj.nbb * NPMAX;
-        float x[H], s[H];
+        float x[Q], s[Q];
         if constexpr (VEC) {
 #pragma unroll
-            for (int q = 0; q < H; q += 4) {
-                const float4 a = q < m ? *(const float4 *)(in + q) : make_float4(0, 0, 0, 0);
-                x[q] = a.x;
-                x[q + 1] = a.y;
-                x[q + 2] = a.z;
-                x[q + 3] = a.w;
+            for (int q = 0; q < Q; q += VW) {
+                vec a = {};
+                if (q < m) a = *(const vec *)(in + q);
+#pragma unroll
+                for (int i = 0; i < VW; ++i) x[q + i] = a[i];
             }
         } else {
 #pragma unroll
-            for (int i = 0; i < H; ++i) x[i] = i < m ? in[i] : 0.0f;
+            for (int i = 0; i < Q; ++i) x[i] = i < m ? in[i] : 0.0f;
         }
-        if (bj.orient[v]) bp_pad_row<W, L, H>(pads, nb1, b1, l1, f1, s);
-        else bp_pad_row<L, W, H>(pads, nb0, b0, l0, f0, s);
+        if (bj.orient[v]) bp_pad_row<W, L, H, Q>(pads, nb1, b1, l1, f1, z0, s);
+        else bp_pad_row<L, W, H, Q>(pads, nb0, b0, l0, f0, z0, s);
 #pragma unroll
-        for (int i = 0; i < H; ++i) sum[i] += x[i] + s[i];
+        for (int i = 0; i < Q; ++i) sum[i] += x[i] + s[i];
     }
     if constexpr (VEC) {
 #pragma unroll
-        for (int q = 0; q < H; q += 4)
-            if (q < m)
-                *(float4 *)(out + j + q) =
-                    make_float4(sum[q], sum[q + 1], sum[q + 2], sum[q + 3]);
+        for (int q = 0; q < Q; q += VW)
+            if (q < m) {
+                vec a;
+#pragma unroll
+                for (int i = 0; i < VW; ++i) a[i] = sum[q + i];
+                *(vec *)(out + j + q) = a;
+            }
     } else {
 #pragma unroll
-        for (int i = 0; i < H; ++i)
+        for (int i = 0; i < Q; ++i)
             if (i < m) out[j + i] = sum[i];
     }
 }
@@ -1458,12 +1495,18 @@ template <int L, int W, int H>
 static hipError_t launch_sum_views(const BwdK &b, const BwdJob &j, hipStream_t s) {
     ProfScope prof_("sum_views", s);
     const int64_t rows = (int64_t)j.g.n[0] * j.g.n[1] * ((j.g.n[2] + H - 1) / H);
-    const unsigned nb = (unsigned)((rows + 255) / 256);
-    if ((j.g.n[2] & 3) == 0 && (j.stride & 3) == 0 &&
-        (((uintptr_t)j.g_vol | (uintptr_t)j.sum) & 15) == 0)
-        k_sum_views<L, W, H, true><<<nb, 256, 0, s>>>(b, j.sum_add, j.sum);
-    else
-        k_sum_views<L, W, H, false><<<nb, 256, 0, s>>>(b, j.sum_add, j.sum);
+    const bool vec = (j.g.n[2] & 3) == 0 && (j.stride & 3) == 0 &&
+                     (((uintptr_t)j.g_vol | (uintptr_t)j.sum) & 15) == 0;
+    // eight waves per SIMD of whole rows fill the chip
+    if (rows >= 8 * 4 * 64 * 256 / 4) {
+        const unsigned nb = (unsigned)((rows + 255) / 256);
+        if (vec) k_sum_views<L, W, H, H, true><<<nb, 256, 0, s>>>(b, j.sum_add, j.sum);
+        else k_sum_views<L, W, H, H, false><<<nb, 256, 0, s>>>(b, j.sum_add, j.sum);
+    } else {
+        const unsigned nb = (unsigned)((rows * (H / 2) + 255) / 256);
+        if (vec) k_sum_views<L, W, H, 2, true><<<nb, 256, 0, s>>>(b, j.sum_add, j.sum);
+        else k_sum_views<L, W, H, 2, false><<<nb, 256, 0, s>>>(b, j.sum_add, j.sum);
+    }
     return hipGetLastError();
 }
 

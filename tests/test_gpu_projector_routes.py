@@ -142,3 +142,17 @@ def test_summed_adjoint_in_rounds():
     got = ops.pmf_project_bwd(gp, grid, cone, ang, shared=True)
     views = ops.pmf_project_bwd(gp, grid, cone, ang, shared=False)
     assert rel(got, in_order(views)) < 1e-5
+
+
+# around the 131,072 rows of eight from which a thread sums whole rows: the last
+# that takes them in pairs, the first whole ones, scalar and with wide loads
+@pytest.mark.parametrize("n", [(128, 127, 64), (128, 127, 61), (128, 128, 64), (200, 90, 62)])
+def test_summed_adjoint_by_rows_and_pairs(n):
+    print(n, flush=True)
+    grid = Grid(n, (1.5, 1.4, 2.0), (1.0, 2.0, -1.0))
+    cone = Cone(1000.0, 1500.0, 96, 61, 3.1, 3.3, off_v=0.4)
+    ang = T(synth.scan_angle([7, 180, 415]))
+    gp = T(synth.random_normal(11, (3, cone.nv, cone.nu)))
+    got = ops.pmf_project_bwd(gp, grid, cone, ang, shared=True)
+    views = ops.pmf_project_bwd(gp, grid, cone, ang, shared=False)
+    assert torch.equal(got, in_order(views))
