@@ -399,7 +399,8 @@ size_t pmf_profile_names(char *buf, size_t len);
  *                              4 (default) = 44x20x8, 5 = 40x20x8,
  *                              6 = 48x16x8, 7 = 64x16x8 with 12
  *                              wavefronts, 8 = 52x16x8 (a launch of few
- *                              views takes shorter chunks, so that it still
+ *                              views takes single bricks, and with the
+ *                              default choice 32x16x8 ones, so that it still
  *                              fills the chip);
  *   PMF_TUNE_VOXELIZE_BWD      Gaussians per workgroup in pmf_voxelize_bwd:
  *                              0 = chosen from the set's size (default),
