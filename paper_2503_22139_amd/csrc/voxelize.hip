@@ -204,6 +204,8 @@ __device__ __forceinline__ void each_pair(const TileBox &t, const VoxTiles &p, i
             }
 }
 
+// (COUNT = false: the records and the large Gaussians only.)
+template <bool COUNT>
 __global__ __launch_bounds__(BIN_T) void k_vox_bin(pmf_gauss_t gs, GridK g, float k, VoxTiles p,
                                                    GaussK *__restrict__ rec,
                                                    int32_t *__restrict__ part,
@@ -214,9 +216,10 @@ __global__ __launch_bounds__(BIN_T) void k_vox_bin(pmf_gauss_t gs, GridK g, floa
     const int64_t i0 = (int64_t)blockIdx.x * p.chunk, i1 = min(i0 + p.chunk, gs.m);
     int32_t *const row = part + (int64_t)blockIdx.x * p.ntiles;
     if (threadIdx.x == 0) nl = 0;
-    for (int w0 = 0; w0 < p.ntiles; w0 += BIN_W) {
+    for (int w0 = 0; w0 < (COUNT ? p.ntiles : 1); w0 += BIN_W) {
         const int nw = min(BIN_W, p.ntiles - w0);
-        for (int t = threadIdx.x; t < nw; t += BIN_T) hist[t] = 0;
+        if (COUNT)
+            for (int t = threadIdx.x; t < nw; t += BIN_T) hist[t] = 0;
         __syncthreads();
         for (int64_t i = i0 + threadIdx.x; i < i1; i += BIN_T) {
             GaussK r = {};
@@ -248,14 +251,15 @@ __global__ __launch_bounds__(BIN_T) void k_vox_bin(pmf_gauss_t gs, GridK g, floa
             const TileBox t = tile_box(r, p.T0, p.T1, p.T2);
             if (t.count > p.maxtiles) {
                 if (w0 == 0) atomicAdd(&nl, 1);
-            } else if (t.count > 0) {
+            } else if (COUNT && t.count > 0) {
                 each_pair(t, p, w0, [&](int w, int q) {
                     slot[(int64_t)q * gs.m + i] = atomicAdd(&hist[w], 1);
                 });
             }
         }
         __syncthreads();
-        for (int t = threadIdx.x; t < nw; t += BIN_T) row[w0 + t] = hist[t];
+        if (COUNT)
+            for (int t = threadIdx.x; t < nw; t += BIN_T) row[w0 + t] = hist[t];
         __syncthreads();
     }
     if (threadIdx.x == 0) nlarge[1 + blockIdx.x] = nl;
@@ -476,8 +480,16 @@ __device__ __forceinline__ int rotated_tile(int b, int nt1, int nt2) {
     return c * nt2 + (z + tx + ty / 2) % nt2;
 }
 
-template <int T0, int T1, int T2, int CT, int NW, int VB>
-__global__ __launch_bounds__(64 * NW) void k_vox_tile(const GaussK *__restrict__ rec,
+// SCAN: a small set (up to VOX_SCAN Gaussians on few tiles) has no lists; each
+// workgroup finds its tile's Gaussians among all of them (nlarge then holds the
+// chunks' counts of large ones behind its first word), which costs less than the
+// launch that would write the lists (4,096 Gaussians in 64^3: 5 + 19 us for
+// records and tiles against 8 + 9 + 14 with lists).
+constexpr int VOX_SCAN = 4096;
+
+template <int T0, int T1, int T2, int CT, int NW, int VB, bool SCAN>
+__global__ __launch_bounds__(64 * NW) void k_vox_tile(const GaussK *__restrict__ rec, int m, int nch,
+                                                  int maxtiles,
                                                   const float *__restrict__ value, int Crt, GridK g,
                                                   float k2, int nt1, int nt2,
                                                   const int32_t *__restrict__ off,
@@ -494,16 +506,44 @@ __global__ __launch_bounds__(64 * NW) void k_vox_tile(const GaussK *__restrict__
     __shared__ float scale[CM];
     __shared__ VoxB bt[NW][VB];
     __shared__ float bv[NW][VB][CM];      // value x scale per batch entry
+    __shared__ int32_t slist[SCAN ? VOX_SCAN : 1];
+    __shared__ int scount[NW];            // [0]: Gaussians found
     for (int i = threadIdx.x; i < C * TV; i += NT) acc[i] = 0;
     const int t = rotated_tile((int)blockIdx.x, nt1, nt2);
     const int tz = t % nt2, ty = (t / nt2) % nt1, tx = t / (nt2 * nt1);
     const int b0 = tx * T0, b1 = ty * T1, b2 = tz * T2;
     const int e0 = min(b0 + T0, g.n[0]) - 1, e1 = min(b1 + T1, g.n[1]) - 1,
               e2 = min(b2 + T2, g.n[2]) - 1;
-    const int beg = off[t], end = off[t + 1];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    const int nl = *nlarge;
+    int beg, end, nl = 0;
+    if constexpr (SCAN) {
+        if (threadIdx.x == 0) scount[0] = 0;
+        __syncthreads();
+        for (int i0 = wave * 64; i0 < m; i0 += NT) {                  // uniform
+            bool in = false;
+            if (i0 + lane < m) {
+                const TileBox q = tile_box(rec[i0 + lane], T0, T1, T2);
+                in = q.count > 0 && q.count <= maxtiles && q.a0 <= tx && tx <= q.b0 &&
+                     q.a1 <= ty && ty <= q.b1 && q.a2 <= tz && tz <= q.b2;
+            }
+            const uint64_t hits = __ballot(in);
+            if (hits == 0) continue;
+            int at = 0;
+            if (lane == 0) at = atomicAdd(&scount[0], __popcll(hits));
+            at = __builtin_amdgcn_readfirstlane(at);
+            if (in) slist[at + __popcll(hits & ((1ull << lane) - 1))] = i0 + lane;
+        }
+        for (int c = 0; c < nch; ++c) nl += nlarge[1 + c];
+        __syncthreads();
+        beg = 0;
+        end = scount[0];
+    } else {
+        beg = off[t];
+        end = off[t + 1];
+        nl = *nlarge;
+    }
+    auto entry = [&](int e) { return SCAN ? slist[e] : list[e]; };
     // per-channel bound S = (the tile's list length) x (the list's largest
     // |value|): every voxel's sum stays below it, and unlike a float sum of
     // the |values| it does not depend on the order the binning's atomics gave
@@ -511,7 +551,7 @@ __global__ __launch_bounds__(64 * NW) void k_vox_tile(const GaussK *__restrict__
     for (int c = 0; c < C; ++c) {
         float mx = 0.0f;
         for (int e = beg + (int)threadIdx.x; e < end; e += NT)
-            mx = fmaxf(mx, fabsf(value[(int64_t)list[e] * C + c]));
+            mx = fmaxf(mx, fabsf(value[(int64_t)entry(e) * C + c]));
         mx = wave_max(mx);
         if (lane == 0) cs[wave][c] = mx;
     }
@@ -533,7 +573,7 @@ __global__ __launch_bounds__(64 * NW) void k_vox_tile(const GaussK *__restrict__
         int ncols = 0;
         VoxB q;
         if (lane < nb) {
-            const int gi = list[eb + lane];
+            const int gi = entry(eb + lane);
             const GaussK p = rec[gi];
             const int lo0 = max(p.lo0, b0), lo1 = max(p.lo1, b1), lo2 = max(p.lo2, b2);
             const int hi0 = min(p.hi0, e0), hi1 = min(p.hi1, e1), hi2 = min(p.hi2, e2);
@@ -616,6 +656,24 @@ __global__ __launch_bounds__(64 * NW) void k_vox_tile(const GaussK *__restrict__
     // order (a fixed order: the results repeat bit for bit)
     if (nl > 0) {
         __syncthreads();
+        if constexpr (SCAN) {
+            // their list, in ascending order, in the found ones' place
+            int n = 0;
+            for (int i0 = 0; i0 < m; i0 += NT) {                      // uniform
+                const int i = i0 + (int)threadIdx.x;
+                const bool f = i < m && tile_box(rec[i], T0, T1, T2).count > maxtiles;
+                const uint64_t hits = __ballot(f);
+                if (lane == 0) scount[wave] = __popcll(hits);
+                __syncthreads();
+                int at = n;
+                for (int w = 0; w < NW; ++w) {
+                    if (w < wave) at += scount[w];
+                    n += scount[w];
+                }
+                if (f) slist[at + __popcll(hits & ((1ull << lane) - 1))] = i;
+                __syncthreads();
+            }
+        }
         for (int li = threadIdx.x; li < TV; li += NT) {
             const int ix = b0 + li / (T1 * T2), iy = b1 + (li / T2) % T1, iz = b2 + li % T2;
             if (ix > e0 || iy > e1 || iz > e2) continue;
@@ -623,7 +681,7 @@ __global__ __launch_bounds__(64 * NW) void k_vox_tile(const GaussK *__restrict__
             const float d1g = fmaf((float)iy, g.h[1], g.c0[1]);
             const float d2g = fmaf((float)iz, g.h[2], g.c0[2]);
             for (int e = 0; e < nl; ++e) {
-                const int gi = __builtin_amdgcn_readfirstlane(large[e]);
+                const int gi = __builtin_amdgcn_readfirstlane(SCAN ? slist[e] : large[e]);
                 const GaussK p = rec[gi];
                 if (ix < p.lo0 || ix > p.hi0 || iy < p.lo1 || iy > p.hi1 || iz < p.lo2 ||
                     iz > p.hi2)
@@ -940,6 +998,7 @@ hipError_t launch_voxelize(const pmf_gauss_t &gs, const GridK &g, float k, float
                   *const nlarge = w.nlarge;
     const float k2 = isinf(k) ? INFINITY : k * k;
     hipError_t e;
+    const bool few = p.ntiles <= VOX_FEW, scan = few && m > 0 && m <= VOX_SCAN;
     if (m == 0) {
         if ((e = launch_fill_i32(off, p.ntiles + 1, 0, s)) != hipSuccess) return e;
         if ((e = launch_fill_i32(nlarge, 1, 0, s)) != hipSuccess) return e;
@@ -956,17 +1015,20 @@ hipError_t launch_voxelize(const pmf_gauss_t &gs, const GridK &g, float k, float
         const size_t hist = sizeof(int32_t) * (size_t)std::min<int64_t>(p.ntiles, BIN_W);
         {
             ProfScope prof_("voxelize_bin", s);
-            k_vox_bin<<<(unsigned)p.nch, BIN_T, hist, s>>>(gs, g, k, t, rec, w.part, w.slot, nlarge);
+            if (scan)
+                k_vox_bin<false><<<(unsigned)p.nch, BIN_T, 0, s>>>(gs, g, k, t, rec, w.part, w.slot, nlarge);
+            else
+                k_vox_bin<true><<<(unsigned)p.nch, BIN_T, hist, s>>>(gs, g, k, t, rec, w.part, w.slot, nlarge);
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
         const bool brief = (int64_t)p.nch * p.ntiles <= BIN_SHORT;
-        if (!brief) {
+        if (!brief && !scan) {
             ProfScope prof_("voxelize_chunks", s);
             k_vox_chunks<<<(unsigned)((p.ntiles + 63) / 64), 1024, 0, s>>>(w.part, t.ntiles, p.nch,
                                                                           w.total);
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        {
+        if (!scan) {
             ProfScope prof_("voxelize_fill", s);
             if (brief)
                 k_vox_fill<true><<<(unsigned)p.nch, BIN_T, hist, s>>>(
@@ -980,7 +1042,6 @@ hipError_t launch_voxelize(const pmf_gauss_t &gs, const GridK &g, float k, float
     const size_t lds = sizeof(float) * (size_t)gs.c * (p.T[0] * p.T[1] * p.T[2]);
     {
         ProfScope prof_("voxelize_tile", s);
-        const bool few = p.ntiles <= VOX_FEW;
         const int sel = (p.T[1] == 16 ? 2 : 0) + (p.T[2] == 16 ? 1 : 0);
         const int cs = gs.c;
         // one channel: the LDS splat (many Gaussians per tile); 3 or 9
@@ -989,20 +1050,23 @@ hipError_t launch_voxelize(const pmf_gauss_t &gs, const GridK &g, float k, float
         // 128x128x64, 64 to 512 tiles: 21, 21 and 66 us with voxel owners, 8,
         // 10 and 21 with the splat; on 8,192 tiles of nine channels 110 us
         // against 152); other channel counts: the LDS splat
+#define VOX_TILE_W(T1_, T2_, CT_, NW_, VB_, SCAN_)                                                 \
+    k_vox_tile<8, T1_, T2_, CT_, NW_, VB_, SCAN_><<<(unsigned)p.ntiles, 64 * NW_, lds, s>>>(      \
+        rec, (int)m, p.nch, p.maxtiles, gs.value, gs.c, g, k2, p.nt[1], p.nt[2], off, list,       \
+        large, nlarge, vol)
+#define VOX_FEW_TILES(T1_, T2_, CT_)                                                              \
+    do {                                                                                          \
+        if (scan) VOX_TILE_W(T1_, T2_, CT_, 16, 8, true);                                         \
+        else VOX_TILE_W(T1_, T2_, CT_, 16, 8, false);                                             \
+    } while (0)
 #define VOX_TILE(T1_, T2_, CT_)                                                                   \
     do {                                                                                          \
-        if (few)                                                                                  \
-            k_vox_tile<8, T1_, T2_, CT_, 16, 8><<<(unsigned)p.ntiles, 1024, lds, s>>>(            \
-                rec, gs.value, gs.c, g, k2, p.nt[1], p.nt[2], off, list, large, nlarge, vol);     \
-        else                                                                                      \
-            k_vox_tile<8, T1_, T2_, CT_, 4, 16><<<(unsigned)p.ntiles, 256, lds, s>>>(             \
-                rec, gs.value, gs.c, g, k2, p.nt[1], p.nt[2], off, list, large, nlarge, vol);     \
+        if (few) VOX_FEW_TILES(T1_, T2_, CT_);                                                    \
+        else VOX_TILE_W(T1_, T2_, CT_, 4, 16, false);                                             \
     } while (0)
 #define VOX_GATHER(T1_, T2_, CT_)                                                                 \
     do {                                                                                          \
-        if (few)                                                                                  \
-            k_vox_tile<8, T1_, T2_, CT_, 16, 8><<<(unsigned)p.ntiles, 1024, lds, s>>>(            \
-                rec, gs.value, gs.c, g, k2, p.nt[1], p.nt[2], off, list, large, nlarge, vol);     \
+        if (few) VOX_FEW_TILES(T1_, T2_, CT_);                                                    \
         else                                                                                      \
             k_vox_gather<8, T1_, T2_, CT_><<<(unsigned)p.ntiles, 256, 0, s>>>(                    \
                 rec, gs.value, g, k2, p.nt[1], p.nt[2], off, list, large, nlarge, vol);           \
@@ -1024,6 +1088,8 @@ hipError_t launch_voxelize(const pmf_gauss_t &gs, const GridK &g, float k, float
 #undef VOX_TILE_C
 #undef VOX_GATHER
 #undef VOX_TILE
+#undef VOX_FEW_TILES
+#undef VOX_TILE_W
     }
     return hipGetLastError();
 }

@@ -114,3 +114,15 @@ def test_adjoint_walks(m, s_vox, n, c):
         w = want[name]
         e = np.linalg.norm(g.cpu().numpy().astype(np.float64) - w)
         assert e <= 1e-3 * np.linalg.norm(w), (name, e)
+
+
+# the largest set whose tiles search all its Gaussians, and one more (lists),
+# with large Gaussians among them
+@pytest.mark.parametrize("m", [4096, 4097])
+@pytest.mark.parametrize("c", [1, 2, 3])
+def test_search_or_lists(m, c):
+    print(m, c, flush=True)
+    grid = Grid((64, 60, 56), (1.0, 1.2, 0.9))
+    gs = unit(np.random.default_rng(m), m, grid, c=c, s_vox=(0.3, 0.6))
+    gs.scale[::500] *= 20.0
+    check(gs, grid, ratio=2.0)
