@@ -324,9 +324,16 @@ def pmf_voxelize(mean, scale, quat, value, grid: Grid, trunc_k: float = 3.0, out
     return out
 
 
-def pmf_voxelize_bwd(mean, scale, quat, value, grid: Grid, trunc_k: float, g_vol):
-    gm, gsc, gq, gv = (_empty_like(mean), _empty_like(scale), _empty_like(quat),
-                       _empty_like(value))
+def gauss_grads(mean, scale, quat, value):
+    """One buffer for the gradients of (mean, scale, quat, value), and its four views."""
+    ts = (mean, scale, quat, value)
+    flat = _empty((sum(t.numel() for t in ts),), mean.device)
+    return flat, tuple(p.view(t.shape) for p, t in zip(flat.split([t.numel() for t in ts]), ts))
+
+
+def pmf_voxelize_bwd(mean, scale, quat, value, grid: Grid, trunc_k: float, g_vol, out=None):
+    gm, gsc, gq, gv = out if out is not None else (_empty_like(mean), _empty_like(scale),
+                                                   _empty_like(quat), _empty_like(value))
     g = make_grid(grid)
     gs = _gauss(mean, scale, quat, value)
     gr = PmfGaussGrad(_ptr(gm), _ptr(gsc), _ptr(gq), _ptr(gv))
@@ -493,13 +500,13 @@ def pmf_rasterize(mean, scale, quat, value, cone: Cone, angles, trunc_k: float =
 
 
 def pmf_rasterize_bwd(mean, scale, quat, value, cone: Cone, angles, trunc_k: float, g_proj,
-                      ws=None, binned: bool = False):
+                      ws=None, binned: bool = False, out=None):
     """Gradients of sum(g_proj * rasterize) w.r.t. (mean, scale, quat, value).
     binned=True reuses the binning that pmf_rasterize left in ws (same
     inputs, nothing written to ws since)."""
     V = angles.numel()
-    gm, gsc, gq, gv = (_empty_like(mean), _empty_like(scale), _empty_like(quat),
-                       _empty_like(value))
+    gm, gsc, gq, gv = out if out is not None else (_empty_like(mean), _empty_like(scale),
+                                                   _empty_like(quat), _empty_like(value))
     c = make_cone(cone)
     gs = _gauss(mean, scale, quat, value)
     gr = PmfGaussGrad(_ptr(gm), _ptr(gsc), _ptr(gq), _ptr(gv))
