@@ -302,14 +302,16 @@ __device__ __forceinline__ void warp_combine_bwd_brick(
                 free2 = disp_free(vz, t2, g.n[2]);
             }
             if (hit && go != 0.0f) {
-                const int64_t base = ((int64_t)i0 * g.n[1] + i1) * g.n[2] + i2;
+                const int base = (i0 * g.n[1] + i1) * g.n[2] + i2;     // a grid has < 2^31 voxels
                 float c000, c001, c010, c011, c100, c101, c110, c111;
                 if (paired) {
                     // the 2x2 (y, z) corners of a cell are 16 contiguous
                     // (8-byte aligned) bytes: one load each for x and x+1
                     typedef float v4a8 __attribute__((ext_vector_type(4), aligned(8)));
-                    const float *pa = ref + 2 * base;
-                    const v4a8 a = *(const v4a8 *)pa, e = *(const v4a8 *)(pa + 2 * (int64_t)s0);
+                    // (paired volumes are below 4 GB: 32-bit byte offsets)
+                    const char *pr = (const char *)ref;
+                    const uint32_t ob = (uint32_t)base * 8u;
+                    const v4a8 a = *(const v4a8 *)(pr + ob), e = *(const v4a8 *)(pr + (ob + (uint32_t)s0 * 8u));
                     c000 = a.x; c010 = a.y; c001 = a.z; c011 = a.w;
                     c100 = e.x; c110 = e.y; c101 = e.z; c111 = e.w;
                 } else {
@@ -336,7 +338,7 @@ __device__ __forceinline__ void warp_combine_bwd_brick(
                     const float q00 = wx0 * (1.0f - f1), q01 = wx0 * f1;
                     const float q10 = wx1 * (1.0f - f1), q11 = wx1 * f1;
                     const float g2 = 1.0f - f2;
-                    const int o = (l0 * HB + l1) * HB + l2;
+                    const int o = __mul24(__mul24(l0, HB) + l1, HB) + l2;
                     const float cw[8] = {q00 * g2, q00 * f2, q01 * g2, q01 * f2,
                                          q10 * g2, q10 * f2, q11 * g2, q11 * f2};
                     const int off[8] = {0, 1, HB, HB + 1, HB * HB, HB * HB + 1, HB * HB + HB,
