@@ -918,11 +918,17 @@ __device__ __forceinline__ void bp_column(const BwdK &bj, int view, int item, in
         // other thread's reads are in the way).
         const bool zfix = b2 == z0 && b2 > 0;     // the z = 0 layer is completed by the fix-up
         const bool full_z = q.B[2] + S2 <= g.n[2] && (g.n[2] & 3) == 0;
+        // (opaque, so that the rows' addresses are not kept, and spilled, across
+        // the bricks' sample loops)
+        int r0 = threadIdx.x;
+        asm volatile("" : "+v"(r0));
 #pragma unroll 1
-        for (int r = threadIdx.x; r < (S0 + 1) * P1; r += NT) {
+        for (int r = r0; r < (S0 + 1) * P1; r += NT) {
             const int x = r / P1, y = r - x * P1;
             const int gx = q.B[0] + x, gy = q.B[1] + y;
             int *row = acc + r * P2;
+            float *const prow = pad + pad_at<S0, S1, S2>(r, 0);
+            float *const phigh = pad + pad_at<S0, S1, S2>(r, S2);
             int raw[P2];
 #pragma unroll
             for (int z = 0; z < P2; ++z) raw[z] = row[z];
@@ -952,12 +958,12 @@ __device__ __forceinline__ void bp_column(const BwdK &bj, int view, int item, in
                         for (int z = 0; z < S2; ++z)
                             if (q.B[2] + z < g.n[2] && !(z == 0 && zfix)) mx = fmaxf(mx, fabsf(val[z]));
                     }
-                    if (lastb && q.B[2] + S2 < g.n[2]) pad[pad_at<S0, S1, S2>(r, S2)] = val[S2];
+                    if (lastb && q.B[2] + S2 < g.n[2]) phigh[0] = val[S2];
                 } else {
 #pragma unroll
-                    for (int z = 0; z < P2; ++z)
-                        if (q.B[2] + z < g.n[2] && (z < S2 || lastb))
-                            pad[pad_at<S0, S1, S2>(r, z)] = val[z];
+                    for (int z = 0; z < S2; ++z)
+                        if (q.B[2] + z < g.n[2]) prow[z] = val[z];
+                    if (lastb && q.B[2] + S2 < g.n[2]) phigh[0] = val[S2];
                 }
             }
             if (!lastb) {
