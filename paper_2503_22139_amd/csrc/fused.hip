@@ -188,7 +188,7 @@ __device__ __forceinline__ int magic_int(float x_plus_magic) {
 // multiplication's slot: the views' coefficients are read from LDS into vector
 // registers, fixed-point words come from magic-number additions, and a wave
 // whose samples all lie strictly between the outermost voxel centres skips the
-// rim's cases.  256x256x128, 32 views, B = 3: 2,693 us before, now 2,463.
+// rim's cases.  256x256x128, 32 views, B = 3: 2,693 us before, now 2,442.
 
 // Coefficients of a view in LDS, padded to whole float4.
 __host__ __device__ constexpr int coeff_pitch(int NC) { return (NC + 3) / 4 * 4; }
