@@ -41,22 +41,16 @@ constexpr int WX0 = WA0 + 2 * WHALO + 1, WX1 = WA1 + 2 * WHALO + 1, WX2 = WA2 + 
 constexpr int WX = WX0 * WX1 * WX2;
 constexpr int WB_THREADS = WA0 * WA1 * WA2 / 2;
 
-// Fixed-point scale of the adjoint: the power of two 2^e in [2^40 / M,
-// 2^41 / M), M the largest |g_out| (float bits), so that scaling a term is
-// exact; 0 when M is 0.  A word holds 2^22 terms of size M.
-__device__ __forceinline__ int warp_fix_exp(uint32_t max_bits) {
-    int e;
-    frexpf(__uint_as_float(max_bits), &e);      // M in [2^(e-1), 2^e)
-    return 41 - e;
-}
-
-// x 2^e rounded to the nearest integer, as 64 bits.  |x| <= M, so the scaled
-// value stays below 2^41: its upper part fits 32 bits.
-__device__ __forceinline__ unsigned long long warp_fix(float x, int e) {
-    const float v = rintf(ldexpf(x, e));
-    const float hi = floorf(v * 0x1p-32f);
-    const uint32_t lo = (uint32_t)fmaf(hi, -0x1p32f, v);    // exact: v has 24 significant bits
-    return ((unsigned long long)(uint32_t)(int)hi << 32) | lo;
+// The double product x scale (|x| <= M, scale = 2^40 / M: below 2^41) rounded to
+// the nearest integer, as 64 bits: the product plus 1.5 2^52 holds it in its low
+// bits.  (fix_add's integer without its conversion; a split into two words in
+// float loses the low ones of a negative term.)
+__device__ __forceinline__ unsigned long long warp_fix(float x, double scale) {
+#pragma clang fp contract(off)
+    constexpr double MAGIC52 = 6755399441055744.0;
+    const double p = (double)x * scale;
+    return (unsigned long long)(__double_as_longlong(p + MAGIC52) -
+                                __double_as_longlong(MAGIC52));
 }
 
 __global__ __launch_bounds__(WB_THREADS) void k_warp_bwd(const float *__restrict__ ref, GridK g,
@@ -75,7 +69,7 @@ __global__ __launch_bounds__(WB_THREADS) void k_warp_bwd(const float *__restrict
     __syncthreads();
     const int64_t N = grid_size(g);
     const int s1 = g.n[2], s0 = g.n[1] * g.n[2];
-    const int fe = warp_fix_exp(*gmax);
+    const double fscale = fix_scale(*gmax);
     const int iz = B2 + (int)threadIdx.x % WA2, iy = B1 + ((int)threadIdx.x / WA2) % WA1;
     for (int q = 0; q < 2; ++q) {
         const int ix = B0 + (int)threadIdx.x / (WA1 * WA2) + q * (WA0 / 2);
@@ -111,7 +105,7 @@ __global__ __launch_bounds__(WB_THREADS) void k_warp_bwd(const float *__restrict
             gd[j] = go * dx * g.inv_h[0] * disp_free(ix, t0, g.n[0]);
             gd[N + j] = go * dy * g.inv_h[1] * disp_free(iy, t1, g.n[1]);
             gd[2 * N + j] = go * dz * g.inv_h[2] * disp_free(iz, t2, g.n[2]);
-            if (go == 0.0f) continue;
+            if (go == 0.0f || !isfinite(go)) continue;     // (an infinite M leaves the scale 0)
             const float w0[2] = {1.0f - f0, f0}, w1[2] = {1.0f - f1, f1}, w2[2] = {1.0f - f2, f2};
             const int l0 = i0 - (B0 - WHALO), l1 = i1 - (B1 - WHALO), l2 = i2 - (B2 - WHALO);
             const bool inbox = l0 >= 0 && l0 + 1 < WX0 && l1 >= 0 && l1 + 1 < WX1 && l2 >= 0 &&
@@ -123,7 +117,7 @@ __global__ __launch_bounds__(WB_THREADS) void k_warp_bwd(const float *__restrict
                 for (int b = 0; b < 2; ++b)
 #pragma unroll
                     for (int c = 0; c < 2; ++c) {
-                        const unsigned long long x = warp_fix(go * w0[a] * w1[b] * w2[c], fe);
+                        const unsigned long long x = warp_fix(go * w0[a] * w1[b] * w2[c], fscale);
                         if (inbox) atomicAdd(&wbox[o + (a * WX1 + b) * WX2 + c], x);
                         else atomicAdd(&fix[base + a * s0 + b * s1 + c], x);
                     }
@@ -159,8 +153,9 @@ __global__ __launch_bounds__(256) void k_warp_gather(
                           l2 = p2 - (b2 * WA2 - WHALO);
                 s += stage[(int64_t)((b0 * nb1 + b1) * nb2 + b2) * WX + (l0 * WX1 + l1) * WX2 + l2];
             }
-    // an infinite |g_out| leaves no scale: zeros
-    g_ref[j] = *gmax < 0x7f800000u ? (float)ldexp((double)(long long)s, -warp_fix_exp(*gmax)) : 0.0f;
+    const double sc = fix_scale(*gmax);
+    const double inv = sc > 0.0 ? 1.0 / sc : 0.0;       // 0 or infinite M: zeros
+    g_ref[j] = (float)((double)(long long)s * inv);
 }
 
 hipError_t launch_warp(const float *ref, const GridK &g, const float *dvf, int V, float *out,
