@@ -39,9 +39,11 @@ constexpr int BP_ZC = 16;              // voxels along axis 2 per back-projectio
 // 2^P >= 2 nu - 1 by FFT.  h is even, so its transform is real, and two rows
 // are filtered at once as the real and imaginary parts of one sequence.  All
 // of it is double: for smooth rows on fine pixels q is a small difference of
-// large terms.  The direct sum over odd lags (~nu / 2 double FMAs per output,
-// issue-bound) took 1.6 ms for 660 views of 512x384; the transforms' ~90 per
-// output leave 1.0 ms.
+// large terms.  The transform's errors go by the larger of its two rows, so the
+// second is first scaled by a power of two to the first's size (exact; beside a
+// dead pixel of 3e38 nothing would be left of the other row).  The direct sum
+// over odd lags (~nu / 2 double FMAs per output, issue-bound) took 1.6 ms for
+// 660 views of 512x384; the transforms' ~90 per output leave 1.0 ms.
 //
 // Transform: 16 points per thread; in-place decimation-in-frequency passes of
 // radix 16 and a last one of radix 2^(P mod 4) (16 when that is 1), whose
@@ -323,6 +325,13 @@ __global__ __launch_bounds__(Fft<P>::THREADS) void k_fdk_ramp(double tau, int nu
         H[(u + (i / F::LR) * F::TPP) * F::LR + i % F::LR] = x[i].x / (double)F::M;
 }
 
+// 2^e, |e| < 1022.
+__device__ __forceinline__ double pow2(int e) {
+    return __longlong_as_double((long long)(1023 + e) << 52);
+}
+// The top word of |x|: ordered like |x|, its upper 11 bits the exponent.
+__device__ __forceinline__ uint32_t top_word(double x) { return (uint32_t)__double2hiint(x) & 0x7fffffffu; }
+
 // Filters FDK_ROWS rows of one view per transform slot, two at a time, and
 // writes them into the padded plane's pairs: padded row i + 1 holds rows i and
 // i + 1, so a row is kept until the next one is there, and only the slot's
@@ -339,6 +348,7 @@ __attribute__((amdgpu_waves_per_eu(Fft<P>::WAVES))) void k_fdk_filter(const floa
                                                                 float2 *__restrict__ qq) {
     using F = Fft<P>;
     __shared__ cplx smem[F::PER * F::M];
+    __shared__ ushort2 wexp[F::THREADS / 64];       // the pair's largest exponents, by wave
     const int nu = c.nu, nv = c.nv, pitch = nu + 3;
     const int u = threadIdx.x % F::TPP, v = blockIdx.y;
     cplx *const sh = smem + (threadIdx.x / F::TPP) * F::M;
@@ -380,14 +390,24 @@ __attribute__((amdgpu_waves_per_eu(Fft<P>::WAVES))) void k_fdk_filter(const floa
                         i + 1 < r1 ? (double)row[nu + n] * (sdd * rsqrt_nr(sb + aa)) : 0.0};
         };
         cplx x[16];
-        bool odd = false;
+        uint32_t ma = 0, mb = 0;
         const int b0 = F::first(0, fresh(u));
 #pragma unroll
         for (int k = 0; k < 8; ++k) {           // n < M / 2 covers the row
             const int n = b0 + k * S;
             x[k] = n < nu ? pixel(n) : cplx{0.0, 0.0};
-            odd = odd || !isfinite(x[k].x) || !isfinite(x[k].y);
+            ma = max(ma, top_word(x[k].x));
+            mb = max(mb, top_word(x[k].y));
         }
+        // the rows' largest exponents, as they stand in the top words
+        typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+        u16x2 ex = {(uint16_t)(ma >> 20), (uint16_t)(mb >> 20)};
+        const bool odd = ex.x == 0x7ff || ex.y == 0x7ff;        // not finite
+#pragma unroll
+        for (int o = 1; o < (F::TPP < 64 ? F::TPP : 64); o <<= 1)
+            ex = __builtin_elementwise_max(
+                ex, __builtin_bit_cast(u16x2, __shfl_xor(__builtin_bit_cast(int, ex), o, 64)));
+        if (F::TPP > 64 && (threadIdx.x & 63) == 0) wexp[threadIdx.x >> 6] = make_ushort2(ex.x, ex.y);
         float qa[8], qb[8];
         if (__syncthreads_or(odd)) {
             // a value that is not finite would spread over both rows of the
@@ -410,6 +430,21 @@ __attribute__((amdgpu_waves_per_eu(Fft<P>::WAVES))) void k_fdk_filter(const floa
                 }
             }
         } else {
+            int ea = ex.x, eb = ex.y;
+            if constexpr (F::TPP > 64) {
+#pragma unroll
+                for (int w = 0; w < F::THREADS / 64; ++w) {
+                    ea = max(ea, (int)wexp[w].x);
+                    eb = max(eb, (int)wexp[w].y);
+                }
+            }
+            // (a row of zeros counts as 2^-300, below any float: the other's
+            // errors then round to zero in it)
+            ea = max(ea, 1023 - 300);
+            eb = max(eb, 1023 - 300);
+            const double down = pow2(ea - eb);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) x[k].y *= down;
             F::template forward<true>(x, sh, tw, u);
             const int uh = fresh(u);
 #pragma unroll
@@ -420,10 +455,11 @@ __attribute__((amdgpu_waves_per_eu(Fft<P>::WAVES))) void k_fdk_filter(const floa
             }
             F::inverse(x, sh, tw, u);
             __syncthreads();                        // sh is free for the next two rows
+            const double up = pow2(eb - ea);
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
                 qa[k] = (float)x[dft_slot<16>(k)].x;
-                qb[k] = (float)x[dft_slot<16>(k)].y;
+                qb[k] = (float)(x[dft_slot<16>(k)].y * up);
             }
         }
         if (i < r1) {
