@@ -184,8 +184,9 @@ int pmf_project(const float *vol, int64_t vol_stride, const pmf_grid_t *grid,
 /* pmf_project with scratch space (same arguments, results bit for bit and
  * errors): the volumes are first copied to a layout in which a sample takes
  * half the loads.  ws: pmf_project_workspace() bytes (8 per voxel; one volume
- * for vol_stride = 0, up to 8 at a time otherwise); where that is 0 (few rays
- * for the volume, or a volume too large for the layout) ws may be NULL.
+ * for vol_stride = 0, otherwise up to 8 at a time while they take at most
+ * 1 GiB); where that is 0 (few rays for the volume, or a volume too large for
+ * the layout) ws may be NULL.
  * PMF_EWORKSPACE if it is missing or short. */
 size_t pmf_project_workspace(const pmf_grid_t *grid, const pmf_cone_t *cone, int V,
                              int64_t vol_stride);

@@ -1276,13 +1276,20 @@ bool use_paired(const GridK &g) {
 // 128x128x64 one view 92 / 64; 64^3 and 16 views of 128x96 24 / 27;
 // 256x256x128 and 96x64, one view 21 / 43, 16 views 106 / 110.  So copies are
 // made from 150,000 rays per volume on, and from one ray per 128 voxels on.
-constexpr int PAIR_VIEWS = 8;           // per-view volumes copied at a time
+constexpr int64_t PAIR_VIEWS = 8;       // per-view volumes copied at a time,
+constexpr int64_t PAIR_BYTES = (int64_t)1 << 30;     // within this much if more than one
+
+static int pair_copies(const GridK &g, int V, int64_t stride) {
+    if (stride == 0) return 1;
+    const int64_t fit = std::max<int64_t>(1, PAIR_BYTES / (8 * grid_size(g)));
+    return (int)std::min<int64_t>(V, std::min(PAIR_VIEWS, fit));
+}
 
 size_t project_workspace(const GridK &g, const ConeK &c, int V, int64_t stride) {
     const int64_t N = grid_size(g);
     const int64_t rays = (int64_t)c.nu * c.nv * (stride == 0 ? V : 1);
     if (!use_paired(g) || rays < 150000 || rays * 128 < N) return 0;
-    return sizeof(float) * 2 * (size_t)N * (size_t)(stride == 0 ? 1 : std::min(V, PAIR_VIEWS));
+    return sizeof(float) * 2 * (size_t)N * (size_t)pair_copies(g, V, stride);
 }
 
 hipError_t launch_project_ws(const float *vol, int64_t stride, const GridK &g, const ConeK &c,
@@ -1291,7 +1298,7 @@ hipError_t launch_project_ws(const float *vol, int64_t stride, const GridK &g, c
         return launch_project(vol, stride, g, c, angles, V, proj, s);
     const int64_t N = grid_size(g);
     float *pair = (float *)ws;
-    const int step = stride == 0 ? V : PAIR_VIEWS;
+    const int step = stride == 0 ? V : pair_copies(g, V, stride);
     for (int v0 = 0; v0 < V; v0 += step) {
         const int R = std::min(step, V - v0);
         hipError_t e;

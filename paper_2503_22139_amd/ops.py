@@ -281,14 +281,17 @@ def workspace(nbytes: int, device) -> torch.Tensor:
     return buf
 
 
-def _ws_at_hand(nbytes: int, device) -> Optional[torch.Tensor]:
-    """workspace(), or None where it would have to be allocated while the
-    current stream is captured (for calls that can do without one)."""
-    key = (str(device), torch.cuda.current_stream(device).cuda_stream)
-    buf = _ws_cache.get(key)
-    if (buf is None or buf.numel() < nbytes) and torch.cuda.is_current_stream_capturing():
+def _call_scratch(nbytes: int, device) -> Optional[torch.Tensor]:
+    """Scratch of one call that can do without it: a block of torch's allocator,
+    given back in stream order, so no other call, thread or graph shares it.
+    None while the current stream is captured (a graph would keep its address)
+    and where it does not fit."""
+    if torch.cuda.is_current_stream_capturing():
         return None
-    return workspace(nbytes, device)
+    try:
+        return torch.empty(int(nbytes), dtype=torch.uint8, device=device)
+    except torch.cuda.OutOfMemoryError:
+        return None
 
 
 def _gauss(mean, scale, quat, value) -> PmfGauss:
@@ -400,7 +403,7 @@ def pmf_project(vol, grid: Grid, cone: Cone, angles, shared: Optional[bool] = No
     cn = make_cone(cone)
     args = (_ptr(vol), stride, C.byref(g), C.byref(cn), _ptr(angles), V, _ptr(out))
     nbytes = lib().pmf_project_workspace(C.byref(g), C.byref(cn), V, stride)
-    ws = _ws_at_hand(nbytes, vol.device) if nbytes else None
+    ws = _call_scratch(nbytes, vol.device) if nbytes else None
     if ws is None:
         _check(lib().pmf_project(*args, _stream()))
     else:
