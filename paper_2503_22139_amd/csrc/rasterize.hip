@@ -144,6 +144,16 @@ struct SplatBins {
     int64_t m, chunk;                  // Gaussians, Gaussians per chunk
 };
 
+// A launch of n < 2^32 workgroups, over two grid dimensions: one of them holds
+// fewer than 2^32 threads (2^22 workgroups of 1,024), and the runtime does not
+// refuse more.
+static dim3 many_blocks(int64_t n) {
+    const int64_t x = std::min<int64_t>(std::max<int64_t>(n, 1), 1 << 21);
+    return dim3((unsigned)x, (unsigned)((n + x - 1) / x));
+}
+// The workgroup's number (the last ones may lie past n).
+__device__ __forceinline__ uint32_t flat_block() { return blockIdx.y * gridDim.x + blockIdx.x; }
+
 // Pixel box of the ellipse of D: its half-extents k sqrt(Sigma^_aa), widened
 // by a bound on the rounding errors that the pixels' float arithmetic makes of
 // the conic (about 2^-24 s00 s11 / det2 of k^2) and of the centre.
@@ -189,11 +199,13 @@ __global__ __launch_bounds__(RS_CT) void k_splat_prep(const float *__restrict__ 
                                                       int *__restrict__ slot,
                                                       int *__restrict__ nlarge) {
     extern __shared__ int hist[];
-    const int v = (int)blockIdx.x / B.nch, ch = (int)blockIdx.x % B.nch;
+    const uint32_t blk = flat_block(), nch = (uint32_t)B.nch;
+    const int v = (int)(blk / nch), ch = (int)(blk - (uint32_t)v * nch);
+    if (v >= B.V) return;
     const int64_t g0 = ch * B.chunk, g1 = min(g0 + B.chunk, B.m);
-    int *const row = part + (int64_t)blockIdx.x * B.T;
+    int *const row = part + (int64_t)blk * B.T;
     const int64_t mv = B.m * B.V;
-    if (blockIdx.x == 0 && threadIdx.x == 0) *nlarge = 0;
+    if (blk == 0 && threadIdx.x == 0) *nlarge = 0;
     for (int w0 = 0; w0 < B.T; w0 += RS_W) {
         const int nw = min(RS_W, B.T - w0);
         for (int t = threadIdx.x; t < nw; t += RS_CT) hist[t] = 0;
@@ -239,9 +251,10 @@ __global__ __launch_bounds__(1024) void k_splat_chunks(int *__restrict__ part, S
                                                        int *__restrict__ total) {
     __shared__ int sums[16][64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int nb = (B.T + 63) / 64;
-    const int v = (int)blockIdx.x / nb;
-    const int t = ((int)blockIdx.x - v * nb) * 64 + lane;
+    const uint32_t blk = flat_block(), nb = (uint32_t)(B.T + 63) / 64;
+    const int v = (int)(blk / nb);
+    if (v >= B.V) return;
+    const int t = (int)(blk - (uint32_t)v * nb) * 64 + lane;
     int *const p = part + (int64_t)v * B.nch * B.T + t;
     const int c0 = (int)((int64_t)B.nch * w / 16), c1 = (int)((int64_t)B.nch * (w + 1) / 16);
     int s = 0;
@@ -295,9 +308,11 @@ __global__ __launch_bounds__(RS_CT) void k_splat_fill(const SplatP *__restrict__
                                                       int *__restrict__ large,
                                                       int *__restrict__ nlarge) {
     extern __shared__ int base[];
-    const int v = (int)blockIdx.x / B.nch, ch = (int)blockIdx.x % B.nch;
+    const uint32_t blk = flat_block(), nch = (uint32_t)B.nch;
+    const int v = (int)(blk / nch), ch = (int)(blk - (uint32_t)v * nch);
+    if (v >= B.V) return;
     const int64_t g0 = ch * B.chunk, g1 = min(g0 + B.chunk, B.m);
-    const int *const row = part + (int64_t)blockIdx.x * B.T;
+    const int *const row = part + (int64_t)blk * B.T;
     const int64_t mv = B.m * B.V;
     for (int w0 = 0; w0 < B.T; w0 += RS_W) {
         const int nw = min(RS_W, B.T - w0);
@@ -364,7 +379,7 @@ __device__ __forceinline__ bool splat_reaches(const SplatP &P, float x0, float y
 constexpr int RF_PARTS = 4;
 constexpr int RF_T = RS_THREADS * RF_PARTS;
 
-__global__ __launch_bounds__(RF_T) void k_splat_fwd(const SplatP *__restrict__ sp, int64_t m,
+__global__ __launch_bounds__(RF_T) void k_splat_fwd(const SplatP *__restrict__ sp, int64_t m, int V,
                                                     RastGeo G,
                                                     const int *__restrict__ offsets,
                                                     const int *__restrict__ list,
@@ -376,9 +391,9 @@ __global__ __launch_bounds__(RF_T) void k_splat_fwd(const SplatP *__restrict__ s
     __shared__ float red[RF_T / 64];
     __shared__ int cnt[RF_T / 64];
     __shared__ int sum[RS_THREADS];
-    const int64_t T = (int64_t)G.tiles_u * G.tiles_v;
-    const int64_t tix = blockIdx.x;
-    const int v = (int)(tix / T), t = (int)(tix - (int64_t)v * T);
+    const uint32_t T = (uint32_t)(G.tiles_u * G.tiles_v), tix = flat_block();
+    const int v = (int)(tix / T), t = (int)(tix - (uint32_t)v * T);
+    if (v >= V) return;
     const int tx = t % G.tiles_u, ty = t / G.tiles_u;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int blk = wave & 3, part = wave >> 2;
@@ -509,13 +524,14 @@ __device__ __forceinline__ void splat_moments(const SplatP &P, float x, float y,
 // Gaussians of about 20 x 20 pixels on 512 x 384.  By tile -- every pixel of
 // the five tiles a splat reaches, and a wave reduction per tile and wave -- it
 // took 275 us and 21 to gather the tiles' partials, now 73 us.
-__global__ __launch_bounds__(256) void k_splat_bwd(const SplatP *__restrict__ sp, int64_t m, int nb,
+__global__ __launch_bounds__(256) void k_splat_bwd(const SplatP *__restrict__ sp, int64_t m, int V, int nb,
                                                    RastGeo G, const float *__restrict__ g_proj,
                                                    float *__restrict__ acc6) {
-    const int v = (int)blockIdx.x / nb;
-    const int64_t g = (int64_t)((int)blockIdx.x - v * nb) * 4 +
+    const uint32_t blk = flat_block();
+    const int v = (int)(blk / (uint32_t)nb);
+    const int64_t g = (int64_t)(blk - (uint32_t)v * (uint32_t)nb) * 4 +
                       __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (g >= m) return;
+    if (v >= V || g >= m) return;
     const int64_t i = (int64_t)v * m + g;
     const int lane = threadIdx.x & 63;
     SplatP P = sp[i];
@@ -803,14 +819,14 @@ static hipError_t rast_bin(const pmf_gauss_t &gs, const RastGeo &G, const float 
                            const RastWs &w, hipStream_t s) {
     const SplatBins B = rast_bins(gs.m, G, V);
     const int64_t T = (int64_t)B.T * V;
-    const unsigned nb = (unsigned)B.nch * (unsigned)V;
+    const dim3 nb = many_blocks((int64_t)B.nch * V);
     const size_t lds = sizeof(int) * (size_t)std::min(B.T, RS_W);
     hipError_t e;
     ProfScope prof_("rasterize_bin", s);
     k_splat_prep<<<nb, RS_CT, lds, s>>>(gs.mean, gs.scale, gs.quat, gs.value, B, G, angles, w.sp,
                                         w.bins, w.slot, w.nlarge);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    k_splat_chunks<<<(unsigned)((B.T + 63) / 64) * (unsigned)V, 1024, 0, s>>>(w.bins, B, w.total);
+    k_splat_chunks<<<many_blocks((int64_t)((B.T + 63) / 64) * V), 1024, 0, s>>>(w.bins, B, w.total);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     k_rast_scan<<<1, 1024, 0, s>>>(w.total, T, w.offsets);
     if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -828,8 +844,8 @@ hipError_t launch_rasterize(const pmf_gauss_t &gs, const pmf_cone_t &c, const fl
     const int64_t T = (int64_t)G.tiles_u * G.tiles_v * V;
     {
         ProfScope prof_("rasterize", s);
-        k_splat_fwd<<<(unsigned)T, RF_T, 0, s>>>(w.sp, gs.m, G, w.offsets, w.list, w.large, w.nlarge,
-                                                 proj);
+        k_splat_fwd<<<many_blocks(T), RF_T, 0, s>>>(w.sp, gs.m, V, G, w.offsets, w.list, w.large,
+                                                    w.nlarge, proj);
     }
     return hipGetLastError();
 }
@@ -847,8 +863,8 @@ hipError_t launch_rasterize_bwd(const pmf_gauss_t &gs, const pmf_cone_t &c, cons
         ProfScope prof_("rasterize_bwd", s);
         const int nb = (int)((gs.m + 3) / 4);
         if (gs.m > 0) {
-            k_splat_bwd<<<(unsigned)nb * (unsigned)V, 256, 0, s>>>(w.sp, gs.m, nb, G, g_proj,
-                                                                   w.acc6);
+            k_splat_bwd<<<many_blocks((int64_t)nb * V), 256, 0, s>>>(w.sp, gs.m, V, nb, G, g_proj,
+                                                                     w.acc6);
             if ((e = hipGetLastError()) != hipSuccess) return e;
         }
         k_splat_large_bwd<<<256, 256, 0, s>>>(w.sp, gs.m, G, w.large, w.nlarge, g_proj, w.acc6);
