@@ -825,9 +825,10 @@ __global__ __launch_bounds__(256, 6) void k_vox_gather(const GaussK *__restrict_
     for (int s = 0; s < SEG; ++s)
 #pragma unroll
         for (int c = 0; c < CT; ++c) acc[s][c] = 0;
+    __syncthreads();                      // scale and, of one chunk, the staged entries are there
     for (int cb = beg; cb < end; cb += VG_CHUNK) {
-        __syncthreads();                  // scale ready / previous chunk consumed
         if (!one) {
+            if (cb > beg) __syncthreads();        // the previous chunk is consumed
             if (wave == 0) {
                 const bool on = cb + lane < end;
                 const int gi = list[on ? cb + lane : cb];
