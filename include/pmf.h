@@ -197,7 +197,11 @@ int pmf_project_ws(const float *vol, int64_t vol_stride, const pmf_grid_t *grid,
 /* Exact adjoint (back-projection) of pmf_project given g_proj [V][nv][nu]:
  * g_vol_v = P_v^T g_proj[v].  vol_stride = N writes one volume per view
  * ([V][N]); vol_stride = 0 writes their sum ([N]).
- * Needs the workspace from pmf_project_bwd_workspace(). */
+ * Needs the workspace from pmf_project_bwd_workspace(): per view, the rays'
+ * constants (nu nv of them) and the bricks' staged faces (about 5 bytes per
+ * voxel).  The sum is made from the views' volumes, which take the place of
+ * other views' parts, in several rounds; with 4 N bytes more per view (up to
+ * 512 MB in all are used) it takes fewer. */
 size_t pmf_project_bwd_workspace(const pmf_grid_t *grid, const pmf_cone_t *cone, int V);
 int pmf_project_bwd(const float *g_proj, const pmf_grid_t *grid, const pmf_cone_t *cone,
                     const float *angles, int V, float *g_vol, int64_t vol_stride, void *ws,

@@ -534,11 +534,11 @@ struct BwdJob {             // one scan's back-projection, one volume per view
 };
 hipError_t launch_project_bwd_jobs(const BwdJob *jobs, int n, hipStream_t s);
 size_t project_bwd_views_workspace(const GridK &g, const pmf_cone_t &c, int V);
-// stride 0: the sum over views into one volume; ws = project_bwd_workspace bytes
-size_t project_bwd_workspace(const GridK &g, const pmf_cone_t &c, int V);
+// ws_bytes: project_bwd_views_workspace at least.  stride 0: the sum over views
+// into one volume, in rounds of as many views as the rest of ws has volumes for
 hipError_t launch_project_bwd(const float *g_proj, const GridK &g, const ConeK &c,
                               const float *angles, int V, float *g_vol, int64_t stride, void *ws,
-                              hipStream_t s);
+                              size_t ws_bytes, hipStream_t s);
 
 // loss
 size_t fdk_workspace(const pmf_cone_t &c, int V);

@@ -1363,19 +1363,18 @@ size_t project_bwd_views_workspace(const GridK &g, const pmf_cone_t &c, int V) {
 // turn leave it idle (64 workgroups for a 64^3 grid, 1,248 long ones for
 // 256x256x128) and stage every pad.  Measured, back-projection only: 10 views
 // of 128x96 onto 64^3 266 -> 30 us; 8 views of 512x384 onto
-// 256x256x128 3.04 -> 2.07 ms.  A round holds at least 16 views (156
-// column chunks each at 256x256x128: above the 1,536 workgroups a full chunk
-// length asks for), more while its volumes stay below 512 MB.
-static int sum_round(const GridK &g, int V) {
-    const int64_t fit = ((int64_t)512 << 20) / (4 * grid_size(g));
-    return (int)std::min<int64_t>(V, std::max<int64_t>(16, fit));
-}
-
-// Workspace of pmf_project_bwd: the per-view part for V views, then one
-// round's volumes.
-size_t project_bwd_workspace(const GridK &g, const pmf_cone_t &c, int V) {
-    return project_bwd_views_workspace(g, c, V) +
-           (V > 1 ? align256(sizeof(float) * (size_t)grid_size(g) * (size_t)sum_round(g, V)) : 0);
+// 256x256x128 3.04 -> 2.07 ms.  A round holds up to 16 views (156 column
+// chunks each at 256x256x128: above the 1,536 workgroups a full chunk length
+// asks for), more while its volumes stay below 512 MB, and no more than the
+// workspace holds: one of V views' per-view parts holds at least one view with
+// its volume (V > 1; a view's pads alone take more than a volume).
+static int sum_round(const GridK &g, const pmf_cone_t &c, int V, size_t ws_bytes) {
+    const int64_t vol = 4 * grid_size(g);
+    int R = (int)std::min<int64_t>(V, std::max<int64_t>(16, ((int64_t)512 << 20) / vol));
+    R = (int)std::min<int64_t>(
+        R, (int64_t)ws_bytes / (int64_t)(sizeof(float) * pad_floats(g) + (size_t)vol));
+    while (R > 1 && project_bwd_views_workspace(g, c, R) + (size_t)(vol * R) > ws_bytes) --R;
+    return std::max(R, 1);
 }
 
 // The pads of Q of the voxels that brick b holds of one line along axis 2 (from
@@ -1643,7 +1642,7 @@ hipError_t launch_project_bwd_jobs(const BwdJob *jobs, int n, hipStream_t s) {
 
 hipError_t launch_project_bwd(const float *g_proj, const GridK &g, const ConeK &c,
                               const float *angles, int V, float *g_vol, int64_t stride, void *ws,
-                              hipStream_t s) {
+                              size_t ws_bytes, hipStream_t s) {
     const int64_t N = grid_size(g);
     if (stride != 0 || V == 1) {
         const BwdJob j{g_proj, g, c, angles, V, g_vol, stride != 0 ? stride : N, ws, nullptr};
@@ -1652,8 +1651,8 @@ hipError_t launch_project_bwd(const float *g_proj, const GridK &g, const ConeK &
     pmf_cone_t pc{};
     pc.nu = c.nu;
     pc.nv = c.nv;
-    float *vols = (float *)((char *)ws + project_bwd_views_workspace(g, pc, V));
-    const int round = sum_round(g, V);
+    const int round = sum_round(g, pc, V, ws_bytes);
+    float *vols = (float *)((char *)ws + project_bwd_views_workspace(g, pc, round));
     for (int v0 = 0; v0 < V; v0 += round) {
         const int R = std::min(round, V - v0);
         BwdJob j{g_proj + (int64_t)v0 * c.nu * c.nv, g, c, angles + v0, R, vols, N, ws, nullptr};
