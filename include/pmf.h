@@ -168,7 +168,7 @@ int pmf_warp(const float *ref, const pmf_grid_t *grid, const float *dvf, int V, 
  * side its displacement puts it on (none: the cell that starts at its voxel).
  * g_ref is summed in 64-bit fixed point (each term exact to 2^-40 of the
  * largest |g_out|), so it repeats bit for bit.  Needs the workspace from
- * pmf_warp_bwd_workspace() (about 43 bytes per voxel of a large grid). */
+ * pmf_warp_bwd_workspace() (8 bytes per voxel, and 34 more up to 1 GiB). */
 size_t pmf_warp_bwd_workspace(const pmf_grid_t *grid);
 int pmf_warp_bwd(const float *ref, const pmf_grid_t *grid, const float *dvf, int V,
                  const float *g_out, float *g_ref, float *g_dvf, void *ws, size_t ws_bytes,

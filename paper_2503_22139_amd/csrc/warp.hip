@@ -9,6 +9,8 @@
 // are staged, and a last pass sums the boxes that cover a voxel and converts
 // to float.  Displacements that leave the halo add into a global 64-bit
 // volume (the last pass adds it in).
+#include <algorithm>
+
 #include "pmf_internal.h"
 
 namespace pmf {
@@ -57,12 +59,12 @@ __global__ __launch_bounds__(WB_THREADS) void k_warp_bwd(const float *__restrict
                                                          const float *__restrict__ dvf, int V,
                                                          const float *__restrict__ g_out,
                                                          const uint32_t *__restrict__ gmax, int nb1,
-                                                         int nb2,
+                                                         int nb2, int first,
                                                          unsigned long long *__restrict__ fix,
                                                          unsigned long long *__restrict__ stage,
                                                          float *__restrict__ g_dvf) {
     __shared__ unsigned long long wbox[WX];
-    const int blk = xcd_block((int)blockIdx.x, (int)gridDim.x);
+    const int local = xcd_block((int)blockIdx.x, (int)gridDim.x), blk = first + local;
     const int b2 = blk % nb2, b1 = (blk / nb2) % nb1, b0 = blk / (nb2 * nb1);
     const int B0 = b0 * WA0, B1 = b1 * WA1, B2 = b2 * WA2;
     for (int i = threadIdx.x; i < WX; i += WB_THREADS) wbox[i] = 0;
@@ -124,19 +126,16 @@ __global__ __launch_bounds__(WB_THREADS) void k_warp_bwd(const float *__restrict
         }
     }
     __syncthreads();
-    unsigned long long *st = stage + (int64_t)blk * WX;
+    unsigned long long *st = stage + (int64_t)local * WX;
     for (int i = threadIdx.x; i < WX; i += WB_THREADS) st[i] = wbox[i];
 }
 
-// g_ref[j] = the staged boxes that cover voxel j (at most two per axis) and
-// the halo overflow, summed in 64 bits, as a float.
-__global__ __launch_bounds__(256) void k_warp_gather(
-    const unsigned long long *__restrict__ stage, GridK g, int nb0, int nb1, int nb2,
-    const unsigned long long *__restrict__ fix, const uint32_t *__restrict__ gmax,
-    float *__restrict__ g_ref) {
-    const unsigned N = (unsigned)grid_size(g);      // < 2^31
-    const unsigned j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= N) return;
+// The staged boxes of bricks [first, first + count) (ALL: of every brick) that
+// cover voxel j (at most two per axis), summed in 64 bits.
+template <bool ALL>
+__device__ __forceinline__ unsigned long long warp_boxes(const unsigned long long *__restrict__ stage,
+                                                         const GridK &g, int nb0, int nb1, int nb2,
+                                                         int first, int count, unsigned j) {
     const unsigned q = j / (unsigned)g.n[2];
     const int p2 = (int)(j - q * (unsigned)g.n[2]);
     const int p0 = (int)(q / (unsigned)g.n[1]);
@@ -145,17 +144,51 @@ __global__ __launch_bounds__(256) void k_warp_gather(
     const int a0 = max(0, (p0 - WHALO - 1) / WA0), e0 = min(nb0 - 1, (p0 + WHALO) / WA0);
     const int a1 = max(0, (p1 - WHALO - 1) / WA1), e1 = min(nb1 - 1, (p1 + WHALO) / WA1);
     const int a2 = max(0, (p2 - WHALO - 1) / WA2), e2 = min(nb2 - 1, (p2 + WHALO) / WA2);
-    unsigned long long s = fix[j];
+    unsigned long long s = 0;
     for (int b0 = a0; b0 <= e0; ++b0)
         for (int b1 = a1; b1 <= e1; ++b1)
             for (int b2 = a2; b2 <= e2; ++b2) {
+                const int blk = (b0 * nb1 + b1) * nb2 + b2 - (ALL ? 0 : first);
+                if (!ALL && (blk < 0 || blk >= count)) continue;
                 const int l0 = p0 - (b0 * WA0 - WHALO), l1 = p1 - (b1 * WA1 - WHALO),
                           l2 = p2 - (b2 * WA2 - WHALO);
-                s += stage[(int64_t)((b0 * nb1 + b1) * nb2 + b2) * WX + (l0 * WX1 + l1) * WX2 + l2];
+                s += stage[(int64_t)blk * WX + (l0 * WX1 + l1) * WX2 + l2];
             }
-    const double sc = fix_scale(*gmax);
+    return s;
+}
+
+__device__ __forceinline__ float warp_unfix(unsigned long long s, uint32_t gmax) {
+    const double sc = fix_scale(gmax);
     const double inv = sc > 0.0 ? 1.0 / sc : 0.0;       // 0 or infinite M: zeros
-    g_ref[j] = (float)((double)(long long)s * inv);
+    return (float)((double)(long long)s * inv);
+}
+
+// g_ref[j] = the boxes of all bricks and the halo overflow, as a float.
+__global__ __launch_bounds__(256) void k_warp_gather(
+    const unsigned long long *__restrict__ stage, GridK g, int nb0, int nb1, int nb2,
+    const unsigned long long *__restrict__ fix, const uint32_t *__restrict__ gmax,
+    float *__restrict__ g_ref) {
+    const unsigned j = blockIdx.x * blockDim.x + threadIdx.x;
+    if (j >= (unsigned)grid_size(g)) return;                // < 2^31
+    g_ref[j] = warp_unfix(fix[j] + warp_boxes<true>(stage, g, nb0, nb1, nb2, 0, 0, j), *gmax);
+}
+
+// A round's boxes added to the 64-bit volume, voxels [j0, j0 + n).
+__global__ __launch_bounds__(256) void k_warp_add_boxes(
+    const unsigned long long *__restrict__ stage, GridK g, int nb0, int nb1, int nb2, int first,
+    int count, unsigned j0, unsigned n, unsigned long long *__restrict__ fix) {
+    const unsigned i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const unsigned long long s =
+        warp_boxes<false>(stage, g, nb0, nb1, nb2, first, count, j0 + i);
+    if (s != 0) fix[j0 + i] += s;
+}
+
+__global__ __launch_bounds__(256) void k_warp_convert(const unsigned long long *__restrict__ fix,
+                                                      unsigned n, const uint32_t *__restrict__ gmax,
+                                                      float *__restrict__ g_ref) {
+    const unsigned j = blockIdx.x * blockDim.x + threadIdx.x;
+    if (j < n) g_ref[j] = warp_unfix(fix[j], *gmax);
 }
 
 hipError_t launch_warp(const float *ref, const GridK &g, const float *dvf, int V, float *out,
@@ -178,11 +211,20 @@ static WarpBricks warp_bricks(const GridK &g) {
     return b;
 }
 
-// Workspace: the 64-bit fixed-point halo overflow, the bricks' staged boxes,
+// Bricks of a round: all, unless their boxes (34 bytes per voxel) would take
+// more than 1 GiB; then each round's boxes are added to the 64-bit volume (the
+// sums are of integers: the same bits).
+constexpr int64_t WSTAGE_BYTES = (int64_t)1 << 30;
+static int warp_round(const WarpBricks &b) {
+    return (int)std::min<int64_t>(b.n, WSTAGE_BYTES / (int64_t)(sizeof(long long) * WX));
+}
+
+// Workspace: the 64-bit fixed-point halo overflow, a round's staged boxes,
 // then the largest |g_out|.
 size_t warp_bwd_workspace(const GridK &g) {
     return align256(sizeof(long long) * (size_t)grid_size(g)) +
-           align256(sizeof(long long) * WX * (size_t)warp_bricks(g).n) + align256(sizeof(uint32_t));
+           align256(sizeof(long long) * WX * (size_t)warp_round(warp_bricks(g))) +
+           align256(sizeof(uint32_t));
 }
 
 hipError_t launch_warp_bwd(const float *ref, const GridK &g, const float *dvf, int V,
@@ -190,24 +232,45 @@ hipError_t launch_warp_bwd(const float *ref, const GridK &g, const float *dvf, i
                            hipStream_t s) {
     const int64_t N = grid_size(g);
     const WarpBricks b = warp_bricks(g);
+    const int round = warp_round(b);
     unsigned long long *fix = (unsigned long long *)ws;
     unsigned long long *stage =
         (unsigned long long *)((char *)ws + align256(sizeof(long long) * (size_t)N));
     uint32_t *gmax =
-        (uint32_t *)((char *)stage + align256(sizeof(long long) * WX * (size_t)b.n));
+        (uint32_t *)((char *)stage + align256(sizeof(long long) * WX * (size_t)round));
     hipError_t e = launch_fill_i32((int32_t *)fix, 2 * N, 0, s);
     if (e != hipSuccess) return e;
     if ((e = launch_absmax(g_out, N * V, gmax, s)) != hipSuccess) return e;
-    {
-        ProfScope prof_("warp_bwd", s);
-        k_warp_bwd<<<(unsigned)b.n, WB_THREADS, 0, s>>>(
-            ref, g, dvf, V, g_out, gmax, b.nb[1], b.nb[2], fix, stage, g_dvf);
+    const int plane = b.nb[1] * b.nb[2];
+    const int64_t row = (int64_t)g.n[1] * g.n[2];
+    for (int64_t first = 0; first < b.n; first += round) {
+        const int count = (int)std::min<int64_t>(round, b.n - first);
+        {
+            ProfScope prof_("warp_bwd", s);
+            k_warp_bwd<<<(unsigned)count, WB_THREADS, 0, s>>>(ref, g, dvf, V, g_out, gmax, b.nb[1],
+                                                              b.nb[2], (int)first, fix, stage, g_dvf);
+        }
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        if (round == b.n) break;
+        // the rows along axis 0 that the round's boxes reach
+        const int64_t x0 = std::max<int64_t>(0, first / plane * WA0 - WHALO);
+        const int64_t x1 = std::min<int64_t>(g.n[0], ((first + count - 1) / plane + 1) * WA0 + WHALO + 1);
+        const unsigned n = (unsigned)((x1 - x0) * row);
+        {
+            ProfScope prof_("warp_gather", s);
+            k_warp_add_boxes<<<(n + 255) / 256, 256, 0, s>>>(stage, g, b.nb[0], b.nb[1], b.nb[2],
+                                                             (int)first, count, (unsigned)(x0 * row), n,
+                                                             fix);
+        }
+        if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    if ((e = hipGetLastError()) != hipSuccess) return e;
     {
         ProfScope prof_("warp_gather", s);
-        k_warp_gather<<<(unsigned)((N + 255) / 256), 256, 0, s>>>(stage, g, b.nb[0], b.nb[1],
-                                                                  b.nb[2], fix, gmax, g_ref);
+        const unsigned nb = (unsigned)((N + 255) / 256);
+        if (round == b.n)
+            k_warp_gather<<<nb, 256, 0, s>>>(stage, g, b.nb[0], b.nb[1], b.nb[2], fix, gmax, g_ref);
+        else
+            k_warp_convert<<<nb, 256, 0, s>>>(fix, (unsigned)N, gmax, g_ref);
     }
     return hipGetLastError();
 }

@@ -27,3 +27,10 @@ def test_back_projection(lib, n, nu, nv, V, want):
     """The views' parts alone, whether the call sums over views or not."""
     g, c = ops.make_grid(Grid(n, (0.5, 0.5, 0.5))), ops.make_cone(Cone(1000.0, 1500.0, nu, nv, 1.0, 1.0))
     assert lib.pmf_project_bwd_workspace(C.byref(g), C.byref(c), V) <= want
+
+
+@pytest.mark.parametrize("n", [(256, 256, 128), (512, 512, 512), (1290, 1290, 1290), (32767, 32767, 2)])
+def test_warp_adjoint(lib, n):
+    """Eight bytes per voxel and at most 1 GiB, however large or flat the grid."""
+    g = ops.make_grid(Grid(n, (0.01, 0.01, 0.01)))
+    assert 0 < lib.pmf_warp_bwd_workspace(C.byref(g)) <= 8 * n[0] * n[1] * n[2] + (1 << 30) + 1024
