@@ -178,7 +178,8 @@ int pmf_warp_bwd(const float *ref, const pmf_grid_t *grid, const float *dvf, int
  * DRRs of V views: proj[v][iv][iu] = delta * sum_s S(vol_v, o + t_s d),
  * t_s = t_n + (s + 1/2) delta (geometry in pmf_cone_t).
  * vol_v = vol + v * vol_stride (floats); vol_stride = 0 projects one volume
- * in every view.  angles: device [V] (rad).  proj: [V][nv][nu]. */
+ * in every view.  angles: device [V] (rad).  proj: [V][nv][nu].  A view's
+ * pixels do not depend, bit for bit, on the views beside it. */
 int pmf_project(const float *vol, int64_t vol_stride, const pmf_grid_t *grid,
                 const pmf_cone_t *cone, const float *angles, int V, float *proj, void *stream);
 /* pmf_project with scratch space (same arguments, results bit for bit and
@@ -196,7 +197,9 @@ int pmf_project_ws(const float *vol, int64_t vol_stride, const pmf_grid_t *grid,
 
 /* Exact adjoint (back-projection) of pmf_project given g_proj [V][nv][nu]:
  * g_vol_v = P_v^T g_proj[v].  vol_stride = N writes one volume per view
- * ([V][N]); vol_stride = 0 writes their sum ([N]).
+ * ([V][N]); vol_stride = 0 writes their sum ([N]).  The bricks that the work is
+ * cut into depend on the number of views, and with them the last bits of a
+ * view's volume.
  * Needs the workspace from pmf_project_bwd_workspace(): per view, the rays'
  * constants (nu nv of them) and the bricks' staged faces (about 5 bytes per
  * voxel).  The sum is made from the views' volumes, which take the place of

@@ -506,7 +506,6 @@ struct ProjJob {            // one scan's forward projection
     int V;
     float *proj;
     bool paired;            // vol in the y-paired layout (2 floats per voxel; all jobs alike)
-    int call_views = 0;     // views of the whole call where this is a round of it
 };
 hipError_t launch_project_jobs(const ProjJob *jobs, int n, hipStream_t s);
 hipError_t launch_project(const float *vol, int64_t stride, const GridK &g, const ConeK &c,

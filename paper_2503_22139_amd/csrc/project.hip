@@ -1,8 +1,9 @@
 // project.hip -- cone-beam line integrals (Eq. 6) and their exact adjoint.
 //
-// Forward: one thread per ray (a wave's 64 rays form a tunable pixel tile so
-// that they sample neighbouring voxels), midpoint rule in voxel units with
-// sample s at u = fma(s, su, bu).
+// Forward: a lane per ray (a wave's 64 rays form a tunable pixel tile so that
+// they sample neighbouring voxels), in launches of few rays four waves per tile,
+// which share its rays' samples; midpoint rule in voxel units with sample s at
+// u = fma(s, su, bu).
 //
 // Adjoint: cell-brick owners, no global atomics.  The cells of the grid are
 // split into disjoint bricks; a workgroup owns one brick of one view, visits
@@ -267,13 +268,14 @@ struct ProjTab {
     int n;
 };
 
-// SPLIT: a wave tile is marched by SPLIT waves of the workgroup, each taking a
-// contiguous share of every ray's samples; the shares are added in order.
-template <int WU, int WV, int AU, bool PAIRED, int SPLIT>
+// A ray's value is the float sum of its samples in a fixed order, the clamped
+// ones of both ends in one sum and the body's in another, whatever the tile,
+// the layout of the volume and the launch: a view has the same bits alone and
+// beside others.
+template <int WU, int WV, int AU, bool PAIRED>
 __global__ __launch_bounds__(256) void k_project(ProjTab t) {
     static_assert(WU * WV == 64 && AU >= 1 && 4 % AU == 0, "wave tile must hold 64 pixels");
-    static_assert(SPLIT == 1 || SPLIT == 4, "one share per wave of the workgroup");
-    constexpr int BU = SPLIT == 1 ? WU * AU : WU, BV = SPLIT == 1 ? WV * (4 / AU) : WV;
+    constexpr int BU = WU * AU, BV = WV * (4 / AU);
     // within each scan, each XCD takes one contiguous range of its (view,
     // tile) items: whole views and neighbouring tiles share an L2 (measured
     // faster than sharing each view across all XCDs), and every XCD gets an
@@ -288,37 +290,27 @@ __global__ __launch_bounds__(256) void k_project(ProjTab t) {
     const int v = local / pj.ntiles, tile = local - v * pj.ntiles;
     const int tu = tile % pj.tiles_u, tv = tile / pj.tiles_u;
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-    const int iu = tu * BU + (SPLIT == 1 ? (w % AU) * WU : 0) + l % WU;
-    const int iv = tv * BV + (SPLIT == 1 ? (w / AU) * WV : 0) + l / WU;
-    const bool on = iu < c.nu && iv < c.nv;
-    if (SPLIT == 1 && !on) return;
+    const int iu = tu * BU + (w % AU) * WU + l % WU;
+    const int iv = tv * BV + (w / AU) * WV + l / WU;
+    if (iu >= c.nu || iv >= c.nv) return;
     const double th = (double)pj.angles[v];
     const RayK r = ray_setup(g, c, cos(th), sin(th), iu, iv);
     const char *__restrict__ vb = (const char *)(pj.vol + (int64_t)v * pj.stride);
-    // this wave's samples [first, end)
-    const int per = SPLIT == 1 ? r.n : (r.n + SPLIT - 1) / SPLIT;
-    const int first = SPLIT == 1 ? 0 : min(w * per, r.n), end = min(first + per, r.n);
     float acc0 = 0.0f, acc1 = 0.0f;
     auto sample = [&](float sf) {
         const float u0 = fmaf(sf, r.su[0], r.bu[0]), u1 = fmaf(sf, r.su[1], r.bu[1]),
                     u2 = fmaf(sf, r.su[2], r.bu[2]);
         return PAIRED ? march_sample_paired(vb, mk, u0, u1, u2) : march_sample(vb, mk, u0, u1, u2);
     };
-    // clamped head, unclamped body, clamped tail (a fixed order per ray
-    // whatever the tile)
+    // clamped head, unclamped body, clamped tail
     int sb, se;
     body_range(r, mk, sb, se);
-    sb = min(max(sb, first), end);
-    se = min(max(se, sb), end);
-    int s = first;
+    sb = min(sb, r.n);
+    se = min(se, r.n);
+    int s = 0;
     for (; s < sb; ++s) acc0 += sample((float)s);
     float sf = (float)s;
-    auto body = [&](float x) {
-        const float u0 = fmaf(x, r.su[0], r.bu[0]), u1 = fmaf(x, r.su[1], r.bu[1]),
-                    u2 = fmaf(x, r.su[2], r.bu[2]);
-        return PAIRED ? march_body_paired(vb, mk, u0, u1, u2) : march_body(vb, mk, u0, u1, u2);
-    };
-    if constexpr (PAIRED && SPLIT == 1) {
+    if constexpr (PAIRED) {
         // Consecutive samples of a ray often share a cell: a lane reloads its
         // eight corners only when the cell changes, which takes that lane out
         // of the gather (the loads are the limit here, not the arithmetic:
@@ -344,7 +336,12 @@ __global__ __launch_bounds__(256) void k_project(ProjTab t) {
             acc1 += lerp1(lerp1(x00, x01, f1), lerp1(x10, x11, f1), f0);
         }
     } else {
-        // four samples' loads in flight (few waves: the march is latency-bound)
+        auto body = [&](float x) {
+            const float u0 = fmaf(x, r.su[0], r.bu[0]), u1 = fmaf(x, r.su[1], r.bu[1]),
+                        u2 = fmaf(x, r.su[2], r.bu[2]);
+            return march_body(vb, mk, u0, u1, u2);
+        };
+        // four samples' loads in flight
         for (; s + 3 < se; s += 4, sf += 4.0f) {
             const float x0 = body(sf), x1 = body(sf + 1.0f), x2 = body(sf + 2.0f),
                         x3 = body(sf + 3.0f);
@@ -352,16 +349,101 @@ __global__ __launch_bounds__(256) void k_project(ProjTab t) {
         }
         for (; s < se; ++s, sf += 1.0f) acc1 += body(sf);
     }
-    for (; s < end; ++s) acc0 += sample((float)s);
-    float sum = acc0 + acc1;
-    if constexpr (SPLIT > 1) {
-        __shared__ float part[SPLIT][64];
-        part[w][l] = sum;
+    for (; s < r.n; ++s) acc0 += sample((float)s);
+    pj.proj[((int64_t)v * c.nv + iv) * c.nu + iu] = (acc0 + acc1) * r.delta;
+}
+
+// The same rays' sums with the samples of a wave tile shared by the workgroup's
+// four waves: each takes SH_K of every 4 SH_K consecutive ones (their loads are
+// in flight together) and leaves the values in LDS, and the waves in turn add
+// a group's values to the rays' sums in k_project's order.
+constexpr int SH_K = 4;
+
+template <int WU, int WV, bool PAIRED>
+__global__ __launch_bounds__(256) void k_project_shared(ProjTab t) {
+    constexpr int GROUP = 4 * SH_K;
+    __shared__ float val[2][GROUP][64];
+    __shared__ float acc[2][64];
+    const int job = job_of(t, (int)blockIdx.x);
+    const ProjK &pj = t.s[job];
+    const int local = job_item(t, job, (int)blockIdx.x);
+    if (local >= pj.items) return;
+    const GridK &g = pj.g;
+    const ConeK &c = pj.c;
+    const MarchK &mk = pj.mk;
+    const int v = local / pj.ntiles, tile = local - v * pj.ntiles;
+    const int tu = tile % pj.tiles_u, tv = tile / pj.tiles_u;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+    const int iu = tu * WU + l % WU, iv = tv * WV + l / WU;
+    const bool on = iu < c.nu && iv < c.nv;
+    const double th = (double)pj.angles[v];
+    const RayK r = ray_setup(g, c, cos(th), sin(th), iu, iv);
+    const char *__restrict__ vb = (const char *)(pj.vol + (int64_t)v * pj.stride);
+    const int n = on ? r.n : 0;
+    int sb, se;
+    body_range(r, mk, sb, se);
+    sb = min(sb, n);
+    se = min(se, n);
+    if (w < 2) acc[w][l] = 0.0f;
+    // (the four waves hold the same rays, so they agree on every branch)
+    int turn = 0;
+    for (int s0 = 0; __ballot(s0 < n) != 0; s0 += GROUP, ++turn) {
+        const int s1 = s0 + w * SH_K;
+        float x[SH_K];
+#pragma unroll
+        for (int j = 0; j < SH_K; ++j) x[j] = 0.0f;
+        if (__ballot(s1 < n && !(s1 >= sb && s1 + SH_K <= se)) == 0) {
+            if (s1 < n) {
+#pragma unroll
+                for (int j = 0; j < SH_K; ++j) {
+                    const float sf = (float)(s1 + j);
+                    const float u0 = fmaf(sf, r.su[0], r.bu[0]), u1 = fmaf(sf, r.su[1], r.bu[1]),
+                                u2 = fmaf(sf, r.su[2], r.bu[2]);
+                    x[j] = PAIRED ? march_body_paired(vb, mk, u0, u1, u2) : march_body(vb, mk, u0, u1, u2);
+                }
+            }
+        } else if (s1 < n) {
+            // an end of some ray: clamped samples (a body sample's bits are the
+            // same), of the last one again past a ray's end
+            float y[SH_K];
+#pragma unroll
+            for (int j = 0; j < SH_K; ++j) {
+                const float sf = (float)min(s1 + j, n - 1);
+                const float u0 = fmaf(sf, r.su[0], r.bu[0]), u1 = fmaf(sf, r.su[1], r.bu[1]),
+                            u2 = fmaf(sf, r.su[2], r.bu[2]);
+                y[j] = PAIRED ? march_sample_paired(vb, mk, u0, u1, u2)
+                              : march_sample(vb, mk, u0, u1, u2);
+            }
+#pragma unroll
+            for (int j = 0; j < SH_K; ++j) x[j] = s1 + j < n ? y[j] : 0.0f;
+        }
+        float(*const vals)[64] = val[turn & 1];
+#pragma unroll
+        for (int j = 0; j < SH_K; ++j) vals[w * SH_K + j][l] = x[j];
         __syncthreads();
-        if (w > 0 || !on) return;
-        sum = (part[0][l] + part[1][l]) + (part[2][l] + part[3][l]);
+        // (one barrier per group: the wave that adds this one reaches the next
+        // barrier after it, and its half of val is written again after that)
+        if ((turn & 3) == w) {
+            float a0 = acc[0][l], a1 = acc[1][l];
+            if (__ballot(n > 0 && !(s0 >= sb && s0 + GROUP <= se)) == 0) {
+#pragma unroll
+                for (int j = 0; j < GROUP; ++j) a1 += vals[j][l];
+            } else {
+#pragma unroll
+                for (int j = 0; j < GROUP; ++j) {
+                    const float y = vals[j][l];
+                    const bool in = s0 + j >= sb && s0 + j < se;
+                    a0 += in ? 0.0f : y;
+                    a1 += in ? y : 0.0f;
+                }
+            }
+            acc[0][l] = a0;
+            acc[1][l] = a1;
+        }
     }
-    pj.proj[((int64_t)v * c.nv + iv) * c.nu + iu] = sum * r.delta;
+    __syncthreads();
+    if (w == 0 && on)
+        pj.proj[((int64_t)v * c.nv + iv) * c.nu + iu] = (acc[0][l] + acc[1][l]) * r.delta;
 }
 
 // Per-ray constants of every view, per view the brick orientation of the
@@ -1174,9 +1256,9 @@ static BoundK make_bound(const GridK &g, const ConeK &c) {
     return b;
 }
 
-template <int WU, int WV, int AU, int SPLIT>
+template <int WU, int WV, int AU, bool SHARED>
 static void project_tiled(const ProjJob *jobs, int n, hipStream_t s) {
-    constexpr int BU = SPLIT == 1 ? WU * AU : WU, BV = SPLIT == 1 ? WV * (4 / AU) : WV;
+    constexpr int BU = SHARED ? WU : WU * AU, BV = SHARED ? WV : WV * (4 / AU);
     ProjTab t{};
     t.n = n;
     t.first[0] = 0;
@@ -1197,28 +1279,33 @@ static void project_tiled(const ProjJob *jobs, int n, hipStream_t s) {
     }
     for (int k = n + 1; k <= MAXS; ++k) t.first[k] = t.first[n];
     if (t.first[n] == 0) return;
-    if (jobs[0].paired)
-        k_project<WU, WV, AU, true, SPLIT><<<(unsigned)t.first[n], 256, 0, s>>>(t);
-    else
-        k_project<WU, WV, AU, false, SPLIT><<<(unsigned)t.first[n], 256, 0, s>>>(t);
+    const unsigned nb = (unsigned)t.first[n];
+    if constexpr (SHARED) {
+        if (jobs[0].paired) k_project_shared<WU, WV, true><<<nb, 256, 0, s>>>(t);
+        else k_project_shared<WU, WV, false><<<nb, 256, 0, s>>>(t);
+    } else {
+        if (jobs[0].paired) k_project<WU, WV, AU, true><<<nb, 256, 0, s>>>(t);
+        else k_project<WU, WV, AU, false><<<nb, 256, 0, s>>>(t);
+    }
 }
 
-// Up to 800,000 rays (four views of 512x384) four waves share every ray:
-// whole rays leave one to three waves on a SIMD, each a serial chain of loads.
-// The shares also keep four samples' loads in flight instead of reusing a
-// cell's corners (which pays once the loads are the bound).  Whole call,
-// whole rays against shares: 256x256x128 paired one view 212 / 139 us, two
-// 252 / 237, four 454 / 419, eight 765 / 784; 128x128x64 paired one view
-// 89 / 64, four 151 / 159; 64^3 plain ten views of 128x96 (122,880 rays) 50 / 15.
-constexpr int64_t SPLIT_RAYS = 800000;
+// Up to 800,000 rays (four views of 512x384) four waves share every ray (the
+// same bits): whole rays leave one to three waves on a SIMD, each a serial chain
+// of loads, where a wave of the shared ones has four samples' loads in flight;
+// with more rays the loads themselves are the bound, and a wave that marches
+// whole rays reuses a cell's corners.  Whole call, whole rays against shared:
+// 256x256x128 paired one view 203 / 138 us, two 229 / 215, four 419 / 385, five
+// 513 / 503, six 633 / 594, eight 760 / 787; 128x128x64 paired one view 91 / 61, two 109 / 98,
+// four 135 / 148 (the smaller the volume, the earlier they cross: the rule does
+// not follow that); 64^3 plain ten views of 128x96 (122,880 rays) 49 / 23.
+constexpr int64_t SHARED_RAYS = 800000;
 
 template <int WU, int WV, int AU>
 static void project_tile(const ProjJob *jobs, int n, hipStream_t s) {
     int64_t rays = 0;
-    for (int k = 0; k < n; ++k)
-        rays += (int64_t)std::max(jobs[k].V, jobs[k].call_views) * jobs[k].c.nu * jobs[k].c.nv;
-    if (rays <= SPLIT_RAYS) project_tiled<WU, WV, AU, 4>(jobs, n, s);
-    else project_tiled<WU, WV, AU, 1>(jobs, n, s);
+    for (int k = 0; k < n; ++k) rays += (int64_t)jobs[k].V * jobs[k].c.nu * jobs[k].c.nv;
+    if (rays <= SHARED_RAYS) project_tiled<WU, WV, AU, true>(jobs, n, s);
+    else project_tiled<WU, WV, AU, false>(jobs, n, s);
 }
 
 hipError_t launch_project_jobs(const ProjJob *jobs, int n, hipStream_t s) {
@@ -1272,10 +1359,12 @@ bool use_paired(const GridK &g) {
 // load instructions (four 8-byte ones per sample in the plain layout, two of
 // 16 bytes in the paired one, about 16 CU cycles each), the copy by its 12
 // bytes per voxel.  Measured, whole call, plain against paired:
-// 256x256x128 and 512x384, one view 198 / 139 us, eight views 1512 / 765;
-// 128x128x64 one view 92 / 64; 64^3 and 16 views of 128x96 24 / 27;
-// 256x256x128 and 96x64, one view 21 / 43, 16 views 106 / 110.  So copies are
-// made from 150,000 rays per volume on, and from one ray per 128 voxels on.
+// 256x256x128 and 512x384, one view 188 / 138 us, eight views 1497 / 763;
+// 128x128x64 one view 82 / 61; 256x256x128 and 96x64, one view 21 / 43, 16 views
+// 106 / 110; 64^3 and 128x96, 13 views (159,744 rays) 24 / 28, 32 views 38 / 40.
+// So copies are made from 150,000 rays per volume on, and from one ray per 128
+// voxels on; a volume as small as 64^3 loses up to 4 us by that line at any
+// number of rays measured.
 constexpr int64_t PAIR_VIEWS = 8;       // per-view volumes copied at a time,
 constexpr int64_t PAIR_BYTES = (int64_t)1 << 30;     // within this much if more than one
 
@@ -1307,7 +1396,7 @@ hipError_t launch_project_ws(const float *vol, int64_t stride, const GridK &g, c
                 hipSuccess)
                 return e;
         const ProjJob j{pair, stride == 0 ? 0 : 2 * N, g, c, angles + v0, R,
-                        proj + (int64_t)v0 * c.nu * c.nv, true, V};
+                        proj + (int64_t)v0 * c.nu * c.nv, true};
         if ((e = launch_project_jobs(&j, 1, s)) != hipSuccess) return e;
     }
     return hipSuccess;
