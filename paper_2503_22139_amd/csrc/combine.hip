@@ -67,15 +67,16 @@ struct BlockAxis {              // the block's four outputs along one axis
     bool in[4];
 };
 
-// axis_cell of four consecutive outputs; an output outside the level's box
-// takes the cell of the nearest inside point (its value is not used).
-__device__ __forceinline__ BlockAxis block_axis(const AxisMap &m, int a, int i0) {
+// axis_cell of four consecutive outputs of n_out; one outside the level's box
+// takes the cell of the nearest inside point (its value is not used, nor that
+// of one past the output grid: the level may go on there).
+__device__ __forceinline__ BlockAxis block_axis(const AxisMap &m, int a, int i0, int n_out) {
     BlockAxis x;
     x.n = m.n[a];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const float u = level_coord(m, a, i0 + q);
-        x.in[q] = u >= -0.5f && u <= (float)m.n[a] - 0.5f;
+        x.in[q] = u >= -0.5f && u <= (float)m.n[a] - 0.5f && i0 + q < n_out;
         const float uc = fminf(fmaxf(u, 0.0f), (float)(m.n[a] - 1));
         const int c = __builtin_amdgcn_readfirstlane(min((int)floorf(uc), m.n[a] - 2));
         x.f[q] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(uc - (float)c)));
@@ -101,11 +102,11 @@ struct LevelBlock {
     bool inz, direct;           // direct: outputs lie on the level's columns
 };
 
-__device__ __forceinline__ LevelBlock level_block(const AxisMap &m, int ix0, int iy0, int iz,
-                                                  bool on) {
+__device__ __forceinline__ LevelBlock level_block(const AxisMap &m, const GridK &out, int ix0,
+                                                  int iy0, int iz, bool on) {
     LevelBlock b;
-    b.x = block_axis(m, 0, ix0);
-    b.y = block_axis(m, 1, iy0);
+    b.x = block_axis(m, 0, ix0, out.n[0]);
+    b.y = block_axis(m, 1, iy0, out.n[1]);
     int i = 0;
     float f = 0.0f;
     b.inz = axis_cell(level_coord(m, 2, iz), m.n[2], i, f) && on;
@@ -220,7 +221,7 @@ __global__ __launch_bounds__(256) void k_combine_block(LevelsK lv, const float *
 #pragma unroll 1
     for (int l = 0; l < lv.L; ++l) {
         const AxisMap &m = lv.map[l];
-        const LevelBlock b = level_block(m, ix0, iy0, iz, on);
+        const LevelBlock b = level_block(m, out, ix0, iy0, iz, on);
         const int64_t Nl = (int64_t)m.n[0] * m.n[1] * m.n[2];
 #pragma unroll 1
         for (int bb = 0; bb < lv.B; ++bb) {
@@ -253,8 +254,10 @@ __global__ __launch_bounds__(256) void k_combine_block(LevelsK lv, const float *
 hipError_t launch_combine(const LevelsK &lv, const float *coeff, int V, const GridK &out, float *dvf,
                           hipStream_t s) {
     const int64_t N = grid_size(out);
-    if (V <= 2 && block_levels(lv)) {
-        const BlockGrid bg = block_grid(out);
+    const BlockGrid bg = block_grid(out);
+    // (a grid of 2^26 blocks, flat along axis 2, has more threads than one
+    // dimension of a launch)
+    if (V <= 2 && block_levels(lv) && bg.n < 1 << 26) {
         const dim3 nb((unsigned)((bg.n + 3) / 4), 3);
         ProfScope prof_("combine", s);
         if (V == 1) k_combine_block<1><<<nb, 256, 0, s>>>(lv, coeff, out, bg, dvf);
@@ -353,7 +356,7 @@ __global__ __launch_bounds__(256) void k_combine_bwd_coeff_block(
 #pragma unroll 1
         for (int l = 0; l < lv.L; ++l) {
             const AxisMap &m = lv.map[l];
-            const LevelBlock b = level_block(m, ix0, iy0, iz, on);
+            const LevelBlock b = level_block(m, out, ix0, iy0, iz, on);
             const int64_t Nl = (int64_t)m.n[0] * m.n[1] * m.n[2];
 #pragma unroll 1
             for (int bb = 0; bb < lv.B; ++bb) {
