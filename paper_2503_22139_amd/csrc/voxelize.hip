@@ -159,8 +159,11 @@ __device__ __forceinline__ bool far_from_grid(const float *__restrict__ mean,
 // and totals, and k_vox_fill scans the totals and writes each pair to its
 // place.  (Counting in global memory took a device-scope atomic per pair, which
 // contend per cache line: 100 + 19 us of 150 for the 200k set, and eight
-// launches; now three and 48 us.)  Counts are held for BIN_W tiles at a time; a grid of
-// more walks its Gaussians again for each further window.
+// launches; now three and 48 us.)  Counts are held for BIN_W tiles; a grid of
+// more has a workgroup per chunk and window of them (grid dimension y), and
+// k_vox_chunks adds up the windows' totals.  (Windows walked one after the
+// other by the chunk's workgroup, few chunks where tiles are many: 2.5 ms for
+// 200k Gaussians in 1024x1024x800, 34 windows, now 0.36.)
 struct VoxTiles {                      // a set's tiles and chunks
     int T0, T1, T2, nt1, nt2, ntiles;
     int maxtiles;                      // more tiles than this: a large Gaussian
@@ -204,72 +207,77 @@ __device__ __forceinline__ void each_pair(const TileBox &t, const VoxTiles &p, i
             }
 }
 
+// Windows win0 + blockIdx.y; the first builds the records that the others read.
 // (COUNT = false: the records and the large Gaussians only.)
 template <bool COUNT>
 __global__ __launch_bounds__(BIN_T) void k_vox_bin(pmf_gauss_t gs, GridK g, float k, VoxTiles p,
                                                    GaussK *__restrict__ rec,
                                                    int32_t *__restrict__ part,
                                                    int32_t *__restrict__ slot,
-                                                   int32_t *__restrict__ nlarge) {
+                                                   int32_t *__restrict__ nlarge, int win0,
+                                                   int32_t *__restrict__ wtotal) {
     extern __shared__ int32_t hist[];
     __shared__ int32_t nl;
     const int64_t i0 = (int64_t)blockIdx.x * p.chunk, i1 = min(i0 + p.chunk, gs.m);
     int32_t *const row = part + (int64_t)blockIdx.x * p.ntiles;
-    if (threadIdx.x == 0) nl = 0;
-    for (int w0 = 0; w0 < (COUNT ? p.ntiles : 1); w0 += BIN_W) {
-        const int nw = min(BIN_W, p.ntiles - w0);
-        if (COUNT)
-            for (int t = threadIdx.x; t < nw; t += BIN_T) hist[t] = 0;
-        __syncthreads();
-        for (int64_t i = i0 + threadIdx.x; i < i1; i += BIN_T) {
-            GaussK r = {};
-            if (w0 > 0) {
-                r = rec[i];
-            } else {
-                if (far_from_grid(gs.mean, gs.scale, i, k, g)) {
-                    r.lo0 = r.lo1 = r.lo2 = 1;        // empty box: no tile, no voxel
-                } else {
-                    GaussFull G;
-                    gauss_full(gs.mean, gs.scale, gs.quat, i, k, g, G);
-                    for (int a = 0; a < 3; ++a) r.mu[a] = G.mu[a];
-                    r.a00 = G.A[0][0];
-                    r.a01 = G.A[0][1];
-                    r.a02 = G.A[0][2];
-                    r.a11 = G.A[1][1];
-                    r.a12 = G.A[1][2];
-                    r.a22 = G.A[2][2];
-                    r.lo0 = G.lo[0];
-                    r.lo1 = G.lo[1];
-                    r.lo2 = G.lo[2];
-                    r.hi0 = G.hi[0];
-                    r.hi1 = G.hi[1];
-                    r.hi2 = G.hi[2];
-                    r.rim = G.rim;
-                }
-                rec[i] = r;
-            }
-            const TileBox t = tile_box(r, p.T0, p.T1, p.T2);
-            if (t.count > p.maxtiles) {
-                if (w0 == 0) atomicAdd(&nl, 1);
-            } else if (COUNT && t.count > 0) {
-                each_pair(t, p, w0, [&](int w, int q) {
-                    slot[(int64_t)q * gs.m + i] = atomicAdd(&hist[w], 1);
-                });
-            }
-        }
-        __syncthreads();
-        if (COUNT)
-            for (int t = threadIdx.x; t < nw; t += BIN_T) row[w0 + t] = hist[t];
-        __syncthreads();
+    const int win = win0 + (int)blockIdx.y, w0 = win * BIN_W;
+    const int nw = min(BIN_W, p.ntiles - w0);
+    if (threadIdx.x == 0) {
+        nl = 0;
+        if (COUNT && blockIdx.x == 0) wtotal[win] = 0;
     }
-    if (threadIdx.x == 0) nlarge[1 + blockIdx.x] = nl;
+    if (COUNT)
+        for (int t = threadIdx.x; t < nw; t += BIN_T) hist[t] = 0;
+    __syncthreads();
+    for (int64_t i = i0 + threadIdx.x; i < i1; i += BIN_T) {
+        GaussK r = {};
+        if (win > 0) {
+            r = rec[i];                           // an earlier launch's
+        } else {
+            if (far_from_grid(gs.mean, gs.scale, i, k, g)) {
+                r.lo0 = r.lo1 = r.lo2 = 1;        // empty box: no tile, no voxel
+            } else {
+                GaussFull G;
+                gauss_full(gs.mean, gs.scale, gs.quat, i, k, g, G);
+                for (int a = 0; a < 3; ++a) r.mu[a] = G.mu[a];
+                r.a00 = G.A[0][0];
+                r.a01 = G.A[0][1];
+                r.a02 = G.A[0][2];
+                r.a11 = G.A[1][1];
+                r.a12 = G.A[1][2];
+                r.a22 = G.A[2][2];
+                r.lo0 = G.lo[0];
+                r.lo1 = G.lo[1];
+                r.lo2 = G.lo[2];
+                r.hi0 = G.hi[0];
+                r.hi1 = G.hi[1];
+                r.hi2 = G.hi[2];
+                r.rim = G.rim;
+            }
+            rec[i] = r;
+        }
+        const TileBox t = tile_box(r, p.T0, p.T1, p.T2);
+        if (t.count > p.maxtiles) {
+            if (win == 0) atomicAdd(&nl, 1);
+        } else if (COUNT && t.count > 0) {
+            each_pair(t, p, w0, [&](int w, int q) {
+                slot[(int64_t)q * gs.m + i] = atomicAdd(&hist[w], 1);
+            });
+        }
+    }
+    __syncthreads();
+    if (COUNT)
+        for (int t = threadIdx.x; t < nw; t += BIN_T) row[w0 + t] = hist[t];
+    if (win == 0 && threadIdx.x == 0) nlarge[1 + blockIdx.x] = nl;
 }
 
 // Per tile: the chunks' counts -> the places of their first pairs in the tile's
 // list, in place, and the tile's total.  A workgroup takes 64 tiles (a lane
-// each), its sixteen waves a sixteenth of the chunks each.
+// each), its sixteen waves a sixteenth of the chunks each.  With several windows
+// their totals are added up too.
 __global__ __launch_bounds__(1024) void k_vox_chunks(int32_t *__restrict__ part, int ntiles, int nch,
-                                                    int32_t *__restrict__ total) {
+                                                    int32_t *__restrict__ total,
+                                                    int32_t *__restrict__ wtotal) {
     __shared__ int32_t sums[16][64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int t = blockIdx.x * 64 + lane;
@@ -281,6 +289,13 @@ __global__ __launch_bounds__(1024) void k_vox_chunks(int32_t *__restrict__ part,
     }
     sums[w][lane] = s;
     __syncthreads();
+    if (w == 0 && ntiles > BIN_W) {
+        static_assert(BIN_W % 64 == 0, "a workgroup's tiles lie in one window");
+        int32_t all = 0;
+        for (int k = 0; k < 16; ++k) all += sums[k][lane];
+        for (int o = 32; o > 0; o >>= 1) all += __shfl_xor(all, o, 64);
+        if (lane == 0) atomicAdd(&wtotal[(int)blockIdx.x * 64 / BIN_W], all);
+    }
     if (t >= ntiles) return;
     int32_t run = 0;
     for (int k = 0; k < w; ++k) run += sums[k][lane];
@@ -314,7 +329,7 @@ __device__ __forceinline__ int32_t block_excl_sum(int32_t v, int32_t *wsum, int3
 // offsets) and writes its pairs to their places, and its large Gaussians, in
 // ascending order, to the large list.
 // With SHORT it also sums the chunks' counts itself: up to BIN_SHORT (chunk,
-// tile) counts that costs less than k_vox_chunks' launch.
+// tile) counts of one window that costs less than k_vox_chunks' launch.
 constexpr int BIN_SHORT = 1 << 14;
 
 template <bool SHORT>
@@ -323,6 +338,7 @@ __global__ __launch_bounds__(BIN_T) void k_vox_fill(int64_t m, const GaussK *__r
                                                     const int32_t *__restrict__ total,
                                                     const int32_t *__restrict__ slot,
                                                     int32_t *__restrict__ nlarge,
+                                                    const int32_t *__restrict__ wtotal,
                                                     int32_t *__restrict__ off,
                                                     int32_t *__restrict__ list,
                                                     int32_t *__restrict__ large) {
@@ -331,55 +347,55 @@ __global__ __launch_bounds__(BIN_T) void k_vox_fill(int64_t m, const GaussK *__r
     const int64_t i0 = (int64_t)blockIdx.x * p.chunk, i1 = min(i0 + p.chunk, m);
     const int32_t *const row = part + (int64_t)blockIdx.x * p.ntiles;
     const bool first = blockIdx.x == 0;
+    const int w0 = (int)blockIdx.y * BIN_W, nw = min(BIN_W, p.ntiles - w0);
     int32_t carry = 0;
-    for (int w0 = 0; w0 < p.ntiles; w0 += BIN_W) {
-        const int nw = min(BIN_W, p.ntiles - w0);
-        for (int t0 = 0; SHORT && t0 < nw; t0 += BIN_T) {
-            const int t = t0 + (int)threadIdx.x;
-            int32_t all = 0, before = 0;
-            if (t < nw) {
+    for (int k = 0; k < (int)blockIdx.y; ++k) carry += wtotal[k];
+    for (int t0 = 0; SHORT && t0 < nw; t0 += BIN_T) {
+        const int t = t0 + (int)threadIdx.x;
+        int32_t all = 0, before = 0;
+        if (t < nw) {
 #pragma unroll 8
-                for (int c = 0; c < (int)gridDim.x; ++c) {
-                    const int32_t x = part[(int64_t)c * p.ntiles + w0 + t];
-                    all += x;
-                    before += c < (int)blockIdx.x ? x : 0;
-                }
-            }
-            const int32_t o = block_excl_sum(all, wsum, carry);
-            if (t < nw) {
-                if (first) off[w0 + t] = o;
-                base[t] = o + before;
+            for (int c = 0; c < (int)gridDim.x; ++c) {
+                const int32_t x = part[(int64_t)c * p.ntiles + t];
+                all += x;
+                before += c < (int)blockIdx.x ? x : 0;
             }
         }
-        for (int t0 = 0; !SHORT && t0 < nw; t0 += 4 * BIN_T) {
-            // four neighbouring tiles per thread
-            const int t = t0 + 4 * (int)threadIdx.x;
-            int32_t v[4], s = 0;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                v[k] = t + k < nw ? total[w0 + t + k] : 0;
-                s += v[k];
-            }
-            int32_t o = block_excl_sum(s, wsum, carry);
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                if (t + k < nw) {
-                    if (first) off[w0 + t + k] = o;
-                    base[t + k] = o + row[w0 + t + k];
-                    o += v[k];
-                }
+        const int32_t o = block_excl_sum(all, wsum, carry);
+        if (t < nw) {
+            if (first) off[t] = o;
+            base[t] = o + before;
         }
-        __syncthreads();
-        for (int64_t i = i0 + threadIdx.x; i < i1; i += BIN_T) {
-            const TileBox t = tile_box(rec[i], p.T0, p.T1, p.T2);
-            if (t.count == 0 || t.count > p.maxtiles) continue;
-            each_pair(t, p, w0, [&](int w, int q) {
-                list[base[w] + slot[(int64_t)q * m + i]] = (int32_t)i;
-            });
-        }
-        __syncthreads();
     }
-    if (first && threadIdx.x == 0) off[p.ntiles] = carry;
+    for (int t0 = 0; !SHORT && t0 < nw; t0 += 4 * BIN_T) {
+        // four neighbouring tiles per thread
+        const int t = t0 + 4 * (int)threadIdx.x;
+        int32_t v[4], s = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            v[k] = t + k < nw ? total[w0 + t + k] : 0;
+            s += v[k];
+        }
+        int32_t o = block_excl_sum(s, wsum, carry);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (t + k < nw) {
+                if (first) off[w0 + t + k] = o;
+                base[t + k] = o + row[w0 + t + k];
+                o += v[k];
+            }
+    }
+    __syncthreads();
+    for (int64_t i = i0 + threadIdx.x; i < i1; i += BIN_T) {
+        const TileBox t = tile_box(rec[i], p.T0, p.T1, p.T2);
+        if (t.count == 0 || t.count > p.maxtiles) continue;
+        each_pair(t, p, w0, [&](int w, int q) {
+            list[base[w] + slot[(int64_t)q * m + i]] = (int32_t)i;
+        });
+    }
+    __syncthreads();
+    if (first && w0 + nw == p.ntiles && threadIdx.x == 0) off[p.ntiles] = carry;
+    if (blockIdx.y > 0) return;
     // the large list: this chunk's place in it, then its entries by ballots
     int32_t before = 0, all = 0;
     for (int c0 = 0; c0 < (int)gridDim.x; c0 += BIN_T) {
@@ -975,7 +991,7 @@ VoxPlan vox_plan(int64_t m, int c, const GridK &g) {
 namespace {
 struct VoxWs {
     GaussK *rec;
-    int32_t *part, *total, *off, *list, *large, *nlarge, *slot;
+    int32_t *part, *total, *wtotal, *off, *list, *large, *nlarge, *slot;
     size_t bytes;
 };
 VoxWs vox_ws(void *base, const VoxPlan &p, int64_t m) {
@@ -991,6 +1007,7 @@ VoxWs vox_ws(void *base, const VoxPlan &p, int64_t m) {
     w.rec = (GaussK *)take(sizeof(GaussK) * n);                                  // records
     w.part = (int32_t *)take(sizeof(int32_t) * (size_t)p.nch * (size_t)p.ntiles);   // chunks' counts
     w.total = (int32_t *)take(sizeof(int32_t) * (size_t)p.ntiles);               // tiles' totals
+    w.wtotal = (int32_t *)take(sizeof(int32_t) * (size_t)((p.ntiles + BIN_W - 1) / BIN_W));  // windows'
     w.off = (int32_t *)take(sizeof(int32_t) * (size_t)(p.ntiles + 1));           // lists' offsets
     w.list = (int32_t *)take(sizeof(int32_t) * cap);
     w.large = (int32_t *)take(sizeof(int32_t) * n);                              // large list
@@ -1027,29 +1044,36 @@ hipError_t launch_voxelize(const pmf_gauss_t &gs, const GridK &g, float k, float
         t.maxtiles = p.maxtiles;
         t.chunk = (m + p.nch - 1) / p.nch;
         const size_t hist = sizeof(int32_t) * (size_t)std::min<int64_t>(p.ntiles, BIN_W);
+        const unsigned nwin = (unsigned)((p.ntiles + BIN_W - 1) / BIN_W);
         {
             ProfScope prof_("voxelize_bin", s);
-            if (scan)
-                k_vox_bin<false><<<(unsigned)p.nch, BIN_T, 0, s>>>(gs, g, k, t, rec, w.part, w.slot, nlarge);
-            else
-                k_vox_bin<true><<<(unsigned)p.nch, BIN_T, hist, s>>>(gs, g, k, t, rec, w.part, w.slot, nlarge);
+            if (scan) {
+                k_vox_bin<false><<<(unsigned)p.nch, BIN_T, 0, s>>>(gs, g, k, t, rec, w.part, w.slot,
+                                                                   nlarge, 0, w.wtotal);
+            } else {
+                k_vox_bin<true><<<(unsigned)p.nch, BIN_T, hist, s>>>(gs, g, k, t, rec, w.part, w.slot,
+                                                                     nlarge, 0, w.wtotal);
+                if (nwin > 1)
+                    k_vox_bin<true><<<dim3((unsigned)p.nch, nwin - 1), BIN_T, hist, s>>>(
+                        gs, g, k, t, rec, w.part, w.slot, nlarge, 1, w.wtotal);
+            }
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        const bool brief = (int64_t)p.nch * p.ntiles <= BIN_SHORT;
+        const bool brief = nwin == 1 && (int64_t)p.nch * p.ntiles <= BIN_SHORT;
         if (!brief && !scan) {
             ProfScope prof_("voxelize_chunks", s);
             k_vox_chunks<<<(unsigned)((p.ntiles + 63) / 64), 1024, 0, s>>>(w.part, t.ntiles, p.nch,
-                                                                          w.total);
+                                                                          w.total, w.wtotal);
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if (!scan) {
             ProfScope prof_("voxelize_fill", s);
             if (brief)
                 k_vox_fill<true><<<(unsigned)p.nch, BIN_T, hist, s>>>(
-                    m, rec, t, w.part, w.total, w.slot, nlarge, off, list, large);
+                    m, rec, t, w.part, w.total, w.slot, nlarge, w.wtotal, off, list, large);
             else
-                k_vox_fill<false><<<(unsigned)p.nch, BIN_T, hist, s>>>(
-                    m, rec, t, w.part, w.total, w.slot, nlarge, off, list, large);
+                k_vox_fill<false><<<dim3((unsigned)p.nch, nwin), BIN_T, hist, s>>>(
+                    m, rec, t, w.part, w.total, w.slot, nlarge, w.wtotal, off, list, large);
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
