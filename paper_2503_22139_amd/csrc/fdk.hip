@@ -170,7 +170,7 @@ struct Fft {
     static constexpr int G = 16 / LR;                           // its groups per thread
     static constexpr int THREADS = TPP < 64 ? 64 : TPP;
     static constexpr int PER = THREADS / TPP;                   // transforms per workgroup
-    static constexpr int WAVES = 2;                             // per SIMD: LDS (16 bytes a point) leaves 2.5
+    static constexpr int WAVES = P <= 10 ? 3 : 2;               // per SIMD: LDS (16 bytes a point) leaves 2.5
 
     // first point and spacing of thread u's 16 points in pass p
     static __device__ __forceinline__ int first(int p, int u) {
@@ -332,6 +332,29 @@ __device__ __forceinline__ double pow2(int e) {
 // The top word of |x|: ordered like |x|, its upper 11 bits the exponent.
 __device__ __forceinline__ uint32_t top_word(double x) { return (uint32_t)__double2hiint(x) & 0x7fffffffu; }
 
+// The values of a thread's eight points of two rows that are not finite.  Every
+// tap of an odd lag is negative, so such a value adds -+infinity (or NaN) to
+// every output of the other parity, whatever the lag, and to its own place the
+// centre tap's +-infinity.
+struct BadPixels {
+    uint32_t own = 0;       // 2 bits per point and row: 1 +infinity, 2 -infinity, 3 NaN
+    uint32_t kinds = 0;     // the rows': 3 bits per row and parity, one per code
+    __device__ __forceinline__ void take(double x, int row, int k, int parity) {
+        if (top_word(x) < 0x7ff00000u) return;
+        const uint32_t code = x != x ? 3u : x > 0.0 ? 1u : 2u;
+        own |= code << (4 * k + 2 * row);
+        kinds |= 1u << (6 * row + 3 * parity + code - 1);
+    }
+    // what they add to the output at point k
+    __device__ __forceinline__ float term(int row, int k, int parity) const {
+        const uint32_t code = own >> (4 * k + 2 * row) & 3u, other = kinds >> (6 * row + 3 * (1 - parity));
+        float t = code == 1u ? INFINITY : code == 2u ? -INFINITY : code == 3u ? NAN : 0.0f;
+        if (other & 1u) t -= INFINITY;
+        if (other & 2u) t += INFINITY;
+        return other & 4u ? NAN : t;
+    }
+};
+
 // Filters FDK_ROWS rows of one view per transform slot, two at a time, and
 // writes them into the padded plane's pairs: padded row i + 1 holds rows i and
 // i + 1, so a row is kept until the next one is there, and only the slot's
@@ -349,6 +372,7 @@ __attribute__((amdgpu_waves_per_eu(Fft<P>::WAVES))) void k_fdk_filter(const floa
     using F = Fft<P>;
     __shared__ cplx smem[F::PER * F::M];
     __shared__ ushort2 wexp[F::THREADS / 64];       // the pair's largest exponents, by wave
+    static_assert(F::step(0) % 2 == 0, "a thread's outputs have one parity");
     const int nu = c.nu, nv = c.nv, pitch = nu + 3;
     const int u = threadIdx.x % F::TPP, v = blockIdx.y;
     cplx *const sh = smem + (threadIdx.x / F::TPP) * F::M;
@@ -380,11 +404,11 @@ __attribute__((amdgpu_waves_per_eu(Fft<P>::WAVES))) void k_fdk_filter(const floa
 #pragma unroll 1
     for (int q = 0; q < FDK_ROWS; q += 2) {
         const int i = r0 + q;
-        const double ba = ((double)i - 0.5 * (nv - 1) + c.off_v) * c.dv;
-        const double bb = ((double)(i + 1) - 0.5 * (nv - 1) + c.off_v) * c.dv;
-        const double sa = sdd * sdd + ba * ba, sb = sdd * sdd + bb * bb;
-        const float *row = proj + ((int64_t)v * nv + i) * nu;
-        auto pixel = [&](int n) {                   // cosine-weighted rows i, i + 1
+        auto pixel = [&](int i, int n) {            // cosine-weighted rows i, i + 1
+            const double ba = ((double)i - 0.5 * (nv - 1) + c.off_v) * c.dv;
+            const double bb = ((double)(i + 1) - 0.5 * (nv - 1) + c.off_v) * c.dv;
+            const double sa = sdd * sdd + ba * ba, sb = sdd * sdd + bb * bb;
+            const float *row = proj + ((int64_t)v * nv + i) * nu;
             const double a = ((double)n - 0.5 * (nu - 1) + c.off_u) * c.du, aa = a * a;
             return cplx{i < r1 ? (double)row[n] * (sdd * rsqrt_nr(sa + aa)) : 0.0,
                         i + 1 < r1 ? (double)row[nu + n] * (sdd * rsqrt_nr(sb + aa)) : 0.0};
@@ -395,72 +419,97 @@ __attribute__((amdgpu_waves_per_eu(Fft<P>::WAVES))) void k_fdk_filter(const floa
 #pragma unroll
         for (int k = 0; k < 8; ++k) {           // n < M / 2 covers the row
             const int n = b0 + k * S;
-            x[k] = n < nu ? pixel(n) : cplx{0.0, 0.0};
+            x[k] = n < nu ? pixel(i, n) : cplx{0.0, 0.0};
             ma = max(ma, top_word(x[k].x));
             mb = max(mb, top_word(x[k].y));
         }
         // the rows' largest exponents, as they stand in the top words
         typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
-        u16x2 ex = {(uint16_t)(ma >> 20), (uint16_t)(mb >> 20)};
-        const bool odd = ex.x == 0x7ff || ex.y == 0x7ff;        // not finite
+        u16x2 ex;
+        auto row_exponents = [&]() {
+            ex = u16x2{(uint16_t)(ma >> 20), (uint16_t)(mb >> 20)};
 #pragma unroll
-        for (int o = 1; o < (F::TPP < 64 ? F::TPP : 64); o <<= 1)
-            ex = __builtin_elementwise_max(
-                ex, __builtin_bit_cast(u16x2, __shfl_xor(__builtin_bit_cast(int, ex), o, 64)));
-        if (F::TPP > 64 && (threadIdx.x & 63) == 0) wexp[threadIdx.x >> 6] = make_ushort2(ex.x, ex.y);
+            for (int o = 1; o < (F::TPP < 64 ? F::TPP : 64); o <<= 1)
+                ex = __builtin_elementwise_max(
+                    ex, __builtin_bit_cast(u16x2, __shfl_xor(__builtin_bit_cast(int, ex), o, 64)));
+            if (F::TPP > 64 && (threadIdx.x & 63) == 0) wexp[threadIdx.x >> 6] = make_ushort2(ex.x, ex.y);
+        };
+        row_exponents();
+        // (not finite; a workgroup of one wave needs no barrier's vote)
+        const bool any = ex.x == 0x7ff || ex.y == 0x7ff;
+        const bool bad = F::THREADS == 64 ? __ballot(any) != 0
+                                          : __builtin_amdgcn_readfirstlane(__syncthreads_or(any)) != 0;
+        if (bad) {
+            // Values that are not finite would spread over both rows of the
+            // transform: they are left out of it and their terms added after it.
+            __syncthreads();
+            ma = mb = 0;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                if (top_word(x[k].x) >= 0x7ff00000u) x[k].x = 0.0;
+                if (top_word(x[k].y) >= 0x7ff00000u) x[k].y = 0.0;
+                ma = max(ma, top_word(x[k].x));
+                mb = max(mb, top_word(x[k].y));
+            }
+            row_exponents();
+            __syncthreads();
+        }
+        int ea = ex.x, eb = ex.y;
+        if constexpr (F::TPP > 64) {
+#pragma unroll
+            for (int w = 0; w < F::THREADS / 64; ++w) {
+                ea = max(ea, (int)wexp[w].x);
+                eb = max(eb, (int)wexp[w].y);
+            }
+        }
+        // (a row of zeros counts as 2^-300, below any float: the other's
+        // errors then round to zero in it)
+        ea = max(ea, 1023 - 300);
+        eb = max(eb, 1023 - 300);
+        const double down = pow2(ea - eb);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) x[k].y *= down;
+        F::template forward<true>(x, sh, tw, u);
+        const int uh = fresh(u);
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const double h = H[(uh + (k / F::LR) * F::TPP) * F::LR + k % F::LR];
+            x[k].x *= h;
+            x[k].y *= h;
+        }
+        F::inverse(x, sh, tw, u);
+        __syncthreads();                        // sh is free for the next two rows
+        const double up = pow2(eb - ea);
         float qa[8], qb[8];
-        if (__syncthreads_or(odd)) {
-            // a value that is not finite would spread over both rows of the
-            // transform: the sum over odd lags itself
-            for (int k = 0; k < 8; ++k) {
-                const int n = b0 + k * S;
-                if (n >= nu) continue;
-                const cplx p = pixel(n);
-                cplx t = {0.25 / tau * p.x, 0.25 / tau * p.y};
-                for (int m = (n + 1) & 1; m < nu; m += 2) {
-                    const double w = -1.0 / (M_PI * M_PI * tau * (double)(n - m) * (double)(n - m));
-                    const cplx y = pixel(m);
-                    t.x = fma(w, y.x, t.x);
-                    t.y = fma(w, y.y, t.y);
-                }
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    qa[j] = j == k ? (float)t.x : qa[j];
-                    qb[j] = j == k ? (float)t.y : qb[j];
-                }
-            }
-        } else {
-            int ea = ex.x, eb = ex.y;
-            if constexpr (F::TPP > 64) {
-#pragma unroll
-                for (int w = 0; w < F::THREADS / 64; ++w) {
-                    ea = max(ea, (int)wexp[w].x);
-                    eb = max(eb, (int)wexp[w].y);
-                }
-            }
-            // (a row of zeros counts as 2^-300, below any float: the other's
-            // errors then round to zero in it)
-            ea = max(ea, 1023 - 300);
-            eb = max(eb, 1023 - 300);
-            const double down = pow2(ea - eb);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) x[k].y *= down;
-            F::template forward<true>(x, sh, tw, u);
-            const int uh = fresh(u);
-#pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                const double h = H[(uh + (k / F::LR) * F::TPP) * F::LR + k % F::LR];
-                x[k].x *= h;
-                x[k].y *= h;
-            }
-            F::inverse(x, sh, tw, u);
-            __syncthreads();                        // sh is free for the next two rows
-            const double up = pow2(eb - ea);
+        for (int k = 0; k < 8; ++k) {
+            qa[k] = (float)x[dft_slot<16>(k)].x;
+            qb[k] = (float)(x[dft_slot<16>(k)].y * up);
+        }
+        if (bad) {
+            // (the rows are read again, and the transform's LDS used: nothing of
+            // this is kept through the passes)
+            const int bn = F::first(0, fresh(u)), ii = fresh(i);
+            BadPixels bp;
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
-                qa[k] = (float)x[dft_slot<16>(k)].x;
-                qb[k] = (float)(x[dft_slot<16>(k)].y * up);
+                if (bn + k * S >= nu) continue;
+                const cplx p = pixel(ii, bn + k * S);
+                bp.take(p.x, 0, k, bn & 1);
+                bp.take(p.y, 1, k, bn & 1);
             }
+            uint32_t *const kinds = (uint32_t *)sh;
+            if (u == 0) *kinds = 0;
+            __syncthreads();
+            if (bp.kinds) atomicOr(kinds, bp.kinds);
+            __syncthreads();
+            bp.kinds = *kinds;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                qa[k] += bp.term(0, k, bn & 1);
+                qb[k] += bp.term(1, k, bn & 1);
+            }
+            __syncthreads();                    // sh is free again
         }
         if (i < r1) {
             store(i, q > 0 || i == 0 ? 0 : 2, prev, qa);
