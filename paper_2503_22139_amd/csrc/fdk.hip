@@ -355,19 +355,20 @@ struct BadPixels {
     }
 };
 
-// Filters FDK_ROWS rows of one view per transform slot, two at a time, and
+// Filters `rows` rows of one view per transform slot, two at a time, and
 // writes them into the padded plane's pairs: padded row i + 1 holds rows i and
 // i + 1, so a row is kept until the next one is there, and only the slot's
 // first and last padded rows are written by halves (the neighbours write the
 // others).  The plane's border columns and rows are written too.
 constexpr int FDK_ROWS = 8;
+constexpr int64_t FDK_FEW = 2560;      // workgroups that the chip holds at once
 
 template <int P>
 __global__ __launch_bounds__(Fft<P>::THREADS)
 __attribute__((amdgpu_waves_per_eu(Fft<P>::WAVES))) void k_fdk_filter(const float *__restrict__ proj,
                                                                 pmf_cone_t c, double tau,
                                                                 const cplx *__restrict__ tw,
-                                                                const double *__restrict__ H,
+                                                                const double *__restrict__ H, int rows,
                                                                 float2 *__restrict__ qq) {
     using F = Fft<P>;
     __shared__ cplx smem[F::PER * F::M];
@@ -376,8 +377,8 @@ __attribute__((amdgpu_waves_per_eu(Fft<P>::WAVES))) void k_fdk_filter(const floa
     const int nu = c.nu, nv = c.nv, pitch = nu + 3;
     const int u = threadIdx.x % F::TPP, v = blockIdx.y;
     cplx *const sh = smem + (threadIdx.x / F::TPP) * F::M;
-    const int r0 = ((int)blockIdx.x * F::PER + (int)threadIdx.x / F::TPP) * FDK_ROWS;
-    const int r1 = min(r0 + FDK_ROWS, nv);          // r0 >= nv: the slot only keeps the barriers
+    const int r0 = ((int)blockIdx.x * F::PER + (int)threadIdx.x / F::TPP) * rows;
+    const int r1 = min(r0 + rows, nv);          // r0 >= nv: the slot only keeps the barriers
     float2 *const plane = qq + (int64_t)v * (nv + 2) * pitch;
     const double sdd = c.sdd;
     constexpr int S = F::step(0);
@@ -402,7 +403,7 @@ __attribute__((amdgpu_waves_per_eu(Fft<P>::WAVES))) void k_fdk_filter(const floa
 #pragma unroll
     for (int k = 0; k < 8; ++k) prev[k] = zero[k] = 0.0f;
 #pragma unroll 1
-    for (int q = 0; q < FDK_ROWS; q += 2) {
+    for (int q = 0; q < rows; q += 2) {
         const int i = r0 + q;
         auto pixel = [&](int i, int n) {            // cosine-weighted rows i, i + 1
             const double ba = ((double)i - 0.5 * (nv - 1) + c.off_v) * c.dv;
@@ -537,10 +538,15 @@ static hipError_t fdk_filter(const float *proj, const pmf_cone_t &c, int V, doub
     k_fdk_ramp<P><<<1, F::THREADS, 0, s>>>(tau, c.nu, tw, H);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int slots = (c.nv + FDK_ROWS - 1) / FDK_ROWS;
+    // eight rows per slot (whole padded rows are stored for all but its ends),
+    // two where that leaves the chip idle: a slot's pairs wait for each other
+    // (whole call, eight / two rows: one view of 512x384 49 / 28 us, four 61 / 42)
+    const int64_t pairs = (int64_t)(c.nv + 1) / 2 * V;
+    const int rows = pairs <= FDK_FEW * F::PER ? 2 : FDK_ROWS;
+    const int slots = (c.nv + rows - 1) / rows;
     ProfScope prof_("fdk_filter", s);
     k_fdk_filter<P><<<dim3((unsigned)((slots + F::PER - 1) / F::PER), (unsigned)V), F::THREADS, 0, s>>>(
-        proj, c, tau, tw, H, qq);
+        proj, c, tau, tw, H, rows, qq);
     return hipGetLastError();
 }
 
