@@ -201,6 +201,20 @@ static BlockGrid block_grid(const GridK &g) {
     return b;
 }
 
+// Whether the outputs fill the blocks well enough (a block takes the same time
+// with few of its lanes on a voxel) and the blocks the chip: at least `fill` of
+// a block's 1,024 outputs and `waves` blocks, by the number of bases that share
+// a block's geometry.
+struct BlockCut {
+    int fill;
+    int64_t waves;
+};
+static bool use_blocks(const LevelsK &lv, const GridK &out, const BlockGrid &bg, int64_t waves,
+                       BlockCut one, BlockCut more) {
+    const BlockCut c = lv.B == 1 ? one : more;
+    return block_levels(lv) && waves >= c.waves && grid_size(out) >= c.fill * (int64_t)bg.n;
+}
+
 template <int VG>
 __global__ __launch_bounds__(256) void k_combine_block(LevelsK lv, const float *__restrict__ coeff,
                                                        GridK out, BlockGrid bg,
@@ -250,14 +264,19 @@ __global__ __launch_bounds__(256) void k_combine_block(LevelsK lv, const float *
 // from three on the per-voxel kernel's samples serve every view.  Three levels
 // (64^3, 128^3, 256x256x128), per voxel against blocks: B = 3 one view
 // 370 / 172 us, two 391 / 210, three 415 / 373 (two passes); B = 1 one view 123 / 89, two
-// 164 / 116; at 128x128x64, B = 3, one view 52 / 34, three 54 / 61.
+// 164 / 116; at 128x128x64, B = 3, one view 52 / 34, three 54 / 61.  The cuts
+// (k_combine alone, one view): 256 x 256 x 40 (640 outputs per block) B = 1
+// 47 / 48, B = 3 121 / 90; x 32 (512) 39 / 48 and 98 / 88, two views 40 / 54 and
+// 98 / 98; x 96 (768) B = 1 two views 96 / 98; 512x512x2 13 / 149 and 29 / 284;
+// 64^3 (256 blocks) 11 / 15 and 18 / 22; 88x88x64 (484) 16 / 16 and 32 / 27;
+// 112x112x64 (784) B = 1 two views 21 / 22.
 hipError_t launch_combine(const LevelsK &lv, const float *coeff, int V, const GridK &out, float *dvf,
                           hipStream_t s) {
     const int64_t N = grid_size(out);
     const BlockGrid bg = block_grid(out);
     // (a grid of 2^26 blocks, flat along axis 2, has more threads than one
     // dimension of a launch)
-    if (V <= 2 && block_levels(lv) && bg.n < 1 << 26) {
+    if (V <= 2 && bg.n < 1 << 26 && use_blocks(lv, out, bg, bg.n, {800, 784}, {576, 480})) {
         const dim3 nb((unsigned)((bg.n + 3) / 4), 3);
         ProfScope prof_("combine", s);
         if (V == 1) k_combine_block<1><<<nb, 256, 0, s>>>(lv, coeff, out, bg, dvf);
@@ -330,7 +349,12 @@ __global__ __launch_bounds__(256) void k_combine_bwd_coeff(LevelsK lv, GridK out
 // blockIdx.y and one component k per blockIdx.z: the lanes' products with
 // g_dvf are kept per channel in LDS (each lane its own word), reduced over the
 // wave and the workgroup at the end.  One view, B = 3, three levels at
-// 256x256x128: 489 us with a voxel per thread, now 202 us.
+// 256x256x128: 489 us with a voxel per thread, now 202 us.  Where the blocks
+// are not filled or few, a voxel per thread is faster (k_combine_bwd_coeff
+// first): 256 x 256 x 44 (704 outputs per block) B = 1 one view 62 / 53, three
+// 143 / 140; x 40 129 / 139 (three); x 32 (512) B = 2 76 / 74, three views 193 / 199;
+// 512x512x2 B = 1 eight views 0.26 / 1.45 ms the call; 64^3 (256 blocks) B = 1 one
+// view 11 / 14, two 16 / 16; 32x32x64 (64) eight views 16 / 16; 88x88x64 (484) 17 / 16.
 __global__ __launch_bounds__(256) void k_combine_bwd_coeff_block(
     LevelsK lv, GridK out, BlockGrid bg, const float *__restrict__ g_dvf,
     float *__restrict__ partial) {
@@ -663,8 +687,8 @@ hipError_t launch_combine_bwd(const LevelsK &lv, const GridK *lvl_grids, const f
     char *adjws = (char *)ws + align256(sizeof(float) * (size_t)CB_BLOCKS * (size_t)V * NLB);
     hipError_t e;
     int nblk;
-    if (block_levels(lv)) {
-        const BlockGrid bg = block_grid(out);
+    const BlockGrid bg = block_grid(out);
+    if (use_blocks(lv, out, bg, (int64_t)bg.n * V, {704, 480}, {576, 480})) {
         nblk = std::min((bg.n + 3) / 4, CB_BLOCKS);
         ProfScope prof_("combine_bwd_coeff", s);
         k_combine_bwd_coeff_block<<<dim3((unsigned)nblk, (unsigned)V, 3), 256, 0, s>>>(
