@@ -450,6 +450,8 @@ struct Shape4 {
 // cells (weights 1 - f and f, as the forward reads them), and emits its
 // outputs in order (a cell is complete once the walk has passed it).  Every
 // output sums its terms in ascending fine order whatever nseg is.
+// SRC: the first pass without an input array (in: the others').
+template <bool SRC>
 __global__ __launch_bounds__(256) void k_adj_line(Shape4 in_s, int ax, int nc, float scale,
                                                   float off, int nseg,
                                                   const float *__restrict__ in, AdjSrc src,
@@ -501,7 +503,8 @@ __global__ __launch_bounds__(256) void k_adj_line(Shape4 in_s, int ax, int nc, f
 #pragma unroll
         for (int u = 0; u < ADJ_U; ++u) {
             const int64_t jj = min(j0 + u, nf - 1);     // past the end: in range, unused
-            xs[u] = in ? in[cbase + ibase + jj * ist] : adj_src(src, c, ibase + jj * ist);
+            if constexpr (SRC) xs[u] = adj_src(src, c, ibase + jj * ist);
+            else xs[u] = in[cbase + ibase + jj * ist];
         }
 #pragma unroll
         for (int u = 0; u < ADJ_U; ++u) {
@@ -653,8 +656,11 @@ hipError_t launch_upsample_adjoint(const LevelsK &lv, int l, const GridK &lvl_gr
         const int64_t threads = lines * nseg;
         {
             ProfScope prof_("upsample_adjoint", s);
-            k_adj_line<<<(unsigned)((threads + 255) / 256), 256, 0, s>>>(
-                sh, ax, m.n[ax], m.scale[ax], m.off[ax], nseg, in, src, dst);
+            const unsigned nb = (unsigned)((threads + 255) / 256);
+            if (in)
+                k_adj_line<false><<<nb, 256, 0, s>>>(sh, ax, m.n[ax], m.scale[ax], m.off[ax], nseg, in, src, dst);
+            else
+                k_adj_line<true><<<nb, 256, 0, s>>>(sh, ax, m.n[ax], m.scale[ax], m.off[ax], nseg, in, src, dst);
         }
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
