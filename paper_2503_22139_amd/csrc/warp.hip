@@ -55,6 +55,68 @@ __device__ __forceinline__ unsigned long long warp_fix(float x, double scale) {
                                 __double_as_longlong(MAGIC52));
 }
 
+// One voxel's share of every view: g_dvf, and the terms of its corners into the
+// box at (B0, B1, B2) where they lie in it (BOX), else into the 64-bit volume.
+template <bool BOX>
+__device__ __forceinline__ void warp_bwd_voxel(const float *__restrict__ ref, const GridK &g,
+                                               const float *__restrict__ dvf, int V,
+                                               const float *__restrict__ g_out, double fscale, int ix,
+                                               int iy, int iz, int B0, int B1, int B2,
+                                               unsigned long long *__restrict__ wbox,
+                                               unsigned long long *__restrict__ fix,
+                                               float *__restrict__ g_dvf) {
+    const int64_t N = grid_size(g);
+    const int s1 = g.n[2], s0 = g.n[1] * g.n[2];
+    const int64_t j = ((int64_t)ix * g.n[1] + iy) * g.n[2] + iz;
+    for (int v = 0; v < V; ++v) {
+        const float *d = dvf + (int64_t)v * 3 * N;
+        const float t0 = d[j] * g.inv_h[0], t1 = d[N + j] * g.inv_h[1],
+                    t2 = d[2 * N + j] * g.inv_h[2];
+        const float go = g_out[(int64_t)v * N + j];
+        float *gd = g_dvf + (int64_t)v * 3 * N;
+        int i0, i1, i2;
+        float f0, f1, f2;
+        if (!disp_cell(ix, t0, g.n[0], i0, f0) || !disp_cell(iy, t1, g.n[1], i1, f1) ||
+            !disp_cell(iz, t2, g.n[2], i2, f2)) {
+            gd[j] = 0.0f;
+            gd[N + j] = 0.0f;
+            gd[2 * N + j] = 0.0f;
+            continue;
+        }
+        const int64_t base = ((int64_t)i0 * g.n[1] + i1) * g.n[2] + i2;
+        const float *p = ref + base;
+        const float c000 = p[0], c001 = p[1], c010 = p[s1], c011 = p[s1 + 1];
+        const float c100 = p[s0], c101 = p[s0 + 1], c110 = p[s0 + s1], c111 = p[s0 + s1 + 1];
+        // derivative of the trilinear blend along each axis (per voxel unit)
+        const float a00 = lerp1(c000, c001, f2), a01 = lerp1(c010, c011, f2);
+        const float a10 = lerp1(c100, c101, f2), a11 = lerp1(c110, c111, f2);
+        const float dx = lerp1(a10, a11, f1) - lerp1(a00, a01, f1);
+        const float dy = lerp1(a01, a11, f0) - lerp1(a00, a10, f0);
+        const float b00 = lerp1(c000, c010, f1), b01 = lerp1(c001, c011, f1);
+        const float b10 = lerp1(c100, c110, f1), b11 = lerp1(c101, c111, f1);
+        const float dz = lerp1(b01, b11, f0) - lerp1(b00, b10, f0);
+        gd[j] = go * dx * g.inv_h[0] * disp_free(ix, t0, g.n[0]);
+        gd[N + j] = go * dy * g.inv_h[1] * disp_free(iy, t1, g.n[1]);
+        gd[2 * N + j] = go * dz * g.inv_h[2] * disp_free(iz, t2, g.n[2]);
+        if (go == 0.0f || !isfinite(go)) continue;     // (an infinite M leaves the scale 0)
+        const float w0[2] = {1.0f - f0, f0}, w1[2] = {1.0f - f1, f1}, w2[2] = {1.0f - f2, f2};
+        const int l0 = i0 - (B0 - WHALO), l1 = i1 - (B1 - WHALO), l2 = i2 - (B2 - WHALO);
+        const bool inbox = BOX && l0 >= 0 && l0 + 1 < WX0 && l1 >= 0 && l1 + 1 < WX1 && l2 >= 0 &&
+                           l2 + 1 < WX2;
+        const int o = (l0 * WX1 + l1) * WX2 + l2;
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    const unsigned long long x = warp_fix(go * w0[a] * w1[b] * w2[c], fscale);
+                    if (inbox) atomicAdd(&wbox[o + (a * WX1 + b) * WX2 + c], x);
+                    else atomicAdd(&fix[base + a * s0 + b * s1 + c], x);
+                }
+    }
+}
+
 __global__ __launch_bounds__(WB_THREADS) void k_warp_bwd(const float *__restrict__ ref, GridK g,
                                                          const float *__restrict__ dvf, int V,
                                                          const float *__restrict__ g_out,
@@ -69,65 +131,33 @@ __global__ __launch_bounds__(WB_THREADS) void k_warp_bwd(const float *__restrict
     const int B0 = b0 * WA0, B1 = b1 * WA1, B2 = b2 * WA2;
     for (int i = threadIdx.x; i < WX; i += WB_THREADS) wbox[i] = 0;
     __syncthreads();
-    const int64_t N = grid_size(g);
-    const int s1 = g.n[2], s0 = g.n[1] * g.n[2];
     const double fscale = fix_scale(*gmax);
     const int iz = B2 + (int)threadIdx.x % WA2, iy = B1 + ((int)threadIdx.x / WA2) % WA1;
     for (int q = 0; q < 2; ++q) {
         const int ix = B0 + (int)threadIdx.x / (WA1 * WA2) + q * (WA0 / 2);
         if (ix >= g.n[0] || iy >= g.n[1] || iz >= g.n[2]) continue;
-        const int64_t j = ((int64_t)ix * g.n[1] + iy) * g.n[2] + iz;
-        for (int v = 0; v < V; ++v) {
-            const float *d = dvf + (int64_t)v * 3 * N;
-            const float t0 = d[j] * g.inv_h[0], t1 = d[N + j] * g.inv_h[1],
-                        t2 = d[2 * N + j] * g.inv_h[2];
-            const float go = g_out[(int64_t)v * N + j];
-            float *gd = g_dvf + (int64_t)v * 3 * N;
-            int i0, i1, i2;
-            float f0, f1, f2;
-            if (!disp_cell(ix, t0, g.n[0], i0, f0) || !disp_cell(iy, t1, g.n[1], i1, f1) ||
-                !disp_cell(iz, t2, g.n[2], i2, f2)) {
-                gd[j] = 0.0f;
-                gd[N + j] = 0.0f;
-                gd[2 * N + j] = 0.0f;
-                continue;
-            }
-            const int64_t base = ((int64_t)i0 * g.n[1] + i1) * g.n[2] + i2;
-            const float *p = ref + base;
-            const float c000 = p[0], c001 = p[1], c010 = p[s1], c011 = p[s1 + 1];
-            const float c100 = p[s0], c101 = p[s0 + 1], c110 = p[s0 + s1], c111 = p[s0 + s1 + 1];
-            // derivative of the trilinear blend along each axis (per voxel unit)
-            const float a00 = lerp1(c000, c001, f2), a01 = lerp1(c010, c011, f2);
-            const float a10 = lerp1(c100, c101, f2), a11 = lerp1(c110, c111, f2);
-            const float dx = lerp1(a10, a11, f1) - lerp1(a00, a01, f1);
-            const float dy = lerp1(a01, a11, f0) - lerp1(a00, a10, f0);
-            const float b00 = lerp1(c000, c010, f1), b01 = lerp1(c001, c011, f1);
-            const float b10 = lerp1(c100, c110, f1), b11 = lerp1(c101, c111, f1);
-            const float dz = lerp1(b01, b11, f0) - lerp1(b00, b10, f0);
-            gd[j] = go * dx * g.inv_h[0] * disp_free(ix, t0, g.n[0]);
-            gd[N + j] = go * dy * g.inv_h[1] * disp_free(iy, t1, g.n[1]);
-            gd[2 * N + j] = go * dz * g.inv_h[2] * disp_free(iz, t2, g.n[2]);
-            if (go == 0.0f || !isfinite(go)) continue;     // (an infinite M leaves the scale 0)
-            const float w0[2] = {1.0f - f0, f0}, w1[2] = {1.0f - f1, f1}, w2[2] = {1.0f - f2, f2};
-            const int l0 = i0 - (B0 - WHALO), l1 = i1 - (B1 - WHALO), l2 = i2 - (B2 - WHALO);
-            const bool inbox = l0 >= 0 && l0 + 1 < WX0 && l1 >= 0 && l1 + 1 < WX1 && l2 >= 0 &&
-                               l2 + 1 < WX2;
-            const int o = (l0 * WX1 + l1) * WX2 + l2;
-#pragma unroll
-            for (int a = 0; a < 2; ++a)
-#pragma unroll
-                for (int b = 0; b < 2; ++b)
-#pragma unroll
-                    for (int c = 0; c < 2; ++c) {
-                        const unsigned long long x = warp_fix(go * w0[a] * w1[b] * w2[c], fscale);
-                        if (inbox) atomicAdd(&wbox[o + (a * WX1 + b) * WX2 + c], x);
-                        else atomicAdd(&fix[base + a * s0 + b * s1 + c], x);
-                    }
-        }
+        warp_bwd_voxel<true>(ref, g, dvf, V, g_out, fscale, ix, iy, iz, B0, B1, B2, wbox, fix, g_dvf);
     }
     __syncthreads();
     unsigned long long *st = stage + (int64_t)local * WX;
     for (int i = threadIdx.x; i < WX; i += WB_THREADS) st[i] = wbox[i];
+}
+
+// A voxel per thread and every term straight into the 64-bit volume: grids whose
+// bricks hold next to nothing (warp_direct).
+__global__ __launch_bounds__(256) void k_warp_bwd_direct(const float *__restrict__ ref, GridK g,
+                                                         const float *__restrict__ dvf, int V,
+                                                         const float *__restrict__ g_out,
+                                                         const uint32_t *__restrict__ gmax,
+                                                         unsigned long long *__restrict__ fix,
+                                                         float *__restrict__ g_dvf) {
+    const unsigned j = blockIdx.x * blockDim.x + threadIdx.x;
+    if (j >= (unsigned)grid_size(g)) return;                // < 2^31
+    const unsigned q = j / (unsigned)g.n[2];
+    const int ix = (int)(q / (unsigned)g.n[1]);
+    warp_bwd_voxel<false>(ref, g, dvf, V, g_out, fix_scale(*gmax), ix,
+                          (int)(q - (unsigned)ix * (unsigned)g.n[1]), (int)(j - q * (unsigned)g.n[2]), 0,
+                          0, 0, nullptr, fix, g_dvf);
 }
 
 // The staged boxes of bricks [first, first + count) (ALL: of every brick) that
@@ -211,6 +241,15 @@ static WarpBricks warp_bricks(const GridK &g) {
     return b;
 }
 
+// Bricks that are nearly empty cost their boxes' traffic for little (512x512x2,
+// one view, displacements of 12 voxels 129 us by voxels, 187 by bricks; 512x512x4
+// 273 / 262, smaller displacements 265 / 152), and on grids of a few bricks a
+// thread's atomics past its box wait for each other (24^3, four views, 12 voxels
+// 38 / 50 us; 32^3, 16 bricks, 66 / 70, smaller displacements 53 / 29).
+static bool warp_direct(const GridK &g, const WarpBricks &b) {
+    return b.n < 12 || grid_size(g) * 10 < (int64_t)(WA0 * WA1 * WA2) * b.n;
+}
+
 // Bricks of a round: all, unless their boxes (34 bytes per voxel) would take
 // more than 1 GiB; then each round's boxes are added to the 64-bit volume (the
 // sums are of integers: the same bits).
@@ -241,6 +280,17 @@ hipError_t launch_warp_bwd(const float *ref, const GridK &g, const float *dvf, i
     hipError_t e = launch_fill_i32((int32_t *)fix, 2 * N, 0, s);
     if (e != hipSuccess) return e;
     if ((e = launch_absmax(g_out, N * V, gmax, s)) != hipSuccess) return e;
+    if (warp_direct(g, b)) {
+        const unsigned nb = (unsigned)((N + 255) / 256);
+        {
+            ProfScope prof_("warp_bwd", s);
+            k_warp_bwd_direct<<<nb, 256, 0, s>>>(ref, g, dvf, V, g_out, gmax, fix, g_dvf);
+        }
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        ProfScope prof_("warp_gather", s);
+        k_warp_convert<<<nb, 256, 0, s>>>(fix, (unsigned)N, gmax, g_ref);
+        return hipGetLastError();
+    }
     const int plane = b.nb[1] * b.nb[2];
     const int64_t row = (int64_t)g.n[1] * g.n[2];
     for (int64_t first = 0; first < b.n; first += round) {
