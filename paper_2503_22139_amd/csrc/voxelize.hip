@@ -1206,13 +1206,14 @@ __device__ __forceinline__ void wave_sums(const float (&x)[N], int n, int lane, 
 }
 
 // One channel: a lane per column, 64 columns at a time; a lane walks its
-// column's z range S voxels at a time (the loads of a whole step merge into wide
-// ones: a lane's column is a cache line of its own) and keeps only sum e g, sum e g d2 and
+// column's z range S voxels at a time (whole steps by one wide load: a lane's
+// column is a cache line of its own) and keeps only sum e g, sum e g d2 and
 // sum e g d2^2 of it, folded into the others when it leaves the column (the
-// factor v_0 of t waits for the chain rule).  Steps of 2, 4 and 8: 256x256x128,
-// 300 Gaussians of s = 12 voxels 756 / 433 / 292 us (495 with four loads in
-// flight before), 50,000 of s = 2 (7 to 13 tall) 155 / 140 / 157, of s = 4 (25 tall)
-// 1.02 / 0.84 / 0.60 ms, of s = 1 (up to 7 tall) 35 / 36 / 40 us.
+// factor v_0 of t waits for the chain rule).  Steps of 2, 4 and 8, 256x256x128:
+// 300 Gaussians of s = 12 voxels 757 / 531 / 432 us (495 with four loads in
+// flight before), 50,000 of s = 4 (25 tall) 1.02 / 0.88 / 0.67 ms, of s = 2 (13 tall)
+// 155 / 146 us with 2 and 4; with more than 64 registers the reference set's 107 us
+// became 119.
 template <int S>
 __device__ __forceinline__ void walk_columns(const VoxG &q, const GridK &g, float k2, bool untrunc,
                                              const float *__restrict__ g_vol, int lane,
@@ -1243,19 +1244,16 @@ __device__ __forceinline__ void walk_columns(const VoxG &q, const GridK &g, floa
         int n = c.zb - c.za + 1;
         if constexpr (S > 2) {
             for (; n >= S; n -= S, gz += S, fz += (float)S) {
-                float gl[S];
-#pragma unroll
-                for (int k = 0; k < S; ++k) gl[k] = gz[k];
+                typedef float vec __attribute__((ext_vector_type(S), aligned(4)));
+                const vec gl = *(const vec *)gz;
 #pragma unroll
                 for (int k = 0; k < S; ++k) voxel(fz + (float)k, gl[k], true);
             }
         }
-        for (; n > 0; n -= S, gz += S, fz += (float)S) {
-            float gl[S];
-#pragma unroll
-            for (int k = 0; k < S; ++k) gl[k] = gz[k < n ? k : 0];
-#pragma unroll
-            for (int k = 0; k < S; ++k) voxel(fz + (float)k, gl[k], k < n);
+        for (; n > 0; n -= 2, gz += 2, fz += 2.0f) {
+            const float g0 = gz[0], g1 = gz[n > 1 ? 1 : 0];
+            voxel(fz, g0, true);
+            voxel(fz + 1.0f, g1, n > 1);
         }
         x[0] += St;
         x[1] = fmaf(c.d0, St, x[1]);
@@ -1355,7 +1353,7 @@ __device__ __forceinline__ void walk_voxels(const VoxG &q, const GridK &g, float
 }
 
 template <int CT>
-__global__ __launch_bounds__(64 * BW_WAVES) void k_vox_bwd(pmf_gauss_t gs, GridK g, float k, int per,
+__global__ __launch_bounds__(64 * BW_WAVES, CT == 1 ? 8 : 1) void k_vox_bwd(pmf_gauss_t gs, GridK g, float k, int per,
                                                            const float *__restrict__ g_vol,
                                                            pmf_gauss_grad_t gr) {
     constexpr int CM = CT > 0 ? CT : MAXC_VOX;
