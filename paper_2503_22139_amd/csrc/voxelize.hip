@@ -504,7 +504,7 @@ __device__ __forceinline__ int rotated_tile(int b, int nt1, int nt2) {
 constexpr int VOX_SCAN = 4096;
 
 template <int T0, int T1, int T2, int CT, int NW, int VB, bool SCAN>
-__global__ __launch_bounds__(64 * NW) void k_vox_tile(const GaussK *__restrict__ rec, int m, int nch,
+__global__ __launch_bounds__(64 * NW, 8) void k_vox_tile(const GaussK *__restrict__ rec, int m, int nch,
                                                   int maxtiles,
                                                   const float *__restrict__ value, int Crt, GridK g,
                                                   float k2, int nt1, int nt2,
@@ -690,27 +690,93 @@ __global__ __launch_bounds__(64 * NW) void k_vox_tile(const GaussK *__restrict__
                 __syncthreads();
             }
         }
-        for (int li = threadIdx.x; li < TV; li += NT) {
-            const int ix = b0 + li / (T1 * T2), iy = b1 + (li / T2) % T1, iz = b2 + li % T2;
-            if (ix > e0 || iy > e1 || iz > e2) continue;
-            const float d0g = fmaf((float)ix, g.h[0], g.c0[0]);
-            const float d1g = fmaf((float)iy, g.h[1], g.c0[1]);
-            const float d2g = fmaf((float)iz, g.h[2], g.c0[2]);
-            for (int e = 0; e < nl; ++e) {
-                const int gi = __builtin_amdgcn_readfirstlane(SCAN ? slist[e] : large[e]);
-                const GaussK p = rec[gi];
-                if (ix < p.lo0 || ix > p.hi0 || iy < p.lo1 || iy > p.hi1 || iz < p.lo2 ||
-                    iz > p.hi2)
-                    continue;
+        // 64 at a time, those that reach the tile in the batches' LDS, their boxes' hi0 and hi1 in place of
+        // ncols and ny (one record after the other, from global memory: 300
+        // Gaussians of s = 12 in 128x128x64, three channels, 314 us, now 88)
+        constexpr int K = TV > NT ? TV / NT : 1;       // a thread's voxels, along axis 2
+        static_assert(T2 % K == 0, "a thread's voxels lie in one column");
+        static_assert(NW * VB >= 64 && TV % (64 * K) == 0, "a wave's entries; whole waves of voxels");
+        constexpr int LU = K > 2 ? 1 : 4;
+        VoxB *const lb = bt[0];
+        float(*const lv)[CM] = bv[0];
+        const int li = (int)threadIdx.x * K;
+        const int ix = b0 + li / (T1 * T2), iy = b1 + (li / T2) % T1, iz = b2 + li % T2;
+        const bool on = li < TV && ix <= e0 && iy <= e1;
+        const float d0g = fmaf((float)ix, g.h[0], g.c0[0]);
+        const float d1g = fmaf((float)iy, g.h[1], g.c0[1]);
+        float d2g[K], out[K][CT > 0 ? CT : 1];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            d2g[k] = fmaf((float)(iz + k), g.h[2], g.c0[2]);
+#pragma unroll
+            for (int c = 0; c < CT; ++c) out[k][c] = on ? accf[c * TV + li + k] : 0.0f;
+        }
+        for (int f = 0; f < nl; f += 64) {                            // uniform
+            __syncthreads();              // slist is there, the entries before are used
+            if (wave == 0) {              // those that reach the tile, in order
+                bool hit = false;
+                GaussK p = {};
+                int gi = 0;
+                if (f + lane < nl) {
+                    gi = SCAN ? slist[f + lane] : large[f + lane];
+                    p = rec[gi];
+                    hit = max(p.lo0, b0) <= min(p.hi0, e0) && max(p.lo1, b1) <= min(p.hi1, e1) &&
+                          max(p.lo2, b2) <= min(p.hi2, e2);
+                }
+                const uint64_t hits = __ballot(hit);
+                if (hit) {
+                    const int j = __popcll(hits & ((1ull << lane) - 1));
+                    VoxB q;
+                    for (int a = 0; a < 3; ++a) q.mu[a] = p.mu[a];
+                    q.a00 = p.a00;
+                    q.a01 = p.a01;
+                    q.a02 = p.a02;
+                    q.a11 = p.a11;
+                    q.a12 = p.a12;
+                    q.a22 = p.a22;
+                    q.lo0 = p.lo0;
+                    q.lo1 = p.lo1;
+                    q.lo2 = p.lo2;
+                    q.hi2 = p.hi2;
+                    q.ny = p.hi1;
+                    q.ncols = p.hi0;
+                    q.cend = 0;
+                    lb[j] = q;
+                    for (int c = 0; c < C; ++c) lv[j][c] = value[(int64_t)gi * C + c];
+                }
+                if (lane == 0) scount[0] = __popcll(hits);
+            }
+            __syncthreads();
+            const int n = scount[0];
+            // (without branches, so that several entries' reads are in flight)
+#pragma unroll LU
+            for (int e = 0; wave * 64 * K < TV && e < n; ++e) {      // uniform
+                const VoxB p = lb[e];
                 float cb2, cq;
                 col_coeffs(p.a00, p.a01, p.a02, p.a11, p.a12, d0g - p.mu[0], d1g - p.mu[1], cb2, cq);
-                const float mm = col_quad(p.a22, cb2, cq, d2g - p.mu[2]);
-                if (!(mm <= k2)) continue;
-                const float ev = half_exp(mm);
-                const float *vv = value + (int64_t)gi * C;
-                for (int c = 0; c < C; ++c) accf[c * TV + li] += vv[c] * ev;
+                const bool col = ix >= p.lo0 && ix <= p.ncols && iy >= p.lo1 && iy <= p.ny;
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    const float mm = col_quad(p.a22, cb2, cq, d2g[k] - p.mu[2]);
+                    const bool in = col && iz + k >= p.lo2 && iz + k <= p.hi2 && mm <= k2;
+                    const float ev = half_exp(mm);
+                    if constexpr (CT > 0) {
+#pragma unroll
+                        for (int c = 0; c < CT; ++c) {
+                            const float t = fmaf(lv[e][c], ev, out[k][c]);
+                            out[k][c] = in ? t : out[k][c];
+                        }
+                    } else if (on && in) {
+                        for (int c = 0; c < C; ++c) accf[c * TV + li + k] += lv[e][c] * ev;
+                    }
+                }
             }
         }
+        if (on)
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+#pragma unroll
+                for (int c = 0; c < CT; ++c) accf[c * TV + li + k] = out[k][c];
     }
     __syncthreads();
     const int64_t N = grid_size(g);
@@ -897,20 +963,34 @@ __global__ __launch_bounds__(256, 6) void k_vox_gather(const GaussK *__restrict_
     // Gaussians too large for the bins, in float, in the list's ascending
     // order (as k_vox_tile)
     const int nl = *nlarge;
-    for (int e = 0; e < nl; ++e) {
-        const int gi = __builtin_amdgcn_readfirstlane(large[e]);
-        const GaussK p = rec[gi];
-        if (ix < p.lo0 || ix > p.hi0 || iy < p.lo1 || iy > p.hi1) continue;
-        float cb2, cq;
-        col_coeffs(p.a00, p.a01, p.a02, p.a11, p.a12, d0g - p.mu[0], d1g - p.mu[1], cb2, cq);
+    for (int f = 0; f < nl; f += VG_CHUNK) {                      // uniform
+        __syncthreads();                  // the entries before are used
+        if (wave == 0) {
+            const bool in = f + lane < nl;
+            const int gi = large[in ? f + lane : f];
+            float v[CT];
 #pragma unroll
-        for (int s = 0; s < SEG; ++s) {
-            if (z0 + s < p.lo2 || z0 + s > p.hi2) continue;
-            const float mm = col_quad(p.a22, cb2, cq, d2g[s] - p.mu[2]);
-            if (!(mm <= k2)) continue;
-            const float ev = half_exp(mm);
+            for (int c = 0; c < CT; ++c) v[c] = value[(int64_t)gi * CT + c];
+            const GaussK p = rec[gi];
+            stage(in, p, v);              // in order
+        }
+        __syncthreads();
+        const int n = nsh;
+        for (int e = 0; e < n; ++e) {
+            const GaussK p = gsh[e];
+            if (p.hi0 < wx0 || p.lo0 > wx1) continue;             // uniform
+            if (ix < p.lo0 || ix > p.hi0 || iy < p.lo1 || iy > p.hi1) continue;
+            float cb2, cq;
+            col_coeffs(p.a00, p.a01, p.a02, p.a11, p.a12, d0g - p.mu[0], d1g - p.mu[1], cb2, cq);
 #pragma unroll
-            for (int c = 0; c < CT; ++c) out[s][c] += value[(int64_t)gi * CT + c] * ev;
+            for (int s = 0; s < SEG; ++s) {
+                if (z0 + s < p.lo2 || z0 + s > p.hi2) continue;
+                const float mm = col_quad(p.a22, cb2, cq, d2g[s] - p.mu[2]);
+                if (!(mm <= k2)) continue;
+                const float ev = half_exp(mm);
+#pragma unroll
+                for (int c = 0; c < CT; ++c) out[s][c] += gvs[e][c] * ev;
+            }
         }
     }
     if (ix > e0 || iy > e1) return;
