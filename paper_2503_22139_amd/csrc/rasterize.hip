@@ -363,7 +363,7 @@ __device__ __forceinline__ bool splat_reaches(const SplatP &P, float x0, float y
 }
 
 // One workgroup per (view, tile); a wave has one 8 x 8 block of the tile, one
-// pixel per lane, and one RF_PARTS-th of the staged splats.  Each pixel sums
+// pixel per lane, and one PARTS-th of the staged splats.  Each pixel sums
 // its splats in 32-bit fixed point with the tile's scale 2^30 / S, S = (number
 // of splats reaching the tile: its list and the view's large Gaussians) x
 // (their largest |amplitude|), so every pixel's sum stays below 2^30: neither
@@ -378,16 +378,25 @@ __device__ __forceinline__ bool splat_reaches(const SplatP &P, float x0, float y
 // and the waves visit only the splats that reach theirs (a bit mask per
 // block): 200k Gaussians of about 20 pixels on 512 x 384: 130 us with every
 // wave on every splat of its tile, now 67 (with two parts 70, with one 81).
-constexpr int RF_PARTS = 4;
-constexpr int RF_T = RS_THREADS * RF_PARTS;
+//
+// Four parts pay where the tiles are few and their lists long; else the
+// sixteen waves of a tile only wait for its start and end.  Kernel alone, four
+// parts / one: 512x384 (768 tiles) one view, 10,000 Gaussians of s to 2 voxels
+// 14 / 10 us, 50,000 21 / 22, 200,000 52 / 65; 256x192 (192) 2,000 7.6 / 7.1, 10,000
+// 8.9 / 9.7; 64x48 (12) 300 7.2 / 7.2, 2,000 8.0 / 9.6; 512x384 four views, 50,000
+// 63 / 52; 1024x768 one view, 200,000 467 / 471, 10 Gaussians 12 / 8.
+constexpr int64_t RF_FEW = 1024;        // tiles of all views
+constexpr int64_t RF_LONG = 40;         // Gaussians per tile of a view
 
-__global__ __launch_bounds__(RF_T) void k_splat_fwd(const SplatP *__restrict__ sp, int64_t m, int V,
+template <int PARTS>
+__global__ __launch_bounds__(RS_THREADS * PARTS) void k_splat_fwd(const SplatP *__restrict__ sp, int64_t m, int V,
                                                     RastGeo G,
                                                     const int *__restrict__ offsets,
                                                     const int *__restrict__ list,
                                                     const int *__restrict__ large,
                                                     const int *__restrict__ nlarge,
                                                     float *__restrict__ proj) {
+    constexpr int RF_T = RS_THREADS * PARTS;
     __shared__ SplatP sh[RF_T + 1];              // the last one adds nothing
     __shared__ uint64_t mask[4][RF_T / 64];
     __shared__ float red[RF_T / 64];
@@ -405,6 +414,10 @@ __global__ __launch_bounds__(RF_T) void k_splat_fwd(const SplatP *__restrict__ s
     const float k2 = G.k * G.k;
     const int b = offsets[tix], e = offsets[tix + 1];
     const int nl = *nlarge;
+    if (b == e && nl == 0) {                     // nothing here
+        if (part == 0 && x < G.nu && y < G.nv) proj[((int64_t)v * G.nv + y) * G.nu + x] = 0.0f;
+        return;
+    }
     auto reaches = [&](const SplatP &P) {
         const SplatTiles q = splat_tiles(P);
         return q.area > 0 && q.tu0 <= tx && tx <= q.tu1 && q.tv0 <= ty && ty <= q.tv1;
@@ -461,7 +474,7 @@ __global__ __launch_bounds__(RF_T) void k_splat_fwd(const SplatP *__restrict__ s
             if (lane == 0) mask[q][wave] = bits;
         }
         __syncthreads();
-        for (int w = part; w * 64 < n; w += RF_PARTS) {
+        for (int w = part; w * 64 < n; w += PARTS) {
             uint64_t bits = mask[blk][w];
             bits = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)bits) |
                    (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(bits >> 32)) << 32;
@@ -497,7 +510,7 @@ __global__ __launch_bounds__(RF_T) void k_splat_fwd(const SplatP *__restrict__ s
         }
         add_staged(n, on, P);
     }
-    if constexpr (RF_PARTS > 1) {
+    if constexpr (PARTS > 1) {
         atomicAdd(&sum[blk * 64 + lane], acc);
         __syncthreads();
         if (part > 0) return;
@@ -853,8 +866,12 @@ hipError_t launch_rasterize(const pmf_gauss_t &gs, const pmf_cone_t &c, const fl
     const int64_t T = (int64_t)G.tiles_u * G.tiles_v * V;
     {
         ProfScope prof_("rasterize", s);
-        k_splat_fwd<<<many_blocks(T), RF_T, 0, s>>>(w.sp, gs.m, V, G, w.offsets, w.list, w.large,
-                                                    w.nlarge, proj);
+        if (T <= RF_FEW && gs.m >= RF_LONG * (T / V))
+            k_splat_fwd<4><<<many_blocks(T), 4 * RS_THREADS, 0, s>>>(w.sp, gs.m, V, G, w.offsets, w.list,
+                                                                     w.large, w.nlarge, proj);
+        else
+            k_splat_fwd<1><<<many_blocks(T), RS_THREADS, 0, s>>>(w.sp, gs.m, V, G, w.offsets, w.list,
+                                                                 w.large, w.nlarge, proj);
     }
     return hipGetLastError();
 }
