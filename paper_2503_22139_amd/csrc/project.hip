@@ -1293,18 +1293,24 @@ static void project_tiled(const ProjJob *jobs, int n, hipStream_t s) {
 // same bits): whole rays leave one to three waves on a SIMD, each a serial chain
 // of loads, where a wave of the shared ones has four samples' loads in flight;
 // with more rays the loads themselves are the bound, and a wave that marches
-// whole rays reuses a cell's corners.  Whole call, whole rays against shared:
-// 256x256x128 paired one view 203 / 138 us, two 229 / 215, four 419 / 385, five
-// 513 / 503, six 633 / 594, eight 760 / 787; 128x128x64 paired one view 91 / 61, two 109 / 98,
-// four 135 / 148 (the smaller the volume, the earlier they cross: the rule does
-// not follow that); 64^3 plain ten views of 128x96 (122,880 rays) 49 / 23.
+// whole rays reuses a cell's corners.  In a small volume rays are short and its
+// loads hit the cache, so the line is lower: one ray per voxel in the paired
+// layout, three in the plain one.  Whole call, whole rays against shared, paired:
+// 256x256x128 one view of 512x384 203 / 138 us, two 229 / 215, four 419 / 385, five
+// 513 / 503, eight 760 / 787; 128x128x64 one view 91 / 61, two 109 / 98, four 135 / 148;
+// ratios at 64^3 0.84 (197,000 rays), 1.13 (294,000), at 96x96x64 0.95 (590,000), 1.03
+// (786,000), at 48^3 1.05 (197,000), at 32^3 1.28; plain 64^3 ten views of 128x96
+// (122,880 rays) 49 / 23 us, ratios at 32^3 0.81 (61,000), 0.98 (98,000), 1.12 (197,000).
 constexpr int64_t SHARED_RAYS = 800000;
 
 template <int WU, int WV, int AU>
 static void project_tile(const ProjJob *jobs, int n, hipStream_t s) {
-    int64_t rays = 0;
-    for (int k = 0; k < n; ++k) rays += (int64_t)jobs[k].V * jobs[k].c.nu * jobs[k].c.nv;
-    if (rays <= SHARED_RAYS) project_tiled<WU, WV, AU, true>(jobs, n, s);
+    int64_t rays = 0, N = 0;
+    for (int k = 0; k < n; ++k) {
+        rays += (int64_t)jobs[k].V * jobs[k].c.nu * jobs[k].c.nv;
+        N = std::max(N, grid_size(jobs[k].g));
+    }
+    if (rays <= std::min(SHARED_RAYS, jobs[0].paired ? N : 3 * N)) project_tiled<WU, WV, AU, true>(jobs, n, s);
     else project_tiled<WU, WV, AU, false>(jobs, n, s);
 }
 

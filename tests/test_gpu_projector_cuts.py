@@ -1,0 +1,54 @@
+"""The projector on both sides of the lines between shared and whole rays."""
+import ctypes as C
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2503_22139_amd import ops, synth
+from paper_2503_22139_amd.synth import Cone, Grid
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    ops.lib()
+    oracle.build()
+    yield
+
+
+def T(a):
+    return torch.from_numpy(np.ascontiguousarray(a, np.float32)).cuda()
+
+
+def plain(vol, grid, cone, ang):
+    out = torch.empty((ang.numel(), cone.nv, cone.nu), device="cuda")
+    g, c = ops.make_grid(grid), ops.make_cone(cone)
+    ops._check(ops.lib().pmf_project(ops._ptr(vol), 0, C.byref(g), C.byref(c), ops._ptr(ang), ang.numel(),
+                                     ops._ptr(out), ops._stream()))
+    return out
+
+
+# up to one ray per voxel paired and three plain: 277,200 voxels (one view paired,
+# three plain are shared) and 13,824 (one view plain)
+@pytest.mark.parametrize("n,nu,nv", [((70, 66, 60), 512, 500), ((24, 24, 24), 203, 200)])
+def test_shared_rays_have_the_bits_of_whole_ones(n, nu, nv):
+    grid = Grid(n, tuple(70.0 / x for x in n), (3.0, -2.0, 1.0))
+    cone = Cone(1000.0, 1500.0, nu, nv, 110.0 / nu, 100.0 / nv, off_u=0.3)
+    ang = T(synth.scan_angle([3, 100, 222, 391]))
+    vol = T(synth.random_volume(8, n))
+    whole = plain(vol, grid, cone, ang)
+    assert torch.equal(ops.pmf_project(vol, grid, cone, ang), whole)
+    for V in (1, 2, 3):
+        assert torch.equal(plain(vol, grid, cone, ang[:V]), whole[:V]), V
+        assert torch.equal(ops.pmf_project(vol, grid, cone, ang[:V]), whole[:V]), V
+    rng = np.random.default_rng(1)
+    rays = np.stack([rng.integers(0, 4, 300), rng.integers(0, nu, 300), rng.integers(0, nv, 300)], 1)
+    ref = oracle.project_rays(vol.cpu().numpy(), grid, cone, ang.cpu().numpy(), rays)
+    got = whole.cpu().numpy()[rays[:, 0], rays[:, 2], rays[:, 1]]
+    assert np.linalg.norm(got - ref) < 1e-4 * np.linalg.norm(ref)
+
