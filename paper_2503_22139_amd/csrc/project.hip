@@ -1619,7 +1619,6 @@ static hipError_t launch_sum_views(const BwdK &b, const BwdJob &j, hipStream_t s
 
 template <int L, int W, int H, int NW, bool MERGE, int ZC>
 static hipError_t project_bwd_bricks(const BwdJob *jobs, int n, hipStream_t s) {
-    constexpr int NPMAX = (L + 1) * (W + 1) * (H + 1);
     BwdTab t{};
     t.n = n;
     t.first[0] = 0;
@@ -1687,8 +1686,14 @@ static hipError_t project_bwd_bricks(const BwdJob *jobs, int n, hipStream_t s) {
             t.s[k]);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    (void)NPMAX;
     return hipSuccess;
+}
+
+// Column chunks of ZC bricks of all jobs.
+static int64_t column_items(const BwdJob *jobs, int n, int L, int W, int H, int zc) {
+    int64_t items = 0;
+    for (int k = 0; k < n; ++k) items += (int64_t)jobs[k].V * column_items_per_view(jobs[k].g, L, W, H, zc);
+    return items;
 }
 
 // Chunks of ZC bricks along axis 2 carry the axis-2 pads in LDS; single
@@ -1699,23 +1704,40 @@ static hipError_t project_bwd_bricks(const BwdJob *jobs, int n, hipStream_t s) {
 // views in chunks of 2: 2.25 / 1.69): chunks from 3,072 of them on.
 template <int L, int W, int H, int NW, int ZC>
 static hipError_t project_bwd_chunked(const BwdJob *jobs, int n, hipStream_t s) {
-    int64_t items = 0;
-    for (int k = 0; k < n; ++k)
-        items += (int64_t)jobs[k].V * column_items_per_view(jobs[k].g, L, W, H, ZC);
-    if (items < 3072) return project_bwd_bricks<L, W, H, NW, true, 1>(jobs, n, s);
+    if (column_items(jobs, n, L, W, H, ZC) < 3072) return project_bwd_bricks<L, W, H, NW, true, 1>(jobs, n, s);
     return project_bwd_bricks<L, W, H, NW, true, ZC>(jobs, n, s);
 }
 
-// The default brick, or a smaller one where the launch has fewer than 1,536
-// of the default (two per slot of the chip: the last round would be nearly
-// empty).  Whole call, 44x20x8 against 32x16x8: 256x256x128 one view (1,248
-// bricks) 374 / 293 us, two views 628 / 586, four 946 / 962; 128x128x64 one view (168)
-// 169 / 120, four views 301 / 266, eight (1,344) 420 / 416, twelve 591 / 578.
+// Few rays: a brick's time is its box's and its pads', so chunks pay from as
+// few of them as fill the chip on, the longest that leave 1,536.  Whole call,
+// single bricks against that: 256x256x128, 64x48, three views 151 / 140 us (chunks
+// of 2), eight 350 / 302 (4), twelve 526 / 419 (8); 128x96, 16 views 801 / 635 (8).
+template <int ZC>
+static hipError_t project_bwd_sparse(const BwdJob *jobs, int n, hipStream_t s) {
+    if constexpr (ZC > 1)
+        if (column_items(jobs, n, 44, 20, 8, ZC) < 1536) return project_bwd_sparse<ZC / 2>(jobs, n, s);
+    return project_bwd_bricks<44, 20, 8, 8, true, ZC>(jobs, n, s);
+}
+
+// The default brick, or a smaller one where the launch has so few of the
+// default that the last round on the chip would be nearly empty: fewer than
+// 1,536 (two per slot), or, as a brick of few rays has less to balance, 800 and
+// 450 from 100,000 and 25,000 rays per view down.  Whole call, 44x20x8 against
+// 32x16x8: 512x384, 256x256x128 one view (1,248 bricks) 265 / 239 us, two views
+// 439 / 434, three 768 / 776; 128x128x64 one view (168) 379 / 277, six (1,008) 795 / 744,
+// eight (1,344) 976 / 973; 256x192, 256x256x16 four views (624) 84 / 81, six (936)
+// 104 / 113, 200x200x100 one (650) 107 / 93; 128x96, 128x128x64 two (336) 62 / 52, three
+// (504) 71 / 73, 256x256x16 two (312) 41 / 40, three (468) 46 / 50, 256x256x128 one 74 / 82.
 static hipError_t project_bwd_default(const BwdJob *jobs, int n, hipStream_t s) {
-    int64_t items = 0;
-    for (int k = 0; k < n; ++k)
-        items += (int64_t)jobs[k].V * column_items_per_view(jobs[k].g, 44, 20, 8, 1);
-    if (items < 1536) return project_bwd_bricks<32, 16, 8, 8, true, 1>(jobs, n, s);
+    int64_t rays = 0, views = 0;
+    for (int k = 0; k < n; ++k) {
+        rays += (int64_t)jobs[k].V * jobs[k].c.nu * jobs[k].c.nv;
+        views += jobs[k].V;
+    }
+    const int64_t per_view = rays / views;
+    const int64_t few = per_view >= 100000 ? 1536 : per_view >= 25000 ? 800 : 450;
+    if (column_items(jobs, n, 44, 20, 8, 1) < few) return project_bwd_bricks<32, 16, 8, 8, true, 1>(jobs, n, s);
+    if (per_view < 25000) return project_bwd_sparse<8>(jobs, n, s);
     return project_bwd_chunked<44, 20, 8, 8, 8>(jobs, n, s);
 }
 

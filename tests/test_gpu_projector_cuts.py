@@ -1,4 +1,5 @@
-"""The projector on both sides of the lines between shared and whole rays."""
+"""The projector on both sides of the lines between shared and whole rays, and the
+back-projection of few rays in chunks of 1, 2, 4 and 8 bricks."""
 import ctypes as C
 
 import numpy as np
@@ -52,3 +53,20 @@ def test_shared_rays_have_the_bits_of_whole_ones(n, nu, nv):
     got = whole.cpu().numpy()[rays[:, 0], rays[:, 2], rays[:, 1]]
     assert np.linalg.norm(got - ref) < 1e-4 * np.linalg.norm(ref)
 
+
+# four columns of 127 bricks a view (the last one cut): the longest chunks that
+# leave 1,536 hold 1, 2, 4 and 8
+@pytest.mark.parametrize("V", [2, 6, 12, 24])
+def test_back_projection_of_few_rays(V):
+    print(V, flush=True)
+    grid = Grid((45, 21, 1013), (1.5, 1.4, 0.1), (1.0, 2.0, -1.0))
+    cone = Cone(1000.0, 1500.0, 24, 20, 4.4, 8.0, off_v=0.4)
+    ang = T(synth.scan_angle((np.arange(V) * 660) // V + 7))
+    gp = T(synth.random_normal(9, (V, cone.nv, cone.nu)))
+    got = ops.pmf_project_bwd(gp, grid, cone, ang)
+    want = oracle.project_bwd(gp.cpu().numpy(), grid, cone, ang.cpu().numpy(), shared=False)
+    assert np.linalg.norm(got.cpu().numpy() - want) < 1e-4 * np.linalg.norm(want)
+    total = got[0].clone()
+    for v in got[1:]:
+        total += v
+    assert torch.equal(ops.pmf_project_bwd(gp, grid, cone, ang, shared=True), total)
