@@ -1289,13 +1289,21 @@ static void project_tiled(const ProjJob *jobs, int n, hipStream_t s) {
     }
 }
 
+// Rays of a view that may meet the volume, about: the detector's pixels within
+// the volume's shadow at the magnification of its centre.
+static int64_t hit_rays(const GridK &g, const ConeK &c) {
+    const double mag = c.sdd / c.sad;
+    const double w = std::max(g.n[0] * g.hd[0], g.n[1] * g.hd[1]) * mag / c.du, h = g.n[2] * g.hd[2] * mag / c.dv;
+    return (int64_t)(std::min((double)c.nu, std::ceil(w)) * std::min((double)c.nv, std::ceil(h)));
+}
+
 // Up to 800,000 rays (four views of 512x384) four waves share every ray (the
 // same bits): whole rays leave one to three waves on a SIMD, each a serial chain
 // of loads, where a wave of the shared ones has four samples' loads in flight;
 // with more rays the loads themselves are the bound, and a wave that marches
 // whole rays reuses a cell's corners.  In a small volume rays are short and its
-// loads hit the cache, so the line is lower: one ray per voxel in the paired
-// layout, three in the plain one.  Whole call, whole rays against shared, paired:
+// loads hit the cache, so the line is lower: one ray that meets it per voxel in
+// the paired layout, three in the plain one.  Whole call, whole rays against shared, paired:
 // 256x256x128 one view of 512x384 203 / 138 us, two 229 / 215, four 419 / 385, five
 // 513 / 503, eight 760 / 787; 128x128x64 one view 91 / 61, two 109 / 98, four 135 / 148;
 // ratios at 64^3 0.84 (197,000 rays), 1.13 (294,000), at 96x96x64 0.95 (590,000), 1.03
@@ -1305,12 +1313,13 @@ constexpr int64_t SHARED_RAYS = 800000;
 
 template <int WU, int WV, int AU>
 static void project_tile(const ProjJob *jobs, int n, hipStream_t s) {
-    int64_t rays = 0, N = 0;
+    int64_t rays = 0, hits = 0, N = 0;
     for (int k = 0; k < n; ++k) {
         rays += (int64_t)jobs[k].V * jobs[k].c.nu * jobs[k].c.nv;
+        hits += jobs[k].V * hit_rays(jobs[k].g, jobs[k].c);
         N = std::max(N, grid_size(jobs[k].g));
     }
-    if (rays <= std::min(SHARED_RAYS, jobs[0].paired ? N : 3 * N)) project_tiled<WU, WV, AU, true>(jobs, n, s);
+    if (rays <= SHARED_RAYS && hits <= (jobs[0].paired ? N : 3 * N)) project_tiled<WU, WV, AU, true>(jobs, n, s);
     else project_tiled<WU, WV, AU, false>(jobs, n, s);
 }
 
@@ -1708,10 +1717,13 @@ static hipError_t project_bwd_chunked(const BwdJob *jobs, int n, hipStream_t s) 
     return project_bwd_bricks<L, W, H, NW, true, ZC>(jobs, n, s);
 }
 
-// Few rays: a brick's time is its box's and its pads', so chunks pay from as
-// few of them as fill the chip on, the longest that leave 1,536.  Whole call,
-// single bricks against that: 256x256x128, 64x48, three views 151 / 140 us (chunks
-// of 2), eight 350 / 302 (4), twelve 526 / 419 (8); 128x96, 16 views 801 / 635 (8).
+// Few rays per brick, a volume per view: a brick's time is its box's and its
+// pads', so chunks pay from as few of them as fill the chip on, the longest that
+// leave 1,536.  Whole call, single bricks against that: 256x256x128, 64x48, three
+// views 151 / 140 us (chunks of 2), eight 350 / 302 (4), twelve 526 / 419 (8); 128x96
+// (10 rays per brick), 16 views 801 / 635 (8); 200x200x100 and 128x96 (19) twelve
+// views 337 / 376 (4).  The sum, which adds the pads in passing, loses by them:
+// 160x150x100, 64x48, 24 views 298 / 331 us.
 template <int ZC>
 static hipError_t project_bwd_sparse(const BwdJob *jobs, int n, hipStream_t s) {
     if constexpr (ZC > 1)
@@ -1721,23 +1733,21 @@ static hipError_t project_bwd_sparse(const BwdJob *jobs, int n, hipStream_t s) {
 
 // The default brick, or a smaller one where the launch has so few of the
 // default that the last round on the chip would be nearly empty: fewer than
-// 1,536 (two per slot), or, as a brick of few rays has less to balance, 800 and
-// 450 from 100,000 and 25,000 rays per view down.  Whole call, 44x20x8 against
-// 32x16x8: 512x384, 256x256x128 one view (1,248 bricks) 265 / 239 us, two views
-// 439 / 434, three 768 / 776; 128x128x64 one view (168) 379 / 277, six (1,008) 795 / 744,
-// eight (1,344) 976 / 973; 256x192, 256x256x16 four views (624) 84 / 81, six (936)
-// 104 / 113, 200x200x100 one (650) 107 / 93; 128x96, 128x128x64 two (336) 62 / 52, three
-// (504) 71 / 73, 256x256x16 two (312) 41 / 40, three (468) 46 / 50, 256x256x128 one 74 / 82.
+// 1,536 (two per slot), or, as a brick of few rays has less to balance, 900 and
+// 450 from 150 and 30 rays per brick down.  Whole call, 44x20x8 against
+// 32x16x8 (rays per brick, bricks): 256x256x128 and 512x384 one view (157, 1,248)
+// 265 / 239 us, two 439 / 434; 128x128x64 and 512x384 six (1,170, 1,008) 795 / 744,
+// eight (1,344) 976 / 973; 64^3 and 128x96 eight (192, 512) 147 / 123; 200x200x100 and
+// 256x192 one (75, 650) 107 / 93, two (1,300) 146 / 151; 128x128x64 and 128x96 three
+// (73, 504) 71 / 73, twelve (2,016) 156 / 172; 256x256x16 and 64x48 two (20, 312)
+// 37 / 36, three (468) 42 / 46; 256x256x128 and 128x96 one (10, 1,248) 74 / 82.
 static hipError_t project_bwd_default(const BwdJob *jobs, int n, hipStream_t s) {
-    int64_t rays = 0, views = 0;
-    for (int k = 0; k < n; ++k) {
-        rays += (int64_t)jobs[k].V * jobs[k].c.nu * jobs[k].c.nv;
-        views += jobs[k].V;
-    }
-    const int64_t per_view = rays / views;
-    const int64_t few = per_view >= 100000 ? 1536 : per_view >= 25000 ? 800 : 450;
-    if (column_items(jobs, n, 44, 20, 8, 1) < few) return project_bwd_bricks<32, 16, 8, 8, true, 1>(jobs, n, s);
-    if (per_view < 25000) return project_bwd_sparse<8>(jobs, n, s);
+    int64_t rays = 0;
+    for (int k = 0; k < n; ++k) rays += jobs[k].V * hit_rays(jobs[k].g, jobs[k].c);
+    const int64_t bricks = column_items(jobs, n, 44, 20, 8, 1);
+    const int64_t few = rays >= 150 * bricks ? 1536 : rays >= 30 * bricks ? 900 : 450;
+    if (bricks < few) return project_bwd_bricks<32, 16, 8, 8, true, 1>(jobs, n, s);
+    if (rays < 15 * bricks && !jobs[0].sum) return project_bwd_sparse<8>(jobs, n, s);
     return project_bwd_chunked<44, 20, 8, 8, 8>(jobs, n, s);
 }
 
