@@ -6,8 +6,9 @@
 // reference, ~150 Gaussians per tile) are splatted: the waves lay the
 // (Gaussian, column) pairs of batches of the tile's Gaussians over their
 // lanes and add into an LDS copy of the tile in fixed point.  Three- and
-// nine-channel sets (the MBC bases, ~10 Gaussians per tile) are gathered:
-// each thread owns a few voxels and keeps their channel sums in registers.
+// nine-channel sets (the MBC bases, ~10 Gaussians per tile) on more than
+// VOX_FEW tiles are gathered: each thread owns a few voxels and keeps their
+// channel sums in registers.
 // Either way the tile is stored once with plain writes -- no global atomics
 // -- and the integer sums do not depend on the order in which the binning's
 // atomics filled the tile lists.  Gaussians whose box spans more tiles than
@@ -15,9 +16,9 @@
 // ascending order, which every tile walks after its own list, adding in
 // float per voxel in that order.
 //
-// Backward: Gaussian owner.  A wave takes a batch of Gaussians, walks each
-// one's voxel box, accumulates the per-Gaussian sums in registers and
-// reduces them across the wave; one lane per Gaussian applies the chain rule
+// Backward: Gaussian owner.  A workgroup takes a batch of Gaussians; each of
+// its waves walks one's voxel box at a time, accumulates the sums in registers
+// and reduces them across the wave; one lane per Gaussian applies the chain rule
 // through Sigma = R diag(s^2) R^T and the quaternion normalisation.
 #include <math.h>
 
@@ -496,12 +497,17 @@ __device__ __forceinline__ int rotated_tile(int b, int nt1, int nt2) {
     return c * nt2 + (z + tx + ty / 2) % nt2;
 }
 
-// SCAN: a small set (up to VOX_SCAN Gaussians on few tiles) has no lists; each
-// workgroup finds its tile's Gaussians among all of them (nlarge then holds the
-// chunks' counts of large ones behind its first word), which costs less than the
-// launch that would write the lists (4,096 Gaussians in 64^3: 5 + 19 us for
-// records and tiles against 8 + 9 + 14 with lists).
+// SCAN: a small set on few tiles has no lists; each workgroup finds its tile's
+// Gaussians among all of them (nlarge then holds the chunks' counts of large
+// ones behind its first word), which costs less than the launch that would write
+// the lists.  Every tile reads every record, so the line falls with the tiles:
+// up to VOX_SCAN (a tile's list in 16 KB of LDS) on one tile per CU, 1,000 on
+// more.  Whole call, lists / search: 32^3 (64 tiles) 1,000 Gaussians 27 / 17 us,
+// 4,096 35 / 27; 64^3 (256) 24 / 18 at 4,096 (12,000 34 / 33 with 64 KB); 128x128x64
+// (512) 500 25 / 19, 1,000 25 / 21, 2,000 26 / 25, 4,096 26 / 30, three channels 500
+// 27 / 26, 1,000 28 / 29, 4,096 30 / 38.
 constexpr int VOX_SCAN = 4096;
+constexpr int VOX_SCAN_MANY = 1000;
 
 template <int T0, int T1, int T2, int CT, int NW, int VB, bool SCAN>
 __global__ __launch_bounds__(64 * NW, 8) void k_vox_tile(const GaussK *__restrict__ rec, int m, int nch,
@@ -1109,7 +1115,7 @@ hipError_t launch_voxelize(const pmf_gauss_t &gs, const GridK &g, float k, float
                   *const nlarge = w.nlarge;
     const float k2 = isinf(k) ? INFINITY : k * k;
     hipError_t e;
-    const bool few = p.ntiles <= VOX_FEW, scan = few && m > 0 && m <= VOX_SCAN;
+    const bool few = p.ntiles <= VOX_FEW, scan = few && m > 0 && m <= (p.ntiles <= 256 ? VOX_SCAN : VOX_SCAN_MANY);
     if (m == 0) {
         if ((e = launch_fill_i32(off, p.ntiles + 1, 0, s)) != hipSuccess) return e;
         if ((e = launch_fill_i32(nlarge, 1, 0, s)) != hipSuccess) return e;
