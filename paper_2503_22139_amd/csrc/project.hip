@@ -1153,7 +1153,7 @@ __device__ __forceinline__ int bp_face(const int p[3], int zc, int b[3], int l[3
 // boundaries); a row is one line of such a plane along its faster axis, and a
 // voxel that a lower family's plane also holds is left to that family, so
 // each face voxel is completed once.  Blocks stride over one view's rows
-// (one atomic for vmax per block).
+// (at most one atomic for vmax per block, see raise_max).
 template <int S0, int S1, int S2, int NPMAX>
 __device__ __forceinline__ void bp_fixup(const BwdK &bj, int view, float *red) {
     const GridK &g = bj.g;
@@ -1303,13 +1303,14 @@ static int64_t hit_rays(const GridK &g, const ConeK &c) {
 // with more rays the loads themselves are the bound, and a wave that marches
 // whole rays reuses a cell's corners.  In a small volume rays are short and its
 // loads hit the cache, so the line is lower: one ray that meets it per voxel in
-// the paired layout, three in the plain one.  Whole call, whole rays against shared, paired:
+// the paired layout, three in the plain one, and 150,000 where that is less (fewer
+// do not fill the chip).  Whole call, whole rays against shared, paired:
 // 256x256x128 one view of 512x384 203 / 138 us, two 229 / 215, four 419 / 385, five
 // 513 / 503, eight 760 / 787; 128x128x64 one view 91 / 61, two 109 / 98, four 135 / 148;
 // ratios at 64^3 0.84 (197,000 rays), 1.13 (294,000), at 96x96x64 0.95 (590,000), 1.03
 // (786,000), at 48^3 1.05 (197,000), at 32^3 1.28; plain 64^3 ten views of 128x96
 // (122,880 rays) 49 / 23 us, ratios at 32^3 0.81 (61,000), 0.98 (98,000), 1.12 (197,000).
-constexpr int64_t SHARED_RAYS = 800000;
+constexpr int64_t SHARED_RAYS = 800000, SHARED_HITS = 150000;
 
 template <int WU, int WV, int AU>
 static void project_tile(const ProjJob *jobs, int n, hipStream_t s) {
@@ -1319,7 +1320,8 @@ static void project_tile(const ProjJob *jobs, int n, hipStream_t s) {
         hits += jobs[k].V * hit_rays(jobs[k].g, jobs[k].c);
         N = std::max(N, grid_size(jobs[k].g));
     }
-    if (rays <= SHARED_RAYS && hits <= (jobs[0].paired ? N : 3 * N)) project_tiled<WU, WV, AU, true>(jobs, n, s);
+    if (rays <= SHARED_RAYS && hits <= std::max(SHARED_HITS, jobs[0].paired ? N : 3 * N))
+        project_tiled<WU, WV, AU, true>(jobs, n, s);
     else project_tiled<WU, WV, AU, false>(jobs, n, s);
 }
 
@@ -1376,10 +1378,9 @@ bool use_paired(const GridK &g) {
 // bytes per voxel.  Measured, whole call, plain against paired:
 // 256x256x128 and 512x384, one view 188 / 138 us, eight views 1497 / 763;
 // 128x128x64 one view 82 / 61; 256x256x128 and 96x64, one view 21 / 43, 16 views
-// 106 / 110; 64^3 and 128x96, 13 views (159,744 rays) 24 / 28, 32 views 38 / 40.
-// So copies are made from 150,000 rays per volume on, and from one ray per 128
-// voxels on; a volume as small as 64^3 loses up to 4 us by that line at any
-// number of rays measured.
+// 106 / 110; 128x96, 13 views (159,744 rays): 64^3 47 / 43, 128^3 49 / 51, 32 views
+// 85 / 74 and 85 / 80.  So copies are made from 150,000 rays per volume on, and from
+// one ray per 128 voxels on.
 constexpr int64_t PAIR_VIEWS = 8;       // per-view volumes copied at a time,
 constexpr int64_t PAIR_BYTES = (int64_t)1 << 30;     // within this much if more than one
 

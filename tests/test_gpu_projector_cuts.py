@@ -34,8 +34,9 @@ def plain(vol, grid, cone, ang):
     return out
 
 
-# up to one ray that meets the volume per voxel paired and three plain: 277,200
-# voxels (one view paired, three plain are shared) and 13,824 (one view plain)
+# up to one ray that meets the volume per voxel paired and three plain, and 150,000
+# where that is less: 277,200 voxels (one view paired, three plain are shared) and
+# 13,824 (three views of 40,600 rays)
 @pytest.mark.parametrize("n,nu,nv", [((70, 66, 60), 512, 500), ((24, 24, 24), 203, 200)])
 def test_shared_rays_have_the_bits_of_whole_ones(n, nu, nv):
     grid = Grid(n, tuple(70.0 / x for x in n), (3.0, -2.0, 1.0))
