@@ -420,9 +420,14 @@ def pmf_project_bwd(g_proj, grid: Grid, cone: Cone, angles, shared: bool = False
     g = make_grid(grid)
     cn = make_cone(cone)
     nbytes = lib().pmf_project_bwd_workspace(C.byref(g), C.byref(cn), V)
+    ws = None
     if shared and V > 1:
-        nbytes += min(4 * N * V, 512 << 20)     # the views' volumes: fewer rounds
-    ws = workspace(nbytes, g_proj.device)
+        try:
+            ws = workspace(nbytes + min(4 * N * V, 512 << 20), g_proj.device)   # fewer rounds
+        except torch.cuda.OutOfMemoryError:
+            pass
+    if ws is None:
+        ws = workspace(nbytes, g_proj.device)
     _check(lib().pmf_project_bwd(_ptr(g_proj.contiguous()), C.byref(g), C.byref(cn), _ptr(angles), V,
                                  _ptr(out), 0 if shared else N, C.c_void_p(ws.data_ptr()),
                                  ws.numel(), _stream()))
