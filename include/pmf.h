@@ -198,8 +198,8 @@ int pmf_project_ws(const float *vol, int64_t vol_stride, const pmf_grid_t *grid,
 /* Exact adjoint (back-projection) of pmf_project given g_proj [V][nv][nu]:
  * g_vol_v = P_v^T g_proj[v].  vol_stride = N writes one volume per view
  * ([V][N]); vol_stride = 0 writes their sum ([N]).  The bricks that the work is
- * cut into depend on the number of views, and with them the last bits of a
- * view's volume.
+ * cut into depend on the number of views, and with few rays on the form, and
+ * with them the last bits of a view's volume.
  * Needs the workspace from pmf_project_bwd_workspace(): per view, the rays'
  * constants (nu nv of them) and the bricks' staged faces (about 5 bytes per
  * voxel).  The sum is made from the views' volumes, which take the place of
@@ -409,7 +409,8 @@ size_t pmf_profile_names(char *buf, size_t len);
  *                              wavefronts, 8 = 52x16x8 (a launch of few
  *                              views takes single bricks, and with the
  *                              default choice 32x16x8 ones, so that it still
- *                              fills the chip);
+ *                              fills the chip; with few rays per brick it
+ *                              does so for fewer bricks);
  *   PMF_TUNE_VOXELIZE_BWD      Gaussians per workgroup in pmf_voxelize_bwd:
  *                              0 = chosen from the set's size (default),
  *                              k = 1..7: 2^(k-1).
