@@ -357,9 +357,7 @@ __global__ __launch_bounds__(256) void k_project(ProjTab t) {
 // four waves: each takes SH_K of every 4 SH_K consecutive ones (their loads are
 // in flight together) and leaves the values in LDS, and the waves in turn add
 // a group's values to the rays' sums in k_project's order.
-constexpr int SH_K = 4;
-
-template <int WU, int WV, bool PAIRED>
+template <int WU, int WV, bool PAIRED, int SH_K>
 __global__ __launch_bounds__(256) void k_project_shared(ProjTab t) {
     constexpr int GROUP = 4 * SH_K;
     __shared__ float val[2][GROUP][64];
@@ -1256,7 +1254,8 @@ static BoundK make_bound(const GridK &g, const ConeK &c) {
     return b;
 }
 
-template <int WU, int WV, int AU, bool SHARED>
+// SHARED: samples of a wave in a group of the shared rays' kernel, 0 for whole rays
+template <int WU, int WV, int AU, int SHARED>
 static void project_tiled(const ProjJob *jobs, int n, hipStream_t s) {
     constexpr int BU = SHARED ? WU : WU * AU, BV = SHARED ? WV : WV * (4 / AU);
     ProjTab t{};
@@ -1280,9 +1279,9 @@ static void project_tiled(const ProjJob *jobs, int n, hipStream_t s) {
     for (int k = n + 1; k <= MAXS; ++k) t.first[k] = t.first[n];
     if (t.first[n] == 0) return;
     const unsigned nb = (unsigned)t.first[n];
-    if constexpr (SHARED) {
-        if (jobs[0].paired) k_project_shared<WU, WV, true><<<nb, 256, 0, s>>>(t);
-        else k_project_shared<WU, WV, false><<<nb, 256, 0, s>>>(t);
+    if constexpr (SHARED > 0) {
+        if (jobs[0].paired) k_project_shared<WU, WV, true, SHARED><<<nb, 256, 0, s>>>(t);
+        else k_project_shared<WU, WV, false, SHARED><<<nb, 256, 0, s>>>(t);
     } else {
         if (jobs[0].paired) k_project<WU, WV, AU, true><<<nb, 256, 0, s>>>(t);
         else k_project<WU, WV, AU, false><<<nb, 256, 0, s>>>(t);
@@ -1310,7 +1309,12 @@ static int64_t hit_rays(const GridK &g, const ConeK &c) {
 // ratios at 64^3 0.84 (197,000 rays), 1.13 (294,000), at 96x96x64 0.95 (590,000), 1.03
 // (786,000), at 48^3 1.05 (197,000), at 32^3 1.28; plain 64^3 ten views of 128x96
 // (122,880 rays) 49 / 23 us, ratios at 32^3 0.81 (61,000), 0.98 (98,000), 1.12 (197,000).
-constexpr int64_t SHARED_RAYS = 800000, SHARED_HITS = 150000;
+// A launch of few rays waits for each group's barrier and sum, so its waves take
+// eight samples of a group, not four: 64^3 ten views of 128x96 23 / 21 us (four /
+// eight), 256x256x128 one view of 128x96 37 / 33, 64x48 eight views 57 / 51; from there
+// on four are ahead: 64^3 twelve views of 128x96 (147,456 rays) 30 / 32, 160x150x100 four
+// views of 512x384 226 / 233.
+constexpr int64_t SHARED_RAYS = 800000, SHARED_HITS = 150000, SHARED_LONG = 130000;
 
 template <int WU, int WV, int AU>
 static void project_tile(const ProjJob *jobs, int n, hipStream_t s) {
@@ -1320,9 +1324,10 @@ static void project_tile(const ProjJob *jobs, int n, hipStream_t s) {
         hits += jobs[k].V * hit_rays(jobs[k].g, jobs[k].c);
         N = std::max(N, grid_size(jobs[k].g));
     }
-    if (rays <= SHARED_RAYS && hits <= std::max(SHARED_HITS, jobs[0].paired ? N : 3 * N))
-        project_tiled<WU, WV, AU, true>(jobs, n, s);
-    else project_tiled<WU, WV, AU, false>(jobs, n, s);
+    if (rays > SHARED_RAYS || hits > std::max(SHARED_HITS, jobs[0].paired ? N : 3 * N))
+        project_tiled<WU, WV, AU, 0>(jobs, n, s);
+    else if (rays <= SHARED_LONG) project_tiled<WU, WV, AU, 8>(jobs, n, s);
+    else project_tiled<WU, WV, AU, 4>(jobs, n, s);
 }
 
 hipError_t launch_project_jobs(const ProjJob *jobs, int n, hipStream_t s) {
